@@ -93,10 +93,11 @@ typedef struct mp_opts {
                              mp_solve_noalloc); 0 for the others */
 } mp_opts;
 
-/* mp_opts.flags: decode with one kernel launch per step even where the whole
-   decode fits one persistent launch (the one-bit form MP_SIGN1, and MP_F32
-   contexts whose dictionary fits the LDS of at most 32 workgroups); the same
-   results bit for bit; no effect on the other forms. */
+/* mp_opts.flags: decode with one kernel launch per step, each a pass over the
+   whole dictionary, even where the whole decode fits one persistent launch
+   (the one-bit form MP_SIGN1, and MP_F32 contexts whose dictionary fits the
+   LDS of at most 32 workgroups) or runs on carried correlations (see
+   mp_solve); the same results bit for bit; no effect on the other forms. */
 #define MP_SOLVE_STEP_LAUNCHES 0x1u
 
 /* mp_opts.flags: a stream-ordered decode (mp_solve and mp_solve_noalloc on
@@ -122,7 +123,8 @@ typedef struct mp_result {
     double yy;            /* ||y||^2, FP64 */
     double rr;            /* ||r||^2 at exit, FP64 (from the FP32 residual) */
     int32_t stop_reason;  /* MP_STOP_* */
-    int32_t persistent;   /* 1: the decode ran as one persistent launch (one-bit form) */
+    int32_t persistent;   /* 1: the decode ran as one persistent launch that holds the
+                             whole dictionary on chip (one-bit and small FP32 forms) */
 } mp_result;
 
 /* Optional per-step record, all arrays device memory of `cap` entries.
@@ -209,6 +211,15 @@ mp_status mp_create(mp_ctx** out, const float* psi, int64_t n, int64_t m, int64_
  * non-negative integer in the environment variable MP_SMALL_SPIN_LIMIT, read
  * at each decode; 0 gives up at the first wait) ends the decode with
  * MP_EDEVICE.
+ *
+ * A larger MP_F32 context (N <= 8192, M <= 32768, column norms within 1% of
+ * 1) decodes on correlations carried from step to step by the Gram columns
+ * of the selected atoms, with a pass over the dictionary only when an atom
+ * without one is selected: the same results bit for bit as one launch per
+ * step, which MP_SOLVE_STEP_LAUNCHES selects.  The first such decode
+ * allocates its work buffers on the context (the Gram columns take at most
+ * about a quarter of the dictionary's bytes, or M * 1 KiB if that is more);
+ * where they cannot be allocated the decode takes one launch per step.
  *
  * y, x and r must not overlap.  Errors: MP_EINVAL (NULL ctx/y/x/opts, eps < 0
  * or not finite, max_iters < 0, unknown flags, rescore_k outside 0..8),
@@ -540,7 +551,9 @@ mp_status mp_get_storage(const mp_ctx* ctx, void* codes, float* scales, void* st
  *             launches (at most 64) with one event before each window and one
  *             after it, so the timed launches run as untimed ones do and the
  *             average includes the gaps between consecutive launches (the
- *             persistent one-bit decode: its launch, over its t + 2 steps); OMP
+ *             persistent one-bit decode: its launch, over its t + 2 steps;
+ *             decodes on carried correlations: all their launches together,
+ *             over the steps taken); OMP
  *             times every k-th selection launch on its own; mp_solve_batched
  *             every k-th round's product launch.
  *   avg_ms    host: mean duration of one timed launch in milliseconds

@@ -1,0 +1,88 @@
+// Correlations carried from step to step by Gram columns: shared declarations.
+//
+// After step k took c psi_i off the residual, every correlation changes by
+// c <psi_m, psi_i> (eq. 9 applied to eq. 11), so a step whose atom's Gram
+// column g_i = Psi^T psi_i is known needs no pass over the dictionary.  The
+// decode alternates two kernels on one stream:
+//
+//   pass   (the whole chip) one read of the dictionary gives the correlations
+//          c~ = Psi^T r and up to kGramReq Gram columns, as one matrix
+//          product with kGramReq + 1 right-hand sides on the FP32 matrix
+//          cores; it stays bound by the dictionary's bytes;
+//   steps  (one workgroup per signal) takes MP steps on the carried
+//          correlations until it selects an atom whose Gram column it does
+//          not hold (or the carried error has grown too large, or the run
+//          stops); it then asks for that column and those of the best other
+//          atoms, which are the likely next choices.
+//
+// The carried correlations only shortlist.  `GramBounds` bounds their
+// difference from the exact products, so every atom whose FP32 inner product
+// could be the largest is on the list; the list is scored with the FP32
+// inner product of the stepping form (dot_column_f32), and the winner, its
+// coefficient, the residual, the norm and the stop test are the stepping
+// form's bit for bit.
+//
+// Against one pass per step (whole decodes, to eps = 1e-5): N = 8192,
+// M = 32768, K = 512: 28.5 ms from 376 ms (2,400 steps, 47 passes); N = 2048,
+// M = 8192, K = 128: 2.55 ms from 8.7 ms.  A signal without structure (noise,
+// every step a new atom) is no slower either: the wanted columns cover the
+// next several choices (N = 2048, M = 8192: 8.4 us a step against 15.0;
+// N = 1000, M = 3001: 6.7 against 7.5).
+#pragma once
+
+#include "mp_internal.h"
+
+namespace mp {
+
+constexpr int kGramReq = 15;        // Gram columns per pass (with r: 16 right-hand sides)
+constexpr int kGramMaxCand = 64;    // atoms scored exactly in one step, at most
+constexpr unsigned kGramNone = 0xFFFFu;  // map entry of an atom without a Gram column
+
+// What the steps kernel leaves for the pass, and the other way round.
+struct GramCtl {
+  float err;           // bound on |c~ - <r, psi_m>| (not used after a pass)
+  int nreq;            // Gram columns wanted: atoms req[0 .. nreq)
+  int slot0;           // the first of the nreq slots they go to
+  int used;            // slots in use
+  int req[kGramReq];
+};
+
+// Rounding bounds, all relative to ||r|| (columns of norm at most nrm).
+struct GramBounds {
+  float pass;          // |c~ - <r, psi>| after a pass
+  float col;           // |g~ - <psi_i, psi_m>|
+  float step;          // added per step: r's and c~'s own rounding
+  float dot;           // |dot_column_f32 - <r, psi>|
+};
+
+// One signal's decode.
+struct GramProb {
+  const float* psi;    // ld x m FP32 columns
+  int64_t ld, n, m;
+  int64_t mp;          // stride of the Gram columns, >= the steps kernel's threads x share
+  float* c;            // mp carried correlations (written by the pass)
+  float* g;            // slots x mp Gram columns
+  uint16_t* map;       // m: slot of each atom's Gram column, or kGramNone
+  int slots;
+  float* rhs;          // 16 x ld: a pass's right-hand sides in operand order
+  float* r;            // ld floats
+  float* x;
+  DevState* st;        // pad[0]: the decode gave up (the host runs the stepping form)
+  GramCtl* ctl;
+};
+
+// Threads and correlations per thread of the steps kernel for m atoms and
+// columns of ld; threads 0 where it does not apply.
+struct GramShape {
+  int threads, per_thread;
+};
+GramShape gram_shape(int64_t ld, int64_t m);
+GramBounds gram_bounds(int64_t n, double max_norm);
+
+// One pass (first: with r only, and the slot map cleared), then the steps it
+// allows.  Both return at once when the state says the run is over.
+hipError_t launch_gram_pass(const GramProb& p, int num_cus, bool first, hipStream_t s);
+hipError_t launch_gram_steps(const GramProb& p, const GramShape& sh, const GramBounds& b,
+                             long long max_iters, bool first, mp_trace tr, hipStream_t s);
+
+}  // namespace mp

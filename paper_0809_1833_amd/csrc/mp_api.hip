@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "k_gram.h"
 #include "mp_internal.h"
 
 namespace {
@@ -95,8 +96,23 @@ void free_omp(mp_ctx* c) {
   b = mp::OmpBufs{};
 }
 
+void free_gram(mp_ctx* c) {
+  (void)hipFree(c->gram_c);
+  (void)hipFree(c->gram_g);
+  (void)hipFree(c->gram_map);
+  (void)hipFree(c->gram_rhs);
+  (void)hipFree(c->gram_ctl);
+  c->gram_c = nullptr;
+  c->gram_g = nullptr;
+  c->gram_map = nullptr;
+  c->gram_rhs = nullptr;
+  c->gram_ctl = nullptr;
+  c->gram_slots = 0;
+}
+
 void free_ctx(mp_ctx* c) {
   if (!c) return;
+  free_gram(c);
   free_batched(c);
   free_ragged(c);
   free_omp(c);
@@ -136,6 +152,13 @@ mp_status open_device(int& dev, hipDeviceProp_t& prop) {
     return fail(nullptr, MP_EUNSUPPORTED, std::string("device is ") + prop.gcnArchName +
                                               ", this library is built for gfx950");
   return MP_OK;
+}
+
+// The largest column norm of the FP64 squared norms.
+double largest_norm(const std::vector<double>& norm2) {
+  double v = 0.0;
+  for (double q : norm2) v = std::max(v, q);
+  return std::sqrt(v);
 }
 
 // Eq. 4 on the FP64 squared column norms: finite always, 1 within kNormTol
@@ -380,9 +403,90 @@ mp_status enqueue_result(mp_ctx* c, const mp::DevState* st, hipStream_t s, int p
   return MP_OK;
 }
 
+// The buffers of the decode on carried correlations, made by the first
+// decode that takes it: Gram columns for at most a quarter of the
+// dictionary's bytes (n / 4 columns; a decode of K atoms needs little more
+// than K of them, and MP recovers K well below n / 4), at least 256.
+// Returns false where the form does not apply (size, column norms that are
+// not near 1) or the memory is not there: the decode then takes one launch
+// per step.
+bool ensure_gram(mp_ctx* c, hipStream_t s) {
+  if (c->gram_tried) return c->gram_slots > 0;
+  c->gram_tried = true;
+  const mp::GramShape sh = mp::gram_shape(c->ld, c->m);
+  if (sh.threads == 0 || !(c->max_norm > 0.99) || !(c->max_norm < 1.01)) return false;
+  c->gram_mp = static_cast<int64_t>(sh.threads) * sh.per_thread;
+  const int64_t want = std::max<int64_t>(256, c->n / 4);
+  const int64_t slots = round_up(std::min<int64_t>(want, c->m) + mp::kGramReq, 16);
+  const size_t row = static_cast<size_t>(c->gram_mp) * sizeof(float);
+  if (hipMalloc(&c->gram_c, row) != hipSuccess ||
+      hipMalloc(&c->gram_g, row * static_cast<size_t>(slots)) != hipSuccess ||
+      hipMalloc(&c->gram_map, sizeof(uint16_t) * static_cast<size_t>(c->m)) != hipSuccess ||
+      hipMalloc(&c->gram_rhs, sizeof(float) * 16 * static_cast<size_t>(c->ld)) != hipSuccess ||
+      hipMalloc(&c->gram_ctl, sizeof(mp::GramCtl)) != hipSuccess ||
+      // entries past m stay zero (the pass writes the tiles of m)
+      hipMemsetAsync(c->gram_c, 0, row, s) != hipSuccess ||
+      hipMemsetAsync(c->gram_g, 0, row * static_cast<size_t>(slots), s) != hipSuccess) {
+    (void)hipGetLastError();
+    free_gram(c);
+    return false;
+  }
+  c->gram_slots = static_cast<int>(slots);
+  return true;
+}
+
+// The decode on carried correlations (k_gram.h), after the init kernel: pairs
+// of a pass and the steps it allows, the host keeping two pairs in flight.
+// `gave_up` is set when the device asks for the stepping form instead (no
+// shortlist narrow enough, or norms outside the bounds' range).
+mp_status solve_gram(mp_ctx* c, float* x, const mp_opts* opts, const mp_trace& tr, hipStream_t s,
+                     bool& gave_up) {
+  const mp::GramShape sh = mp::gram_shape(c->ld, c->m);
+  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm);
+  const mp::GramProb p{c->psi32, c->ld, c->n, c->m, c->gram_mp, c->gram_c, c->gram_g, c->gram_map,
+                       c->gram_slots, c->gram_rhs, c->r_work, x, c->st,
+                       static_cast<mp::GramCtl*>(c->gram_ctl)};
+  gave_up = false;
+  const bool timed = c->profiling;
+  if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
+  // a pair takes at least one step, unless it only renews the correlations,
+  // which the next one then follows with a step
+  const long long most = 2 * static_cast<long long>(opts->max_iters) + 2;
+  long long issued = 0, seen = 0;
+  bool over = opts->max_iters <= 0;
+  while (!over && seen < most) {
+    while (issued < most && issued - seen < 2) {
+      HIP_TRY(c, mp::launch_gram_pass(p, c->num_cus, issued == 0, s));
+      HIP_TRY(c, mp::launch_gram_steps(p, sh, bounds, opts->max_iters, issued == 0, tr, s));
+      const int k = static_cast<int>(issued & 1);
+      HIP_TRY(c, hipMemcpyAsync(&c->h_st[1 + k], c->st, sizeof(mp::DevState),
+                                hipMemcpyDeviceToHost, s));
+      HIP_TRY(c, hipEventRecord(c->done_ev[k], s));
+      ++issued;
+    }
+    const int k = static_cast<int>(seen & 1);
+    HIP_TRY(c, hipEventSynchronize(c->done_ev[k]));
+    ++seen;
+    over = c->h_st[1 + k].done != 0;
+    gave_up = c->h_st[1 + k].pad[0] != 0;
+  }
+  if (timed) {
+    // the decode's time on the device over the steps it took
+    HIP_TRY(c, hipEventRecord(c->ev[1], s));
+    HIP_TRY(c, hipEventSynchronize(c->ev[1]));
+    float ms = 0.f;
+    if (hipEventElapsedTime(&ms, c->ev[0], c->ev[1]) == hipSuccess) {
+      const mp::DevState& d = c->h_st[1 + static_cast<int>((seen - 1) & 1)];
+      c->prof_ms = ms;
+      c->prof_launches = seen > 0 && d.t > 0 ? d.t : 1;
+    }
+  }
+  return MP_OK;
+}
+
 mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_opts* opts,
                         mp_result* res, const mp_trace& tr, hipStream_t s, const CarriedBufs& b,
-                        bool allow_one_launch) {
+                        bool allow_one_launch, bool allow_gram) {
   const bool async = (opts->flags & MP_SOLVE_ASYNC) != 0;
   HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
                              static_cast<long long>(opts->max_iters), s));
@@ -417,6 +521,22 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
     const mp_status fs = finish_result(c, res);
     if (fs == MP_OK && res) res->persistent = 1;
     return fs;
+  }
+  if (allow_gram && c->storage == MP_F32 && !async && !(opts->flags & MP_SOLVE_STEP_LAUNCHES) &&
+      ensure_gram(c, s)) {
+    bool gave_up = false;
+    const mp_status gs = solve_gram(c, x, opts, tr, s, gave_up);
+    if (gs != MP_OK) return gs;
+    if (!gave_up) {
+      if (r) HIP_TRY(c, mp::launch_copy_selected(b.r_work, c->ld, c->n, b.st, r, s));
+      HIP_TRY(c, hipMemcpyAsync(c->h_st, b.st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
+      HIP_TRY(c, hipStreamSynchronize(s));
+      return finish_result(c, res);
+    }
+    c->prof_ms = 0.0;
+    c->prof_launches = 0;
+    HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
+                               static_cast<long long>(opts->max_iters), s));
   }
   long long k = 0;
   const long long T = opts->max_iters;
@@ -584,6 +704,7 @@ mp_status mp_create(mp_ctx** out, const float* psi, int64_t n, int64_t m, int64_
     std::string msg;
     const mp_status ns = check_norms(norm2, flags, msg);
     if (ns != MP_OK) return bail(ns, msg);
+    c->max_norm = largest_norm(norm2);
   }
   // Reduced-precision copy the correlation pass streams (same padded layout).
   if (storage == MP_BF16 || storage == MP_FP8_E4M3) {
@@ -680,7 +801,7 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
 
   if (c->storage != MP_SIGN1)
     return solve_carried(c, y, x, r, opts, res, tr, s,
-                         CarriedBufs{c->st, c->r_work, c->partials, c->bal}, true);
+                         CarriedBufs{c->st, c->r_work, c->partials, c->bal}, true, true);
 
   HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st, opts->eps,
                              static_cast<long long>(opts->max_iters), s));
@@ -790,7 +911,7 @@ mp_status mp_solve_noalloc(mp_ctx* ctx, const float* y, float* x, float* r, cons
                                    reinterpret_cast<float*>(b + mp::kNoAllocR),
                                    reinterpret_cast<uint64_t*>(b + mp::kNoAllocKeys),
                                    reinterpret_cast<mp::BalState*>(b + mp::kNoAllocBal)},
-                       false);
+                       false, false);
 }
 
 mp_status mp_solve_result(mp_ctx* ctx, mp_result* res) {

@@ -395,5 +395,16 @@ struct mp_ctx {
   std::vector<unsigned char> r_graph_key;
   // OMP decode buffers (grown on demand)
   mp::OmpBufs omp;
+  // the decode on carried correlations (k_gram.h): largest column norm (0: not
+  // known) and buffers made by the first decode that takes it
+  double max_norm = 0.0;
+  bool gram_tried = false;       // allocation attempted (once)
+  int gram_slots = 0;            // Gram columns held (0: not available)
+  int64_t gram_mp = 0;           // their stride
+  float* gram_c = nullptr;       // carried correlations, gram_mp
+  float* gram_g = nullptr;       // gram_slots x gram_mp
+  uint16_t* gram_map = nullptr;  // m
+  float* gram_rhs = nullptr;     // 16 x ld
+  void* gram_ctl = nullptr;      // mp::GramCtl
   std::string err;
 };
