@@ -212,8 +212,8 @@ mp_status mp_create(mp_ctx** out, const float* psi, int64_t n, int64_t m, int64_
  * at each decode; 0 gives up at the first wait) ends the decode with
  * MP_EDEVICE.
  *
- * A larger MP_F32 context (N <= 8192, M <= 32768, column norms within 1% of
- * 1) decodes on correlations carried from step to step by the Gram columns
+ * A larger MP_F32 context (M <= 32768, 8 N + 2 M <= 153600 with N rounded up
+ * to a multiple of 64, column norms within 1% of 1) decodes on correlations carried from step to step by the Gram columns
  * of the selected atoms, with a pass over the dictionary only when an atom
  * without one is selected: the same results bit for bit as one launch per
  * step, which MP_SOLVE_STEP_LAUNCHES selects.  The first such decode
@@ -350,10 +350,15 @@ mp_status mp_create_f64(mp_ctx** out, const double* psi, int64_t n, int64_t m, i
  *   y        device: N doubles, not modified
  *   x        device: M doubles, overwritten with x~
  *   r        device: N doubles or NULL; receives the final residual
- *   opts     host: eps, max_iters (rescore_k is ignored), flags 0 (or
- *            MP_SOLVE_STEP_LAUNCHES, which has no effect here)
+ *   opts     host: eps, max_iters (rescore_k is ignored), flags 0 or
+ *            MP_SOLVE_STEP_LAUNCHES
  *   res      host or NULL (rr is the FP64 norm of the FP64 residual)
  *   trace    host struct of device arrays, or NULL (see mp_trace_f64)
+ *
+ * Decodes on carried correlations as mp_solve does (M <= 32768, N <= 9600,
+ * column norms within 1% of 1), with the same results bit for bit as one
+ * launch per step; the carried correlations are FP32 and only shortlist the
+ * atoms that are scored in FP64.
  *
  * y, x and r must not overlap.  Errors: MP_EINVAL (not an MP_F64 context,
  * NULL ctx/y/x/opts, bad opts), MP_ENONFINITE (y holds NaN/Inf),

@@ -27,7 +27,8 @@
 // M = 8192, K = 128: 2.55 ms from 8.7 ms.  A signal without structure (noise,
 // every step a new atom) is no slower either: the wanted columns cover the
 // next several choices (N = 2048, M = 8192: 8.4 us a step against 15.0;
-// N = 1000, M = 3001: 6.7 against 7.5).
+// N = 1000, M = 3001: 6.7 against 7.5).  FP64, N = 8192, M = 32768,
+// K = 512: 43.8 ms from 768 ms.
 #pragma once
 
 #include "mp_internal.h"
@@ -55,9 +56,12 @@ struct GramBounds {
   float dot;           // |dot_column_f32 - <r, psi>|
 };
 
-// One signal's decode.
+// One signal's decode; T = float or double, the type of the dictionary, r and
+// x~ (the carried correlations and Gram columns are float for both: they
+// only shortlist).
+template <typename T>
 struct GramProb {
-  const float* psi;    // ld x m FP32 columns
+  const T* psi;        // ld x m columns
   int64_t ld, n, m;
   int64_t mp;          // stride of the Gram columns, >= the steps kernel's threads x share
   float* c;            // mp carried correlations (written by the pass)
@@ -65,24 +69,36 @@ struct GramProb {
   uint16_t* map;       // m: slot of each atom's Gram column, or kGramNone
   int slots;
   float* rhs;          // 16 x ld: a pass's right-hand sides in operand order
-  float* r;            // ld floats
-  float* x;
+  T* r;                // ld elements
+  T* x;
   DevState* st;        // pad[0]: the decode gave up (the host runs the stepping form)
   GramCtl* ctl;
 };
 
 // Threads and correlations per thread of the steps kernel for m atoms and
-// columns of ld; threads 0 where it does not apply.
+// columns of ld elements of `esize` bytes; threads 0 where it does not apply.
 struct GramShape {
   int threads, per_thread;
 };
-GramShape gram_shape(int64_t ld, int64_t m);
-GramBounds gram_bounds(int64_t n, double max_norm);
+GramShape gram_shape(int64_t ld, int64_t m, int esize);
+GramBounds gram_bounds(int64_t n, double max_norm, bool f64);
+
+template <typename T>
+struct GramTrace {
+  typedef mp_trace type;
+};
+template <>
+struct GramTrace<double> {
+  typedef mp_trace_f64 type;
+};
 
 // One pass (first: with r only, and the slot map cleared), then the steps it
 // allows.  Both return at once when the state says the run is over.
-hipError_t launch_gram_pass(const GramProb& p, int num_cus, bool first, hipStream_t s);
-hipError_t launch_gram_steps(const GramProb& p, const GramShape& sh, const GramBounds& b,
-                             long long max_iters, bool first, mp_trace tr, hipStream_t s);
+template <typename T>
+hipError_t launch_gram_pass(const GramProb<T>& p, int num_cus, bool first, hipStream_t s);
+template <typename T>
+hipError_t launch_gram_steps(const GramProb<T>& p, const GramShape& sh, const GramBounds& b,
+                             long long max_iters, bool first, typename GramTrace<T>::type tr,
+                             hipStream_t s);
 
 }  // namespace mp

@@ -3,6 +3,7 @@
 
 #include "k_common.h"
 #include "k_gram.h"
+#include "k_key2.h"
 
 namespace mp {
 
@@ -18,7 +19,7 @@ namespace mp {
 // (N = 8192, M = 32768: 266 us).  Each wave therefore turns its 16 atoms x 64
 // rows over in 4 KB of LDS of its own (no barriers; float4 f of atom a at
 // position f ^ a of its row, so that neither side meets bank conflicts),
-// with the next two pieces in flight in registers.  The right-hand sides
+// with the next pieces (8 KB) in flight in registers.  The right-hand sides
 // are laid out in operand order by k_gram_pack and come from L2.
 //
 // Each 16-atom tile's rows are split over `split` waves of the workgroup, so
@@ -26,6 +27,21 @@ namespace mp {
 // in a fixed order.  Two FP32 chains (even and odd steps) are cut every
 // 2 kPassRows rows and the cuts are summed in FP64, which keeps the rounding
 // bound of the products at that of a kChain-term sum.
+template <typename T>
+struct Vec16 {
+  typedef v4f type;
+};
+template <>
+struct Vec16<double> {
+  typedef double type __attribute__((ext_vector_type(2)));
+};
+// 16 bytes of a column as floats.
+__device__ inline void put_floats(float* p, const v4f& v) { *reinterpret_cast<v4f*>(p) = v; }
+__device__ inline void put_floats(float* p, const Vec16<double>::type& v) {
+  typedef float v2f __attribute__((ext_vector_type(2)));
+  *reinterpret_cast<v2f*>(p) = v2f{static_cast<float>(v.x), static_cast<float>(v.y)};
+}
+
 constexpr int kPassThreads = 512;
 constexpr int kPassWaves = kPassThreads / kWave;
 constexpr int kPassRows = 64;           // rows of a piece: 4 steps of 16
@@ -34,7 +50,8 @@ constexpr int kChain = kPassRows;       // rows summed in one FP32 chain, at mos
 // The right-hand sides in operand order: float4 s * 64 + 16 q + i holds rows
 // 16 s + 4 q .. + 3 of right-hand side i (r, the wanted columns, then zeros).
 // The first pass also clears the slot map.
-__global__ __launch_bounds__(256) void k_gram_pack(GramProb p, int first) {
+template <typename T>
+__global__ __launch_bounds__(256) void k_gram_pack(GramProb<T> p, int first) {
   if (p.st->done) return;
   const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int64_t all = static_cast<int64_t>(gridDim.x) * 256;
@@ -44,8 +61,9 @@ __global__ __launch_bounds__(256) void k_gram_pack(GramProb p, int first) {
     const int64_t row4 = e / 64 * 4 + e % 64 / 16;  // float4 of the column
     v4f v = v4f{0.f, 0.f, 0.f, 0.f};
     if (i <= nreq) {
-      const float* src = i == 0 ? p.r : p.psi + static_cast<int64_t>(p.ctl->req[i - 1]) * p.ld;
-      v = reinterpret_cast<const v4f*>(src)[row4];
+      const T* src = i == 0 ? p.r : p.psi + static_cast<int64_t>(p.ctl->req[i - 1]) * p.ld;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = static_cast<float>(src[4 * row4 + k]);
     }
     reinterpret_cast<v4f*>(p.rhs)[e] = v;
   }
@@ -53,7 +71,13 @@ __global__ __launch_bounds__(256) void k_gram_pack(GramProb p, int first) {
     for (int64_t e = t; e < p.m; e += all) p.map[e] = static_cast<uint16_t>(kGramNone);
 }
 
-__global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_gram_pass(GramProb p, int split, int first) {
+template <typename T>
+__global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_gram_pass(
+    GramProb<T> p, int split, int first) {
+  constexpr int NL = kPassRows * 16 * sizeof(T) / 16 / kWave;  // 16-byte loads of a piece
+  constexpr int LPA = kWave / (16 / NL);                        // lanes of a load per atom
+  constexpr int D = sizeof(T) == 4 ? 2 : 1;  // pieces in flight: 8 KB per wave
+  typedef typename Vec16<T>::type vec;
   if (p.st->done) return;
   __shared__ v4f turn[kPassWaves][16 * 16];  // then the split sums
   const int lane = threadIdx.x % kWave;
@@ -65,32 +89,35 @@ __global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(4)
   const int nreq = first ? 0 : p.ctl->nreq;
   double tot[4] = {0.0, 0.0, 0.0, 0.0};
   if (m0 < p.m) {
-    // load j of a piece: atoms 4 j + q, float4 i of their 16
-    const v4f* a[4];
-    int put[4];
+    // load j of a piece: atoms j 64 / LPA + lane / LPA, 16 bytes lane % LPA
+    const vec* a[NL];
+    int put[NL];  // in floats
+    const int li = lane % LPA;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int at = 4 * j + q;
+    for (int j = 0; j < NL; ++j) {
+      const int at = j * (kWave / LPA) + lane / LPA;
       const int64_t atom = m0 + at < p.m ? m0 + at : p.m - 1;
-      a[j] = reinterpret_cast<const v4f*>(p.psi + atom * p.ld) + i;
-      put[j] = at * 16 + (i ^ at);
+      a[j] = reinterpret_cast<const vec*>(p.psi + atom * p.ld) + li;
+      const int f = li * (16 / static_cast<int>(sizeof(T)));  // first row of the 16 bytes
+      put[j] = 4 * (at * 16 + ((f / 4) ^ at)) + f % 4;
     }
     const v4f* b = reinterpret_cast<const v4f*>(p.rhs) + lane;
     v4f* my = turn[wave];
     const int pieces = static_cast<int>(p.ld / kPassRows);
     const int k0 = pieces * part / split, k1 = pieces * (part + 1) / split;
     v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
-    v4f va[2][4], vb[2][4];
-    auto load = [&](v4f(&x)[4], v4f(&y)[4], int k) {
+    vec va[D][NL];
+    v4f vb[D][4];
+    auto load = [&](vec(&x)[NL], v4f(&y)[4], int k) {
       const int kk = k < k1 ? k : k1 - 1;  // past the end: read again, not used
 #pragma unroll
-      for (int j = 0; j < 4; ++j) x[j] = __builtin_nontemporal_load(a[j] + 16 * kk);
+      for (int j = 0; j < NL; ++j) x[j] = __builtin_nontemporal_load(a[j] + LPA * kk);
 #pragma unroll
       for (int j = 0; j < 4; ++j) y[j] = b[(4 * kk + j) * 64];
     };
-    auto use = [&](v4f(&x)[4], v4f(&y)[4], int next) {
+    auto use = [&](vec(&x)[NL], v4f(&y)[4], int next) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) my[put[j]] = x[j];
+      for (int j = 0; j < NL; ++j) put_floats(reinterpret_cast<float*>(my) + put[j], x[j]);
       v4f rb[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) rb[j] = y[j];
@@ -114,18 +141,15 @@ __global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(4)
       }
     };
     if (k0 < k1) {
-      load(va[0], vb[0], k0);
-      load(va[1], vb[1], k0 + 1);
-      int k = k0;
-      for (; k + 1 < k1; k += 2) {
-        use(va[0], vb[0], k + 2);
-        use(va[1], vb[1], k + 3);
-        flush();
-      }
-      if (k < k1) {
-        use(va[0], vb[0], k1);
-        flush();
-      }
+#pragma unroll
+      for (int d = 0; d < D; ++d) load(va[d], vb[d], k0 + d);
+      for (int k = k0; k < k1; k += D)
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+          if (k + d < k1) {
+            use(va[d], vb[d], k + d + D);
+            if (d == D - 1 || k + d + 1 >= k1) flush();
+          }
     }
   }
   __syncthreads();
@@ -148,9 +172,10 @@ __global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(4)
     *reinterpret_cast<v4f*>(p.g + static_cast<int64_t>(p.ctl->slot0 + i - 1) * p.mp + base) = o;
 }
 
-hipError_t launch_gram_pass(const GramProb& p, int num_cus, bool first, hipStream_t s) {
+template <typename T>
+hipError_t launch_gram_pass(const GramProb<T>& p, int num_cus, bool first, hipStream_t s) {
   const int64_t packs = p.ld * 4 / 256;  // ld is a multiple of 64
-  k_gram_pack<<<dim3(static_cast<unsigned>(packs)), dim3(256), 0, s>>>(p, first ? 1 : 0);
+  k_gram_pack<T><<<dim3(static_cast<unsigned>(packs)), dim3(256), 0, s>>>(p, first ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t tiles = (p.m + 15) / 16;
@@ -158,25 +183,30 @@ hipError_t launch_gram_pass(const GramProb& p, int num_cus, bool first, hipStrea
   int split = 1;
   while (split < kPassWaves && tiles * split / kPassWaves < 2 * num_cus) split *= 2;
   const int per = kPassWaves / split;
-  k_gram_pass<<<dim3(static_cast<unsigned>((tiles + per - 1) / per)), dim3(kPassThreads), 0, s>>>(
+  k_gram_pass<T><<<dim3(static_cast<unsigned>((tiles + per - 1) / per)), dim3(kPassThreads), 0, s>>>(
       p, split, first ? 1 : 0);
   return hipGetLastError();
 }
 
+template hipError_t launch_gram_pass<float>(const GramProb<float>&, int, bool, hipStream_t);
+template hipError_t launch_gram_pass<double>(const GramProb<double>&, int, bool, hipStream_t);
+
 // The bounds (u = 2^-24): a product of the pass is a chain of at most kChain
-// terms, rounded once more to FP32; dot_column_f32 is two
-// lane chains of ld / 128 terms, then 7 additions.  Each is at most
-// (terms + additions) u sum |a b| <= (...) u ||a|| ||b||; a step adds r's
-// rounding (u ||r'|| against a unit column) and c~'s own (u |c~|).
-GramBounds gram_bounds(int64_t n, double max_norm) {
+// terms, rounded once more to FP32 (and, from an FP64 dictionary, both
+// operands rounded to FP32 first); dot_column_f32 is two lane chains of
+// ld / 128 terms, then 7 additions (in FP64 its rounding is far below the
+// rest).  Each is at most (terms + additions) u sum |a b| <= (...) u ||a||
+// ||b||; a step adds r's rounding (u ||r'|| against a unit column), c~'s own
+// (u |c~|) and that of the coefficient (u |c|, in col).
+GramBounds gram_bounds(int64_t n, double max_norm, bool f64) {
   const double u = 1.0 / 16777216.0, nn = static_cast<double>(n + 64);
   const double slack = 1.01;
-  const double prod = (std::min<double>(nn, kChain) + 4) * u * slack;
+  const double prod = (std::min<double>(nn, kChain) + 7) * u * slack;
   GramBounds b;
   b.pass = static_cast<float>(prod * max_norm);
   b.col = static_cast<float>(prod * max_norm * max_norm);
   b.step = static_cast<float>(2.1 * u * max_norm * slack);
-  b.dot = static_cast<float>((nn / 128 + 10) * u * max_norm * slack);
+  b.dot = static_cast<float>((f64 ? 0.1 : nn / 128 + 10) * u * max_norm * slack);
   return b;
 }
 
@@ -197,8 +227,7 @@ GramBounds gram_bounds(int64_t n, double max_norm) {
 // (float4 i belongs to thread i mod 1024 of a 1024-thread workgroup: here to
 // wave i / 64 mod 16 in that numbering, and a wave of this kernel plays
 // 1024 / NT of those in turn).
-constexpr int kStepLd4 = 4;    // float4s of a column per data thread, at most
-constexpr int kStepChain = 16; // float4s of a chain's column in flight per lane
+constexpr int kStepChain = 16; // 16-byte chunks of a chain's column in flight per lane
 
 // Row-wise maximum of a non-negative float: afterwards every lane of a
 // 16-lane row holds the row's maximum.
@@ -217,15 +246,52 @@ __device__ inline float wave_max_f32(float v) {
                          __builtin_fmaxf(lane_f32(v, 32), lane_f32(v, 48)));
 }
 
-// dot_column_f32 (the same chains, so the same result) with fewer loads in
-// flight, for a kernel whose registers hold the carried correlations.
-__device__ inline float dot_column_narrow(const v4f* __restrict__ p,
-                                          const v4f* __restrict__ r, int ld4, int lane) {
-  const int h0 = ld4 / 2;
-  float acc_a = 0.0f, acc_b = 0.0f;
-  int i = lane;
-  while (i + kWave * 1 < h0) dot_block2<2, false>(p, r, h0, i, acc_a, acc_b);
-  if (i < h0) dot_block2<1, false>(p, r, h0, i, acc_a, acc_b);
+// acc += <a, b> over 16 bytes, in the order of the stepping forms' products.
+__device__ inline void fma_chunk(const v4f& a, const v4f& b, float& acc) {
+  acc = __builtin_fmaf(a.x, b.x, acc);
+  acc = __builtin_fmaf(a.y, b.y, acc);
+  acc = __builtin_fmaf(a.z, b.z, acc);
+  acc = __builtin_fmaf(a.w, b.w, acc);
+}
+typedef Vec16<double>::type v2dd;
+__device__ inline void fma_chunk(const v2dd& a, const v2dd& b, double& acc) {
+  acc = __builtin_fma(a.x, b.x, acc);
+  acc = __builtin_fma(a.y, b.y, acc);
+}
+// r - c psi over 16 bytes, and the sum of squares added to s (the stepping
+// forms' order).
+__device__ inline v4f update_chunk(float c, const v4f& a, const v4f& r, double& s) {
+  v4f o;
+  o.x = __builtin_fmaf(-c, a.x, r.x);
+  o.y = __builtin_fmaf(-c, a.y, r.y);
+  o.z = __builtin_fmaf(-c, a.z, r.z);
+  o.w = __builtin_fmaf(-c, a.w, r.w);
+  s += static_cast<double>(o.x) * o.x + static_cast<double>(o.y) * o.y +
+       (static_cast<double>(o.z) * o.z + static_cast<double>(o.w) * o.w);
+  return o;
+}
+__device__ inline v2dd update_chunk(double c, const v2dd& a, const v2dd& r, double& s) {
+  v2dd o;
+  o.x = __builtin_fma(-c, a.x, r.x);
+  o.y = __builtin_fma(-c, a.y, r.y);
+  s = __builtin_fma(o.x, o.x, s);
+  s = __builtin_fma(o.y, o.y, s);
+  return o;
+}
+
+// dot_column_f32 / dot_column_f64 (the same chains, so the same result) with
+// few loads in flight, for a kernel whose registers hold the correlations.
+template <typename T, typename V>
+__device__ inline T dot_column_narrow(const V* __restrict__ p, const V* __restrict__ r, int ldu,
+                                      int lane) {
+  const int h0 = ldu / 2;
+  T acc_a = 0, acc_b = 0;
+#pragma unroll 2
+  for (int i = lane; i < h0; i += kWave) {
+    const V a = p[i], b = p[h0 + i];
+    fma_chunk(a, r[i], acc_a);
+    fma_chunk(b, r[h0 + i], acc_b);
+  }
   return wave_sum(acc_a + acc_b);
 }
 
@@ -238,14 +304,14 @@ __device__ inline float max_abs4(float m, const v4f& v) {
 }
 
 // LDS of the steps kernel beside r, the column and the slot map.
-template <int NT, int CPT>
+template <typename T, int NT, int CPT>
 struct StepShared {
   static constexpr int W = NT / kWave;
   double red[16];
-  uint64_t keys[kGramMaxCand];
+  Key2 keys[kGramMaxCand];
   v4f spread[W][CPT / 4];
   float wmax[16];
-  float chain[2][kWave];
+  T chain[2][kWave];
   int n[2];
   int cand[kGramMaxCand];
   int want[(kGramReq + W - 1) / W * W];
@@ -254,29 +320,34 @@ struct StepShared {
 // The kernel's program for the data waves (DATA) and for the two chain waves:
 // one source, so that both take every barrier and every decision alike, and
 // two copies, so that the chain waves' registers hold no correlations.
-template <int NT, int CPT, bool DATA>
-__device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long max_iters, int first,
-                           const mp_trace& tr, v4f* r_lds, StepShared<NT, CPT>& sh) {
+template <typename T, int NT, int CPT, bool DATA>
+__device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long max_iters,
+                           int first, const typename GramTrace<T>::type& tr,
+                           typename Vec16<T>::type* r_lds, StepShared<T, NT, CPT>& sh) {
+  typedef typename Vec16<T>::type V16;
+  constexpr int E = 16 / sizeof(T);
+  // the slot map is in LDS beside r and the column where there is room (FP32)
+  constexpr bool map_lds = sizeof(T) == 4;
   constexpr int W = NT / kWave;    // data waves; waves W and W + 1 run the chains
   constexpr int V = 1024 / NT;     // 1024-thread waves each data wave plays
   constexpr int NA = NT + 2 * kWave;
   constexpr int C4 = CPT / 4;
   constexpr int TOP = (kGramReq + W - 1) / W;  // columns each wave proposes
   DevState* st = p.st;
-  v4f* s_col = r_lds + p.ld / 4;
-  uint16_t* s_map = reinterpret_cast<uint16_t*>(s_col + p.ld / 4);
+  V16* s_col = r_lds + p.ld / E;
+  uint16_t* s_map = map_lds ? reinterpret_cast<uint16_t*>(s_col + p.ld / E) : p.map;
   float* s_wmax = sh.wmax;
   double* s_red = sh.red;
-  float(*s_chain)[kWave] = sh.chain;
+  T(*s_chain)[kWave] = sh.chain;
   int* s_n = sh.n;
   int* s_cand = sh.cand;
-  uint64_t* s_keys = sh.keys;
+  Key2* s_keys = sh.keys;
   int* s_want = sh.want;
   v4f(*s_spread)[CPT / 4] = sh.spread;
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int tid = static_cast<int>(threadIdx.x);
-  const int ld4 = static_cast<int>(p.ld / 4), h0 = ld4 / 2;
+  const int ldu = static_cast<int>(p.ld / E), h0 = ldu / 2;
   const int m = static_cast<int>(p.m);
   constexpr bool data = DATA;
 
@@ -293,8 +364,9 @@ __device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long ma
   double rr = st->rr;
   const double thr = st->thr;
   int used = first ? 0 : p.ctl->used;
-  for (int i = tid; i < ld4; i += NA) r_lds[i] = reinterpret_cast<const v4f*>(p.r)[i];
-  for (int i = tid; i < m; i += NA) s_map[i] = p.map[i];
+  for (int i = tid; i < ldu; i += NA) r_lds[i] = reinterpret_cast<const V16*>(p.r)[i];
+  if constexpr (map_lds)
+    for (int i = tid; i < m; i += NA) s_map[i] = p.map[i];
   if (tid < 16) {
     s_wmax[tid] = 0.0f;
     s_red[tid] = 0.0;
@@ -354,29 +426,29 @@ __device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long ma
 
     // ---- the winner (largest FP32 |c|, smallest index) and its coefficient --
     int win;
-    float c = 0.0f;
+    T c = 0;
     if (nc > 1) {
       for (int q = wave; q < nc; q += W + 2) {
         const int a = s_cand[q];
-        const float v = dot_column_narrow(
-            reinterpret_cast<const v4f*>(p.psi + static_cast<int64_t>(a) * p.ld), r_lds, ld4,
+        const T v = dot_column_narrow<T>(
+            reinterpret_cast<const V16*>(p.psi + static_cast<int64_t>(a) * p.ld), r_lds, ldu,
             lane);
-        if (lane == 0) s_keys[q] = make_key(v, a);
+        if (lane == 0) s_keys[q] = make_key2(static_cast<double>(v), a);
       }
       __syncthreads();
-      const uint64_t best = wave_max(lane < nc ? s_keys[lane] : 0ull);
-      win = key_index(best);
-      c = key_value(best);
+      const Key2 best = wave_max_key2(lane < nc ? s_keys[lane] : Key2{0, 0});
+      win = key2_index(best);
+      c = static_cast<T>(key2_value(best));
     } else {
       win = s_cand[0];
     }
     win = __builtin_amdgcn_readfirstlane(win);
     // every request of the step at once
-    const v4f* col = reinterpret_cast<const v4f*>(p.psi + static_cast<int64_t>(win) * p.ld);
+    const V16* col = reinterpret_cast<const V16*>(p.psi + static_cast<int64_t>(win) * p.ld);
     const unsigned slot = static_cast<unsigned>(
         __builtin_amdgcn_readfirstlane(static_cast<int>(s_map[win])));
     const bool have = slot != kGramNone;
-    float x_old = 0.0f;
+    T x_old = 0;
     v4f g[C4];
     if constexpr (data) {
       const v4f* gp =
@@ -388,9 +460,9 @@ __device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long ma
       // lane chain of the product
       if (tid == NT) x_old = p.x[win];
       const int off = wave == W ? 0 : h0;
-      float acc = 0.0f;
+      T acc = 0;
       for (int base = lane; base < h0; base += kStepChain * kWave) {
-        v4f ch[kStepChain];
+        V16 ch[kStepChain];
 #pragma unroll
         for (int u = 0; u < kStepChain; ++u) {
           const int i = base + kWave * u;
@@ -401,12 +473,8 @@ __device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long ma
         for (int u = 0; u < kStepChain; ++u) {
           const int i = base + kWave * u;
           if (i < h0) {
-            const v4f b = r_lds[off + i];
             s_col[off + i] = ch[u];
-            acc = __builtin_fmaf(ch[u].x, b.x, acc);
-            acc = __builtin_fmaf(ch[u].y, b.y, acc);
-            acc = __builtin_fmaf(ch[u].z, b.z, acc);
-            acc = __builtin_fmaf(ch[u].w, b.w, acc);
+            fma_chunk(ch[u], r_lds[off + i], acc);
           }
         }
       }
@@ -414,7 +482,7 @@ __device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long ma
     }
     __syncthreads();
     if (nc == 1) c = wave_sum(s_chain[0][lane] + s_chain[1][lane]);
-    if (c == 0.0f) {
+    if (c == 0) {
       stop = MP_STOP_STALLED;
       break;
     }
@@ -424,32 +492,24 @@ __device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long ma
       double sq[V];
 #pragma unroll
       for (int v = 0; v < V; ++v) sq[v] = 0.0;
+      for (int i0 = tid; i0 < ldu; i0 += NT * V)
 #pragma unroll
-      for (int u = 0; u < kStepLd4; ++u) {
-        const int i = tid + NT * u;
-        if (i < ld4) {
-          const v4f rv = r_lds[i], a = s_col[i];
-          v4f o;
-          o.x = __builtin_fmaf(-c, a.x, rv.x);
-          o.y = __builtin_fmaf(-c, a.y, rv.y);
-          o.z = __builtin_fmaf(-c, a.z, rv.z);
-          o.w = __builtin_fmaf(-c, a.w, rv.w);
-          r_lds[i] = o;
-          sq[u % V] += static_cast<double>(o.x) * o.x + static_cast<double>(o.y) * o.y +
-                       (static_cast<double>(o.z) * o.z + static_cast<double>(o.w) * o.w);
+        for (int v = 0; v < V; ++v) {
+          const int i = i0 + NT * v;
+          if (i < ldu) r_lds[i] = update_chunk(c, s_col[i], r_lds[i], sq[v]);
         }
-      }
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const double sv = wave_sum(sq[v]);
         if (lane == 0) s_red[wave + W * v] = sv;
       }
       if (have) {
+        const float cf = static_cast<float>(c);
         lm = 0.0f;
 #pragma unroll
         for (int u = 0; u < C4; ++u) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) cv[u][e] = __builtin_fmaf(-c, g[u][e], cv[u][e]);
+          for (int e = 0; e < 4; ++e) cv[u][e] = __builtin_fmaf(-cf, g[u][e], cv[u][e]);
           lm = max_abs4(lm, cv[u]);
         }
         wm = wave_max_f32(lm);
@@ -459,9 +519,10 @@ __device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long ma
     __syncthreads();
     rr = wave_sum(lane < 16 ? s_red[lane] : 0.0);
     if (tr.r && t < tr.cap) {  // the residual's trace entry, if asked for
-      float* rt = tr.r + t * tr.ldr;
+      T* rt = tr.r + t * tr.ldr;
+      const T* rs = reinterpret_cast<const T*>(r_lds);
 #pragma unroll 1
-      for (int i = tid; i < ld4; i += NA) trace_rows4(rt, i, p.n, r_lds[i]);
+      for (int64_t i = tid; i < p.n; i += NA) rt[i] = rs[i];
     }
     if (tid == NT) {
       p.x[win] = x_old + c;
@@ -473,7 +534,7 @@ __device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long ma
     }
     ++t;
     rn = static_cast<float>(__builtin_sqrt(rr));
-    err += __builtin_fabsf(c) * bd.col + bd.step * rn;
+    err += __builtin_fabsf(static_cast<float>(c)) * bd.col + bd.step * rn;
     fresh = false;
     if (!(rr > thr)) {
       stop = MP_STOP_CONVERGED;
@@ -491,7 +552,7 @@ __device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long ma
 
   // ---- out: r and the state; unless the run is over, the next pass's list ---
   __syncthreads();
-  for (int i = tid; i < ld4; i += NA) reinterpret_cast<v4f*>(p.r)[i] = r_lds[i];
+  for (int i = tid; i < ldu; i += NA) reinterpret_cast<V16*>(p.r)[i] = r_lds[i];
   if (tid == 0) {
     st->t = t;
     st->rr = rr;
@@ -556,56 +617,72 @@ __device__ void gram_steps(const GramProb& p, const GramBounds& bd, long long ma
   }
 }
 
-template <int NT, int CPT>
-__global__ __launch_bounds__(NT + 2 * kWave) void k_gram_steps(GramProb p, GramBounds bd,
-                                                               long long max_iters, int first,
-                                                               mp_trace tr) {
-  extern __shared__ v4f r_lds[];
-  __shared__ StepShared<NT, CPT> sh;
+template <typename T, int NT, int CPT>
+__global__ __launch_bounds__(NT + 2 * kWave) void k_gram_steps(
+    GramProb<T> p, GramBounds bd, long long max_iters, int first,
+    typename GramTrace<T>::type tr) {
+  extern __shared__ v4f lds[];
+  typename Vec16<T>::type* r_lds = reinterpret_cast<typename Vec16<T>::type*>(lds);
+  __shared__ StepShared<T, NT, CPT> sh;
   if (p.st->done) return;
-  if (threadIdx.x < NT) gram_steps<NT, CPT, true>(p, bd, max_iters, first, tr, r_lds, sh);
-  else gram_steps<NT, CPT, false>(p, bd, max_iters, first, tr, r_lds, sh);
+  if (threadIdx.x < NT) gram_steps<T, NT, CPT, true>(p, bd, max_iters, first, tr, r_lds, sh);
+  else gram_steps<T, NT, CPT, false>(p, bd, max_iters, first, tr, r_lds, sh);
+}
+
+constexpr int64_t kStepLds = 150 * 1024;  // r, a column and (FP32) the slot map, at most
+
+static int64_t step_lds(int64_t ld, int64_t m, int esize) {
+  return 2 * ld * esize + (esize == 4 ? 2 * m : 0);
 }
 
 // The smallest workgroup that holds the correlations: fewer waves make the
-// reductions and barriers of a step shorter; a column takes at most kStepLd4
-// float4s per thread.
-GramShape gram_shape(int64_t ld, int64_t m) {
+// reductions and barriers of a step shorter.  Columns above 4096 rows take
+// 512 threads, so that no thread updates more than a few chunks of r.
+GramShape gram_shape(int64_t ld, int64_t m, int esize) {
   const GramShape shapes[] = {{256, 4}, {256, 16}, {512, 16}, {512, 32}, {512, 64}};
+  if (step_lds(ld, m, esize) > kStepLds) return GramShape{0, 0};
   for (const GramShape& s : shapes)
-    if (m <= static_cast<int64_t>(s.threads) * s.per_thread && ld <= 4 * kStepLd4 * s.threads &&
-        ld <= 8192)
+    if (m <= static_cast<int64_t>(s.threads) * s.per_thread &&
+        (ld * esize <= 16384 || s.threads == 512))
       return s;
   return GramShape{0, 0};
 }
 
-template <int NT, int CPT>
-static hipError_t launch_steps_t(const GramProb& p, const GramBounds& b, long long max_iters,
-                                 bool first, mp_trace tr, hipStream_t s) {
-  constexpr int kMax = 2 * 8192 * 4 + NT * CPT * 2;  // r, a column and the slot map
+template <typename T, int NT, int CPT>
+static hipError_t launch_steps_t(const GramProb<T>& p, const GramBounds& b, long long max_iters,
+                                 bool first, typename GramTrace<T>::type tr, hipStream_t s) {
   static const hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(k_gram_steps<NT, CPT>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, kMax);
+      hipFuncSetAttribute(reinterpret_cast<const void*>(k_gram_steps<T, NT, CPT>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, kStepLds);
   if (attr != hipSuccess) return attr;
-  const size_t lds = static_cast<size_t>(p.ld) * 8 + static_cast<size_t>(p.m) * 2;
-  k_gram_steps<NT, CPT><<<dim3(1), dim3(NT + 2 * kWave), lds, s>>>(p, b, max_iters,
-                                                             first ? 1 : 0, tr);
+  k_gram_steps<T, NT, CPT><<<dim3(1), dim3(NT + 2 * kWave),
+                             static_cast<size_t>(step_lds(p.ld, p.m, sizeof(T))), s>>>(
+      p, b, max_iters, first ? 1 : 0, tr);
   return hipGetLastError();
 }
 
-hipError_t launch_gram_steps(const GramProb& p, const GramShape& sh, const GramBounds& b,
-                             long long max_iters, bool first, mp_trace tr, hipStream_t s) {
+template <typename T>
+hipError_t launch_gram_steps(const GramProb<T>& p, const GramShape& sh, const GramBounds& b,
+                             long long max_iters, bool first, typename GramTrace<T>::type tr,
+                             hipStream_t s) {
+  if (step_lds(p.ld, p.m, sizeof(T)) > kStepLds) return hipErrorInvalidValue;
   if (sh.threads == 256 && sh.per_thread == 4)
-    return launch_steps_t<256, 4>(p, b, max_iters, first, tr, s);
+    return launch_steps_t<T, 256, 4>(p, b, max_iters, first, tr, s);
   if (sh.threads == 256 && sh.per_thread == 16)
-    return launch_steps_t<256, 16>(p, b, max_iters, first, tr, s);
+    return launch_steps_t<T, 256, 16>(p, b, max_iters, first, tr, s);
   if (sh.threads == 512 && sh.per_thread == 16)
-    return launch_steps_t<512, 16>(p, b, max_iters, first, tr, s);
+    return launch_steps_t<T, 512, 16>(p, b, max_iters, first, tr, s);
   if (sh.threads == 512 && sh.per_thread == 32)
-    return launch_steps_t<512, 32>(p, b, max_iters, first, tr, s);
+    return launch_steps_t<T, 512, 32>(p, b, max_iters, first, tr, s);
   if (sh.threads == 512 && sh.per_thread == 64)
-    return launch_steps_t<512, 64>(p, b, max_iters, first, tr, s);
+    return launch_steps_t<T, 512, 64>(p, b, max_iters, first, tr, s);
   return hipErrorInvalidValue;
 }
+template hipError_t launch_gram_steps<float>(const GramProb<float>&, const GramShape&,
+                                             const GramBounds&, long long, bool, mp_trace,
+                                             hipStream_t);
+template hipError_t launch_gram_steps<double>(const GramProb<double>&, const GramShape&,
+                                              const GramBounds&, long long, bool, mp_trace_f64,
+                                              hipStream_t);
 
 }  // namespace mp

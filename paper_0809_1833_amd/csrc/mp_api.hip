@@ -413,7 +413,7 @@ mp_status enqueue_result(mp_ctx* c, const mp::DevState* st, hipStream_t s, int p
 bool ensure_gram(mp_ctx* c, hipStream_t s) {
   if (c->gram_tried) return c->gram_slots > 0;
   c->gram_tried = true;
-  const mp::GramShape sh = mp::gram_shape(c->ld, c->m);
+  const mp::GramShape sh = mp::gram_shape(c->ld, c->m, c->storage == MP_F64 ? 8 : 4);
   if (sh.threads == 0 || !(c->max_norm > 0.99) || !(c->max_norm < 1.01)) return false;
   c->gram_mp = static_cast<int64_t>(sh.threads) * sh.per_thread;
   const int64_t want = std::max<int64_t>(256, c->n / 4);
@@ -439,13 +439,14 @@ bool ensure_gram(mp_ctx* c, hipStream_t s) {
 // of a pass and the steps it allows, the host keeping two pairs in flight.
 // `gave_up` is set when the device asks for the stepping form instead (no
 // shortlist narrow enough, or norms outside the bounds' range).
-mp_status solve_gram(mp_ctx* c, float* x, const mp_opts* opts, const mp_trace& tr, hipStream_t s,
-                     bool& gave_up) {
-  const mp::GramShape sh = mp::gram_shape(c->ld, c->m);
-  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm);
-  const mp::GramProb p{c->psi32, c->ld, c->n, c->m, c->gram_mp, c->gram_c, c->gram_g, c->gram_map,
-                       c->gram_slots, c->gram_rhs, c->r_work, x, c->st,
-                       static_cast<mp::GramCtl*>(c->gram_ctl)};
+template <typename T>
+mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* opts,
+                     const typename mp::GramTrace<T>::type& tr, hipStream_t s, bool& gave_up) {
+  const mp::GramShape sh = mp::gram_shape(c->ld, c->m, sizeof(T));
+  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, sizeof(T) == 8);
+  const mp::GramProb<T> p{psi, c->ld, c->n, c->m, c->gram_mp, c->gram_c, c->gram_g, c->gram_map,
+                          c->gram_slots, c->gram_rhs, r_work, x, c->st,
+                          static_cast<mp::GramCtl*>(c->gram_ctl)};
   gave_up = false;
   const bool timed = c->profiling;
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
@@ -522,10 +523,10 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
     if (fs == MP_OK && res) res->persistent = 1;
     return fs;
   }
-  if (allow_gram && c->storage == MP_F32 && !async && !(opts->flags & MP_SOLVE_STEP_LAUNCHES) &&
-      ensure_gram(c, s)) {
+  if (allow_gram && c->storage == MP_F32 && !async &&
+      !(opts->flags & MP_SOLVE_STEP_LAUNCHES) && ensure_gram(c, s)) {
     bool gave_up = false;
-    const mp_status gs = solve_gram(c, x, opts, tr, s, gave_up);
+    const mp_status gs = solve_gram<float>(c, c->psi32, b.r_work, x, opts, tr, s, gave_up);
     if (gs != MP_OK) return gs;
     if (!gave_up) {
       if (r) HIP_TRY(c, mp::launch_copy_selected(b.r_work, c->ld, c->n, b.st, r, s));
@@ -1061,6 +1062,7 @@ mp_status mp_create_f64(mp_ctx** out, const double* psi, int64_t n, int64_t m, i
     std::string msg;
     const mp_status ns = check_norms(norm2, flags, msg);
     if (ns != MP_OK) return bail(ns, msg);
+    c->max_norm = largest_norm(norm2);
   }
   *out = c;
   return MP_OK;
@@ -1150,12 +1152,25 @@ mp_status mp_solve_f64(mp_ctx* ctx, const double* y, double* x, double* r, const
                                  static_cast<long long>(opts->max_iters), s));
   HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
+  bool carried = false;  // decoded on carried correlations (r is in half 0)
+  if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done && ensure_gram(c, s)) {
+    bool gave_up = false;
+    const mp_status gs = solve_gram<double>(c, c->psi64, c->r64_work, x, opts, tr, s, gave_up);
+    if (gs != MP_OK) return gs;
+    carried = !gave_up;
+    if (gave_up) {
+      c->prof_ms = 0.0;
+      c->prof_launches = 0;
+      HIP_TRY(c, mp::launch_init_f64(y, c->n, c->ld, x, c->m, c->r64_work, c->st, opts->eps,
+                                     static_cast<long long>(opts->max_iters), s));
+    }
+  }
   // launch k takes step k (k >= 1) and runs pass k+1: T steps take T+1
   // launches; r ends in the half the state names
   long long k = 0;
   const long long T = opts->max_iters;
   const double thr = c->h_st->thr;
-  const mp_status st = run_iterations(c, T > 0 ? T + 1 : 0, s, true, [&](hipEvent_t e0, hipEvent_t e1) {
+  const mp_status st = carried ? MP_OK : run_iterations(c, T > 0 ? T + 1 : 0, s, true, [&](hipEvent_t e0, hipEvent_t e1) {
     hipError_t e;
     if (e0 && (e = hipEventRecord(e0, s)) != hipSuccess) return e;
     e = mp::launch_mp_step_f64(c->psi64, c->ld, c->n, c->m, c->r64_work, c->geom, c->partials,

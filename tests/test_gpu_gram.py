@@ -28,17 +28,17 @@ def _need_gpu():
     mp.library()
 
 
-def _draw(n, m, k, noise=0.0, seed=0):
+def _draw(n, m, k, noise=0.0, seed=0, dtype=torch.float32):
     g = torch.Generator(device="cuda").manual_seed(1000 * seed + n * 7 + m)
     rows = torch.randn((m, n), generator=g, device="cuda", dtype=torch.float64)
-    rows = (rows / rows.norm(dim=1, keepdim=True)).float()
+    rows = (rows / rows.norm(dim=1, keepdim=True)).to(dtype)
     sup = torch.randperm(m, generator=g, device="cuda")[:k]
     v = torch.randn(k, generator=g, device="cuda", dtype=torch.float64)
     y = v @ rows[sup].double()
     if noise:
         y = y + noise * y.norm() / math.sqrt(n) * torch.randn(n, generator=g, device="cuda",
                                                                dtype=torch.float64)
-    return rows, y.float()
+    return rows.to(dtype), y.to(dtype)
 
 
 def _same(rows, y, eps, cap, trace=True, storage="f32"):
@@ -62,7 +62,7 @@ def _same(rows, y, eps, cap, trace=True, storage="f32"):
     (200, 8192), (190, 8193),            # 512 x 16 | 512 x 32
     (100, 16384), (97, 16385),           # 512 x 32 | 512 x 64
     (40, 32768), (39, 32769),            # 512 x 64 | one launch per step
-    (4097, 401), (8192, 200), (8193, 190),  # the longest columns | one launch per step
+    (4097, 401), (8192, 200), (16384, 150),  # the longest columns
     (1000, 1999), (65, 20001),
 ])
 def test_equals_step_launches(n, m):
@@ -70,6 +70,26 @@ def test_equals_step_launches(n, m):
     rows, y = _draw(n, m, max(2, min(n, m) // 20), noise=0.01)
     a = _same(rows, y, 0.005, 120)
     assert a["iters"] > 0
+
+
+@pytest.mark.parametrize("n,m", [
+    (700, 1024), (600, 1025), (2048, 300), (2049, 300), (150, 8193), (40, 32768), (39, 32769),
+    (8192, 100), (9600, 90), (9601, 90), (63, 4097), (1000, 1999),
+])
+def test_f64_equals_step_launches(n, m):
+    """The FP64 form (its products shortlisted in FP32, scored in FP64), at the
+    edges of its shares and of the longest column it takes."""
+    print(f"[gram f64 {n}x{m}]", flush=True)
+    rows, y = _draw(n, m, max(2, min(n, m) // 20), noise=0.01, dtype=torch.float64)
+    a = _same(rows, y, 0.005, 120, storage="f64")
+    assert a["iters"] > 0
+
+
+def test_f64_full_decay_and_handing_back():
+    rows, y = _draw(512, 3000, 40, dtype=torch.float64)
+    a = _same(rows, y, 1e-10, 2000, storage="f64")
+    assert a["stop"] == "converged" and a["iters"] > 100
+    _same(rows, y * 1e-60, 1e-4, 50, storage="f64")
 
 
 @pytest.mark.parametrize("cap", [0, 1, 2, 5])
