@@ -216,7 +216,10 @@ mp_status mp_create(mp_ctx** out, const float* psi, int64_t n, int64_t m, int64_
  * to a multiple of 64, column norms within 1% of 1) decodes on correlations carried from step to step by the Gram columns
  * of the selected atoms, with a pass over the dictionary only when an atom
  * without one is selected: the same results bit for bit as one launch per
- * step, which MP_SOLVE_STEP_LAUNCHES selects.  The first such decode
+ * step, which MP_SOLVE_STEP_LAUNCHES selects.  MP_BF16 and MP_FP8_E4M3
+ * contexts with opts.rescore_k = 8 (or 0) do too, on their FP32 columns: the
+ * atom selected is the FP32 form's (one launch per step finds the same one
+ * wherever it is among the pass's 8 candidates).  The first such decode
  * allocates its work buffers on the context (the Gram columns take at most
  * about a quarter of the dictionary's bytes, or M * 1 KiB if that is more);
  * where they cannot be allocated the decode takes one launch per step.

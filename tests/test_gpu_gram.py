@@ -92,6 +92,16 @@ def test_f64_full_decay_and_handing_back():
     _same(rows, y * 1e-60, 1e-4, 50, storage="f64")
 
 
+@pytest.mark.parametrize("storage", ["bf16", "fp8"])
+@pytest.mark.parametrize("n,m,eps", [(600, 3000, 1e-6), (1000, 8193, 1e-5), (250, 900, 1e-6)])
+def test_reduced_precision_equals_step_launches(storage, n, m, eps):
+    """With all 8 candidates re-scored the reduced-precision forms select the
+    FP32 form's atom, on carried correlations as with a pass per step."""
+    rows, y = _draw(n, m, max(2, n // 20))
+    a = _same(rows, y, eps, 400, storage=storage)
+    assert a["stop"] == "converged"
+
+
 @pytest.mark.parametrize("cap", [0, 1, 2, 5])
 def test_short_caps(cap):
     rows, y = _draw(600, 3000, 20)
