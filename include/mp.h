@@ -279,6 +279,14 @@ mp_status mp_solve_noalloc(mp_ctx* ctx, const float* y, float* x, float* r, cons
  * of later products as soon as they stop.  A context created with MP_F32 or
  * MP_FP8_E4M3 storage gets a BF16 copy of its dictionary on first use.
  *
+ * Where M <= 16384, rescore_k is 8 (or 0), the column norms are within 1% of 1
+ * and the caps allow enough steps to pay for them, the context computes the
+ * Gram columns of all atoms on first use (M * M floats, rounded up, kept until
+ * it is destroyed) and every signal decodes on carried correlations (see
+ * mp_solve) in a workgroup of its own: the atom selected each step is the
+ * FP32 form's, the one the rounds of products select wherever it is among
+ * their 8 candidates.
+ *
  *   Y         device: N x B, column b = y of signal b, leading dimension ldy >= N
  *   X         device: M x B, overwritten with the x~ columns, ldx >= M
  *   R         device: N x B or NULL, receives the final residuals, ldr >= N
@@ -300,7 +308,7 @@ mp_status mp_solve_batched(mp_ctx* ctx, const float* Y, int64_t ldy, int64_t B, 
                            const int64_t* max_iters_b, mp_result* res, const mp_trace* trace,
                            void* stream);
 
-/* Tile of the batched product by the number of signals still active (chosen
+/* Tile of the rounds' batched product by the number of signals still active (chosen
    by the autotuner; results do not depend on it beyond which 8 candidates of
    each signal reach the FP32 re-score, and the selection is the re-scored
    one): 128 atoms x 64 signals per workgroup while more than atoms128_above
@@ -563,7 +571,8 @@ mp_status mp_get_storage(const mp_ctx* ctx, void* codes, float* scales, void* st
  *             decodes on carried correlations: all their launches together,
  *             over the steps taken); OMP
  *             times every k-th selection launch on its own; mp_solve_batched
- *             every k-th round's product launch.
+ *             every k-th round's product launch, or on carried correlations
+ *             all its launches together, over the steps of its longest signal.
  *   avg_ms    host: mean duration of one timed launch in milliseconds
  *   launches  host: number of launches averaged (only launches that performed
  *             an iteration are counted, a window only when all its launches

@@ -101,4 +101,30 @@ hipError_t launch_gram_steps(const GramProb<T>& p, const GramShape& sh, const Gr
                              long long max_iters, bool first, typename GramTrace<T>::type tr,
                              hipStream_t s);
 
+// ---- signals that share one dictionary (k_gram_batched.hip) ----------------
+struct GramBatch {
+  const float* psi;    // ld x m
+  int64_t ld, n, m;
+  int64_t mp;          // stride of g and c
+  const float* g;      // every atom's Gram column: m x mp
+  float* c;            // per signal: mp carried correlations
+  float* r;            // per signal: ld floats
+  float* x;            // per signal: ldx floats (the caller's)
+  int64_t ldx;
+  DevState* states;    // per signal; pad[0]: gave up
+};
+GramBounds gram_bounds_full(int64_t n, double max_norm);
+hipError_t launch_gram_full(const float* psi, int64_t ld, int64_t m, float* g, int64_t mp,
+                            int num_cus, hipStream_t s);
+hipError_t launch_gram_binit(const float* Y, int64_t ldy, int64_t n, int64_t ld, float* X,
+                             int64_t ldx, int64_t m, float* R, DevState* states,
+                             const long long* tcap, long long tcap_all, double eps, int nb,
+                             hipStream_t s);
+// Round `round`: the correlations of the signals still running, then their
+// steps.  again: two words; word round mod 2 is set if some signal goes on
+// (both launches return at once where the previous round's word is clear).
+hipError_t launch_gram_bround(const GramBatch& b, const GramShape& sh, const GramBounds& bd,
+                              int nb, int num_cus, long long round, int* again, mp_trace tr,
+                              hipStream_t s);
+
 }  // namespace mp

@@ -110,9 +110,29 @@ void free_gram(mp_ctx* c) {
   c->gram_slots = 0;
 }
 
+void free_gram_batch(mp_ctx* c) {
+  (void)hipFree(c->gram_bc);
+  (void)hipFree(c->gram_br);
+  (void)hipFree(c->gram_bst);
+  (void)hipFree(c->gram_again);
+  (void)hipFree(c->gram_btcap);
+  if (c->gram_hbst) (void)hipHostFree(c->gram_hbst);
+  if (c->gram_hagain) (void)hipHostFree(c->gram_hagain);
+  c->gram_bc = nullptr;
+  c->gram_br = nullptr;
+  c->gram_bst = nullptr;
+  c->gram_again = nullptr;
+  c->gram_btcap = nullptr;
+  c->gram_hbst = nullptr;
+  c->gram_hagain = nullptr;
+  c->gram_bcap = 0;
+}
+
 void free_ctx(mp_ctx* c) {
   if (!c) return;
   free_gram(c);
+  free_gram_batch(c);
+  (void)hipFree(c->gram_full);
   free_batched(c);
   free_ragged(c);
   free_omp(c);
@@ -596,6 +616,140 @@ mp_status finish_result(mp_ctx* c, mp_result* res) {
     res->stop_reason = d.reason;
     res->persistent = 0;
   }
+  return MP_OK;
+}
+
+// Whether a batched decode of at most tmax steps takes the carried
+// correlations, and the Gram columns and buffers for B signals if so.
+//
+// The Gram columns of all atoms cost m^2 n multiply-adds, once per context,
+// and m^2 floats; a step costs about 4 us on carried correlations and a round
+// of products and selections about 15.  They are made where a decode to the
+// cap would pay for them at once (at the 45 TFLOP/s the symmetric product
+// reaches, its 2 m^2 n / 2 operations against 11 us a step: N = 2048, M = 8192
+// from a cap of 280 steps on) and they fit 1 GiB (M <= 16384).
+bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
+  const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
+  if (sh.threads == 0 || c->m > 16384 || !(c->max_norm > 0.99) || !(c->max_norm < 1.01))
+    return false;
+  if (!c->gram_full) {
+    const double cost_us = static_cast<double>(c->m) * static_cast<double>(c->m) *
+                           static_cast<double>(c->ld) / 45e6;
+    if (cost_us > 11.0 * static_cast<double>(tmax) || c->gram_full_tried) return false;
+    c->gram_full_tried = true;
+    const int64_t stride = static_cast<int64_t>(sh.threads) * sh.per_thread;
+    const size_t bytes = sizeof(float) * static_cast<size_t>(stride) * static_cast<size_t>(c->m);
+    if (hipMalloc(&c->gram_full, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      c->gram_full = nullptr;
+      return false;
+    }
+    c->gram_full_mp = stride;
+    if ((stride != c->m && hipMemsetAsync(c->gram_full, 0, bytes, s) != hipSuccess) ||
+        mp::launch_gram_full(c->psi32, c->ld, c->m, c->gram_full, stride, c->num_cus, s) !=
+            hipSuccess) {
+      (void)hipFree(c->gram_full);
+      c->gram_full = nullptr;
+      return false;
+    }
+  }
+  if (B <= c->gram_bcap) return true;
+  free_gram_batch(c);
+  const size_t b = static_cast<size_t>(B);
+  const size_t cbytes = sizeof(float) * static_cast<size_t>(c->gram_full_mp) * b;
+  if (hipMalloc(&c->gram_bc, cbytes) != hipSuccess ||
+      hipMalloc(&c->gram_br, sizeof(float) * static_cast<size_t>(c->ld) * b) != hipSuccess ||
+      hipMalloc(&c->gram_bst, sizeof(mp::DevState) * b) != hipSuccess ||
+      hipMalloc(&c->gram_again, 2 * sizeof(int)) != hipSuccess ||
+      hipMalloc(&c->gram_btcap, sizeof(long long) * b) != hipSuccess ||
+      hipHostMalloc(&c->gram_hbst, sizeof(mp::DevState) * b, hipHostMallocDefault) !=
+          hipSuccess ||
+      hipHostMalloc(&c->gram_hagain, 4 * sizeof(int), hipHostMallocDefault) != hipSuccess ||
+      hipMemsetAsync(c->gram_bc, 0, cbytes, s) != hipSuccess) {
+    (void)hipGetLastError();
+    free_gram_batch(c);
+    return false;
+  }
+  c->gram_bcap = B;
+  return true;
+}
+
+// The batched decode on carried correlations.  `gave_up`: some signal needs
+// the rounds of products instead (the whole batch is then decoded again).
+mp_status solve_gram_batch(mp_ctx* c, const float* Y, int64_t ldy, int64_t B, float* X,
+                           int64_t ldx, const mp_opts* opts, const int64_t* max_iters_b,
+                           const mp_trace& tr, hipStream_t s, bool& gave_up) {
+  gave_up = false;
+  const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
+  const mp::GramBounds bounds = mp::gram_bounds_full(c->n, c->max_norm);
+  if (max_iters_b)
+    HIP_TRY(c, hipMemcpyAsync(c->gram_btcap, max_iters_b, sizeof(long long) * B,
+                              hipMemcpyHostToDevice, s));
+  const bool timed = c->profiling;
+  if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
+  HIP_TRY(c, mp::launch_gram_binit(Y, ldy, c->n, c->ld, X, ldx, c->m, c->gram_br, c->gram_bst,
+                                   max_iters_b ? c->gram_btcap : nullptr, opts->max_iters,
+                                   opts->eps, static_cast<int>(B), s));
+  const mp::GramBatch b{c->psi32, c->ld, c->n, c->m, c->gram_full_mp, c->gram_full, c->gram_bc,
+                        c->gram_br, X, ldx, c->gram_bst};
+  // rounds until no signal goes on, two in flight; every round takes each
+  // running signal at least one step on (or it gives up)
+  long long issued = 0, seen = 0;
+  bool over = false;
+  while (!over) {
+    while (issued - seen < 2) {
+      HIP_TRY(c, mp::launch_gram_bround(b, sh, bounds, static_cast<int>(B), c->num_cus, issued,
+                                        c->gram_again, tr, s));
+      const int k = static_cast<int>(issued & 1);
+      HIP_TRY(c, hipMemcpyAsync(c->gram_hagain + 2 * k, c->gram_again, 2 * sizeof(int),
+                                hipMemcpyDeviceToHost, s));
+      HIP_TRY(c, hipEventRecord(c->done_ev[k], s));
+      ++issued;
+    }
+    const int k = static_cast<int>(seen & 1);
+    HIP_TRY(c, hipEventSynchronize(c->done_ev[k]));
+    over = c->gram_hagain[2 * k + k] == 0;
+    ++seen;
+  }
+  if (timed) HIP_TRY(c, hipEventRecord(c->ev[1], s));
+  HIP_TRY(c, hipMemcpyAsync(c->gram_hbst, c->gram_bst, sizeof(mp::DevState) * B,
+                            hipMemcpyDeviceToHost, s));
+  HIP_TRY(c, hipStreamSynchronize(s));
+  long long most = 0;
+  for (int64_t j = 0; j < B; ++j) {
+    gave_up |= c->gram_hbst[j].pad[0] != 0;
+    most = std::max(most, c->gram_hbst[j].t);
+  }
+  if (timed) {
+    // the decode's time on the device over the steps of its longest signal
+    float ms = 0.f;
+    if (hipEventElapsedTime(&ms, c->ev[0], c->ev[1]) == hipSuccess) {
+      c->prof_ms = ms;
+      c->prof_launches = most > 0 ? most : 1;
+    }
+  }
+  return MP_OK;
+}
+
+// Results of a batched decode: one entry per signal and the call's status.
+template <class State>
+mp_status batched_results(mp_ctx* c, const State* slots, int64_t B, mp_result* res) {
+  bool nonfinite = false, internal = false;
+  for (int64_t b = 0; b < B; ++b) {
+    const State& d = slots[b];
+    nonfinite |= d.reason == mp::kStopNonFinite;
+    internal |= d.reason == mp::kStopInternal;
+    if (res) {
+      res[b].iters = d.t;
+      res[b].yy = d.yy;
+      res[b].rr = d.rr;
+      res[b].stop_reason = d.reason;
+      res[b].persistent = 0;
+    }
+  }
+  if (internal)
+    return fail(c, MP_EDEVICE, "internal error: a selected index fell outside the dictionary");
+  if (nonfinite) return fail(c, MP_ENONFINITE, "a column of Y holds NaN or Inf");
   return MP_OK;
 }
 
@@ -1270,11 +1424,28 @@ mp_status mp_solve_batched(mp_ctx* ctx, const float* Y, int64_t ldy, int64_t B, 
   if (trace) tr = *trace;
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  mp_status st = ensure_batched(c, B, s);
-  if (st != MP_OK) return st;
   const int rk = opts->rescore_k == 0 ? mp::kLpTopK : opts->rescore_k;
   c->prof_ms = 0.0;
   c->prof_launches = 0;
+  // with all 8 candidates re-scored the atom selected is the FP32 argmax,
+  // which the carried correlations give without a product per round
+  if (rk == mp::kLpTopK && tmax > 0 && ensure_gram_batch(c, B, tmax, s)) {
+    bool gave_up = false;
+    const mp_status gs = solve_gram_batch(c, Y, ldy, B, X, ldx, opts, max_iters_b, tr, s, gave_up);
+    if (gs != MP_OK) return gs;
+    if (!gave_up) {
+      if (R) {
+        HIP_TRY(c, hipMemcpy2DAsync(R, ldr * sizeof(float), c->gram_br, c->ld * sizeof(float),
+                                    c->n * sizeof(float), B, hipMemcpyDeviceToDevice, s));
+        HIP_TRY(c, hipStreamSynchronize(s));
+      }
+      return batched_results(c, c->gram_hbst, B, res);
+    }
+    c->prof_ms = 0.0;
+    c->prof_launches = 0;
+  }
+  mp_status st = ensure_batched(c, B, s);
+  if (st != MP_OK) return st;
   if (max_iters_b)
     HIP_TRY(c, hipMemcpyAsync(c->b_tcap, max_iters_b, sizeof(long long) * B,
                               hipMemcpyHostToDevice, s));
@@ -1377,23 +1548,7 @@ mp_status mp_solve_batched(mp_ctx* ctx, const float* Y, int64_t ldy, int64_t B, 
   HIP_TRY(c, hipMemcpyAsync(c->h_slots, c->b_slots, sizeof(mp::BSlot) * B, hipMemcpyDeviceToHost,
                             s));
   HIP_TRY(c, hipStreamSynchronize(s));
-  bool nonfinite = false, internal = false;
-  for (int64_t b = 0; b < B; ++b) {
-    const mp::BSlot& d = c->h_slots[b];
-    nonfinite |= d.reason == mp::kStopNonFinite;
-    internal |= d.reason == mp::kStopInternal;
-    if (res) {
-      res[b].iters = d.t;
-      res[b].yy = d.yy;
-      res[b].rr = d.rr;
-      res[b].stop_reason = d.reason;
-      res[b].persistent = 0;
-    }
-  }
-  if (internal)
-    return fail(c, MP_EDEVICE, "internal error: a selected index fell outside the dictionary");
-  if (nonfinite) return fail(c, MP_ENONFINITE, "a column of Y holds NaN or Inf");
-  return MP_OK;
+  return batched_results(c, c->h_slots, B, res);
 }
 
 

@@ -406,5 +406,18 @@ struct mp_ctx {
   uint16_t* gram_map = nullptr;  // m
   float* gram_rhs = nullptr;     // 16 x ld
   void* gram_ctl = nullptr;      // mp::GramCtl
+  // the batched decode on carried correlations: every atom's Gram column (made
+  // by the first decode that takes it) and buffers per signal (grown on demand)
+  bool gram_full_tried = false;
+  float* gram_full = nullptr;    // m x gram_full_mp
+  int64_t gram_full_mp = 0;
+  int64_t gram_bcap = 0;
+  float* gram_bc = nullptr;      // gram_bcap x gram_full_mp
+  float* gram_br = nullptr;      // gram_bcap x ld
+  mp::DevState* gram_bst = nullptr;    // gram_bcap
+  mp::DevState* gram_hbst = nullptr;   // pinned
+  int* gram_again = nullptr;     // 2
+  int* gram_hagain = nullptr;    // pinned, 2 x 2
+  long long* gram_btcap = nullptr;     // gram_bcap
   std::string err;
 };

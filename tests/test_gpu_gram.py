@@ -192,3 +192,98 @@ def test_two_streams_and_repeats():
             assert o["iters"] == alone[i]["iters"] and torch.equal(o["x"], alone[i]["x"])
             assert torch.equal(o["r"], alone[i]["r"])
         decs[i].close()
+
+
+# ---- the batched decode (all Gram columns at once) ---------------------------
+
+def _batched_same(rows, ys, eps, caps, storage="f32", solo=None):
+    """Every signal of the batch as mp_solve decodes it alone, one launch per
+    step: the same atoms, coefficients, x~ and r (||r||^2 to the last digits:
+    it is summed in the batched form's order)."""
+    from paper_0809_1833_amd.mp import Decoder
+    b = ys.shape[1]
+    per = caps if isinstance(caps, list) else [caps] * b
+    cap = max(max(per), 1)
+    with Decoder(rows.t(), storage=storage) as dec, Decoder(rows.t()) as one:
+        out = dec.solve_batched(ys, eps, caps, trace_cap=cap, trace_r=True)
+        again = dec.solve_batched(ys, eps, caps)
+        torch.cuda.synchronize()
+        assert torch.equal(out["x"], again["x"]) and torch.equal(out["r"], again["r"])
+        assert out["iters"] == again["iters"] and out["rr"] == again["rr"]
+        for j in (range(b) if solo is None else solo):
+            a = one.solve(ys[:, j].contiguous(), eps, per[j], trace_cap=cap, trace_r=True,
+                          step_launches=True)
+            t = a["iters"]
+            assert out["iters"][j] == t and out["stop"][j] == a["stop"], j
+            assert torch.equal(out["x"][:, j].contiguous(), a["x"]), j
+            assert torch.equal(out["r"][:, j].contiguous(), a["r"]), j
+            assert torch.equal(out["idx"][j, :t], a["idx"]) and torch.equal(out["coef"][j, :t],
+                                                                            a["coef"]), j
+            assert torch.equal(out["r_trace"][j, :t], a["r_trace"]), j
+            assert abs(out["rr"][j] - a["rr"]) <= 1e-13 * a["rr"], j
+    return out
+
+
+def _signals(rows, ks, seed=0, noise=0.01):
+    g = torch.Generator(device="cuda").manual_seed(seed + len(ks))
+    m, n = rows.shape
+    ys = torch.empty((len(ks), n), device="cuda")
+    for j, k in enumerate(ks):
+        sup = torch.randperm(m, generator=g, device="cuda")[:k]
+        v = torch.randn(k, generator=g, device="cuda", dtype=torch.float64)
+        y = v @ rows[sup].double()
+        y += noise * y.norm() / math.sqrt(n) * torch.randn(n, generator=g, device="cuda",
+                                                            dtype=torch.float64)
+        ys[j] = y.float()
+    return ys.t()
+
+
+@pytest.mark.parametrize("n,m,b", [
+    (300, 1024, 3), (300, 1025, 2), (128, 4096, 65), (129, 4097, 64), (500, 63, 5),
+    (64, 8192, 2), (60, 8193, 2), (40, 16384, 2), (40, 16385, 2),
+    (513, 129, 130), (1, 7, 3), (2049, 600, 2),
+])
+def test_batched_equals_single(n, m, b):
+    print(f"[gram batched {n}x{m} b{b}]", flush=True)
+    rows, _ = _draw(n, m, 1)
+    # (columns that do not span the rows would leave noise no atom can take)
+    ys = _signals(rows, [1 + (j * 7) % max(1, min(n, m) // 15) for j in range(b)],
+                  noise=0.01 if m > n else 0.0)
+    _batched_same(rows, ys, 0.005, 2000, solo=range(min(b, 6)))
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16", "fp8"])
+def test_batched_caps_and_odd_signals(storage):
+    """Caps per signal (zero among them), a zero signal, and a decay that
+    renews the correlations; then a signal with NaN, which fails the call and
+    leaves the others decoded."""
+    from paper_0809_1833_amd import mp
+    from paper_0809_1833_amd.mp import Decoder
+    rows, _ = _draw(256, 900, 1, seed=5)
+    ys = _signals(rows, [4, 9, 3, 12, 7], noise=0.0).contiguous()
+    ys = torch.empty((5, 256), device="cuda").copy_(ys.t()).t()
+    ys[:, 2] = 0
+    out = _batched_same(rows, ys, 1e-6, [2000, 3, 50, 0, 2000], storage=storage)
+    assert out["stop"] == ["converged", "max_iters", "zero_input", "max_iters", "converged"]
+    good = _batched_same(rows, ys, 1e-6, 2000, storage=storage, solo=[0])
+    ys[17, 3] = float("nan")
+    with Decoder(rows.t(), storage=storage) as dec:
+        with pytest.raises(mp.MPError) as e:
+            dec.solve_batched(ys, 1e-6, 2000)
+        assert e.value.status == mp.MP_ENONFINITE
+        ys[:, 3] = 0
+        again = dec.solve_batched(ys, 1e-6, 2000)
+    assert torch.equal(again["x"][:, 0], good["x"][:, 0])
+
+
+def test_batched_ties_and_handing_back():
+    """Exact ties take the smallest index; a signal on which more atoms tie
+    than a step can score sends the batch back to the rounds of products."""
+    rows, _ = _draw(200, 1200, 1, seed=6)
+    rows[600:] = -rows[:600]
+    ys = _signals(rows, [5, 8, 3], seed=2)
+    out = _batched_same(rows, ys, 0.005, 400)
+    assert int(out["idx"].max()) < 600
+    rows[300:400] = rows[300]
+    ys = torch.stack([rows[300], ys[:, 1]], dim=0).t()
+    _batched_same(rows, ys, 0.005, 400)
