@@ -494,8 +494,17 @@ mp_status mp_create_ragged(mp_ctx** out, const mp_instance* inst, int64_t count,
 
 /*
  * mp_solve_ragged -- decode every instance of a ragged context (the
- * Section 3 loop per instance) in one persistent launch, replayed from a
- * captured HIP graph while the arguments stay the same.  Workgroups take
+ * Section 3 loop per instance).  On carried correlations (see mp_solve),
+ * all instances' passes in one launch and each instance's steps in a
+ * workgroup of its own, where every instance has M <= 32768 and 8 N + 2 M <=
+ * 153600, the column norms are within 1% of 1, rescore_k is 8 or 0 (MP_BF16)
+ * and the Gram columns, allocated with the context (at most the dictionaries'
+ * FP32 bytes and 64 MiB), were available; MP_RAGGED_SPIN_LIMIT, if set in the
+ * environment, selects the persistent launch below, whose waits it limits.
+ * The same atoms, coefficients, x~ and r either way.
+ *
+ * Otherwise in one persistent launch, replayed from a captured HIP graph
+ * while the arguments stay the same.  Workgroups take
  * instances largest first; each runs one instance's whole loop, or one part
  * of it for an instance cut into parts (mp_ragged_config.split).  The parts
  * of an instance wait for each other every step: the launch needs at least
@@ -520,8 +529,8 @@ mp_status mp_solve_ragged(mp_ctx* ctx, const float* Y, float* X, float* R, const
                           const int64_t* max_iters, mp_result* res, const mp_trace* trace,
                           void* stream);
 
-/* mp_ragged_set_config / mp_ragged_get_config -- launch shape of
-   mp_solve_ragged (results do not depend on it).  Errors: MP_EINVAL (not a
+/* mp_ragged_set_config / mp_ragged_get_config -- launch shape of the persistent
+   launch of mp_solve_ragged (results do not depend on it).  Errors: MP_EINVAL (not a
    ragged context, or a shape outside the listed values). */
 mp_status mp_ragged_set_config(mp_ctx* ctx, const mp_ragged_config* cfg);
 mp_status mp_ragged_get_config(const mp_ctx* ctx, mp_ragged_config* cfg);

@@ -127,4 +127,32 @@ hipError_t launch_gram_bround(const GramBatch& b, const GramShape& sh, const Gra
                               int nb, int num_cus, long long round, int* again, mp_trace tr,
                               hipStream_t s);
 
+// ---- many independent problems (k_gram.hip) ---------------------------------
+struct GramGroup {     // one workgroup of the pass: tiles of problem id
+  int id, group;
+};
+struct GramRagged {
+  const GramProb<float>* probs;  // device, count (x is filled in from X)
+  const RInst* inst;             // device: offsets of y and x~
+  const GramBounds* bounds;      // device, count
+  const int* order;              // device: problems, most work first
+  const GramGroup* groups;       // device: the pass's work list
+  int* again;                    // device, two words (see GramBatch)
+  int count, ngroups, split;
+  int64_t max_ld, lds;           // lds: of the steps kernel
+  bool small;                    // every problem has at most 4096 atoms and rows
+  bool one;                      // the product is one lane chain (the FP32 form's)
+};
+GramBounds gram_bounds_one(int64_t n, double max_norm);
+// Stride of a problem's Gram columns in a set whose largest are max_ld, max_m
+// (m <= 32768), and tiles per workgroup of the pass for `tiles` in all.
+int64_t gram_ragged_stride(int64_t max_ld, int64_t max_m, int64_t m);
+int gram_ragged_groups(int64_t tiles, int num_cus);
+hipError_t launch_gram_rinit(const GramRagged& g, const float* Y, float* X, const long long* caps,
+                             long long cap_all, double eps, hipStream_t s);
+hipError_t launch_gram_rcopy(const GramProb<float>* probs, const RInst* inst, int count, float* R,
+                             hipStream_t s);
+hipError_t launch_gram_rround(const GramRagged& g, float* X, long long round, mp_trace tr,
+                              hipStream_t s);
+
 }  // namespace mp

@@ -256,8 +256,8 @@ __global__ __launch_bounds__(NT + 2 * kWave) void k_gram_bsteps(GramBatch b, Gra
   if (t.rr) t.rr += j * tr.cap;
   if (t.r) t.r += j * tr.cap * tr.ldr;
   const long long cap = st->max_iters;
-  if (threadIdx.x < NT) gram_steps<float, NT, CPT, true, true, 512>(p, bd, cap, 0, t, lds, sh);
-  else gram_steps<float, NT, CPT, false, true, 512>(p, bd, cap, 0, t, lds, sh);
+  if (threadIdx.x < NT) gram_steps<float, NT, CPT, true, true, 512, false>(p, bd, cap, 0, t, lds, sh);
+  else gram_steps<float, NT, CPT, false, true, 512, false>(p, bd, cap, 0, t, lds, sh);
   if (threadIdx.x == 0 && !st->done)
     (void)__hip_atomic_fetch_or(again, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

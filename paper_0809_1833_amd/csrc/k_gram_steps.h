@@ -88,11 +88,17 @@ __device__ inline v2dd update_chunk(double c, const v2dd& a, const v2dd& r, doub
 
 // dot_column_f32 / dot_column_f64 (the same chains, so the same result) with
 // few loads in flight, for a kernel whose registers hold the correlations.
-template <typename T, typename V>
+// ONE: one chain over the whole column, the ragged FP32 form's product.
+template <typename T, bool ONE, typename V>
 __device__ inline T dot_column_narrow(const V* __restrict__ p, const V* __restrict__ r, int ldu,
                                       int lane) {
-  const int h0 = ldu / 2;
   T acc_a = 0, acc_b = 0;
+  if constexpr (ONE) {
+#pragma unroll 2
+    for (int i = lane; i < ldu; i += kWave) fma_chunk(p[i], r[i], acc_a);
+    return wave_sum(acc_a);
+  }
+  const int h0 = ldu / 2;
 #pragma unroll 2
   for (int i = lane; i < h0; i += kWave) {
     const V a = p[i], b = p[h0 + i];
@@ -129,8 +135,9 @@ struct StepShared {
 // two copies, so that the chain waves' registers hold no correlations.
 // FULL: p.g holds every atom's Gram column (no slot map; the decode leaves
 // only at its stop or to have the correlations renewed).  VN: threads of the
-// workgroup whose order ||r||^2 is summed in.
-template <typename T, int NT, int CPT, bool DATA, bool FULL, int VN>
+// workgroup whose order ||r||^2 is summed in.  ONE: the product is one lane
+// chain over the whole column (wave W runs it).
+template <typename T, int NT, int CPT, bool DATA, bool FULL, int VN, bool ONE>
 __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long max_iters,
                            int first, const typename GramTrace<T>::type& tr,
                            typename Vec16<T>::type* r_lds, StepShared<T, NT, CPT>& sh) {
@@ -240,7 +247,7 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
     if (nc > 1) {
       for (int q = wave; q < nc; q += W + 2) {
         const int a = s_cand[q];
-        const T v = dot_column_narrow<T>(
+        const T v = dot_column_narrow<T, ONE>(
             reinterpret_cast<const V16*>(p.psi + static_cast<int64_t>(a) * p.ld), r_lds, ldu,
             lane);
         if (lane == 0) s_keys[q] = make_key2(static_cast<double>(v), a);
@@ -270,20 +277,21 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
       // wave W + h: half h of the column into LDS for the update, and its
       // lane chain of the product
       if (tid == NT) x_old = p.x[win];
-      const int off = wave == W ? 0 : h0;
+      const int off = wave == W ? 0 : (ONE ? ldu : h0);
+      const int len = ONE ? ldu - off : h0;
       T acc = 0;
-      for (int base = lane; base < h0; base += kStepChain * kWave) {
+      for (int base = lane; base < len; base += kStepChain * kWave) {
         V16 ch[kStepChain];
 #pragma unroll
         for (int u = 0; u < kStepChain; ++u) {
           const int i = base + kWave * u;
-          ch[u] = col[off + (i < h0 ? i : h0 - 1)];
+          ch[u] = col[off + (i < len ? i : len - 1)];
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < kStepChain; ++u) {
           const int i = base + kWave * u;
-          if (i < h0) {
+          if (i < len) {
             s_col[off + i] = ch[u];
             fma_chunk(ch[u], r_lds[off + i], acc);
           }

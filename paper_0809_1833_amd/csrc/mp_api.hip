@@ -128,9 +128,20 @@ void free_gram_batch(mp_ctx* c) {
   c->gram_bcap = 0;
 }
 
+void free_gram_ragged(mp_ctx* c) {
+  (void)hipFree(c->gram_rmem);
+  if (c->gram_hrmem) (void)hipHostFree(c->gram_hrmem);
+  for (hipEvent_t& e : c->gram_rev) {
+    if (e) (void)hipEventDestroy(e);
+    e = nullptr;
+  }
+  c->gram_rmem = c->gram_hrmem = nullptr;
+}
+
 void free_ctx(mp_ctx* c) {
   if (!c) return;
   free_gram(c);
+  free_gram_ragged(c);
   free_gram_batch(c);
   (void)hipFree(c->gram_full);
   free_batched(c);
@@ -731,9 +742,180 @@ mp_status solve_gram_batch(mp_ctx* c, const float* Y, int64_t ldy, int64_t B, fl
   return MP_OK;
 }
 
+// The problems, Gram columns and buffers of the ragged decode on carried
+// correlations, made with the context.  Gram columns per problem:
+// max(64, n / 4), as for one signal; in all at most the dictionaries' bytes
+// and 64 MiB (many tiny problems, whose rounding up would dominate, keep the
+// persistent launch, as do problems past the steps kernel's limits, and a
+// context whose memory does not reach).
+void make_gram_ragged(mp_ctx* c, hipStream_t s) {
+  if (!(c->max_norm > 0.99) || !(c->max_norm < 1.01) || c->r_count > 65535) return;
+  const size_t count = static_cast<size_t>(c->r_count);
+  const int64_t max_m = *std::max_element(c->r_m.begin(), c->r_m.end());
+  if (max_m > 32768) return;
+  int64_t lds = 0, work = 0, gcols = 0, maps = 0, tiles = 0, dict = 0;
+  std::vector<int64_t> stride(count), slots(count);
+  for (size_t i = 0; i < count; ++i) {
+    const int64_t ld = round_up(c->r_n[i], kLdAlign), m = c->r_m[i];
+    stride[i] = mp::gram_ragged_stride(c->r_max_ld, max_m, m);
+    slots[i] = round_up(std::min<int64_t>(std::max<int64_t>(64, c->r_n[i] / 4), m) + mp::kGramReq,
+                        16);
+    lds = std::max(lds, 8 * ld + 2 * m);
+    work += stride[i] + 17 * ld;
+    gcols += slots[i] * stride[i];
+    maps += round_up(m, 8);
+    tiles += (m + 15) / 16;
+    dict += ld * m;
+  }
+  if (lds > 150 * 1024 || gcols > dict + (int64_t{1} << 24)) return;
+  const int per = mp::gram_ragged_groups(tiles, c->num_cus);
+  std::vector<mp::GramGroup> groups;
+  for (int id : c->r_order) {
+    const int64_t t = (c->r_m[id] + 15) / 16;
+    for (int64_t k = 0; k * per < t; ++k)
+      groups.push_back(mp::GramGroup{id, static_cast<int>(k)});
+  }
+  // one allocation, cut into pieces on 256-byte lines
+  size_t total = 0;
+  auto piece = [&total](size_t bytes) {
+    const size_t at = total;
+    total += (bytes + 255) / 256 * 256;
+    return at;
+  };
+  const size_t o_work = piece(sizeof(float) * work), o_g = piece(sizeof(float) * gcols);
+  const size_t zeroed = total;  // entries past a problem's atoms stay zero
+  const size_t o_probs = piece(sizeof(mp::GramProb<float>) * count),
+               o_bounds = piece(sizeof(mp::GramBounds) * count),
+               o_order = piece(sizeof(int) * count),
+               o_groups = piece(sizeof(mp::GramGroup) * groups.size()),
+               o_map = piece(sizeof(uint16_t) * maps),
+               o_ctl = piece(sizeof(mp::GramCtl) * count),
+               o_st = piece(sizeof(mp::DevState) * count), o_again = piece(2 * sizeof(int));
+  auto make = [&]() {
+    if (hipMalloc(&c->gram_rmem, total) != hipSuccess) return false;
+    if (hipHostMalloc(&c->gram_hrmem, sizeof(mp::DevState) * count + 4 * sizeof(int),
+                      hipHostMallocDefault) != hipSuccess)
+      return false;
+    for (hipEvent_t& e : c->gram_rev)
+      if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+        e = nullptr;
+        return false;
+      }
+    char* mem = static_cast<char*>(c->gram_rmem);
+    c->gram_rprobs = mem + o_probs;
+    c->gram_rbounds = mem + o_bounds;
+    c->gram_rorder = reinterpret_cast<int*>(mem + o_order);
+    c->gram_rgroups = mem + o_groups;
+    c->gram_rst = reinterpret_cast<mp::DevState*>(mem + o_st);
+    c->gram_ragain = reinterpret_cast<int*>(mem + o_again);
+    c->gram_hrst = static_cast<mp::DevState*>(c->gram_hrmem);
+    c->gram_hragain = reinterpret_cast<int*>(c->gram_hrst + count);
+    std::vector<mp::GramProb<float>> probs(count);
+    std::vector<mp::GramBounds> bounds(count);
+    float *w = reinterpret_cast<float*>(mem + o_work), *g = reinterpret_cast<float*>(mem + o_g);
+    uint16_t* map = reinterpret_cast<uint16_t*>(mem + o_map);
+    for (size_t i = 0; i < count; ++i) {
+      const int64_t ld = round_up(c->r_n[i], kLdAlign);
+      mp::GramProb<float>& p = probs[i];
+      p.psi = c->r_psi32 + c->r_psi_off[i];
+      p.ld = ld;
+      p.n = c->r_n[i];
+      p.m = c->r_m[i];
+      p.mp = stride[i];
+      p.c = w;
+      p.rhs = w + stride[i];
+      p.r = p.rhs + 16 * ld;
+      w += stride[i] + 17 * ld;
+      p.g = g;
+      g += slots[i] * stride[i];
+      p.slots = static_cast<int>(slots[i]);
+      p.map = map;
+      map += round_up(p.m, 8);
+      p.x = nullptr;
+      p.st = c->gram_rst + i;
+      p.ctl = reinterpret_cast<mp::GramCtl*>(mem + o_ctl) + i;
+      bounds[i] = c->storage == MP_BF16 ? mp::gram_bounds(p.n, c->max_norm, false)
+                                        : mp::gram_bounds_one(p.n, c->max_norm);
+    }
+    return hipMemsetAsync(mem, 0, zeroed, s) == hipSuccess &&
+           hipMemcpyAsync(c->gram_rprobs, probs.data(), sizeof(probs[0]) * count,
+                          hipMemcpyHostToDevice, s) == hipSuccess &&
+           hipMemcpyAsync(c->gram_rbounds, bounds.data(), sizeof(bounds[0]) * count,
+                          hipMemcpyHostToDevice, s) == hipSuccess &&
+           hipMemcpyAsync(c->gram_rorder, c->r_order.data(), sizeof(int) * count,
+                          hipMemcpyHostToDevice, s) == hipSuccess &&
+           hipMemcpyAsync(c->gram_rgroups, groups.data(), sizeof(groups[0]) * groups.size(),
+                          hipMemcpyHostToDevice, s) == hipSuccess &&
+           hipStreamSynchronize(s) == hipSuccess;
+  };
+  if (!make()) {
+    (void)hipGetLastError();
+    free_gram_ragged(c);
+    return;
+  }
+  c->gram_rngroups = static_cast<int>(groups.size());
+  c->gram_rsplit = 8 / per;
+  c->gram_rlds = lds;
+  c->gram_rsmall = max_m <= 4096 && c->r_max_ld <= 4096;
+}
+
+// The ragged decode on carried correlations.  `gave_up`: some problem needs
+// the persistent launch instead (all are then solved again).
+mp_status solve_gram_ragged(mp_ctx* c, const float* Y, float* X, const mp_opts* opts,
+                            const long long* caps, const mp_trace& tr, hipStream_t s,
+                            bool& gave_up) {
+  gave_up = false;
+  const mp::GramRagged g{static_cast<const mp::GramProb<float>*>(c->gram_rprobs),
+                         c->r_inst,
+                         static_cast<const mp::GramBounds*>(c->gram_rbounds),
+                         c->gram_rorder,
+                         static_cast<const mp::GramGroup*>(c->gram_rgroups),
+                         c->gram_ragain,
+                         static_cast<int>(c->r_count),
+                         c->gram_rngroups,
+                         c->gram_rsplit,
+                         c->r_max_ld,
+                         c->gram_rlds,
+                         c->gram_rsmall,
+                         c->storage == MP_F32};
+  const bool timed = c->profiling;
+  if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
+  HIP_TRY(c, mp::launch_gram_rinit(g, Y, X, caps, opts->max_iters, opts->eps, s));
+  long long issued = 0, seen = 0;
+  bool over = false;
+  while (!over) {
+    while (issued - seen < 2) {
+      HIP_TRY(c, mp::launch_gram_rround(g, X, issued, tr, s));
+      const int k = static_cast<int>(issued & 1);
+      HIP_TRY(c, hipMemcpyAsync(c->gram_hragain + 2 * k, c->gram_ragain, 2 * sizeof(int),
+                                hipMemcpyDeviceToHost, s));
+      HIP_TRY(c, hipEventRecord(c->gram_rev[k], s));
+      ++issued;
+    }
+    const int k = static_cast<int>(seen & 1);
+    HIP_TRY(c, hipEventSynchronize(c->gram_rev[k]));
+    over = c->gram_hragain[2 * k + k] == 0;
+    ++seen;
+  }
+  if (timed) HIP_TRY(c, hipEventRecord(c->ev[1], s));
+  HIP_TRY(c, hipMemcpyAsync(c->gram_hrst, c->gram_rst, sizeof(mp::DevState) * c->r_count,
+                            hipMemcpyDeviceToHost, s));
+  HIP_TRY(c, hipStreamSynchronize(s));
+  for (int64_t i = 0; i < c->r_count; ++i) gave_up |= c->gram_hrst[i].pad[0] != 0;
+  if (timed) {
+    float ms = 0.f;
+    if (hipEventElapsedTime(&ms, c->ev[0], c->ev[1]) == hipSuccess) {
+      c->prof_ms = ms;
+      c->prof_launches = 1;
+    }
+  }
+  return MP_OK;
+}
+
 // Results of a batched decode: one entry per signal and the call's status.
 template <class State>
-mp_status batched_results(mp_ctx* c, const State* slots, int64_t B, mp_result* res) {
+mp_status batched_results(mp_ctx* c, const State* slots, int64_t B, mp_result* res,
+                          const char* bad_y = "a column of Y holds NaN or Inf") {
   bool nonfinite = false, internal = false;
   for (int64_t b = 0; b < B; ++b) {
     const State& d = slots[b];
@@ -749,7 +931,7 @@ mp_status batched_results(mp_ctx* c, const State* slots, int64_t B, mp_result* r
   }
   if (internal)
     return fail(c, MP_EDEVICE, "internal error: a selected index fell outside the dictionary");
-  if (nonfinite) return fail(c, MP_ENONFINITE, "a column of Y holds NaN or Inf");
+  if (nonfinite) return fail(c, MP_ENONFINITE, bad_y);
   return MP_OK;
 }
 
@@ -1688,6 +1870,8 @@ mp_status mp_create_ragged(mp_ctx** out, const mp_instance* inst, int64_t count,
     e = mp::launch_quant_bf16(c->r_psi32, elems, 1, c->r_psib, s);
     if (e != hipSuccess) return bail(MP_EDEVICE, "quantise");
   }
+  c->max_norm = largest_norm(norm2);
+  c->r_psi_off = psi_off;
   for (int64_t i = 0; i < count; ++i) {
     desc[i].psi32 = c->r_psi32 + psi_off[i];
     desc[i].psib = storage == MP_BF16 ? c->r_psib + psi_off[i] : nullptr;
@@ -1704,6 +1888,7 @@ mp_status mp_create_ragged(mp_ctx** out, const mp_instance* inst, int64_t count,
   e = hipMemcpyAsync(c->r_inst, desc.data(), sizeof(mp::RInst) * count, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return bail(MP_EDEVICE, std::string("upload: ") + hipGetErrorString(e));
+  make_gram_ragged(c, s);
   *out = c;
   return MP_OK;
 }
@@ -1808,6 +1993,23 @@ mp_status mp_solve_ragged(mp_ctx* ctx, const float* Y, float* X, float* R, const
   if (max_iters)
     HIP_TRY(c, hipMemcpyAsync(c->r_caps, max_iters, sizeof(long long) * c->r_count,
                               hipMemcpyHostToDevice, s));
+  // MP_RAGGED_SPIN_LIMIT limits the waits of the persistent launch, so it
+  // selects that launch
+  if ((!lp || rk == mp::kLpTopK) && !getenv("MP_RAGGED_SPIN_LIMIT") && c->gram_rmem) {
+    c->prof_ms = 0.0;
+    c->prof_launches = 0;
+    bool gave_up = false;
+    const mp_status gs = solve_gram_ragged(c, Y, X, opts, caps, tr, s, gave_up);
+    if (gs != MP_OK) return gs;
+    if (!gave_up) {
+      if (R) {
+        HIP_TRY(c, mp::launch_gram_rcopy(static_cast<const mp::GramProb<float>*>(c->gram_rprobs),
+                                         c->r_inst, static_cast<int>(c->r_count), R, s));
+        HIP_TRY(c, hipStreamSynchronize(s));
+      }
+      return batched_results(c, c->gram_hrst, c->r_count, res, "an instance's y holds NaN or Inf");
+    }
+  }
   int grid = c->num_cus * c->r_cfg.wgs_per_cu;
   if (mp_status is = ragged_items(c, grid, s); is != MP_OK) return is;
   if (grid > c->r_nitems) grid = c->r_nitems;

@@ -393,6 +393,23 @@ struct mp_ctx {
   hipStream_t r_cap_stream = nullptr;
   hipGraphExec_t r_graph = nullptr;
   std::vector<unsigned char> r_graph_key;
+  // the ragged decode on carried correlations (made with the context):
+  // problems, Gram columns and work buffers, all in one allocation
+  void* gram_rmem = nullptr;     // null: not available
+  void* gram_rprobs = nullptr;   // mp::GramProb<float>, count
+  void* gram_rbounds = nullptr;  // mp::GramBounds, count
+  int* gram_rorder = nullptr;
+  void* gram_rgroups = nullptr;  // mp::GramGroup
+  mp::DevState* gram_rst = nullptr;   // count
+  int* gram_ragain = nullptr;    // 2
+  void* gram_hrmem = nullptr;    // pinned:
+  mp::DevState* gram_hrst = nullptr;  // count
+  int* gram_hragain = nullptr;   // 2 x 2
+  hipEvent_t gram_rev[2] = {nullptr, nullptr};
+  int gram_rngroups = 0, gram_rsplit = 0;
+  int64_t gram_rlds = 0;
+  bool gram_rsmall = false;
+  std::vector<int64_t> r_psi_off;     // host: offsets of the dictionaries in r_psi32
   // OMP decode buffers (grown on demand)
   mp::OmpBufs omp;
   // the decode on carried correlations (k_gram.h): largest column norm (0: not

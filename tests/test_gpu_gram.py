@@ -287,3 +287,69 @@ def test_batched_ties_and_handing_back():
     rows[300:400] = rows[300]
     ys = torch.stack([rows[300], ys[:, 1]], dim=0).t()
     _batched_same(rows, ys, 0.005, 400)
+
+
+# ---- many problems of uneven size ---------------------------------------------
+
+def _ragged_probs(sizes, seed=0):
+    return [_draw(n, m, max(1, min(n, m) // 16), noise=0.005 if m > n else 0.0, seed=seed + i)
+            for i, (n, m) in enumerate(sizes)]
+
+
+def _ragged_out(dec, y, eps, caps, cap):
+    out = dec.solve(y, eps, caps, trace_cap=cap, trace_r=True)
+    torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("sizes", [
+    [(64, 256), (63, 200), (128, 1024), (129, 1025), (1, 5), (300, 4096), (1000, 3999), (200, 100)],
+    [(4096, 900), (70, 4096), (256, 4095)],          # the largest set of 256 threads
+    [(4097, 700), (64, 300), (100, 4097)],           # 512 threads
+    [(100, 8192), (90, 8193), (300, 1200), (40, 32768)],
+])
+def test_ragged_equals_persistent_launch(storage, sizes, monkeypatch):
+    """Every problem as the persistent launch (which MP_RAGGED_SPIN_LIMIT
+    selects) decodes it: the same atoms, coefficients, x~ and r."""
+    from paper_0809_1833_amd.mp import RaggedDecoder
+    print(f"[gram ragged {storage} {sizes}]", flush=True)
+    probs = _ragged_probs(sizes)
+    caps = [20 * max(1, min(s) // 16) + i for i, s in enumerate(sizes)]
+    cap = max(caps)
+    with RaggedDecoder([rows.t() for rows, _ in probs], storage=storage) as dec:
+        y = dec.pack([p[1] for p in probs])
+        a = _ragged_out(dec, y, 0.003, caps, cap)
+        again = dec.solve(y, 0.003, caps)
+        monkeypatch.setenv("MP_RAGGED_SPIN_LIMIT", "4194304")
+        b = _ragged_out(dec, y, 0.003, caps, cap)
+    assert a["iters"] == b["iters"] and a["stop"] == b["stop"] and max(a["iters"]) > 0
+    assert torch.equal(a["x"], again["x"]) and torch.equal(a["r"], again["r"])
+    for key in ("x", "r", "idx", "coef", "r_trace"):
+        assert torch.equal(a[key], b[key]), key
+    for key in ("yy", "rr"):
+        assert all(abs(u - v) <= 1e-13 * v for u, v in zip(a[key], b[key])), key
+
+
+def test_ragged_odd_inputs_and_handing_back():
+    """A zero y, a cap of zero, exact ties; a problem on which more atoms tie
+    than a step can score sends the set to the persistent launch; NaN fails
+    the call and leaves the others decoded."""
+    from paper_0809_1833_amd import mp
+    from paper_0809_1833_amd.mp import RaggedDecoder
+    probs = _ragged_probs([(200, 800), (150, 600), (100, 400)], seed=20)
+    rows0 = probs[0][0]
+    rows0[400:] = -rows0[:400]
+    for many in (False, True):
+        if many:
+            rows0[100:200] = rows0[100]
+            probs[0] = (rows0, rows0[100].clone())
+        with RaggedDecoder([rows.t() for rows, _ in probs]) as dec:
+            y = dec.pack([probs[0][1], torch.zeros(150, device="cuda"), probs[2][1]])
+            a = _ragged_out(dec, y, 0.01, [200, 50, 0], 200)
+            assert a["stop"][1:] == ["zero_input", "max_iters"] and a["iters"][1:] == [0, 0]
+            assert int(a["idx"][0].max()) < (400 if not many else 101)
+            y[3] = float("nan")
+            with pytest.raises(mp.MPError) as e:
+                dec.solve(y, 0.01, 50)
+            assert e.value.status == mp.MP_ENONFINITE
