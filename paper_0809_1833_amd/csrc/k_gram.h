@@ -36,6 +36,7 @@
 namespace mp {
 
 constexpr int kGramReq = 15;        // Gram columns per pass (with r: 16 right-hand sides)
+constexpr int kGramMaxAtoms = 32768;  // of a dictionary that decodes on carried correlations
 constexpr int kGramMaxCand = 64;    // atoms scored exactly in one step, at most
 constexpr unsigned kGramNone = 0xFFFFu;  // map entry of an atom without a Gram column
 
@@ -52,7 +53,8 @@ struct GramCtl {
 struct GramBounds {
   float pass;          // |c~ - <r, psi>| after a pass
   float col;           // |g~ - <psi_i, psi_m>|
-  float step;          // added per step: r's and c~'s own rounding
+  float step;          // added per step, times ||r||: r's own rounding
+  float carry;         // added per step, times the largest |c~|: c~'s own rounding
   float dot;           // |dot_column_f32 - <r, psi>|
 };
 
@@ -77,10 +79,15 @@ struct GramProb {
 
 // Threads and correlations per thread of the steps kernel for m atoms and
 // columns of ld elements of `esize` bytes; threads 0 where it does not apply.
+// c~ and a Gram column have gram_stride entries.
 struct GramShape {
   int threads, per_thread;
 };
 GramShape gram_shape(int64_t ld, int64_t m, int esize);
+inline int64_t gram_stride(const GramShape& sh) {
+  const int64_t all = static_cast<int64_t>(sh.threads) * sh.per_thread;
+  return all < kGramMaxAtoms ? all : kGramMaxAtoms;
+}
 GramBounds gram_bounds(int64_t n, double max_norm, bool f64);
 
 template <typename T>

@@ -24,9 +24,9 @@ namespace mp {
 //
 // Each 16-atom tile's rows are split over `split` waves of the workgroup, so
 // that a short dictionary still gives every CU waves; their sums meet in LDS
-// in a fixed order.  Two FP32 chains (even and odd steps) are cut every
-// 2 kPassRows rows and the cuts are summed in FP64, which keeps the rounding
-// bound of the products at that of a kChain-term sum.
+// in a fixed order.  Every 16 rows are an FP32 chain of their own, summed in
+// FP64 (with 64-row chains the bounds, and with them the lists of more than
+// one atom, were three times as wide, and the pass no faster).
 // 16 bytes of a column as floats.
 __device__ inline void put_floats(float* p, const v4f& v) { *reinterpret_cast<v4f*>(p) = v; }
 __device__ inline void put_floats(float* p, const Vec16<double>::type& v) {
@@ -37,7 +37,7 @@ __device__ inline void put_floats(float* p, const Vec16<double>::type& v) {
 constexpr int kPassThreads = 512;
 constexpr int kPassWaves = kPassThreads / kWave;
 constexpr int kPassRows = 64;           // rows of a piece: 4 steps of 16
-constexpr int kChain = kPassRows;       // rows summed in one FP32 chain, at most
+constexpr int kChain = 16;              // rows summed in one FP32 chain, at most
 
 // The right-hand sides in operand order: float4 s * 64 + 16 q + i holds rows
 // 16 s + 4 q .. + 3 of right-hand side i (r, the wanted columns, then zeros).
@@ -101,7 +101,9 @@ __device__ inline void gram_pass(const GramProb<T>& p, int64_t group, int split,
     v4f* my = turn[wave];
     const int pieces = static_cast<int>(p.ld / kPassRows);
     const int k0 = pieces * part / split, k1 = pieces * (part + 1) / split;
-    v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
+    v4f acc[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc[s] = v4f{0.f, 0.f, 0.f, 0.f};
     vec va[D][NL];
     v4f vb[D][4];
     auto load = [&](vec(&x)[NL], v4f(&y)[4], int k) {
@@ -125,15 +127,16 @@ __device__ inline void gram_pass(const GramProb<T>& p, int64_t group, int split,
         const v4f xa = my[i * 16 + ((4 * s + q) ^ i)];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[e], rb[s][e], acc[s & 1], 0, 0, 0);
+          acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[e], rb[s][e], acc[s], 0, 0, 0);
       }
       __builtin_amdgcn_wave_barrier();
     };
     auto flush = [&]() {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        tot[e] += static_cast<double>(acc[0][e]) + static_cast<double>(acc[1][e]);
-        acc[0][e] = acc[1][e] = 0.0f;
+        tot[e] += (static_cast<double>(acc[0][e]) + static_cast<double>(acc[1][e])) +
+                  (static_cast<double>(acc[2][e]) + static_cast<double>(acc[3][e]));
+        acc[0][e] = acc[1][e] = acc[2][e] = acc[3][e] = 0.0f;
       }
     };
     if (k0 < k1) {
@@ -144,7 +147,7 @@ __device__ inline void gram_pass(const GramProb<T>& p, int64_t group, int split,
         for (int d = 0; d < D; ++d)
           if (k + d < k1) {
             use(va[d], vb[d], k + d + D);
-            if (d == D - 1 || k + d + 1 >= k1) flush();
+            flush();
           }
     }
   }
@@ -204,8 +207,8 @@ template hipError_t launch_gram_pass<double>(const GramProb<double>&, int, bool,
 // operands rounded to FP32 first); dot_column_f32 is two lane chains of
 // ld / 128 terms, then 7 additions (in FP64 its rounding is far below the
 // rest).  Each is at most (terms + additions) u sum |a b| <= (...) u ||a||
-// ||b||; a step adds r's rounding (u ||r'|| against a unit column), c~'s own
-// (u |c~|) and that of the coefficient (u |c|, in col).
+// ||b||; a step adds r's rounding (u ||r'|| against a unit column; far less in
+// FP64), c~'s own (u |c~|) and that of the coefficient (u |c|, in col).
 GramBounds gram_bounds(int64_t n, double max_norm, bool f64) {
   const double u = 1.0 / 16777216.0, nn = static_cast<double>(n + 64);
   const double slack = 1.01;
@@ -213,7 +216,8 @@ GramBounds gram_bounds(int64_t n, double max_norm, bool f64) {
   GramBounds b;
   b.pass = static_cast<float>(prod * max_norm);
   b.col = static_cast<float>(prod * max_norm * max_norm);
-  b.step = static_cast<float>(2.1 * u * max_norm * slack);
+  b.step = static_cast<float>((f64 ? 1e-3 : 1.01) * u * max_norm * slack);
+  b.carry = static_cast<float>(1.01 * u * slack);
   b.dot = static_cast<float>((f64 ? 0.1 : nn / 128 + 10) * u * max_norm * slack);
   return b;
 }
@@ -239,14 +243,16 @@ static int64_t step_lds(int64_t ld, int64_t m, int esize) {
 }
 
 // The smallest workgroup that holds the correlations: fewer waves make the
-// reductions and barriers of a step shorter.  Columns above 4096 rows take
+// reductions and barriers of a step shorter.  Above 16384 atoms 14 waves share
+// them: a wave's correlations and Gram entries then fit the 128 registers of
+// four waves per SIMD (8 waves with 64 each spilled 34 registers a lane).  Columns above 4096 rows take
 // 512 threads, so that no thread updates more than a few chunks of r.
 GramShape gram_shape(int64_t ld, int64_t m, int esize) {
-  const GramShape shapes[] = {{256, 4}, {256, 16}, {512, 16}, {512, 32}, {512, 64}};
-  if (step_lds(ld, m, esize) > kStepLds) return GramShape{0, 0};
+  const GramShape shapes[] = {{256, 4}, {256, 16}, {512, 16}, {512, 32}, {896, 40}};
+  if (m > kGramMaxAtoms || step_lds(ld, m, esize) > kStepLds) return GramShape{0, 0};
   for (const GramShape& s : shapes)
     if (m <= static_cast<int64_t>(s.threads) * s.per_thread &&
-        (ld * esize <= 16384 || s.threads == 512))
+        (ld * esize <= 16384 || s.threads >= 512))
       return s;
   return GramShape{0, 0};
 }
@@ -277,8 +283,8 @@ hipError_t launch_gram_steps(const GramProb<T>& p, const GramShape& sh, const Gr
     return launch_steps_t<T, 512, 16>(p, b, max_iters, first, tr, s);
   if (sh.threads == 512 && sh.per_thread == 32)
     return launch_steps_t<T, 512, 32>(p, b, max_iters, first, tr, s);
-  if (sh.threads == 512 && sh.per_thread == 64)
-    return launch_steps_t<T, 512, 64>(p, b, max_iters, first, tr, s);
+  if (sh.threads == 896 && sh.per_thread == 40)
+    return launch_steps_t<T, 896, 40>(p, b, max_iters, first, tr, s);
   return hipErrorInvalidValue;
 }
 template hipError_t launch_gram_steps<float>(const GramProb<float>&, const GramShape&,

@@ -87,23 +87,34 @@ __device__ inline v2dd update_chunk(double c, const v2dd& a, const v2dd& r, doub
 }
 
 // dot_column_f32 / dot_column_f64 (the same chains, so the same result) with
-// few loads in flight, for a kernel whose registers hold the correlations.
-// ONE: one chain over the whole column, the ragged FP32 form's product.
-template <typename T, bool ONE, typename V>
+// 2 S loads in flight.  ONE: one chain over the whole column, the ragged FP32
+// form's product.
+template <typename T, bool ONE, int S, typename V>
 __device__ inline T dot_column_narrow(const V* __restrict__ p, const V* __restrict__ r, int ldu,
                                       int lane) {
   T acc_a = 0, acc_b = 0;
-  if constexpr (ONE) {
-#pragma unroll 2
-    for (int i = lane; i < ldu; i += kWave) fma_chunk(p[i], r[i], acc_a);
-    return wave_sum(acc_a);
-  }
-  const int h0 = ldu / 2;
-#pragma unroll 2
-  for (int i = lane; i < h0; i += kWave) {
-    const V a = p[i], b = p[h0 + i];
-    fma_chunk(a, r[i], acc_a);
-    fma_chunk(b, r[h0 + i], acc_b);
+  constexpr int U = ONE ? 2 * S : S;
+  const int len = ONE ? ldu : ldu / 2;
+  const V* pb = p + len;
+  const V* rb = r + len;
+  for (int base = lane; base < len; base += U * kWave) {
+    V a[U], b[ONE ? 1 : U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = base + kWave * u;
+      const int at = i < len ? i : len - 1;
+      a[u] = p[at];
+      if constexpr (!ONE) b[u] = pb[at];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = base + kWave * u;
+      if (i < len) {
+        fma_chunk(a[u], r[i], acc_a);
+        if constexpr (!ONE) fma_chunk(b[u], rb[i], acc_b);
+      }
+    }
   }
   return wave_sum(acc_a + acc_b);
 }
@@ -146,7 +157,8 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
   // the slot map is in LDS beside r and the column where there is room (FP32)
   constexpr bool map_lds = !FULL && sizeof(T) == 4;
   constexpr int W = NT / kWave;    // data waves; waves W and W + 1 run the chains
-  constexpr int V = VN / NT;       // waves of that workgroup each data wave plays
+  constexpr int NR = NT > 512 ? 512 : NT;  // threads that update r
+  constexpr int V = VN / NR;       // waves of that workgroup each of their waves plays
   constexpr int NA = NT + 2 * kWave;
   constexpr int C4 = CPT / 4;
   constexpr int TOP = (kGramReq + W - 1) / W;  // columns each wave proposes
@@ -168,11 +180,18 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
   const int m = static_cast<int>(p.m);
   constexpr bool data = DATA;
 
+  // (the last correlations of a share that is not all of c~)
+  auto held = [&](int u) {
+    return NT <= 512 || u + 1 < C4 || 4 * (tid + NT * u) < static_cast<int>(p.mp);
+  };
+
   // this launch's state: the correlations into registers, r and the map into LDS
   v4f cv[C4];
   if constexpr (data) {
 #pragma unroll
-    for (int u = 0; u < C4; ++u) cv[u] = reinterpret_cast<const v4f*>(p.c)[tid + NT * u];
+    for (int u = 0; u < C4; ++u)
+      cv[u] = held(u) ? reinterpret_cast<const v4f*>(p.c)[tid + NT * u]
+                      : v4f{0.f, 0.f, 0.f, 0.f};
   } else {
 #pragma unroll
     for (int u = 0; u < C4; ++u) cv[u] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -208,6 +227,7 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
   for (;;) {
     // ---- the shortlist: atoms within the band of the largest |c~| ----------
     const float cmax = row_max(s_wmax[lane % 16]);
+    if (!fresh) err += bd.carry * cmax;  // c~'s own rounding in the last step
     const float band = 2.002f * (err + bd.dot * rn);
     if (!(band <= 0.125f * cmax) || !(rr > 1e-48) || !(rr < 1e60)) {
       bail = fresh;  // no band narrow enough even on fresh products
@@ -245,9 +265,12 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
     int win;
     T c = 0;
     if (nc > 1) {
-      for (int q = wave; q < nc; q += W + 2) {
+      // the chain waves, which have the registers for 16 loads in flight, take
+      // the first two (4 loads in flight in any wave: 18,000 clocks at
+      // N = 8192, on a quarter of the steps)
+      for (int q = data ? wave + 2 : wave - W; q < nc; q += W + 2) {
         const int a = s_cand[q];
-        const T v = dot_column_narrow<T, ONE>(
+        const T v = dot_column_narrow<T, ONE, DATA ? 2 : 8>(
             reinterpret_cast<const V16*>(p.psi + static_cast<int64_t>(a) * p.ld), r_lds, ldu,
             lane);
         if (lane == 0) s_keys[q] = make_key2(static_cast<double>(v), a);
@@ -272,7 +295,8 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
       const v4f* gp =
           reinterpret_cast<const v4f*>(p.g + static_cast<int64_t>(have ? slot : 0u) * p.mp);
 #pragma unroll
-      for (int u = 0; u < C4; ++u) g[u] = gp[tid + NT * u];
+      for (int u = 0; u < C4; ++u)
+        g[u] = held(u) ? gp[tid + NT * u] : v4f{0.f, 0.f, 0.f, 0.f};
     } else {
       // wave W + h: half h of the column into LDS for the update, and its
       // lane chain of the product
@@ -308,19 +332,21 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
 
     // ---- the update: r, ||r||^2, x~, the carried correlations ---------------
     if constexpr (data) {
-      double sq[V];
+      if (wave < NR / kWave) {
+        double sq[V];
 #pragma unroll
-      for (int v = 0; v < V; ++v) sq[v] = 0.0;
-      for (int i0 = tid; i0 < ldu; i0 += NT * V)
+        for (int v = 0; v < V; ++v) sq[v] = 0.0;
+        for (int i0 = tid; i0 < ldu; i0 += NR * V)
+#pragma unroll
+          for (int v = 0; v < V; ++v) {
+            const int i = i0 + NR * v;
+            if (i < ldu) r_lds[i] = update_chunk(c, s_col[i], r_lds[i], sq[v]);
+          }
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-          const int i = i0 + NT * v;
-          if (i < ldu) r_lds[i] = update_chunk(c, s_col[i], r_lds[i], sq[v]);
+          const double sv = wave_sum(sq[v]);
+          if (lane == 0) s_red[wave + NR / kWave * v] = sv;
         }
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const double sv = wave_sum(sq[v]);
-        if (lane == 0) s_red[wave + W * v] = sv;
       }
       if (have) {
         const float cf = static_cast<float>(c);

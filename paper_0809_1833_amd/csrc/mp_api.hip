@@ -446,7 +446,7 @@ bool ensure_gram(mp_ctx* c, hipStream_t s) {
   c->gram_tried = true;
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, c->storage == MP_F64 ? 8 : 4);
   if (sh.threads == 0 || !(c->max_norm > 0.99) || !(c->max_norm < 1.01)) return false;
-  c->gram_mp = static_cast<int64_t>(sh.threads) * sh.per_thread;
+  c->gram_mp = mp::gram_stride(sh);
   const int64_t want = std::max<int64_t>(256, c->n / 4);
   const int64_t slots = round_up(std::min<int64_t>(want, c->m) + mp::kGramReq, 16);
   const size_t row = static_cast<size_t>(c->gram_mp) * sizeof(float);
@@ -648,7 +648,7 @@ bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
                            static_cast<double>(c->ld) / 45e6;
     if (cost_us > 11.0 * static_cast<double>(tmax) || c->gram_full_tried) return false;
     c->gram_full_tried = true;
-    const int64_t stride = static_cast<int64_t>(sh.threads) * sh.per_thread;
+    const int64_t stride = mp::gram_stride(sh);
     const size_t bytes = sizeof(float) * static_cast<size_t>(stride) * static_cast<size_t>(c->m);
     if (hipMalloc(&c->gram_full, bytes) != hipSuccess) {
       (void)hipGetLastError();
