@@ -108,6 +108,31 @@ hipError_t launch_gram_steps(const GramProb<T>& p, const GramShape& sh, const Gr
                              long long max_iters, bool first, typename GramTrace<T>::type tr,
                              hipStream_t s);
 
+// ---- Orthogonal Matching Pursuit (k_omp_gram.hip) ---------------------------
+struct OmpCarry {
+  int hold;              // the next step waits for a block's pass
+  int cur;               // block position of the last selected atom; -1: P holds it already
+  long long t0;          // directions before the block
+  float err;             // bound on |c~ - <r, psi_m>|
+  int slot[kGramReq];    // block positions of the atoms selected from it, in order
+  float perr[kGramReq];  // bounds on their columns of P
+  GramCtl ctl;           // the block's candidates
+};
+// The block's two passes, where *hold is set: right-hand sides packed, then
+// over the first st->t (at most pq.m) columns of pq; and over p.
+hipError_t launch_gram_block(const GramProb<float>& p, const GramProb<float>& pq, const int* hold,
+                             int num_cus, hipStream_t s);
+hipError_t launch_gram_block_pass(const GramProb<float>& p, const int* hold, int num_cus,
+                                  hipStream_t s);
+hipError_t launch_omp_carry_init(const OmpBufs& b, hipStream_t s);
+hipError_t launch_omp_block(const float* psi, int64_t ld, int64_t n, int64_t m, float* r,
+                            const OmpBufs& b, DevState* st, long long t_bound, int num_cus,
+                            hipStream_t s);
+hipError_t launch_omp_pick(const float* psi, int64_t ld, int64_t m, const float* r,
+                           const OmpBufs& b, const GramBounds& bd, bool after_pass,
+                           bool want_coef, DevState* st, hipStream_t s);
+int64_t omp_tops(int64_t m);   // keys k_omp_carry publishes
+
 // ---- signals that share one dictionary (k_gram_batched.hip) ----------------
 struct GramBatch {
   const float* psi;    // ld x m

@@ -202,6 +202,44 @@ hipError_t launch_gram_pass(const GramProb<T>& p, int num_cus, bool first, hipSt
 template hipError_t launch_gram_pass<float>(const GramProb<float>&, int, bool, hipStream_t);
 template hipError_t launch_gram_pass<double>(const GramProb<double>&, int, bool, hipStream_t);
 
+// The passes of an OMP block (k_omp_gram.hip).
+__global__ __launch_bounds__(256) void k_gram_block_pack(GramProb<float> p,
+                                                         const int* __restrict__ hold) {
+  if (!p.st->done && *hold) gram_pack(p, 0);
+}
+
+// count: columns of p in use (null: all of them).
+__global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(4))) void
+k_gram_block_pass(GramProb<float> p, int split, const int* __restrict__ hold,
+                  const long long* __restrict__ count) {
+  if (p.st->done || !*hold) return;
+  if (count) p.m = *count;
+  if (p.m > 0) gram_pass(p, static_cast<int64_t>(blockIdx.x), split, 0);
+}
+
+static hipError_t block_pass(const GramProb<float>& p, const int* hold, const long long* count,
+                             int num_cus, hipStream_t s) {
+  const int64_t tiles = (p.m + 15) / 16;
+  const int split = pass_split(tiles, num_cus);
+  const int per = kPassWaves / split;
+  k_gram_block_pass<<<dim3(static_cast<unsigned>((tiles + per - 1) / per)), dim3(kPassThreads), 0,
+                      s>>>(p, split, hold, count);
+  return hipGetLastError();
+}
+
+hipError_t launch_gram_block(const GramProb<float>& p, const GramProb<float>& pq, const int* hold,
+                             int num_cus, hipStream_t s) {
+  k_gram_block_pack<<<dim3(static_cast<unsigned>(p.ld * 4 / 256)), dim3(256), 0, s>>>(p, hold);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || pq.m <= 0) return e;
+  return block_pass(pq, hold, &p.st->t, num_cus, s);
+}
+
+hipError_t launch_gram_block_pass(const GramProb<float>& p, const int* hold, int num_cus,
+                                  hipStream_t s) {
+  return block_pass(p, hold, nullptr, num_cus, s);
+}
+
 // The bounds (u = 2^-24): a product of the pass is a chain of at most kChain
 // terms, rounded once more to FP32 (and, from an FP64 dictionary, both
 // operands rounded to FP32 first); dot_column_f32 is two lane chains of

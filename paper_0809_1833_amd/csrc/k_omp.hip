@@ -15,6 +15,7 @@
 // Each stage is its own launch; all of them return at once when the device
 // state says the run is over, so the host can enqueue iterations ahead.
 #include "k_common.h"
+#include "k_gram.h"
 #include "mp_internal.h"
 
 namespace mp {
@@ -88,8 +89,9 @@ __global__ __launch_bounds__(kOmpThreads) void k_omp_select(
 __global__ __launch_bounds__(kOmpThreads) void k_omp_proj(
     const float* __restrict__ q, int64_t ld, const float* __restrict__ psi,
     const float* __restrict__ wv, bool from_atom, float* __restrict__ hp,
-    const DevState* __restrict__ st, const OmpState* __restrict__ os) {
-  if (st->done) return;
+    const DevState* __restrict__ st, const OmpState* __restrict__ os,
+    const OmpCarry* __restrict__ oc) {
+  if (st->done || (oc && oc->hold)) return;
   const long long t = st->t;
   const int64_t j0 = static_cast<int64_t>(blockIdx.x) * kOmpWaves;
   if (j0 >= t) return;  // workgroup-uniform
@@ -123,15 +125,21 @@ __global__ __launch_bounds__(kOmpThreads) void k_omp_proj(
 // workgroup 0 also stores h for R's column): wave w sums j = w mod 16 in
 // increasing order, one row per lane; the 16 partial sums are added in a
 // fixed tree; the workgroup's FP64 sum of w^2 goes to part[b].
+// Pass 2 of a step on carried correlations (dpart): also the sum of squares of
+// d = w - (W_i - sum_s h_s q_s), s over the directions of the block the atom
+// was taken from at position i (one wave each), with h the sum of both passes.
 __global__ __launch_bounds__(kOrthThreads) void k_omp_orth(
     const float* __restrict__ q, int64_t ld, const float* __restrict__ psi,
     const float* __restrict__ wv_in, bool from_atom, const float* __restrict__ hp,
     float* __restrict__ h_out, float* __restrict__ w_out, double* __restrict__ part,
-    const DevState* __restrict__ st, const OmpState* __restrict__ os) {
-  if (st->done) return;
+    const DevState* __restrict__ st, const OmpState* __restrict__ os,
+    const OmpCarry* __restrict__ oc, const float* __restrict__ h1,
+    const float* __restrict__ w15, double* __restrict__ dpart) {
+  if (st->done || (oc && oc->hold)) return;
   extern __shared__ float h_lds[];  // t floats
   __shared__ float ps[kOrthWaves][kOrthRows];
-  __shared__ double red[1];
+  __shared__ float pd[kOrthWaves][kOrthRows];
+  __shared__ double red[2];
   const long long t = st->t;
   for (long long j = threadIdx.x; j < t; j += kOrthThreads) {
     float hs = 0.0f;
@@ -148,6 +156,10 @@ __global__ __launch_bounds__(kOrthThreads) void k_omp_orth(
   for (long long j = wave; j < t; j += kOrthWaves)
     acc = __builtin_fmaf(h_lds[j], q[j * ld + nrow], acc);
   ps[wave][lane] = acc;
+  if (dpart) {
+    const long long j = oc->t0 + wave;
+    pd[wave][lane] = j < t ? (h1[j] + h_lds[j]) * q[j * ld + nrow] : 0.0f;
+  }
   __syncthreads();
   if (wave == 0) {
     float p8[8];
@@ -159,9 +171,20 @@ __global__ __launch_bounds__(kOrthThreads) void k_omp_orth(
     w_out[nrow] = wn;
     const double sq = wave_sum(static_cast<double>(wn) * wn);
     if (lane == 0) red[0] = sq;
+    if (dpart) {
+      float b = 0.0f;
+#pragma unroll
+      for (int k = 0; k < kOrthWaves; ++k) b += pd[k][lane];
+      const float d = wn - (w15[oc->cur * ld + nrow] - b);
+      const double dq = wave_sum(static_cast<double>(d) * d);
+      if (lane == 0) red[1] = dq;
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) {
+    part[blockIdx.x] = red[0];
+    if (dpart) dpart[blockIdx.x] = red[1];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -171,8 +194,9 @@ __global__ __launch_bounds__(kOmpThreads) void k_omp_update(
     float* __restrict__ q, int64_t ld, int64_t n, int64_t tq, const float* __restrict__ w,
     const float* __restrict__ h1, const float* __restrict__ h2, const double* __restrict__ part,
     int nparts, float* __restrict__ rmat, double* __restrict__ z, float* __restrict__ r,
-    DevState* __restrict__ st, const OmpState* __restrict__ os, mp_trace tr) {
-  if (st->done) return;
+    DevState* __restrict__ st, const OmpState* __restrict__ os,
+    const OmpCarry* __restrict__ oc, mp_trace tr) {
+  if (st->done || (oc && oc->hold)) return;
   __shared__ double dred[kOmpWaves];
   const long long t = st->t;
   // w and r in registers for the whole kernel (thread i holds elements
@@ -274,10 +298,9 @@ __global__ __launch_bounds__(kOmpThreads) void k_omp_solve(
 
 // ---------------------------------------------------------------------------
 
-hipError_t launch_omp_iteration(const float* psi, int64_t ld, int64_t n, int64_t m, float* r,
-                                const CorrGeom& g, uint64_t* keys, DevState* st, OmpBufs& b,
-                                long long t_bound, mp_trace tr, hipStream_t s, hipEvent_t e0,
-                                hipEvent_t e1) {
+hipError_t launch_omp_select(const float* psi, int64_t ld, int64_t m, const float* r,
+                             const CorrGeom& g, uint64_t* keys, DevState* st, const OmpBufs& b,
+                             hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const size_t lds = static_cast<size_t>(ld) * sizeof(float);
   static bool big_lds = false;
   hipError_t e;
@@ -292,13 +315,20 @@ hipError_t launch_omp_iteration(const float* psi, int64_t ld, int64_t n, int64_t
                                                             b.os, b.in_s, b.sel);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (e1 && (e = hipEventRecord(e1, s)) != hipSuccess) return e;
-  // t <= t_bound (one more atom per iteration at most)
+  return hipSuccess;
+}
+
+// One iteration after its selection (launch_omp_select, or launch_omp_pick
+// with carry): t <= t_bound directions so far.
+hipError_t launch_omp_fit(const float* psi, int64_t ld, int64_t n, float* r, DevState* st,
+                          const OmpBufs& b, long long t_bound, bool carry, mp_trace tr, hipStream_t s) {
+  hipError_t e;
   const unsigned pgrid = static_cast<unsigned>(t_bound > 0 ? (t_bound + kOmpWaves - 1) / kOmpWaves : 1);
   const unsigned ogrid = static_cast<unsigned>(ld / kOrthRows);
-  // h staged in LDS: tq <= 16384 floats, beside 4 KB of static LDS
+  // h staged in LDS: tq <= 16384 floats, beside 8 KB of static LDS
   const size_t h_lds = static_cast<size_t>(b.tq) * sizeof(float);
   static bool orth_big_lds = false;
-  if (!orth_big_lds && h_lds > 56 * 1024) {
+  if (!orth_big_lds && h_lds > 52 * 1024) {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_omp_orth),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
     if (e != hipSuccess) return e;
@@ -306,19 +336,21 @@ hipError_t launch_omp_iteration(const float* psi, int64_t ld, int64_t n, int64_t
   }
   if (ld % (4 * kOmpProjSlices) != 0 || ld / 4 / kOmpProjSlices > kProjSliceMax)
     return hipErrorInvalidValue;
+  const OmpCarry* oc = carry ? b.oc : nullptr;
   for (int pass = 0; pass < 2; ++pass) {
     const bool from_atom = pass == 0;
     float* h = pass == 0 ? b.h1 : b.h2;
-    k_omp_proj<<<dim3(pgrid, kOmpProjSlices), dim3(kOmpThreads), 0, s>>>(b.q, ld, psi, b.w,
-                                                                       from_atom, b.hp, st, b.os);
+    k_omp_proj<<<dim3(pgrid, kOmpProjSlices), dim3(kOmpThreads), 0, s>>>(
+        b.q, ld, psi, b.w, from_atom, b.hp, st, b.os, oc);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_omp_orth<<<dim3(ogrid), dim3(kOrthThreads), h_lds, s>>>(b.q, ld, psi, b.w, from_atom, b.hp,
-                                                             h, b.w, b.part, st, b.os);
+    k_omp_orth<<<dim3(ogrid), dim3(kOrthThreads), h_lds, s>>>(
+        b.q, ld, psi, b.w, from_atom, b.hp, h, b.w, b.part, st, b.os, oc, b.h1, b.w15,
+        carry && pass == 1 ? b.dpart : nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   k_omp_update<<<dim3(1), dim3(kOmpThreads), 0, s>>>(b.q, ld, n, b.tq, b.w, b.h1, b.h2, b.part,
                                                      static_cast<int>(ogrid), b.rmat, b.z, r, st,
-                                                     b.os, tr);
+                                                     b.os, oc, tr);
   return hipGetLastError();
 }
 

@@ -80,6 +80,23 @@ void free_ragged(mp_ctx* c) {
   if (c->r_cap_stream) (void)hipStreamDestroy(c->r_cap_stream);
 }
 
+void free_omp_carry(mp_ctx* c) {
+  mp::OmpBufs& b = c->omp;
+  (void)hipFree(b.oc);
+  (void)hipFree(b.c);
+  (void)hipFree(b.p);
+  (void)hipFree(b.w15);
+  (void)hipFree(b.rhs);
+  (void)hipFree(b.hr);
+  (void)hipFree(b.hq);
+  (void)hipFree(b.dpart);
+  (void)hipFree(b.tops);
+  b.oc = nullptr;
+  b.c = b.p = b.w15 = b.rhs = b.hr = b.hq = nullptr;
+  b.dpart = nullptr;
+  b.tops = nullptr;
+}
+
 void free_omp(mp_ctx* c) {
   mp::OmpBufs& b = c->omp;
   (void)hipFree(b.q);
@@ -93,6 +110,7 @@ void free_omp(mp_ctx* c) {
   (void)hipFree(b.hp);
   (void)hipFree(b.part);
   (void)hipFree(b.os);
+  free_omp_carry(c);
   b = mp::OmpBufs{};
 }
 
@@ -1268,6 +1286,9 @@ mp_status mp_solve_result(mp_ctx* ctx, mp_result* res) {
   return fs;
 }
 
+// Dictionaries below this many bytes select by a pass every step.
+constexpr int64_t kOmpCarryBytes = int64_t{1} << 22;
+
 static mp_status ensure_omp(mp_ctx* c, int64_t tq) {
   mp::OmpBufs& b = c->omp;
   if (b.tq >= tq) return MP_OK;
@@ -1289,6 +1310,99 @@ static mp_status ensure_omp(mp_ctx* c, int64_t tq) {
     return fail(c, MP_ENOMEM, "OMP work buffers");
   }
   b.tq = tq;
+  return MP_OK;
+}
+
+// Whether OMP's selection takes the carried correlations, and their buffers if
+// so.  They save the pass of all steps but about one in twelve and cost two
+// launches more a step and five more a pass.
+// Without them (column norms not near 1, no memory) every step selects by a
+// pass.
+static bool ensure_omp_carry(mp_ctx* c) {
+  mp::OmpBufs& b = c->omp;
+  if (c->ld * c->m * 4 < kOmpCarryBytes || !(c->max_norm > 0.99) || !(c->max_norm < 1.01))
+    return false;
+  if (b.oc) return true;
+  const size_t ld = static_cast<size_t>(c->ld), req = mp::kGramReq;
+  b.mp = round_up(c->m, 16);
+  b.ldh = round_up(b.tq, 16);
+  const size_t stride = static_cast<size_t>(b.mp), ldh = static_cast<size_t>(b.ldh);
+  if (hipMalloc(&b.oc, sizeof(mp::OmpCarry)) != hipSuccess ||
+      hipMalloc(&b.c, sizeof(float) * stride) != hipSuccess ||
+      hipMalloc(&b.p, sizeof(float) * stride * req) != hipSuccess ||
+      hipMalloc(&b.w15, sizeof(float) * ld * req) != hipSuccess ||
+      hipMalloc(&b.rhs, sizeof(float) * ld * 16) != hipSuccess ||
+      hipMalloc(&b.hr, sizeof(float) * ldh) != hipSuccess ||
+      hipMalloc(&b.hq, sizeof(float) * ldh * req) != hipSuccess ||
+      hipMalloc(&b.dpart, sizeof(double) * (ld / 64)) != hipSuccess ||
+      hipMalloc(&b.tops, sizeof(uint64_t) * static_cast<size_t>(mp::omp_tops(c->m))) !=
+          hipSuccess) {
+    (void)hipGetLastError();
+    free_omp_carry(c);
+    return false;
+  }
+  return true;
+}
+
+// The OMP decode on carried correlations (k_omp_gram.hip), after the init
+// kernel: rounds of a block (which returns at once while the current one
+// lasts) and kOmpSlots steps (which return at once while they wait for a
+// block), enqueued in chunks of kOmpRounds with two chunks in flight.  A
+// block lasts 4 to 15 steps: with 4 steps a round the launches that return at
+// once come to about 3 us a step.  `gave_up`: as in solve_gram.
+static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipStream_t s,
+                                bool& gave_up) {
+  constexpr int kOmpSlots = 4, kOmpRounds = 4;
+  mp::OmpBufs& b = c->omp;
+  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, false);
+  const bool timed = c->profiling;
+  gave_up = false;
+  if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
+  HIP_TRY(c, mp::launch_omp_carry_init(b, s));
+  // every two rounds take a step: a block is followed by a step of its own
+  // atom unless it renewed the correlations, and then the next one is
+  const long long most = (2 * T + 2) / kOmpRounds + 1;
+  long long issued = 0, seen = 0, known = 0, bound = 0;
+  bool over = T <= 0;
+  while (!over && seen < most) {
+    while (issued < most && issued - seen < 2) {
+      for (int round = 0; round < kOmpRounds; ++round) {
+        HIP_TRY(c, mp::launch_omp_block(c->psi32, c->ld, c->n, c->m, c->r_work, b, c->st, bound,
+                                        c->num_cus, s));
+        for (int k = 0; k < kOmpSlots; ++k) {
+          HIP_TRY(c, mp::launch_omp_pick(c->psi32, c->ld, c->m, c->r_work, b, bounds, k == 0,
+                                         tr.coef != nullptr, c->st, s));
+          HIP_TRY(c, mp::launch_omp_fit(c->psi32, c->ld, c->n, c->r_work, c->st, b, bound, true,
+                                        tr, s));
+          bound = std::min(bound + 1, T);
+        }
+      }
+      const int k = static_cast<int>(issued & 1);
+      HIP_TRY(c, hipMemcpyAsync(&c->h_st[1 + k], c->st, sizeof(mp::DevState),
+                                hipMemcpyDeviceToHost, s));
+      HIP_TRY(c, hipEventRecord(c->done_ev[k], s));
+      ++issued;
+    }
+    const int k = static_cast<int>(seen & 1);
+    HIP_TRY(c, hipEventSynchronize(c->done_ev[k]));
+    ++seen;
+    over = c->h_st[1 + k].done != 0;
+    gave_up = c->h_st[1 + k].pad[0] != 0;
+    known = c->h_st[1 + k].t;
+    // directions there can be once the chunks in flight are done
+    bound = std::min(known + (issued - seen) * kOmpRounds * kOmpSlots, T);
+  }
+  if (!over) gave_up = true;
+  if (timed) {
+    // the decode's time on the device over the steps it took
+    HIP_TRY(c, hipEventRecord(c->ev[1], s));
+    HIP_TRY(c, hipEventSynchronize(c->ev[1]));
+    float ms = 0.f;
+    if (hipEventElapsedTime(&ms, c->ev[0], c->ev[1]) == hipSuccess) {
+      c->prof_ms = ms;
+      c->prof_launches = known > 0 ? known : 1;
+    }
+  }
   return MP_OK;
 }
 
@@ -1316,18 +1430,32 @@ mp_status mp_solve_omp(mp_ctx* ctx, const float* y, float* x, float* r, const mp
   const long long T = std::min<long long>(opts->max_iters, c->n);
   if (mp_status bs = ensure_omp(c, std::max<long long>(T, 1)); bs != MP_OK) return bs;
   mp::OmpBufs& b = c->omp;
-  HIP_TRY(c, hipMemsetAsync(b.in_s, 0, static_cast<size_t>(c->m), s));
-  HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st, opts->eps, T, s));
-  HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
-  HIP_TRY(c, hipStreamSynchronize(s));
-  long long it = 0;  // iterations enqueued so far: a bound on the atoms selected
-  const mp_status st = run_iterations(c, T, s, false, [&](hipEvent_t e0, hipEvent_t e1) {
-    const hipError_t e = mp::launch_omp_iteration(c->psi32, c->ld, c->n, c->m, c->r_work, c->geom,
-                                                  c->partials, c->st, b, it, tr, s, e0, e1);
-    ++it;
-    return e;
-  });
-  if (st != MP_OK) return st;
+  auto init = [&]() {
+    const hipError_t e = hipMemsetAsync(b.in_s, 0, static_cast<size_t>(c->m), s);
+    return e != hipSuccess ? e : mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st,
+                                                 opts->eps, T, s);
+  };
+  HIP_TRY(c, init());
+  bool stepping = true;
+  if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && ensure_omp_carry(c)) {
+    const mp_status gs = solve_omp_gram(c, tr, T, s, stepping);
+    if (gs != MP_OK) return gs;
+    if (stepping) HIP_TRY(c, init());
+  }
+  if (stepping) {
+    HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
+    HIP_TRY(c, hipStreamSynchronize(s));
+    long long it = 0;  // iterations enqueued so far: a bound on the atoms selected
+    const mp_status st = run_iterations(c, T, s, false, [&](hipEvent_t e0, hipEvent_t e1) {
+      hipError_t e = mp::launch_omp_select(c->psi32, c->ld, c->m, c->r_work, c->geom, c->partials,
+                                           c->st, b, s, e0, e1);
+      if (e == hipSuccess)
+        e = mp::launch_omp_fit(c->psi32, c->ld, c->n, c->r_work, c->st, b, it, false, tr, s);
+      ++it;
+      return e;
+    });
+    if (st != MP_OK) return st;
+  }
   HIP_TRY(c, mp::launch_omp_solve(b, c->st, x, s));
   HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
   if (r)

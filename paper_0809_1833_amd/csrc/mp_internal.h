@@ -179,6 +179,8 @@ struct OmpState {           // the atom selected in the current iteration
   float c;                  // its correlation <r, psi_sel>
   int pad[2];
 };
+struct OmpCarry;            // the selection on carried correlations (k_gram.h)
+
 struct OmpBufs {            // work buffers of one OMP decode (context-owned)
   int64_t tq = 0;           // capacity: atoms (rows of q, order of R)
   float* q = nullptr;       // tq x ld: orthonormal basis of the selected atoms
@@ -192,15 +194,29 @@ struct OmpBufs {            // work buffers of one OMP decode (context-owned)
   float* hp = nullptr;      // tq x kOmpProjSlices: the projections by slice of rows
   double* part = nullptr;   // ld / 64: per-workgroup sums of w^2
   OmpState* os = nullptr;
+  // the selection on carried correlations (null: not available)
+  OmpCarry* oc = nullptr;
+  int64_t mp = 0, ldh = 0;  // strides of c and p (atoms), of hq (directions)
+  float* c = nullptr;       // mp carried correlations
+  float* p = nullptr;       // kGramReq x mp: Psi^T w_i of the block, then Psi^T q_t
+  float* w15 = nullptr;     // kGramReq x ld: the block's candidates, orthogonal to Q
+  float* rhs = nullptr;     // 16 x ld: the pass's right-hand sides
+  float* hr = nullptr;      // ldh
+  float* hq = nullptr;      // kGramReq x ldh: Q^T psi_i of the block
+  double* dpart = nullptr;  // ld / 64
+  uint64_t* tops = nullptr; // two keys per workgroup of k_omp_carry
 };
 // Slices of rows the projections of an OMP iteration are split into.
 constexpr int kOmpProjSlices = 8;
-// One OMP iteration (five launches); t_bound >= the number of atoms selected
-// so far (sizes the projection grid).  e0/e1 time the selection pass.
-hipError_t launch_omp_iteration(const float* psi, int64_t ld, int64_t n, int64_t m, float* r,
-                                const CorrGeom& g, uint64_t* keys, DevState* st, OmpBufs& b,
-                                long long t_bound, mp_trace tr, hipStream_t s, hipEvent_t e0,
-                                hipEvent_t e1);
+// One OMP iteration: the selection by a pass over the dictionary (e0/e1 time
+// it), then the fit (five launches); t_bound >= the number of atoms selected
+// so far (sizes the projection grid).  carry: the selection was launch_omp_pick.
+hipError_t launch_omp_select(const float* psi, int64_t ld, int64_t m, const float* r,
+                             const CorrGeom& g, uint64_t* keys, DevState* st, const OmpBufs& b,
+                             hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+hipError_t launch_omp_fit(const float* psi, int64_t ld, int64_t n, float* r, DevState* st,
+                          const OmpBufs& b, long long t_bound, bool carry, mp_trace tr,
+                          hipStream_t s);
 hipError_t launch_omp_solve(const OmpBufs& b, const DevState* st, float* x, hipStream_t s);
 
 // ---- batched decode against one dictionary (k_batched.hip) ------------------

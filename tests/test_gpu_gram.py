@@ -353,3 +353,54 @@ def test_ragged_odd_inputs_and_handing_back():
             with pytest.raises(mp.MPError) as e:
                 dec.solve(y, 0.01, 50)
             assert e.value.status == mp.MP_ENONFINITE
+
+
+# ---- Orthogonal Matching Pursuit ----------------------------------------------
+
+def _omp_same(rows, y, eps, cap):
+    from paper_0809_1833_amd.mp import Decoder
+    kw = dict(trace_cap=max(cap, 1), trace_r=True, omp=True)
+    with Decoder(rows.t()) as dec:
+        a = dec.solve(y, eps, cap, **kw)
+        plain = dec.solve(y, eps, cap, omp=True)
+        b = dec.solve(y, eps, cap, step_launches=True, **kw)
+        torch.cuda.synchronize()
+    for key in ("iters", "stop", "yy", "rr"):
+        assert a[key] == b[key] == plain[key], (key, a[key], b[key], plain[key])
+    for key in ("x", "r", "idx", "coef", "rr_trace", "r_trace"):
+        assert torch.equal(a[key], b[key]), key
+    assert torch.equal(plain["x"], b["x"]) and torch.equal(plain["r"], b["r"])
+    return a
+
+
+@pytest.mark.parametrize("n,m,k,noise", [
+    (1024, 1025, 60, 0.01), (1025, 1151, 40, 0.0), (700, 2049, 30, 0.01), (130, 16384, 12, 0.0),
+    (129, 8321, 6, 0.01), (4097, 300, 17, 0.0), (2048, 2000, 100, 0.0), (512, 4097, 2, 3.0),
+])
+def test_omp_equals_a_pass_per_step(n, m, k, noise):
+    """OMP's selection on carried correlations: the atoms, coefficients, x~ and
+    r of a pass per step, at the edges of the tiles and groups of atoms, over
+    one and several blocks, and with more noise than signal."""
+    print(f"[gram omp {n}x{m}]", flush=True)
+    rows, y = _draw(n, m, k, noise=noise)
+    a = _omp_same(rows, y, min(max(1.2 * noise, 1e-5), 0.5), min(3 * k + 20, n))
+    assert a["iters"] >= (k if noise < 1 else 20) // 2
+
+
+def test_omp_ties_caps_and_handing_back():
+    """Exact ties take the smallest index; near copies of selected atoms; caps
+    of 0 and 1; zero input; more ties than a step can score."""
+    rows, y = _draw(640, 2400, 24, seed=3)
+    rows[1200:1800] = rows[:600]
+    rows[1800:] = -rows[600:1200]
+    a = _omp_same(rows, y, 1e-5, 60)
+    assert int(a["idx"].max()) < 1200
+    for cap in (0, 1):
+        assert _omp_same(rows, y, 1e-5, cap)["iters"] == cap
+    _omp_same(rows, torch.zeros_like(y), 1e-5, 20)
+    near = rows.clone()
+    near[1200:1800] += 1e-3 * torch.randn_like(near[1200:1800]) / math.sqrt(640)
+    near /= near.norm(dim=1, keepdim=True)
+    _omp_same(near, (near[:40] + 0.5 * near[1200:1240]).sum(0), 1e-6, 120)
+    rows[300:400] = rows[300]
+    _omp_same(rows, rows[300].contiguous(), 1e-6, 20)
