@@ -138,7 +138,7 @@ struct StepShared {
   T chain[2][kWave];
   int n[2];
   int cand[kGramMaxCand];
-  int want[(kGramReq + W - 1) / W * W];
+  uint64_t want[kWave];
 };
 
 // The kernel's program for the data waves (DATA) and for the two chain waves:
@@ -161,7 +161,7 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
   constexpr int V = VN / NR;       // waves of that workgroup each of their waves plays
   constexpr int NA = NT + 2 * kWave;
   constexpr int C4 = CPT / 4;
-  constexpr int TOP = (kGramReq + W - 1) / W;  // columns each wave proposes
+  constexpr int TOP = W >= 16 ? 4 : (kWave / W < 6 ? kWave / W : 6);  // columns each wave proposes
   DevState* st = p.st;
   V16* s_col = r_lds + p.ld / E;
   uint16_t* s_map = map_lds ? reinterpret_cast<uint16_t*>(s_col + p.ld / E) : p.map;
@@ -171,7 +171,7 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
   int* s_n = sh.n;
   int* s_cand = sh.cand;
   Key2* s_keys = sh.keys;
-  int* s_want = sh.want;
+  uint64_t* s_want = sh.want;
   v4f(*s_spread)[CPT / 4] = sh.spread;
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
@@ -408,7 +408,8 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
     }
   }
   if (FULL || stop >= 0 || bail) return;
-  // the missing column first, then each wave's best atoms without one
+  // the missing column first, then the largest of each wave's best atoms
+  // without one
   // (cv: |c~| of this thread's atoms without a Gram column, -1 for the rest)
 #pragma unroll
   for (int u = 0; u < C4; ++u)
@@ -438,7 +439,7 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
         for (int e = 0; e < 4; ++e)
           if (at == 4 * u + e) cv[u][e] = -1.0f;
     }
-    if (data && lane == 0) s_want[k * W + wave] = w != 0 ? key_index(w) : -1;
+    if (data && lane == 0) s_want[k * W + wave] = w;
   }
   __syncthreads();
   // a full cache starts over
@@ -448,17 +449,28 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
     for (int i = tid; i < m; i += NA) p.map[i] = static_cast<uint16_t>(kGramNone);
     __syncthreads();
   }
-  if (tid == 0) {
+  if (wave == 0) {  // the proposals by rank
     GramCtl* ctl = p.ctl;
-    int nreq = 0;
-    if (idx >= 0) ctl->req[nreq++] = idx;
-    for (int k = 0; k < W * TOP && nreq < kGramReq; ++k)
-      if (s_want[k] >= 0) ctl->req[nreq++] = s_want[k];
-    for (int k = 0; k < nreq; ++k) p.map[ctl->req[k]] = static_cast<uint16_t>(used + k);
-    ctl->nreq = nreq;
-    ctl->slot0 = used;
-    ctl->used = used + nreq;
-    ctl->err = err;
+    const int base = idx >= 0 ? 1 : 0;
+    const uint64_t key = lane < W * TOP ? s_want[lane] : 0;
+    int rank = 0;
+    for (int k = 0; k < W * TOP; ++k) rank += s_want[k] > key;
+    if (key != 0 && base + rank < kGramReq) {
+      ctl->req[base + rank] = key_index(key);
+      p.map[key_index(key)] = static_cast<uint16_t>(used + base + rank);
+    }
+    const int found = base + static_cast<int>(__popcll(__ballot(key != 0)));
+    if (lane == 0) {
+      if (idx >= 0) {
+        ctl->req[0] = idx;
+        p.map[idx] = static_cast<uint16_t>(used);
+      }
+      const int nreq = found < kGramReq ? found : kGramReq;
+      ctl->nreq = nreq;
+      ctl->slot0 = used;
+      ctl->used = used + nreq;
+      ctl->err = err;
+    }
   }
 }
 

@@ -29,7 +29,7 @@ namespace mp {
 constexpr int kCarryThreads = 128;   // atoms per workgroup of k_omp_carry
 constexpr int kPickThreads = 1024;
 constexpr int kPickWaves = kPickThreads / kWave;
-constexpr int kPickTop = 2;          // atoms each wave proposes for the next block
+constexpr int kPickTop = 4;          // atoms each wave proposes for the next block
 constexpr int kOrthRowsB = 64;       // rows per workgroup of k_omp_borth
 constexpr int kOrthWavesB = 16;
 constexpr int kOrthChunk = 256;      // rows of H staged at a time
