@@ -35,7 +35,9 @@
 
 namespace mp {
 
-constexpr int kGramReq = 15;        // Gram columns per pass (with r: 16 right-hand sides)
+constexpr int kGramReq = 31;        // Gram columns per pass (with r: 32 right-hand sides)
+constexpr int kGramTile = 32;       // atoms of one wave's tile of a pass
+constexpr int kGramRaggedWaves = 4; // waves per workgroup of the ragged pass
 constexpr int kGramMaxAtoms = 32768;  // of a dictionary that decodes on carried correlations
 constexpr int kGramMaxCand = 64;    // atoms scored exactly in one step, at most
 constexpr unsigned kGramNone = 0xFFFFu;  // map entry of an atom without a Gram column
@@ -70,12 +72,18 @@ struct GramProb {
   float* g;            // slots x mp Gram columns
   uint16_t* map;       // m: slot of each atom's Gram column, or kGramNone
   int slots;
-  float* rhs;          // 16 x ld: a pass's right-hand sides in operand order
+  float* rhs;          // 32 x ld: a pass's right-hand sides in operand order
   T* r;                // ld elements
   T* x;
   DevState* st;        // pad[0]: the decode gave up (the host runs the stepping form)
   GramCtl* ctl;
 };
+
+// Where a pass's right-hand side i keeps row `row`: float4 64 s + 32 q + i
+// holds rows 8 s + 4 q .. + 3.
+__host__ __device__ inline int64_t gram_rhs_at(int64_t row, int i) {
+  return (row / 4 * (kGramReq + 1) + i) * 4 + row % 4;
+}
 
 // Threads and correlations per thread of the steps kernel for m atoms and
 // columns of ld elements of `esize` bytes; threads 0 where it does not apply.
@@ -88,7 +96,7 @@ inline int64_t gram_stride(const GramShape& sh) {
   const int64_t all = static_cast<int64_t>(sh.threads) * sh.per_thread;
   return all < kGramMaxAtoms ? all : kGramMaxAtoms;
 }
-GramBounds gram_bounds(int64_t n, double max_norm, bool f64);
+GramBounds gram_bounds(int64_t n, double max_norm, bool f64, bool ragged);
 
 template <typename T>
 struct GramTrace {

@@ -8,25 +8,38 @@
 namespace mp {
 
 // ---------------------------------------------------------------------------
-// The pass: [c~ | g_req] = Psi^T [r | psi_req], 16 atoms x 16 right-hand sides
-// per wave on v_mfma_f32_16x16x4_f32.
+// The pass: [c~ | g_req] = Psi^T [r | psi_req], 32 atoms x 32 right-hand sides
+// per wave on v_mfma_f32_32x32x2_f32.
 //
-// Bound by the dictionary's bytes, so its reads are whole 256-byte pieces of
-// a column (16 lanes each).  The matrix operand wants lane l to hold atom
-// l % 16 at rows 4 (l / 16) of a 16-row step, where no two neighbouring lanes
-// share a column: read straight from memory that is one cache access per
-// lane, 64 per load, and the pass ran at 4.0 TB/s on the L1's access rate
-// (N = 8192, M = 32768: 266 us).  Each wave therefore turns its 16 atoms x 64
-// rows over in 4 KB of LDS of its own (no barriers; float4 f of atom a at
-// position f ^ a of its row, so that neither side meets bank conflicts),
-// with the next pieces (8 KB) in flight in registers.  The right-hand sides
-// are laid out in operand order by k_gram_pack and come from L2.
+// Bound by the dictionary's bytes (the products take two thirds of the time
+// its bytes do), so its reads are whole 256-byte pieces of a column (16 lanes
+// each).  The matrix operand wants lane l to hold atom l % 32 at rows
+// 4 (l / 32) of an 8-row step, where no two neighbouring lanes share a column:
+// read straight from memory that is one cache access per lane.  Each wave
+// therefore turns its 32 atoms x 64 rows over in 8 KB of LDS of its own (no
+// barriers; float4 f of atom a at position f ^ a of its row, so that neither
+// side meets bank conflicts), with the next pieces (16 KB) in flight in
+// registers.  The right-hand sides are laid out in operand order by
+// k_gram_pack and come from L2.
 //
-// Each 16-atom tile's rows are split over `split` waves of the workgroup, so
+// Each 32-atom tile's rows are split over `split` waves of the workgroup, so
 // that a short dictionary still gives every CU waves; their sums meet in LDS
-// in a fixed order.  Every 16 rows are an FP32 chain of their own, summed in
-// FP64 (with 64-row chains the bounds, and with them the lists of more than
-// one atom, were three times as wide, and the pass no faster).
+// in a fixed order.  Every 16 or 32 rows (gram_chain) are an FP32 chain of
+// their own, summed in FP64, which keeps the rounding bound of the products at
+// that of one chain.
+//
+// 16 right-hand sides (16 atoms a wave) took 196 us at N = 8192, M = 32768
+// (5.5 TB/s) and 40 passes a decode.
+constexpr int kPassThreads = 512;
+constexpr int kPassWaves = kPassThreads / kWave;
+constexpr int kPassRows = 64;           // rows of a piece: 8 steps of 8
+constexpr int kPassSteps = kPassRows / 8;
+// Rows summed in one FP32 chain with `d` pieces in flight.
+constexpr int gram_chain(int d) { return d == 1 ? 16 : 32; }
+constexpr int kRhs = kGramReq + 1;
+static_assert(kRhs == 32 && kGramTile == 32, "one 32 x 32 tile per wave");
+typedef float v16f __attribute__((ext_vector_type(16)));
+
 // 16 bytes of a column as floats.
 __device__ inline void put_floats(float* p, const v4f& v) { *reinterpret_cast<v4f*>(p) = v; }
 __device__ inline void put_floats(float* p, const Vec16<double>::type& v) {
@@ -34,22 +47,16 @@ __device__ inline void put_floats(float* p, const Vec16<double>::type& v) {
   *reinterpret_cast<v2f*>(p) = v2f{static_cast<float>(v.x), static_cast<float>(v.y)};
 }
 
-constexpr int kPassThreads = 512;
-constexpr int kPassWaves = kPassThreads / kWave;
-constexpr int kPassRows = 64;           // rows of a piece: 4 steps of 16
-constexpr int kChain = 16;              // rows summed in one FP32 chain, at most
-
-// The right-hand sides in operand order: float4 s * 64 + 16 q + i holds rows
-// 16 s + 4 q .. + 3 of right-hand side i (r, the wanted columns, then zeros).
-// The first pass also clears the slot map.
+// The right-hand sides in operand order (gram_rhs_at): r, the wanted columns,
+// then zeros.  The first pass also clears the slot map.
 template <typename T>
 __device__ inline void gram_pack(const GramProb<T>& p, int first) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int64_t all = static_cast<int64_t>(gridDim.x) * 256;
   const int nreq = first ? 0 : p.ctl->nreq;
-  for (int64_t e = t; e < p.ld * 4; e += all) {
-    const int i = static_cast<int>(e % 16);
-    const int64_t row4 = e / 64 * 4 + e % 64 / 16;  // float4 of the column
+  for (int64_t e = t; e < p.ld * (kRhs / 4); e += all) {
+    const int i = static_cast<int>(e % kRhs);
+    const int64_t row4 = e / kRhs;  // float4 of the column
     v4f v = v4f{0.f, 0.f, 0.f, 0.f};
     if (i <= nreq) {
       const T* src = i == 0 ? p.r : p.psi + static_cast<int64_t>(p.ctl->req[i - 1]) * p.ld;
@@ -67,131 +74,144 @@ __global__ __launch_bounds__(256) void k_gram_pack(GramProb<T> p, int first) {
   if (!p.st->done) gram_pack(p, first);
 }
 
-// One workgroup's share of the pass: tiles group * (kPassWaves / split) ...
+// One workgroup's share of the pass: tiles group * (WAVES / split) ..., with D
+// pieces in flight per wave.
 // (every thread of the workgroup calls; there are barriers).
-template <typename T>
+template <typename T, int D, int WAVES>
 __device__ inline void gram_pass(const GramProb<T>& p, int64_t group, int split, int first) {
-  constexpr int NL = kPassRows * 16 * sizeof(T) / 16 / kWave;  // 16-byte loads of a piece
-  constexpr int LPA = kWave / (16 / NL);                        // lanes of a load per atom
-  constexpr int D = sizeof(T) == 4 ? 2 : 1;  // pieces in flight: 8 KB per wave
+  constexpr int NL = kPassRows * kGramTile * sizeof(T) / 16 / kWave;  // 16-byte loads of a piece
+  constexpr int LPA = kPassRows * sizeof(T) / 16;                     // of them per atom
+  // steps of an FP32 chain: two more flushes of 16 sums cost registers that two
+  // pieces in flight do not leave (232 us a pass from 192, 10 registers spilled)
+  constexpr int C = gram_chain(D) / 8;
   typedef typename Vec16<T>::type vec;
-  __shared__ v4f turn[kPassWaves][16 * 16];  // then the split sums
+  __shared__ v4f turn[WAVES][kGramTile * 16];  // then the split sums
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
-  const int tiles = kPassWaves / split;  // per workgroup
+  const int tiles = WAVES / split;  // per workgroup
   const int part = wave % split;
-  const int64_t m0 = (group * tiles + wave / split) * 16;
-  const int i = lane % 16, q = lane / 16;
+  const int64_t m0 = (group * tiles + wave / split) * kGramTile;
+  const int i = lane % kGramTile, q = lane / kGramTile;
   const int nreq = first ? 0 : p.ctl->nreq;
-  double tot[4] = {0.0, 0.0, 0.0, 0.0};
+  double tot[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) tot[e] = 0.0;
   if (m0 < p.m) {
-    // load j of a piece: atoms j 64 / LPA + lane / LPA, 16 bytes lane % LPA
-    const vec* a[NL];
-    int put[NL];  // in floats
-    const int li = lane % LPA;
+    // load j of a piece: 16 bytes (j 64 + lane) % LPA of atom (j 64 + lane) / LPA
+    const vec* a0 = reinterpret_cast<const vec*>(p.psi + m0 * p.ld);
+    unsigned at[NL];  // in 16 bytes
+    int put[NL];      // in floats
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
-      const int at = j * (kWave / LPA) + lane / LPA;
-      const int64_t atom = m0 + at < p.m ? m0 + at : p.m - 1;
-      a[j] = reinterpret_cast<const vec*>(p.psi + atom * p.ld) + li;
+      const int atom = (j * kWave + lane) / LPA, li = (j * kWave + lane) % LPA;
+      const int64_t in = m0 + atom < p.m ? atom : p.m - 1 - m0;
+      at[j] = static_cast<unsigned>(in * (p.ld * static_cast<int>(sizeof(T)) / 16) + li);
       const int f = li * (16 / static_cast<int>(sizeof(T)));  // first row of the 16 bytes
-      put[j] = 4 * (at * 16 + ((f / 4) ^ at)) + f % 4;
+      put[j] = 4 * (atom * 16 + ((f / 4) ^ (atom % 16))) + f % 4;
     }
-    const v4f* b = reinterpret_cast<const v4f*>(p.rhs) + lane;
+    const v4f* b = reinterpret_cast<const v4f*>(p.rhs);
     v4f* my = turn[wave];
     const int pieces = static_cast<int>(p.ld / kPassRows);
     const int k0 = pieces * part / split, k1 = pieces * (part + 1) / split;
-    v4f acc[4];
+    v16f acc[2];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) acc[s] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = 0.0f;
     vec va[D][NL];
-    v4f vb[D][4];
-    auto load = [&](vec(&x)[NL], v4f(&y)[4], int k) {
-      const int kk = k < k1 ? k : k1 - 1;  // past the end: read again, not used
+    v4f vb[D][kPassSteps];
+    // (past the end: read again, not used)
+    auto load_a = [&](vec(&x)[NL], int k) {
+      const vec* ak = a0 + LPA * static_cast<int64_t>(k < k1 ? k : k1 - 1);
 #pragma unroll
-      for (int j = 0; j < NL; ++j) x[j] = __builtin_nontemporal_load(a[j] + LPA * kk);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) y[j] = b[(4 * kk + j) * 64];
+      for (int j = 0; j < NL; ++j) x[j] = __builtin_nontemporal_load(ak + at[j]);
     };
-    auto use = [&](vec(&x)[NL], v4f(&y)[4], int next) {
+    auto load_b = [&](v4f(&y)[kPassSteps], int k) {
+      const v4f* bk = b + kPassSteps * kWave * static_cast<int64_t>(k < k1 ? k : k1 - 1);
+#pragma unroll
+      for (int j = 0; j < kPassSteps; ++j) y[j] = bk[j * kWave + lane];
+    };
+    auto flush = [&](v16f& x) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        tot[e] += static_cast<double>(x[e]);
+        x[e] = 0.0f;
+      }
+    };
+    auto use = [&](vec(&x)[NL], v4f(&y)[kPassSteps], int next) {
 #pragma unroll
       for (int j = 0; j < NL; ++j) put_floats(reinterpret_cast<float*>(my) + put[j], x[j]);
-      v4f rb[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rb[j] = y[j];
       __builtin_amdgcn_wave_barrier();
-      load(x, y, next);
+      load_a(x, next);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const v4f xa = my[i * 16 + ((4 * s + q) ^ i)];
+      for (int s = 0; s < kPassSteps; ++s) {
+        const v4f xa = my[i * 16 + ((2 * s + q) ^ (i % 16))];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[e], rb[s][e], acc[s], 0, 0, 0);
+          acc[s / C & 1] =
+              __builtin_amdgcn_mfma_f32_32x32x2f32(xa[e], y[s][e], acc[s / C & 1], 0, 0, 0);
+        if (s % C == C - 1 && s > C) flush(acc[(s / C & 1) ^ 1]);  // the chain before
       }
+      if (C == kPassSteps / 2) flush(acc[0]);
+      flush(acc[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      load_b(y, next);
       __builtin_amdgcn_wave_barrier();
-    };
-    auto flush = [&]() {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        tot[e] += (static_cast<double>(acc[0][e]) + static_cast<double>(acc[1][e])) +
-                  (static_cast<double>(acc[2][e]) + static_cast<double>(acc[3][e]));
-        acc[0][e] = acc[1][e] = acc[2][e] = acc[3][e] = 0.0f;
-      }
     };
     if (k0 < k1) {
 #pragma unroll
-      for (int d = 0; d < D; ++d) load(va[d], vb[d], k0 + d);
+      for (int d = 0; d < D; ++d) {
+        load_a(va[d], k0 + d);
+        load_b(vb[d], k0 + d);
+      }
       for (int k = k0; k < k1; k += D)
 #pragma unroll
         for (int d = 0; d < D; ++d)
-          if (k + d < k1) {
-            use(va[d], vb[d], k + d + D);
-            flush();
-          }
+          if (k + d < k1) use(va[d], vb[d], k + d + D);
     }
   }
   __syncthreads();
-  double(*red)[4][kWave] = reinterpret_cast<double(*)[4][kWave]>(&turn[0][0]);
+  double(*red)[16][kWave] = reinterpret_cast<double(*)[16][kWave]>(&turn[0][0]);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) red[wave][e][lane] = tot[e];
+  for (int e = 0; e < 16; ++e) red[wave][e][lane] = tot[e];
   __syncthreads();
   if (part != 0 || m0 >= p.m) return;
   for (int w = 1; w < split; ++w)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) tot[e] += red[wave + w][e][lane];
-  // this lane: right-hand side i of atoms m0 + 4 q .. + 3 (zero past the last)
-  const int64_t base = m0 + 4 * q;
-  v4f o;
+    for (int e = 0; e < 16; ++e) tot[e] += red[wave + w][e][lane];
+  // this lane: right-hand side i of atoms m0 + 8 g + 4 q .. + 3 (zero past the last)
+  if (i > nreq) return;
+  float* out = i == 0 ? p.c : p.g + static_cast<int64_t>(p.ctl->slot0 + i - 1) * p.mp;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) o[e] = base + e < p.m ? static_cast<float>(tot[e]) : 0.0f;
-  if (i == 0)
-    *reinterpret_cast<v4f*>(p.c + base) = o;
-  else if (i <= nreq)
-    *reinterpret_cast<v4f*>(p.g + static_cast<int64_t>(p.ctl->slot0 + i - 1) * p.mp + base) = o;
+  for (int g = 0; g < 4; ++g) {
+    const int64_t base = m0 + 8 * g + 4 * q;
+    v4f o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = base + e < p.m ? static_cast<float>(tot[4 * g + e]) : 0.0f;
+    *reinterpret_cast<v4f*>(out + base) = o;
+  }
 }
 
-// Waves each tile's rows are split over: the fewest that give two workgroups
-// per CU.
+// Waves each tile's rows are split over: the fewest that give every CU a
+// workgroup (8 waves with 256 registers fill it).
 static int pass_split(int64_t tiles, int num_cus) {
   int split = 1;
-  while (split < kPassWaves && tiles * split / kPassWaves < 2 * num_cus) split *= 2;
+  while (split < kPassWaves && tiles * split / kPassWaves < num_cus) split *= 2;
   return split;
 }
 
 template <typename T>
-__global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_gram_pass(
+__global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gram_pass(
     GramProb<T> p, int split, int first) {
-  if (!p.st->done) gram_pass(p, static_cast<int64_t>(blockIdx.x), split, first);
+  if (!p.st->done) gram_pass<T, sizeof(T) == 4 ? 2 : 1, kPassWaves>(p, static_cast<int64_t>(blockIdx.x), split, first);
 }
 
 template <typename T>
 hipError_t launch_gram_pass(const GramProb<T>& p, int num_cus, bool first, hipStream_t s) {
-  const int64_t packs = p.ld * 4 / 256;  // ld is a multiple of 64
+  const int64_t packs = p.ld * (kRhs / 4) / 256;  // ld is a multiple of 64
   k_gram_pack<T><<<dim3(static_cast<unsigned>(packs)), dim3(256), 0, s>>>(p, first ? 1 : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t tiles = (p.m + 15) / 16;
+  const int64_t tiles = (p.m + kGramTile - 1) / kGramTile;
   const int split = pass_split(tiles, num_cus);
   const int per = kPassWaves / split;
   k_gram_pass<T><<<dim3(static_cast<unsigned>((tiles + per - 1) / per)), dim3(kPassThreads), 0, s>>>(
@@ -209,17 +229,17 @@ __global__ __launch_bounds__(256) void k_gram_block_pack(GramProb<float> p,
 }
 
 // count: columns of p in use (null: all of them).
-__global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(4))) void
+__global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 k_gram_block_pass(GramProb<float> p, int split, const int* __restrict__ hold,
                   const long long* __restrict__ count) {
   if (p.st->done || !*hold) return;
   if (count) p.m = *count;
-  if (p.m > 0) gram_pass(p, static_cast<int64_t>(blockIdx.x), split, 0);
+  if (p.m > 0) gram_pass<float, 2, kPassWaves>(p, static_cast<int64_t>(blockIdx.x), split, 0);
 }
 
 static hipError_t block_pass(const GramProb<float>& p, const int* hold, const long long* count,
                              int num_cus, hipStream_t s) {
-  const int64_t tiles = (p.m + 15) / 16;
+  const int64_t tiles = (p.m + kGramTile - 1) / kGramTile;
   const int split = pass_split(tiles, num_cus);
   const int per = kPassWaves / split;
   k_gram_block_pass<<<dim3(static_cast<unsigned>((tiles + per - 1) / per)), dim3(kPassThreads), 0,
@@ -229,7 +249,7 @@ static hipError_t block_pass(const GramProb<float>& p, const int* hold, const lo
 
 hipError_t launch_gram_block(const GramProb<float>& p, const GramProb<float>& pq, const int* hold,
                              int num_cus, hipStream_t s) {
-  k_gram_block_pack<<<dim3(static_cast<unsigned>(p.ld * 4 / 256)), dim3(256), 0, s>>>(p, hold);
+  k_gram_block_pack<<<dim3(static_cast<unsigned>(p.ld * (kRhs / 4) / 256)), dim3(256), 0, s>>>(p, hold);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || pq.m <= 0) return e;
   return block_pass(pq, hold, &p.st->t, num_cus, s);
@@ -240,17 +260,18 @@ hipError_t launch_gram_block_pass(const GramProb<float>& p, const int* hold, int
   return block_pass(p, hold, nullptr, num_cus, s);
 }
 
-// The bounds (u = 2^-24): a product of the pass is a chain of at most kChain
-// terms, rounded once more to FP32 (and, from an FP64 dictionary, both
+// The bounds (u = 2^-24): a product of the pass is a chain of at most
+// gram_chain terms, rounded once more to FP32 (and, from an FP64 dictionary, both
 // operands rounded to FP32 first); dot_column_f32 is two lane chains of
 // ld / 128 terms, then 7 additions (in FP64 its rounding is far below the
 // rest).  Each is at most (terms + additions) u sum |a b| <= (...) u ||a||
 // ||b||; a step adds r's rounding (u ||r'|| against a unit column; far less in
 // FP64), c~'s own (u |c~|) and that of the coefficient (u |c|, in col).
-GramBounds gram_bounds(int64_t n, double max_norm, bool f64) {
+GramBounds gram_bounds(int64_t n, double max_norm, bool f64, bool ragged) {
   const double u = 1.0 / 16777216.0, nn = static_cast<double>(n + 64);
   const double slack = 1.01;
-  const double prod = (std::min<double>(nn, kChain) + 7) * u * slack;
+  const double prod =
+      (std::min<double>(nn, gram_chain(f64 || ragged ? 1 : 2)) + 7) * u * slack;
   GramBounds b;
   b.pass = static_cast<float>(prod * max_norm);
   b.col = static_cast<float>(prod * max_norm * max_norm);
@@ -393,12 +414,12 @@ __global__ __launch_bounds__(256) void k_gram_rpack(const GramProb<float>* __res
   if (!p.st->done) gram_pack(p, first);
 }
 
-__global__ __launch_bounds__(kPassThreads) __attribute__((amdgpu_waves_per_eu(4))) void
+__global__ __launch_bounds__(kGramRaggedWaves* kWave) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 k_gram_rpass(const GramProb<float>* __restrict__ probs, const GramGroup* __restrict__ groups,
              int split, int first) {
   const GramGroup g = groups[blockIdx.x];
   const GramProb<float> p = probs[g.id];
-  if (!p.st->done) gram_pass(p, g.group, split, first);
+  if (!p.st->done) gram_pass<float, 1, kGramRaggedWaves>(p, g.group, split, first);
 }
 
 template <int NT, int CPT, bool ONE>
@@ -439,7 +460,7 @@ __global__ __launch_bounds__(NT + 2 * kWave) void k_gram_rsteps(
 }
 
 GramBounds gram_bounds_one(int64_t n, double max_norm) {
-  GramBounds b = gram_bounds(n, max_norm, false);
+  GramBounds b = gram_bounds(n, max_norm, false, true);
   const double nn = static_cast<double>(n + 64);
   b.dot = static_cast<float>((nn / 64 + 10) / 16777216.0 * max_norm * 1.01);
   return b;
@@ -451,7 +472,9 @@ int64_t gram_ragged_stride(int64_t max_ld, int64_t max_m, int64_t m) {
 }
 
 int gram_ragged_groups(int64_t tiles, int num_cus) {
-  return kPassWaves / pass_split(tiles, num_cus);
+  int split = 1;
+  while (split < kGramRaggedWaves && tiles * split / kGramRaggedWaves < 3 * num_cus) split *= 2;
+  return kGramRaggedWaves / split;
 }
 
 hipError_t launch_gram_rinit(const GramRagged& g, const float* Y, float* X, const long long* caps,
@@ -492,11 +515,11 @@ hipError_t launch_gram_rround(const GramRagged& g, float* X, long long round, mp
                               hipStream_t s) {
   if (g.lds > kStepLds) return hipErrorInvalidValue;
   const int par = static_cast<int>(round & 1), first = round == 0 ? 1 : 0;
-  const unsigned packs = static_cast<unsigned>((g.max_ld * 4 + 1023) / 1024);
+  const unsigned packs = static_cast<unsigned>((g.max_ld * (kRhs / 4) + 1023) / 1024);
   k_gram_rpack<<<dim3(packs, g.count), dim3(256), 0, s>>>(g.probs, g.again, par, first);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_gram_rpass<<<dim3(g.ngroups), dim3(kPassThreads), 0, s>>>(g.probs, g.groups, g.split, first);
+  k_gram_rpass<<<dim3(g.ngroups), dim3(kGramRaggedWaves * kWave), 0, s>>>(g.probs, g.groups, g.split, first);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (g.small)
     return g.one ? launch_rsteps_t<256, 4, 16, true>(g, X, tr, par, first, s)

@@ -161,7 +161,7 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
   constexpr int V = VN / NR;       // waves of that workgroup each of their waves plays
   constexpr int NA = NT + 2 * kWave;
   constexpr int C4 = CPT / 4;
-  constexpr int TOP = W >= 16 ? 4 : (kWave / W < 6 ? kWave / W : 6);  // columns each wave proposes
+  constexpr int TOP = kWave / W < 10 ? kWave / W : 10;  // columns each wave proposes
   DevState* st = p.st;
   V16* s_col = r_lds + p.ld / E;
   uint16_t* s_map = map_lds ? reinterpret_cast<uint16_t*>(s_col + p.ld / E) : p.map;
@@ -442,8 +442,11 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
     if (data && lane == 0) s_want[k * W + wave] = w;
   }
   __syncthreads();
-  // a full cache starts over
-  const bool reset = used + kGramReq > p.slots;
+  // a cache that is nearly full starts over; before that it takes what fits.
+  // A pass that only renews the correlations adds columns while there is
+  // plenty of room: late in a decode they would push out those in use.
+  const bool add = idx >= 0 || p.slots - used >= 4 * kGramReq;
+  const bool reset = add && used + kGramReq / 4 > p.slots;
   if (reset) {
     used = 0;
     for (int i = tid; i < m; i += NA) p.map[i] = static_cast<uint16_t>(kGramNone);
@@ -452,10 +455,11 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
   if (wave == 0) {  // the proposals by rank
     GramCtl* ctl = p.ctl;
     const int base = idx >= 0 ? 1 : 0;
-    const uint64_t key = lane < W * TOP ? s_want[lane] : 0;
+    const int room = p.slots - used < kGramReq ? p.slots - used : kGramReq;
+    const uint64_t key = add && lane < W * TOP ? s_want[lane] : 0;
     int rank = 0;
     for (int k = 0; k < W * TOP; ++k) rank += s_want[k] > key;
-    if (key != 0 && base + rank < kGramReq) {
+    if (key != 0 && base + rank < room) {
       ctl->req[base + rank] = key_index(key);
       p.map[key_index(key)] = static_cast<uint16_t>(used + base + rank);
     }
@@ -465,7 +469,7 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
         ctl->req[0] = idx;
         p.map[idx] = static_cast<uint16_t>(used);
       }
-      const int nreq = found < kGramReq ? found : kGramReq;
+      const int nreq = found < room ? found : room;
       ctl->nreq = nreq;
       ctl->slot0 = used;
       ctl->used = used + nreq;

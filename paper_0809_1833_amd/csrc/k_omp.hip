@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kOmpThreads) void k_omp_proj(
 // fixed tree; the workgroup's FP64 sum of w^2 goes to part[b].
 // Pass 2 of a step on carried correlations (dpart): also the sum of squares of
 // d = w - (W_i - sum_s h_s q_s), s over the directions of the block the atom
-// was taken from at position i (one wave each), with h the sum of both passes.
+// was taken from at position i (split over the waves), with h the sum of both passes.
 __global__ __launch_bounds__(kOrthThreads) void k_omp_orth(
     const float* __restrict__ q, int64_t ld, const float* __restrict__ psi,
     const float* __restrict__ wv_in, bool from_atom, const float* __restrict__ hp,
@@ -157,8 +157,13 @@ __global__ __launch_bounds__(kOrthThreads) void k_omp_orth(
     acc = __builtin_fmaf(h_lds[j], q[j * ld + nrow], acc);
   ps[wave][lane] = acc;
   if (dpart) {
-    const long long j = oc->t0 + wave;
-    pd[wave][lane] = j < t ? (h1[j] + h_lds[j]) * q[j * ld + nrow] : 0.0f;
+    float b = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kGramReq; k += kOrthWaves) {
+      const long long j = oc->t0 + wave + k;
+      if (j < t) b = __builtin_fmaf(h1[j] + h_lds[j], q[j * ld + nrow], b);
+    }
+    pd[wave][lane] = b;
   }
   __syncthreads();
   if (wave == 0) {

@@ -31,7 +31,7 @@ constexpr int kPickThreads = 1024;
 constexpr int kPickWaves = kPickThreads / kWave;
 constexpr int kPickTop = 4;          // atoms each wave proposes for the next block
 constexpr int kOrthRowsB = 64;       // rows per workgroup of k_omp_borth
-constexpr int kOrthWavesB = 16;
+constexpr int kOrthWavesB = 8;
 constexpr int kOrthChunk = 256;      // rows of H staged at a time
 
 __global__ void k_omp_carry_init(OmpCarry* oc) {
@@ -46,7 +46,7 @@ __global__ void k_omp_carry_init(OmpCarry* oc) {
 // ---------------------------------------------------------------------------
 // W = V - Q H for the block's candidates V (rhs: their operand order for the
 // pass that follows).  H = Q^T V comes from the pass kernel over Q.  One row
-// per lane, the sum over j split over 16 waves and added in a fixed order.
+// per lane, the sum over j split over the waves and added in a fixed order.
 __global__ __launch_bounds__(kOrthWavesB* kWave) void k_omp_borth(
     const float* __restrict__ psi, int64_t ld, const float* __restrict__ q,
     const float* __restrict__ h, int64_t ldh, const DevState* __restrict__ st,
@@ -80,15 +80,14 @@ __global__ __launch_bounds__(kOrthWavesB* kWave) void k_omp_borth(
 #pragma unroll
   for (int i = 0; i < kGramReq; ++i) ps[wave][i][lane] = acc[i];
   __syncthreads();
-  if (wave >= nreq) return;
-  // this wave: candidate `wave`, one row per lane
-  float s = 0.0f;
+  for (int i = wave; i < nreq; i += kOrthWavesB) {  // one row per lane
+    float s = 0.0f;
 #pragma unroll
-  for (int k = 0; k < kOrthWavesB; ++k) s += ps[k][wave][lane];
-  const float v = psi[static_cast<int64_t>(oc->ctl.req[wave]) * ld + row] - s;
-  w[wave * ld + row] = v;
-  // float4 16 row / 16 ... of the operand order (gram_pack)
-  rhs[((row / 16) * 64 + 16 * (row % 16 / 4) + wave + 1) * 4 + row % 4] = v;
+    for (int k = 0; k < kOrthWavesB; ++k) s += ps[k][i][lane];
+    const float v = psi[static_cast<int64_t>(oc->ctl.req[i]) * ld + row] - s;
+    w[i * ld + row] = v;
+    rhs[gram_rhs_at(row, i + 1)] = v;
+  }
 }
 
 // ---------------------------------------------------------------------------

@@ -471,7 +471,8 @@ bool ensure_gram(mp_ctx* c, hipStream_t s) {
   if (hipMalloc(&c->gram_c, row) != hipSuccess ||
       hipMalloc(&c->gram_g, row * static_cast<size_t>(slots)) != hipSuccess ||
       hipMalloc(&c->gram_map, sizeof(uint16_t) * static_cast<size_t>(c->m)) != hipSuccess ||
-      hipMalloc(&c->gram_rhs, sizeof(float) * 16 * static_cast<size_t>(c->ld)) != hipSuccess ||
+      hipMalloc(&c->gram_rhs, sizeof(float) * (mp::kGramReq + 1) * static_cast<size_t>(c->ld)) !=
+          hipSuccess ||
       hipMalloc(&c->gram_ctl, sizeof(mp::GramCtl)) != hipSuccess ||
       // entries past m stay zero (the pass writes the tiles of m)
       hipMemsetAsync(c->gram_c, 0, row, s) != hipSuccess ||
@@ -492,7 +493,7 @@ template <typename T>
 mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* opts,
                      const typename mp::GramTrace<T>::type& tr, hipStream_t s, bool& gave_up) {
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, sizeof(T));
-  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, sizeof(T) == 8);
+  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, sizeof(T) == 8, false);
   const mp::GramProb<T> p{psi, c->ld, c->n, c->m, c->gram_mp, c->gram_c, c->gram_g, c->gram_map,
                           c->gram_slots, c->gram_rhs, r_work, x, c->st,
                           static_cast<mp::GramCtl*>(c->gram_ctl)};
@@ -762,8 +763,9 @@ mp_status solve_gram_batch(mp_ctx* c, const float* Y, int64_t ldy, int64_t B, fl
 
 // The problems, Gram columns and buffers of the ragged decode on carried
 // correlations, made with the context.  Gram columns per problem:
-// max(64, n / 4), as for one signal; in all at most the dictionaries' bytes
-// and 64 MiB (many tiny problems, whose rounding up would dominate, keep the
+// max(64, n / 4) and five passes' (a cache that starts over costs more passes:
+// 17 rounds against 11 for 512 problems); in all at most the dictionaries'
+// bytes and 128 MiB (many tiny problems, whose rounding up would dominate, keep the
 // persistent launch, as do problems past the steps kernel's limits, and a
 // context whose memory does not reach).
 void make_gram_ragged(mp_ctx* c, hipStream_t s) {
@@ -776,20 +778,21 @@ void make_gram_ragged(mp_ctx* c, hipStream_t s) {
   for (size_t i = 0; i < count; ++i) {
     const int64_t ld = round_up(c->r_n[i], kLdAlign), m = c->r_m[i];
     stride[i] = mp::gram_ragged_stride(c->r_max_ld, max_m, m);
-    slots[i] = round_up(std::min<int64_t>(std::max<int64_t>(64, c->r_n[i] / 4), m) + mp::kGramReq,
-                        16);
+    slots[i] = round_up(
+        std::min<int64_t>(std::max<int64_t>(64, c->r_n[i] / 4) + 4 * mp::kGramReq, m) +
+            mp::kGramReq, 16);
     lds = std::max(lds, 8 * ld + 2 * m);
-    work += stride[i] + 17 * ld;
+    work += stride[i] + (mp::kGramReq + 2) * ld;
     gcols += slots[i] * stride[i];
     maps += round_up(m, 8);
-    tiles += (m + 15) / 16;
+    tiles += (m + mp::kGramTile - 1) / mp::kGramTile;
     dict += ld * m;
   }
-  if (lds > 150 * 1024 || gcols > dict + (int64_t{1} << 24)) return;
+  if (lds > 150 * 1024 || gcols > dict + (int64_t{1} << 25)) return;
   const int per = mp::gram_ragged_groups(tiles, c->num_cus);
   std::vector<mp::GramGroup> groups;
   for (int id : c->r_order) {
-    const int64_t t = (c->r_m[id] + 15) / 16;
+    const int64_t t = (c->r_m[id] + mp::kGramTile - 1) / mp::kGramTile;
     for (int64_t k = 0; k * per < t; ++k)
       groups.push_back(mp::GramGroup{id, static_cast<int>(k)});
   }
@@ -842,8 +845,8 @@ void make_gram_ragged(mp_ctx* c, hipStream_t s) {
       p.mp = stride[i];
       p.c = w;
       p.rhs = w + stride[i];
-      p.r = p.rhs + 16 * ld;
-      w += stride[i] + 17 * ld;
+      p.r = p.rhs + (mp::kGramReq + 1) * ld;
+      w += stride[i] + (mp::kGramReq + 2) * ld;
       p.g = g;
       g += slots[i] * stride[i];
       p.slots = static_cast<int>(slots[i]);
@@ -852,7 +855,7 @@ void make_gram_ragged(mp_ctx* c, hipStream_t s) {
       p.x = nullptr;
       p.st = c->gram_rst + i;
       p.ctl = reinterpret_cast<mp::GramCtl*>(mem + o_ctl) + i;
-      bounds[i] = c->storage == MP_BF16 ? mp::gram_bounds(p.n, c->max_norm, false)
+      bounds[i] = c->storage == MP_BF16 ? mp::gram_bounds(p.n, c->max_norm, false, true)
                                         : mp::gram_bounds_one(p.n, c->max_norm);
     }
     return hipMemsetAsync(mem, 0, zeroed, s) == hipSuccess &&
@@ -872,7 +875,7 @@ void make_gram_ragged(mp_ctx* c, hipStream_t s) {
     return;
   }
   c->gram_rngroups = static_cast<int>(groups.size());
-  c->gram_rsplit = 8 / per;
+  c->gram_rsplit = mp::kGramRaggedWaves / per;
   c->gram_rlds = lds;
   c->gram_rsmall = max_m <= 4096 && c->r_max_ld <= 4096;
 }
@@ -1324,14 +1327,14 @@ static bool ensure_omp_carry(mp_ctx* c) {
     return false;
   if (b.oc) return true;
   const size_t ld = static_cast<size_t>(c->ld), req = mp::kGramReq;
-  b.mp = round_up(c->m, 16);
-  b.ldh = round_up(b.tq, 16);
+  b.mp = round_up(c->m, mp::kGramTile);
+  b.ldh = round_up(b.tq, mp::kGramTile);
   const size_t stride = static_cast<size_t>(b.mp), ldh = static_cast<size_t>(b.ldh);
   if (hipMalloc(&b.oc, sizeof(mp::OmpCarry)) != hipSuccess ||
       hipMalloc(&b.c, sizeof(float) * stride) != hipSuccess ||
       hipMalloc(&b.p, sizeof(float) * stride * req) != hipSuccess ||
       hipMalloc(&b.w15, sizeof(float) * ld * req) != hipSuccess ||
-      hipMalloc(&b.rhs, sizeof(float) * ld * 16) != hipSuccess ||
+      hipMalloc(&b.rhs, sizeof(float) * ld * (req + 1)) != hipSuccess ||
       hipMalloc(&b.hr, sizeof(float) * ldh) != hipSuccess ||
       hipMalloc(&b.hq, sizeof(float) * ldh * req) != hipSuccess ||
       hipMalloc(&b.dpart, sizeof(double) * (ld / 64)) != hipSuccess ||
@@ -1354,7 +1357,7 @@ static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipS
                                 bool& gave_up) {
   constexpr int kOmpSlots = 4, kOmpRounds = 4;
   mp::OmpBufs& b = c->omp;
-  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, false);
+  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, false, false);
   const bool timed = c->profiling;
   gave_up = false;
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));

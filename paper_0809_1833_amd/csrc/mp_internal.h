@@ -200,7 +200,7 @@ struct OmpBufs {            // work buffers of one OMP decode (context-owned)
   float* c = nullptr;       // mp carried correlations
   float* p = nullptr;       // kGramReq x mp: Psi^T w_i of the block, then Psi^T q_t
   float* w15 = nullptr;     // kGramReq x ld: the block's candidates, orthogonal to Q
-  float* rhs = nullptr;     // 16 x ld: the pass's right-hand sides
+  float* rhs = nullptr;     // 32 x ld: the pass's right-hand sides
   float* hr = nullptr;      // ldh
   float* hq = nullptr;      // kGramReq x ldh: Q^T psi_i of the block
   double* dpart = nullptr;  // ld / 64
@@ -437,7 +437,7 @@ struct mp_ctx {
   float* gram_c = nullptr;       // carried correlations, gram_mp
   float* gram_g = nullptr;       // gram_slots x gram_mp
   uint16_t* gram_map = nullptr;  // m
-  float* gram_rhs = nullptr;     // 16 x ld
+  float* gram_rhs = nullptr;     // 32 x ld
   void* gram_ctl = nullptr;      // mp::GramCtl
   // the batched decode on carried correlations: every atom's Gram column (made
   // by the first decode that takes it) and buffers per signal (grown on demand)
