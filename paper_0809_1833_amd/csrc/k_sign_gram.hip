@@ -1,0 +1,577 @@
+// The one-bit decode (k_sign.hip) in batches of steps taken on part of the
+// atoms and checked against all of them.
+//
+// A step changes every correlation by c* times an exact integer (the Gram
+// entry), in FP64, atom by atom: the steps of a few hundred active atoms can
+// run ahead in one workgroup without the others, and whether another atom
+// would have been selected can be asked of all atoms at once afterwards.  A
+// round is four launches:
+//
+//   steps   one workgroup: up to kSignSteps steps over the active atoms, each
+//           a wave-wide maximum, one barrier and a row of the active atoms'
+//           Gram entries; the steps' atoms and coefficients are logged;
+//   check   all atoms replay the log against their own Gram entries and name
+//           the first step at which they beat its atom; all rows of r replay
+//           it and leave each step's partial ||r||^2;
+//   decide  one workgroup: the steps up to the first stop or the first such
+//           beat stand; x~, the state, the trace; the atoms that beat a step
+//           become active;
+//   commit  all atoms and all rows of r take the steps that stand; Gram
+//           entries (16-bit integers, exact) of the atoms that became active
+//           against every atom.
+//
+// Every value that stands is computed from the same operands in the same
+// order as one launch per step does (k_mp_step_sign), so the results are the
+// same bit for bit; which atoms are active decides only how many steps a
+// round brings.  Bound by the steps' chain of latencies and the launches of
+// a round.  N = 8192, M = 32768, K = 512: 1.3 us a step from 9.6 in one
+// persistent launch that exchanged every step between all CUs.
+#include "k_common.h"
+#include "k_sign_gram.h"
+#include "mp_internal.h"
+
+namespace mp {
+
+constexpr int kStepThreads = 256;
+constexpr int kStepWaves = kStepThreads / kWave;
+constexpr int kPerThread = kSignActive / kStepThreads;  // active atoms per thread
+constexpr int kCheckThreads = 128;
+constexpr int kDecideThreads = 1024;
+constexpr int kDecideWaves = kDecideThreads / kWave;
+constexpr int kCommitAtoms = kWave;     // atoms per workgroup of the commit, one per lane
+constexpr int kCommitThreads = 256;
+constexpr int kCommitWaves = kCommitThreads / kWave;
+constexpr int kNewGroup = 8;            // new atoms a wave counts at once
+constexpr int kFirstActive = 256;       // active atoms to begin with, about
+constexpr int kNewMost = 64;            // atoms that become active in a round, at most
+constexpr int kBins = 1024;
+constexpr int kReplay = 16;             // Gram entries in flight per lane of a replay
+constexpr unsigned short kNoPos = 0xFFFFu;
+static_assert(kPerThread == 4, "a thread's Gram entries are one 8-byte load");
+
+typedef short v4s __attribute__((ext_vector_type(4)));
+
+__device__ inline double wave_max_f64(double v) {
+  v = __builtin_fmax(v, dpp_f64<kDppQuadSwap1>(v));
+  v = __builtin_fmax(v, dpp_f64<kDppQuadSwap2>(v));
+  v = __builtin_fmax(v, dpp_f64<kDppRowRor4>(v));
+  v = __builtin_fmax(v, dpp_f64<kDppRowRor8>(v));
+  return __builtin_fmax(__builtin_fmax(lane_f64(v, 0), lane_f64(v, 16)),
+                        __builtin_fmax(lane_f64(v, 32), lane_f64(v, 48)));
+}
+
+__global__ __launch_bounds__(256) void k_sgram_init(SignCarry* g, unsigned short* pos, int64_t m) {
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < m;
+       i += static_cast<int64_t>(gridDim.x) * 256)
+    pos[i] = kNoPos;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    g->nact = g->nnew = g->count = g->stalled = g->take = g->nbeat = 0;
+    g->first = kSignSteps;
+    g->fill = 1;
+    g->steps = m <= kSignActive ? kSignSteps : 32;
+  }
+}
+
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kStepThreads) void k_sgram_steps(
+    const double* __restrict__ c64, const short* __restrict__ h, double inv_n,
+    long long max_iters, const DevState* __restrict__ st, SignCarry* __restrict__ g) {
+  if (st->done) return;
+  struct Rec {
+    double mag, c;
+    int atom, pos;
+  };
+  __shared__ Rec rec[2][kStepWaves];
+  const int tid = static_cast<int>(threadIdx.x);
+  const int lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int nact = g->nact;
+  int steps = nact > 0 ? g->steps : 0;
+  const long long left = max_iters - st->t;
+  if (left < steps) steps = static_cast<int>(left);
+  double c[kPerThread];
+  int atom[kPerThread];
+#pragma unroll
+  for (int e = 0; e < kPerThread; ++e) {
+    const int p = kPerThread * tid + e;
+    atom[e] = p < nact ? g->atom[p] : 0x7FFFFFFF;
+    c[e] = p < nact ? c64[atom[e]] : 0.0;
+  }
+  int s = 0;
+  bool stalled = false;
+  for (; s < steps; ++s) {
+    // this thread's best, then the wave's: the largest |c|, smallest atom
+    double mag = -1.0, val = 0.0;
+    int at = 0x7FFFFFFF, where = 0;
+#pragma unroll
+    for (int e = 0; e < kPerThread; ++e) {
+      const double a = __builtin_fabs(c[e]);
+      const bool live = kPerThread * tid + e < nact;
+      if (live && (a > mag || (a == mag && atom[e] < at))) {
+        mag = a;
+        val = c[e];
+        at = atom[e];
+        where = kPerThread * tid + e;
+      }
+    }
+    const double top = wave_max_f64(mag);
+    unsigned long long lanes = top < 0.0 ? 1ull : __ballot(mag == top);
+    int l = __builtin_ctzll(lanes);
+    for (lanes &= lanes - 1; lanes != 0; lanes &= lanes - 1) {
+      const int o = __builtin_ctzll(lanes);
+      if (__builtin_amdgcn_readlane(at, o) < __builtin_amdgcn_readlane(at, l)) l = o;
+    }
+    if (lane == l) rec[s & 1][wave] = Rec{mag, val, at, where};
+    __syncthreads();
+    Rec w = rec[s & 1][0];
+#pragma unroll
+    for (int k = 1; k < kStepWaves; ++k) {
+      const Rec o = rec[s & 1][k];
+      if (o.mag > w.mag || (o.mag == w.mag && o.atom < w.atom)) w = o;
+    }
+    const int row = __builtin_amdgcn_readfirstlane(w.pos);
+    const v4s e4 =
+        reinterpret_cast<const v4s*>(h + static_cast<int64_t>(row) * kSignActive)[tid];
+    if (tid == 0) {
+      g->log_pos[s] = w.pos;
+      g->log_atom[s] = w.atom;
+      g->log_c[s] = w.c;
+    }
+    if (w.c == 0.0) {  // (the check asks whether every other atom's is)
+      stalled = true;
+      break;
+    }
+    const double a = w.c * inv_n;
+#pragma unroll
+    for (int e = 0; e < kPerThread; ++e)
+      c[e] = __builtin_fma(-a, static_cast<double>(static_cast<int>(e4[e])), c[e]);
+  }
+  if (tid == 0) {
+    g->count = s;
+    g->stalled = stalled ? 1 : 0;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// One atom through the first `count` logged steps; returns the first step at
+// which it beats the step's atom (count: none).
+template <bool CHECK>
+__device__ inline int replay_atom(const short* __restrict__ gcol, int64_t mstride, int64_t a,
+                                  const SignCarry* __restrict__ g, int count, double inv_n,
+                                  double& c) {
+  int beat = count;
+  for (int s0 = 0; s0 < count; s0 += kReplay) {
+    short e[kReplay];
+#pragma unroll
+    for (int u = 0; u < kReplay; ++u) {
+      const int s = s0 + u < count ? s0 + u : count - 1;
+      e[u] = gcol[static_cast<int64_t>(g->log_pos[s]) * mstride + a];
+    }
+#pragma unroll
+    for (int u = 0; u < kReplay; ++u) {
+      const int s = s0 + u;
+      if (s < count) {
+        const double w = g->log_c[s];
+        if (CHECK) {
+          const double x = __builtin_fabs(c), y = __builtin_fabs(w);
+          if (beat == count && (x > y || (x == y && a < g->log_atom[s]))) beat = s;
+        }
+        c = __builtin_fma(-(w * inv_n), static_cast<double>(static_cast<int>(e[u])), c);
+      }
+    }
+  }
+  return beat;
+}
+
+// One wave: the rows of workgroup v of the stepping form through the first
+// `count` logged steps (r_n -/+ c* / sqrt(N), rows with a set bit get +).
+// CHECK: the steps' partial ||r||^2, summed as k_mp_step_sign does; otherwise
+// r is stored, and its trace entries from step t0 on.
+template <bool CHECK>
+__device__ inline void replay_rows(const uint32_t* __restrict__ bits, int64_t ws, int n,
+                                   int64_t ld, int rows_per_wg, int v, int lane, int count,
+                                   double inv_sqrt_n, const SignCarry* __restrict__ g,
+                                   double* __restrict__ r64, float* __restrict__ r32,
+                                   double* __restrict__ parts, int grid, long long t0,
+                                   const mp_trace& tr) {
+  const int64_t row0 = static_cast<int64_t>(v) * rows_per_wg;
+  const int64_t row1 = row0 + rows_per_wg < ld ? row0 + rows_per_wg : ld;
+  double r[kSignRows];
+#pragma unroll
+  for (int q = 0; q < kSignRows; ++q) {
+    const int64_t i = row0 + lane + kWave * q;
+    r[q] = i < row1 ? r64[i] : 0.0;
+  }
+  constexpr int U = 8;
+  for (int s0 = 0; s0 < count; s0 += U) {
+    uint32_t w[U][kSignRows];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int s = s0 + u < count ? s0 + u : count - 1;
+      const uint32_t* col = bits + static_cast<int64_t>(g->log_atom[s]) * ws;
+#pragma unroll
+      for (int q = 0; q < kSignRows; ++q) {
+        const int64_t i = row0 + lane + kWave * q;
+        w[u][q] = i < row1 && i < n ? col[i >> 5] : 0u;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int st = s0 + u;
+      if (st >= count) break;
+      const double step = g->log_c[st] * inv_sqrt_n;
+      float* rt = !CHECK && tr.r && t0 + st < tr.cap ? tr.r + (t0 + st) * tr.ldr : nullptr;
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < kSignRows; ++q) {
+        const int64_t i = row0 + lane + kWave * q;
+        if (i < row1) {
+          double x = r[q];
+          if (i < n) {
+            x = ((w[u][q] >> (i & 31)) & 1u) ? x + step : x - step;
+            r[q] = x;
+            if (!CHECK && rt) rt[i] = static_cast<float>(x);
+          }
+          s += x * x;
+        }
+      }
+      if (CHECK) {
+        s = wave_sum(s);
+        if (lane == 0) parts[static_cast<int64_t>(st) * grid + v] = s;
+      }
+    }
+  }
+  if (!CHECK && count > 0) {
+#pragma unroll
+    for (int q = 0; q < kSignRows; ++q) {
+      const int64_t i = row0 + lane + kWave * q;
+      if (i < row1 && i < n) {
+        r64[i] = r[q];
+        r32[i] = static_cast<float>(r[q]);
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(kCheckThreads) void k_sgram_check(
+    const uint32_t* __restrict__ bits, int64_t ws, int n, int64_t m, int64_t ld,
+    const double* __restrict__ c64, double* __restrict__ r64, const short* __restrict__ gcol,
+    int64_t mstride, double inv_n, double inv_sqrt_n, int grid, int rows_per_wg, int ablocks,
+    double* __restrict__ parts, const DevState* __restrict__ st, SignCarry* g) {
+  const int count = g->count, total = count + g->stalled;
+  if (st->done || total == 0) return;
+  const int lane = static_cast<int>(threadIdx.x) % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  if (static_cast<int>(blockIdx.x) >= ablocks) {
+    const int v = (static_cast<int>(blockIdx.x) - ablocks) * (kCheckThreads / kWave) + wave;
+    if (v < grid)
+      replay_rows<true>(bits, ws, n, ld, rows_per_wg, v, lane, count, inv_sqrt_n, g, r64, nullptr,
+                        parts, grid, 0, mp_trace{});
+    return;
+  }
+  const int64_t a = static_cast<int64_t>(blockIdx.x) * kCheckThreads + threadIdx.x;
+  int beat = total;
+  if (a < m) {
+    double c = c64[a];
+    beat = replay_atom<true>(gcol, mstride, a, g, total, inv_n, c);
+  }
+  const unsigned long long who = __ballot(beat < total);
+  if (who == 0) return;
+  int base = 0;
+  if (lane == 0)
+    base = __hip_atomic_fetch_add(&g->nbeat, static_cast<int>(__popcll(who)), __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
+  base = __builtin_amdgcn_readfirstlane(base);
+  if (beat < total) {
+    (void)__hip_atomic_fetch_min(&g->first, beat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int at = base + static_cast<int>(__popcll(who & ((1ull << lane) - 1)));
+    if (at < kSignBeats) {
+      g->beat_step[at] = beat;
+      g->beat_atom[at] = static_cast<int>(a);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
+    const double* __restrict__ c64, int64_t m, const double* __restrict__ parts, int grid,
+    double thr, long long max_iters, float* __restrict__ x, unsigned short* __restrict__ pos,
+    DevState* __restrict__ st, SignCarry* __restrict__ g, mp_trace tr) {
+  const int tid = static_cast<int>(threadIdx.x);
+  const int lane = tid % kWave, wave = tid / kWave;
+  if (st->done) {
+    if (tid == 0) g->take = g->nnew = 0;
+    return;
+  }
+  __shared__ double red[kDecideWaves][16];
+  __shared__ double s_rr[kSignSteps], s_c[kSignSteps];
+  __shared__ int s_atom[kSignSteps];
+  __shared__ int s_stop, s_pos, s_cut;
+  __shared__ int hist[kBins];
+  __shared__ unsigned s_max;
+  const int count = g->count, first = g->first, fill = g->fill;
+  const int nbeat = g->nbeat < kSignBeats ? g->nbeat : kSignBeats;
+  const long long t0 = st->t;
+  int nact = g->nact;
+  if (tid == 0) {
+    s_stop = kSignSteps;
+    s_max = 0;
+  }
+  if (tid < count) {
+    s_c[tid] = g->log_c[tid];
+    s_atom[tid] = g->log_atom[tid];
+  }
+  for (int i = tid; i < kBins; i += kDecideThreads) hist[i] = 0;
+  // ||r||^2 after each step: the block sum of k_mp_step_sign over the partials
+  for (int s = wave; s < count; s += kDecideWaves) {
+    for (int k = 0; k < kDecideWaves; ++k) {
+      const int i = k * kWave + lane;
+      const double v = k * kWave < grid
+                           ? wave_sum(i < grid ? parts[static_cast<int64_t>(s) * grid + i] : 0.0)
+                           : 0.0;
+      if (lane == 0) red[wave][k] = v;
+    }
+    __builtin_amdgcn_wave_barrier();
+    const double rr = wave_sum(lane < kDecideWaves ? red[wave][lane] : 0.0);
+    if (lane == 0) s_rr[s] = rr;
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  if (tid < count && !(s_rr[tid] > thr)) atomicMin(&s_stop, tid);
+  __syncthreads();
+  const int stop = s_stop;
+  int take = count;
+  if (stop + 1 < take) take = stop + 1;
+  if (first < take) take = first;
+  const long long t = t0 + take;
+  int reason = -1;
+  if (take == stop + 1) reason = MP_STOP_CONVERGED;
+  else if (t >= max_iters) reason = MP_STOP_MAX_ITERS;
+  else if (g->stalled && take == count && first > count) reason = MP_STOP_STALLED;
+  // x~: the first of an atom's steps adds all of them in order
+  if (tid < take) {
+    const int a = s_atom[tid];
+    bool lead = true;
+    for (int k = 0; k < tid; ++k) lead = lead && s_atom[k] != a;
+    if (lead) {
+      float v = x[a];
+      for (int k = tid; k < take; ++k)
+        if (s_atom[k] == a) v += static_cast<float>(s_c[k]);
+      x[a] = v;
+    }
+    if (t0 + tid < tr.cap) {
+      if (tr.idx) tr.idx[t0 + tid] = a;
+      if (tr.coef) tr.coef[t0 + tid] = static_cast<float>(s_c[tid]);
+      if (tr.rr) tr.rr[t0 + tid] = s_rr[tid];
+    }
+  }
+  const bool over = reason != -1;
+  bool refill = false;
+  int nnew = 0;
+  if (!over && fill) {
+    // the atoms of largest |c|: whole bins of its leading bits, down to about
+    // kFirstActive atoms (every atom where all can be active)
+    const int want = m <= kSignActive ? static_cast<int>(m) : kFirstActive;
+    const int room = m <= kSignActive ? kSignActive : 2 * kFirstActive;
+    auto mag = [&](int64_t a) {
+      return __builtin_bit_cast(unsigned, static_cast<float>(__builtin_fabs(c64[a]))) >> 19;
+    };
+    unsigned top = 0;
+    for (int64_t a = tid; a < m; a += kDecideThreads) top = max(top, mag(a));
+    atomicMax(&s_max, top);
+    __syncthreads();
+    top = s_max;
+    auto bin = [&](int64_t a) {
+      const unsigned b = top - mag(a);
+      return static_cast<int>(b < kBins ? b : kBins - 1);
+    };
+    for (int64_t a = tid; a < m; a += kDecideThreads) atomicAdd(&hist[bin(a)], 1);
+    __syncthreads();
+    if (tid == 0) {
+      int b = 0, sum = 0;
+      while (b < kBins && sum < want) sum += hist[b++];
+      s_cut = b;
+      s_pos = 0;
+    }
+    __syncthreads();
+    for (int64_t a = tid; a < m; a += kDecideThreads)
+      if (bin(a) < s_cut) {
+        const int p = atomicAdd(&s_pos, 1);
+        if (p < room) {
+          g->atom[p] = static_cast<int>(a);
+          pos[a] = static_cast<unsigned short>(p);
+        }
+      }
+    __syncthreads();
+    nnew = s_pos < room ? s_pos : room;
+  } else if (!over && nbeat > 0) {
+    // the atoms that beat the earliest steps
+    if (nact + kNewMost > kSignActive) {
+      refill = true;
+      for (int p = tid; p < nact; p += kDecideThreads) pos[g->atom[p]] = kNoPos;
+    } else {
+      for (int i = tid; i < nbeat; i += kDecideThreads) atomicAdd(&hist[g->beat_step[i]], 1);
+      __syncthreads();
+      if (tid == 0) {
+        int b = 0, sum = 0;
+        while (b <= count && sum + hist[b] <= kNewMost) sum += hist[b++];
+        s_cut = sum > 0 ? b : b + 1;  // (more than fit beat one step: some of them)
+        s_pos = 0;
+      }
+      __syncthreads();
+      for (int i = tid; i < nbeat; i += kDecideThreads)
+        if (g->beat_step[i] < s_cut) {
+          const int p = atomicAdd(&s_pos, 1);
+          if (p < kNewMost) {
+            g->atom[nact + p] = g->beat_atom[i];
+            pos[g->beat_atom[i]] = static_cast<unsigned short>(nact + p);
+          }
+        }
+      __syncthreads();
+      nnew = s_pos < kNewMost ? s_pos : kNewMost;
+    }
+  }
+  if (tid == 0) {
+    if (take > 0) st->rr = s_rr[take - 1];
+    st->t = t;
+    if (over) {
+      st->reason = reason;
+      st->done = 1;
+    }
+    g->take = take;
+    g->t0 = t0;
+    g->nnew = nnew;
+    g->nact = refill ? 0 : nact + nnew;
+    g->fill = refill ? 1 : 0;
+    // steps taken for nothing cost their time: twice what stood
+    int steps = g->steps;
+    if (first <= count) steps = 2 * take < 16 ? 16 : 2 * take;
+    else if (count > 0) steps = 2 * steps;
+    g->steps = steps < kSignSteps ? steps : kSignSteps;
+    g->first = kSignSteps;
+    g->nbeat = 0;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The Gram entries n - 2 popcount(b_i XOR b_m) of the new atoms i: lane = atom
+// m, its bits turned over in LDS (16-byte chunk ch of atom a at a ^ ch of the
+// chunk's row, which keeps both sides off each other's banks), the new atoms'
+// bits in scalar registers.  Bound by the bit counts.
+__global__ __launch_bounds__(kCommitThreads) void k_sgram_commit(
+    const uint32_t* __restrict__ bits, int64_t ws, int n, int64_t m, int64_t ld,
+    double* __restrict__ c64, double* __restrict__ r64, float* __restrict__ r32,
+    short* __restrict__ gcol, int64_t mstride, short* __restrict__ h,
+    const unsigned short* __restrict__ pos, double inv_n, double inv_sqrt_n, int grid,
+    int rows_per_wg, int ablocks, const SignCarry* __restrict__ g, mp_trace tr) {
+  extern __shared__ v4u own[];  // nch x kCommitAtoms
+  const int take = g->take, nnew = g->nnew;
+  const int lane = static_cast<int>(threadIdx.x) % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  if (static_cast<int>(blockIdx.x) >= ablocks) {
+    const int v = (static_cast<int>(blockIdx.x) - ablocks) * kCommitWaves + wave;
+    if (v < grid && take > 0)
+      replay_rows<false>(bits, ws, n, ld, rows_per_wg, v, lane, take, inv_sqrt_n, g, r64, r32,
+                         nullptr, grid, g->t0, tr);
+    return;
+  }
+  const int64_t a0 = static_cast<int64_t>(blockIdx.x) * kCommitAtoms;
+  const int64_t a = a0 + lane;
+  if (take > 0 && wave == 0 && a < m) {
+    double c = c64[a];
+    (void)replay_atom<false>(gcol, mstride, a, g, take, inv_n, c);
+    c64[a] = c;
+  }
+  if (nnew == 0) return;
+  const int nch = static_cast<int>(ws / 4);
+  for (int i = static_cast<int>(threadIdx.x); i < nch * kCommitAtoms; i += kCommitThreads) {
+    const int at = i / nch, ch = i % nch;
+    const int64_t from = a0 + at < m ? a0 + at : m - 1;
+    own[ch * kCommitAtoms + (at ^ (ch % kCommitAtoms))] =
+        reinterpret_cast<const v4u*>(bits + from * ws)[ch];
+  }
+  __syncthreads();
+  const int base = g->nact - nnew;
+  const int mine = a < m ? pos[a] : kNoPos;
+  for (int i0 = kNewGroup * wave; i0 < nnew; i0 += kNewGroup * kCommitWaves) {
+    const v4u* col[kNewGroup];
+    int acc[kNewGroup];
+#pragma unroll
+    for (int k = 0; k < kNewGroup; ++k) {
+      const int p = base + (i0 + k < nnew ? i0 + k : nnew - 1);
+      const int atom = __builtin_amdgcn_readfirstlane(g->atom[p]);
+      col[k] = reinterpret_cast<const v4u*>(bits + static_cast<int64_t>(atom) * ws);
+      acc[k] = 0;
+    }
+    for (int ch = 0; ch < nch; ++ch) {
+      const v4u o = own[ch * kCommitAtoms + (lane ^ (ch % kCommitAtoms))];
+#pragma unroll
+      for (int k = 0; k < kNewGroup; ++k) {
+        const v4u b = col[k][ch];
+        acc[k] += __builtin_popcount(o.x ^ b.x);
+        acc[k] += __builtin_popcount(o.y ^ b.y);
+        acc[k] += __builtin_popcount(o.z ^ b.z);
+        acc[k] += __builtin_popcount(o.w ^ b.w);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kNewGroup; ++k) {
+      if (i0 + k >= nnew || a >= m) continue;
+      const int p = base + i0 + k;
+      const short e = static_cast<short>(n - 2 * acc[k]);
+      gcol[static_cast<int64_t>(p) * mstride + a] = e;
+      if (mine != kNoPos) {
+        h[static_cast<int64_t>(p) * kSignActive + mine] = e;
+        h[static_cast<int64_t>(mine) * kSignActive + p] = e;
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+int64_t sign_gram_stride(int64_t m) { return (m + kWave - 1) / kWave * kWave; }
+
+hipError_t launch_sgram_init(const SignGram& b, int64_t m, hipStream_t s) {
+  int64_t blocks = (m + 255) / 256;
+  if (blocks > 64) blocks = 64;
+  k_sgram_init<<<dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s>>>(b.carry, b.pos, m);
+  return hipGetLastError();
+}
+
+hipError_t launch_sgram_round(const uint32_t* bits, int64_t ws, int64_t n, int64_t m, int64_t ld,
+                              double* c64, double* r64, float* r32, const CorrGeom& geom,
+                              const SignGram& b, long long max_iters, double thr, float* x,
+                              DevState* st, mp_trace tr, hipStream_t s) {
+  const double inv_n = 1.0 / static_cast<double>(n);
+  const double inv_sqrt_n = 1.0 / sqrt(static_cast<double>(n));
+  const int nn = static_cast<int>(n), grid = geom.grid;
+  const int rows_per_wg = static_cast<int>((ld + grid - 1) / grid);
+  const size_t lds = static_cast<size_t>(ws) * 4 * kCommitAtoms;
+  if (rows_per_wg > kWave * kSignRows || grid > kDecideThreads || lds > 128 * 1024)
+    return hipErrorInvalidValue;
+  static const hipError_t attr =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(k_sgram_commit),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+  if (attr != hipSuccess) return attr;
+  const int64_t mstride = sign_gram_stride(m);
+  hipError_t e;
+  k_sgram_steps<<<dim3(1), dim3(kStepThreads), 0, s>>>(c64, b.h, inv_n, max_iters, st, b.carry);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const int ca = static_cast<int>((m + kCheckThreads - 1) / kCheckThreads);
+  const int cr = (grid + kCheckThreads / kWave - 1) / (kCheckThreads / kWave);
+  k_sgram_check<<<dim3(ca + cr), dim3(kCheckThreads), 0, s>>>(
+      bits, ws, nn, m, ld, c64, r64, b.g, mstride, inv_n, inv_sqrt_n, grid, rows_per_wg, ca,
+      b.parts, st, b.carry);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  k_sgram_decide<<<dim3(1), dim3(kDecideThreads), 0, s>>>(c64, m, b.parts, grid, thr, max_iters, x,
+                                                          b.pos, st, b.carry, tr);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const int oa = static_cast<int>((m + kCommitAtoms - 1) / kCommitAtoms);
+  const int orows = (grid + kCommitWaves - 1) / kCommitWaves;
+  k_sgram_commit<<<dim3(oa + orows), dim3(kCommitThreads), lds, s>>>(
+      bits, ws, nn, m, ld, c64, r64, r32, b.g, mstride, b.h, b.pos, inv_n, inv_sqrt_n, grid,
+      rows_per_wg, oa, b.carry, tr);
+  return hipGetLastError();
+}
+
+}  // namespace mp

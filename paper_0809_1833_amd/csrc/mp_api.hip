@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "k_gram.h"
+#include "k_sign_gram.h"
 #include "mp_internal.h"
 
 namespace {
@@ -114,6 +115,16 @@ void free_omp(mp_ctx* c) {
   b = mp::OmpBufs{};
 }
 
+void free_sign_gram(mp_ctx* c) {
+  mp::SignGram& b = c->sign_gram;
+  (void)hipFree(b.carry);
+  (void)hipFree(b.pos);
+  (void)hipFree(b.g);
+  (void)hipFree(b.h);
+  (void)hipFree(b.parts);
+  b = mp::SignGram{};
+}
+
 void free_gram(mp_ctx* c) {
   (void)hipFree(c->gram_c);
   (void)hipFree(c->gram_g);
@@ -159,6 +170,7 @@ void free_gram_ragged(mp_ctx* c) {
 void free_ctx(mp_ctx* c) {
   if (!c) return;
   free_gram(c);
+  free_sign_gram(c);
   free_gram_ragged(c);
   free_gram_batch(c);
   (void)hipFree(c->gram_full);
@@ -1135,6 +1147,66 @@ mp_status mp_get_storage(const mp_ctx* ctx, void* codes, float* scales, void* st
   return MP_OK;
 }
 
+// The buffers of the one-bit decode in batches of steps; false where it does
+// not apply (more rows of r per workgroup of the stepping form than a replay
+// holds: M below N / 16) or the memory is not there.
+static bool ensure_sign_gram(mp_ctx* c) {
+  mp::SignGram& b = c->sign_gram;
+  if (b.tried) return b.carry != nullptr;
+  const size_t grid = static_cast<size_t>(c->geom.grid);
+  b.tried = true;
+  if ((c->ld + c->geom.grid - 1) / c->geom.grid > 64 * mp::kSignRows) return false;
+  const size_t act = mp::kSignActive;
+  if (hipMalloc(&b.carry, sizeof(mp::SignCarry)) != hipSuccess ||
+      hipMalloc(&b.pos, sizeof(unsigned short) * static_cast<size_t>(c->m)) != hipSuccess ||
+      hipMalloc(&b.g, sizeof(short) * act * static_cast<size_t>(mp::sign_gram_stride(c->m))) !=
+          hipSuccess ||
+      hipMalloc(&b.h, sizeof(short) * act * act) != hipSuccess ||
+      hipMalloc(&b.parts, sizeof(double) * mp::kSignSteps * grid) != hipSuccess) {
+    (void)hipGetLastError();
+    free_sign_gram(c);
+    b.tried = true;
+    return false;
+  }
+  return true;
+}
+
+// The one-bit decode in batches of steps (k_sign_gram.hip), two chunks of
+// rounds in flight.  `over`: it reached its stop.
+static mp_status solve_sign_gram(mp_ctx* c, float* x, long long T, double thr, const mp_trace& tr,
+                                 hipStream_t s, bool& over) {
+  constexpr int kRounds = 2;
+  const bool timed = c->profiling;
+  if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
+  HIP_TRY(c, mp::launch_sgram_init(c->sign_gram, c->m, s));
+  // a round takes a step, makes an atom active or fills the active atoms anew
+  const long long most = 4 * T + 64;
+  long long issued = 0, seen = 0;
+  over = false;
+  while (!over && seen < most) {
+    while (issued < most && issued - seen < 2) {
+      for (int k = 0; k < kRounds; ++k)
+        HIP_TRY(c, mp::launch_sgram_round(c->psis, c->sign_ws, c->n, c->m, c->ld, c->sign_c64,
+                                          c->sign_r64, c->r_work, c->geom, c->sign_gram, T, thr, x,
+                                          c->st, tr, s));
+      const int k = static_cast<int>(issued & 1);
+      HIP_TRY(c, hipMemcpyAsync(&c->h_st[1 + k], c->st, sizeof(mp::DevState),
+                                hipMemcpyDeviceToHost, s));
+      HIP_TRY(c, hipEventRecord(c->done_ev[k], s));
+      ++issued;
+    }
+    const int k = static_cast<int>(seen & 1);
+    HIP_TRY(c, hipEventSynchronize(c->done_ev[k]));
+    ++seen;
+    over = c->h_st[1 + k].done != 0;
+  }
+  if (timed) {
+    HIP_TRY(c, hipEventRecord(c->ev[1], s));
+    HIP_TRY(c, hipEventSynchronize(c->ev[1]));
+  }
+  return MP_OK;
+}
+
 mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opts* opts,
                    mp_result* res, const mp_trace* trace, void* stream) {
   if (!ctx) return MP_EINVAL;
@@ -1179,10 +1251,22 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
                                     c->sign_r64, s));
     const long long T = opts->max_iters;
     const double thr = c->h_st->thr;
-    // the whole decode as one persistent launch when it fits, unless the
-    // caller asks for one launch per step; a launch the device refuses
-    // falls back to stepping
-    if (c->sign_persist && !(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done) {
+    // batches of steps, unless the caller asks for one launch per step or
+    // limits the waits of the persistent launch, which only that has
+    if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done &&
+        !getenv("MP_SIGN_SPIN_LIMIT") && ensure_sign_gram(c)) {
+      const mp_status gs = solve_sign_gram(c, x, T, thr, tr, s, persistent);
+      if (gs != MP_OK) return gs;
+      if (!persistent) {  // (not reached: every round makes progress)
+        HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st, opts->eps,
+                                   static_cast<long long>(opts->max_iters), s));
+        HIP_TRY(c, mp::launch_sign_c0(c->psis, c->sign_ws, c->n, c->m, y, c->ld, c->sign_c64,
+                                      c->sign_r64, s));
+      }
+    }
+    // otherwise the whole decode as one persistent launch when it fits; a
+    // launch the device refuses falls back to stepping
+    if (!persistent && c->sign_persist && !(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done) {
       if (c->profiling) HIP_TRY(c, hipEventRecord(c->ev[0], s));
       // a new tag epoch for every decode (never 0 mod kSignEpochMod: the
       // zeroed words match no step); when it wraps, clear the words so that

@@ -136,6 +136,17 @@ hipError_t launch_mp_step_f64(const double* psi, int64_t ld, int64_t n, int64_t 
                               long long max_iters, double thr, double* x, DevState* st,
                               mp_trace_f64 tr, hipStream_t s);
 
+// ---- the one-bit decode in checked batches of steps (k_sign_gram.hip) ---------
+struct SignCarry;
+struct SignGram {                // work buffers (context-owned; carry null: not available)
+  bool tried = false;            // allocation attempted (once)
+  SignCarry* carry = nullptr;
+  unsigned short* pos = nullptr; // m: position of an active atom
+  short* g = nullptr;            // kSignActive x sign_gram_stride(m)
+  short* h = nullptr;            // kSignActive x kSignActive: between active atoms
+  double* parts = nullptr;       // kSignSteps x grid
+};
+
 // ---- sign-bit Bernoulli dictionary (k_sign.hip) ------------------------------
 // 16-byte chunks of a column each lane reads (1 for n <= 8192, 2 above).
 int sign_chunks_per_lane(int64_t n);
@@ -344,6 +355,7 @@ struct mp_ctx {
   double* sign_rrp = nullptr;    // MP_SIGN1: per-workgroup partial ||r||^2, 2 x grid
   unsigned long long* sign_slots = nullptr;  // MP_SIGN1 persistent decode: step records
   unsigned sign_epoch = 0;       // MP_SIGN1 persistent decode: tag epoch of the last decode
+  mp::SignGram sign_gram;        // MP_SIGN1: made by the first decode
   bool sign_persist = false;     // MP_SIGN1: the persistent decode fits this device
   float* scales = nullptr;       // FP8 per-column scales
   // per-decode work buffers
