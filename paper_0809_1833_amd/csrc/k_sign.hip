@@ -86,46 +86,59 @@ __device__ inline uint32_t disagree(const v4u& a, const v4u& b) {
 
 // ---------------------------------------------------------------------------
 // c(0)_m = <y, psi_m> = (sum_n (1 - 2 b_nm) y_n) / sqrt(N) in FP64 for every
-// column (eq. 9 at t = 0), and r = y in FP64.  One wave per column; lane l
-// sums the rows of its chunks in increasing order, then the wave sums the
-// lanes.  y is staged in LDS (32 ws floats, zero past n).
-constexpr int kC0Threads = 256;
+// column (eq. 9 at t = 0), and r = y in FP64.  kC0Cols columns per wave; lane
+// l sums the rows of its chunks in increasing order, then the wave sums the
+// lanes.  y is staged in LDS as FP64, zero past n, row b of every chunk side
+// by side (stride nch), so that the lanes of a wave, a chunk each, meet no
+// bank conflicts: with the rows in order all of them read one bank, and the
+// product of N = 8192, M = 32768 took 460 us.
+constexpr int kC0Threads = 512;
+constexpr int kC0Cols = 4;
 __global__ __launch_bounds__(kC0Threads) void k_sign_c0(const uint32_t* __restrict__ bits,
                                                         int64_t ws, int n, int64_t m,
                                                         const float* __restrict__ y,
                                                         double inv_sqrt_n, int64_t ld,
                                                         double* __restrict__ c64,
                                                         double* __restrict__ r64) {
-  extern __shared__ float y_lds[];
+  extern __shared__ double y_lds[];
   const int rows = static_cast<int>(32 * ws);
-  for (int i = threadIdx.x; i < rows; i += kC0Threads) y_lds[i] = i < n ? y[i] : 0.0f;
+  const int nch = static_cast<int>(ws / 4);
+  for (int i = threadIdx.x; i < rows; i += kC0Threads)
+    y_lds[i % 128 * nch + i / 128] = i < n ? static_cast<double>(y[i]) : 0.0;
   if (blockIdx.x == 0)
     for (int64_t i = threadIdx.x; i < ld; i += kC0Threads)
       r64[i] = i < n ? static_cast<double>(y[i]) : 0.0;
   __syncthreads();
   const int lane = threadIdx.x % kWave;
-  const int nch = static_cast<int>(ws / 4);
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * (kC0Threads / kWave);
-  for (int64_t col = static_cast<int64_t>(blockIdx.x) * (kC0Threads / kWave) +
-                     threadIdx.x / kWave;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * (kC0Threads / kWave) * kC0Cols;
+  for (int64_t col = (static_cast<int64_t>(blockIdx.x) * (kC0Threads / kWave) +
+                      threadIdx.x / kWave) * kC0Cols;
        col < m; col += stride) {
-    const v4u* p = reinterpret_cast<const v4u*>(bits + col * ws);
-    double acc = 0.0;
+    double acc[kC0Cols];
+#pragma unroll
+    for (int k = 0; k < kC0Cols; ++k) acc[k] = 0.0;
     for (int ch = lane; ch < nch; ch += kWave) {
-      const v4u w = p[ch];
-      const uint32_t word[4] = {w.x, w.y, w.z, w.w};
+      v4u w[kC0Cols];
+#pragma unroll
+      for (int k = 0; k < kC0Cols; ++k)
+        w[k] = reinterpret_cast<const v4u*>(bits + (col + k < m ? col + k : m - 1) * ws)[ch];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int row0 = 128 * ch + 32 * q;
 #pragma unroll 8
         for (int b = 0; b < 32; ++b) {
-          const double v = static_cast<double>(y_lds[row0 + b]);
-          acc += ((word[q] >> b) & 1u) ? -v : v;
+          const uint64_t v = __builtin_bit_cast(uint64_t, y_lds[(32 * q + b) * nch + ch]);
+#pragma unroll
+          for (int k = 0; k < kC0Cols; ++k)
+            acc[k] += __builtin_bit_cast(
+                double, v ^ (static_cast<uint64_t>((w[k][q] >> b) & 1u) << 63));
         }
       }
     }
-    acc = wave_sum(acc);
-    if (lane == 0) c64[col] = acc * inv_sqrt_n;
+#pragma unroll
+    for (int k = 0; k < kC0Cols; ++k) {
+      const double c = wave_sum(acc[k]);
+      if (lane == 0 && col + k < m) c64[col + k] = c * inv_sqrt_n;
+    }
   }
 }
 
@@ -613,13 +626,13 @@ hipError_t launch_copy_signs(const uint32_t* in, int64_t ldw, int64_t n, int64_t
 
 hipError_t launch_sign_c0(const uint32_t* bits, int64_t ws, int64_t n, int64_t m, const float* y,
                           int64_t ld, double* c64, double* r64, hipStream_t s) {
-  const size_t lds = sizeof(float) * 32 * static_cast<size_t>(ws);  // <= 64 KB (n <= 16384)
-  int64_t blocks = (m + kC0Threads / kWave - 1) / (kC0Threads / kWave);
-  if (blocks > 4096) blocks = 4096;
+  const size_t lds = sizeof(double) * 32 * static_cast<size_t>(ws);  // <= 128 KB (n <= 16384)
+  int64_t blocks = (m + kC0Threads / kWave * kC0Cols - 1) / (kC0Threads / kWave * kC0Cols);
+  if (blocks > 512) blocks = 512;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_sign_c0),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
   }

@@ -79,9 +79,11 @@ __global__ __launch_bounds__(kStepThreads) void k_sgram_steps(
   if (st->done) return;
   struct Rec {
     double mag, c;
-    int atom, pos;
+    int pos;
   };
   __shared__ Rec rec[2][kStepWaves];
+  __shared__ int s_atom[kSignActive];
+  __shared__ int s_log[kSignSteps];
   const int tid = static_cast<int>(threadIdx.x);
   const int lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -89,52 +91,56 @@ __global__ __launch_bounds__(kStepThreads) void k_sgram_steps(
   int steps = nact > 0 ? g->steps : 0;
   const long long left = max_iters - st->t;
   if (left < steps) steps = static_cast<int>(left);
+  // (a position past the active atoms: -1 in every maximum)
   double c[kPerThread];
-  int atom[kPerThread];
+  bool live[kPerThread];
 #pragma unroll
   for (int e = 0; e < kPerThread; ++e) {
     const int p = kPerThread * tid + e;
-    atom[e] = p < nact ? g->atom[p] : 0x7FFFFFFF;
-    c[e] = p < nact ? c64[atom[e]] : 0.0;
+    live[e] = p < nact;
+    const int atom = live[e] ? g->atom[p] : 0;
+    s_atom[p] = atom;
+    c[e] = live[e] ? c64[atom] : 0.0;
   }
+  __syncthreads();
   int s = 0;
   bool stalled = false;
   for (; s < steps; ++s) {
-    // this thread's best, then the wave's: the largest |c|, smallest atom
-    double mag = -1.0, val = 0.0;
-    int at = 0x7FFFFFFF, where = 0;
+    // the wave's largest |c|; of equal ones the smallest atom
+    double mag[kPerThread], best = -1.0;
 #pragma unroll
     for (int e = 0; e < kPerThread; ++e) {
-      const double a = __builtin_fabs(c[e]);
-      const bool live = kPerThread * tid + e < nact;
-      if (live && (a > mag || (a == mag && atom[e] < at))) {
-        mag = a;
-        val = c[e];
-        at = atom[e];
-        where = kPerThread * tid + e;
-      }
+      mag[e] = live[e] ? __builtin_fabs(c[e]) : -1.0;
+      best = __builtin_fmax(best, mag[e]);
     }
-    const double top = wave_max_f64(mag);
-    unsigned long long lanes = top < 0.0 ? 1ull : __ballot(mag == top);
-    int l = __builtin_ctzll(lanes);
-    for (lanes &= lanes - 1; lanes != 0; lanes &= lanes - 1) {
-      const int o = __builtin_ctzll(lanes);
-      if (__builtin_amdgcn_readlane(at, o) < __builtin_amdgcn_readlane(at, l)) l = o;
+    const double top = wave_max_f64(best);
+    int pos = -1;
+    double val = 0.0;
+    if (top >= 0.0) {
+#pragma unroll
+      for (int e = 0; e < kPerThread; ++e)
+        for (unsigned long long l = __ballot(mag[e] == top); l != 0; l &= l - 1) {
+          const int o = __builtin_ctzll(l);
+          const int p = kPerThread * (kWave * wave + o) + e;
+          if (pos < 0 || s_atom[p] < s_atom[pos]) {
+            pos = p;
+            val = lane_f64(c[e], o);
+          }
+        }
     }
-    if (lane == l) rec[s & 1][wave] = Rec{mag, val, at, where};
+    if (lane == 0) rec[s & 1][wave] = Rec{top, val, pos};
     __syncthreads();
     Rec w = rec[s & 1][0];
 #pragma unroll
     for (int k = 1; k < kStepWaves; ++k) {
       const Rec o = rec[s & 1][k];
-      if (o.mag > w.mag || (o.mag == w.mag && o.atom < w.atom)) w = o;
+      if (o.mag > w.mag || (o.mag == w.mag && o.pos >= 0 && s_atom[o.pos] < s_atom[w.pos])) w = o;
     }
     const int row = __builtin_amdgcn_readfirstlane(w.pos);
     const v4s e4 =
         reinterpret_cast<const v4s*>(h + static_cast<int64_t>(row) * kSignActive)[tid];
     if (tid == 0) {
-      g->log_pos[s] = w.pos;
-      g->log_atom[s] = w.atom;
+      s_log[s] = w.pos;
       g->log_c[s] = w.c;
     }
     if (w.c == 0.0) {  // (the check asks whether every other atom's is)
@@ -145,6 +151,11 @@ __global__ __launch_bounds__(kStepThreads) void k_sgram_steps(
 #pragma unroll
     for (int e = 0; e < kPerThread; ++e)
       c[e] = __builtin_fma(-a, static_cast<double>(static_cast<int>(e4[e])), c[e]);
+  }
+  __syncthreads();
+  if (tid < s + (stalled ? 1 : 0)) {
+    g->log_pos[tid] = s_log[tid];
+    g->log_atom[tid] = s_atom[s_log[tid]];
   }
   if (tid == 0) {
     g->count = s;
@@ -184,73 +195,92 @@ __device__ inline int replay_atom(const short* __restrict__ gcol, int64_t mstrid
 }
 
 // One wave: the rows of workgroup v of the stepping form through the first
-// `count` logged steps (r_n -/+ c* / sqrt(N), rows with a set bit get +).
-// CHECK: the steps' partial ||r||^2, summed as k_mp_step_sign does; otherwise
-// r is stored, and its trace entries from step t0 on.
-template <bool CHECK>
+// `count` logged steps (r_n -/+ c* / sqrt(N), rows with a set bit get +), R
+// per lane.  CHECK: the steps' partial ||r||^2, summed as k_mp_step_sign does;
+// otherwise r is stored, and its trace entries from step t0 on.
+template <bool CHECK, int R>
 __device__ inline void replay_rows(const uint32_t* __restrict__ bits, int64_t ws, int n,
-                                   int64_t ld, int rows_per_wg, int v, int lane, int count,
+                                   int64_t row0, int64_t row1, int v, int lane, int count,
                                    double inv_sqrt_n, const SignCarry* __restrict__ g,
                                    double* __restrict__ r64, float* __restrict__ r32,
                                    double* __restrict__ parts, int grid, long long t0,
                                    const mp_trace& tr) {
-  const int64_t row0 = static_cast<int64_t>(v) * rows_per_wg;
-  const int64_t row1 = row0 + rows_per_wg < ld ? row0 + rows_per_wg : ld;
-  double r[kSignRows];
+  constexpr int U = 16 / R;  // steps whose words are in flight
+  double r[R];
+  bool in[R];   // rows of this workgroup
+  bool up[R];   // and of Psi
+  int word[R], bit[R];
 #pragma unroll
-  for (int q = 0; q < kSignRows; ++q) {
+  for (int q = 0; q < R; ++q) {
     const int64_t i = row0 + lane + kWave * q;
-    r[q] = i < row1 ? r64[i] : 0.0;
+    in[q] = i < row1;
+    up[q] = in[q] && i < n;
+    r[q] = in[q] ? r64[i] : 0.0;
+    word[q] = up[q] ? static_cast<int>(i >> 5) : 0;
+    bit[q] = static_cast<int>(i & 31);
   }
-  constexpr int U = 8;
   for (int s0 = 0; s0 < count; s0 += U) {
-    uint32_t w[U][kSignRows];
+    uint32_t w[U][R];
+    double sum[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int s = s0 + u < count ? s0 + u : count - 1;
       const uint32_t* col = bits + static_cast<int64_t>(g->log_atom[s]) * ws;
 #pragma unroll
-      for (int q = 0; q < kSignRows; ++q) {
-        const int64_t i = row0 + lane + kWave * q;
-        w[u][q] = i < row1 && i < n ? col[i >> 5] : 0u;
-      }
+      for (int q = 0; q < R; ++q) w[u][q] = col[word[q]];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int st = s0 + u;
-      if (st >= count) break;
-      const double step = g->log_c[st] * inv_sqrt_n;
-      float* rt = !CHECK && tr.r && t0 + st < tr.cap ? tr.r + (t0 + st) * tr.ldr : nullptr;
+      const bool on = st < count;
+      const double step = on ? g->log_c[st] * inv_sqrt_n : 0.0;
+      float* rt = !CHECK && on && tr.r && t0 + st < tr.cap ? tr.r + (t0 + st) * tr.ldr : nullptr;
       double s = 0.0;
 #pragma unroll
-      for (int q = 0; q < kSignRows; ++q) {
-        const int64_t i = row0 + lane + kWave * q;
-        if (i < row1) {
-          double x = r[q];
-          if (i < n) {
-            x = ((w[u][q] >> (i & 31)) & 1u) ? x + step : x - step;
-            r[q] = x;
-            if (!CHECK && rt) rt[i] = static_cast<float>(x);
-          }
-          s += x * x;
-        }
+      for (int q = 0; q < R; ++q) {
+        double x = r[q];
+        if (up[q] && on) x = ((w[u][q] >> bit[q]) & 1u) ? x + step : x - step;
+        r[q] = x;
+        if (!CHECK && rt && up[q]) rt[row0 + lane + kWave * q] = static_cast<float>(x);
+        if (in[q]) s += x * x;
       }
-      if (CHECK) {
-        s = wave_sum(s);
-        if (lane == 0) parts[static_cast<int64_t>(st) * grid + v] = s;
-      }
+      sum[u] = s;
+    }
+    if constexpr (CHECK) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) sum[u] = wave_sum(sum[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (lane == 0 && s0 + u < count)
+          parts[static_cast<int64_t>(s0 + u) * grid + v] = sum[u];
     }
   }
-  if (!CHECK && count > 0) {
+  if constexpr (!CHECK) {
 #pragma unroll
-    for (int q = 0; q < kSignRows; ++q) {
-      const int64_t i = row0 + lane + kWave * q;
-      if (i < row1 && i < n) {
+    for (int q = 0; q < R; ++q)
+      if (up[q] && count > 0) {
+        const int64_t i = row0 + lane + kWave * q;
         r64[i] = r[q];
         r32[i] = static_cast<float>(r[q]);
       }
-    }
   }
+}
+
+template <bool CHECK>
+__device__ inline void replay_rows_of(const uint32_t* __restrict__ bits, int64_t ws, int n,
+                                      int64_t ld, int rows_per_wg, int v, int lane, int count,
+                                      double inv_sqrt_n, const SignCarry* __restrict__ g,
+                                      double* __restrict__ r64, float* __restrict__ r32,
+                                      double* __restrict__ parts, int grid, long long t0,
+                                      const mp_trace& tr) {
+  const int64_t row0 = static_cast<int64_t>(v) * rows_per_wg;
+  const int64_t row1 = row0 + rows_per_wg < ld ? row0 + rows_per_wg : ld;
+  if (rows_per_wg <= kWave)
+    replay_rows<CHECK, 1>(bits, ws, n, row0, row1, v, lane, count, inv_sqrt_n, g, r64, r32, parts,
+                          grid, t0, tr);
+  else
+    replay_rows<CHECK, kSignRows>(bits, ws, n, row0, row1, v, lane, count, inv_sqrt_n, g, r64,
+                                  r32, parts, grid, t0, tr);
 }
 
 __global__ __launch_bounds__(kCheckThreads) void k_sgram_check(
@@ -265,7 +295,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_sgram_check(
   if (static_cast<int>(blockIdx.x) >= ablocks) {
     const int v = (static_cast<int>(blockIdx.x) - ablocks) * (kCheckThreads / kWave) + wave;
     if (v < grid)
-      replay_rows<true>(bits, ws, n, ld, rows_per_wg, v, lane, count, inv_sqrt_n, g, r64, nullptr,
+      replay_rows_of<true>(bits, ws, n, ld, rows_per_wg, v, lane, count, inv_sqrt_n, g, r64, nullptr,
                         parts, grid, 0, mp_trace{});
     return;
   }
@@ -303,7 +333,7 @@ __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
     if (tid == 0) g->take = g->nnew = 0;
     return;
   }
-  __shared__ double red[kDecideWaves][16];
+  __shared__ double red[kSignSteps][16];
   __shared__ double s_rr[kSignSteps], s_c[kSignSteps];
   __shared__ int s_atom[kSignSteps];
   __shared__ int s_stop, s_pos, s_cut;
@@ -323,18 +353,33 @@ __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
   }
   for (int i = tid; i < kBins; i += kDecideThreads) hist[i] = 0;
   // ||r||^2 after each step: the block sum of k_mp_step_sign over the partials
-  for (int s = wave; s < count; s += kDecideWaves) {
-    for (int k = 0; k < kDecideWaves; ++k) {
-      const int i = k * kWave + lane;
-      const double v = k * kWave < grid
-                           ? wave_sum(i < grid ? parts[static_cast<int64_t>(s) * grid + i] : 0.0)
-                           : 0.0;
-      if (lane == 0) red[wave][k] = v;
+  // (piece e: 64 partials of a step, as that sum's wave; then 16 lanes a step)
+  const int per = (grid + kWave - 1) / kWave, pieces = count * per;
+  constexpr int U = 8;
+  for (int e0 = wave; e0 < pieces; e0 += U * kDecideWaves) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * kDecideWaves < pieces ? e0 + u * kDecideWaves : pieces - 1;
+      const int i = e % per * kWave + lane;
+      v[u] = i < grid ? parts[static_cast<int64_t>(e / per) * grid + i] : 0.0;
     }
-    __builtin_amdgcn_wave_barrier();
-    const double rr = wave_sum(lane < kDecideWaves ? red[wave][lane] : 0.0);
-    if (lane == 0) s_rr[s] = rr;
-    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = wave_sum(v[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * kDecideWaves;
+      if (lane == 0 && e < pieces) red[e / per][e % per] = v[u];
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < count * 16; e += kDecideThreads) {  // (whole rows of 16 lanes)
+    double v = e % 16 < per ? red[e / 16][e % 16] : 0.0;
+    v += dpp_f64<kDppQuadSwap1>(v);
+    v += dpp_f64<kDppQuadSwap2>(v);
+    v += dpp_f64<kDppRowRor4>(v);
+    v += dpp_f64<kDppRowRor8>(v);
+    if (e % 16 == 0) s_rr[e / 16] = v;
   }
   __syncthreads();
   if (tid < count && !(s_rr[tid] > thr)) atomicMin(&s_stop, tid);
@@ -389,6 +434,7 @@ __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
     __syncthreads();
     if (tid == 0) {
       int b = 0, sum = 0;
+      if (want == m) b = kBins;
       while (b < kBins && sum < want) sum += hist[b++];
       s_cut = b;
       s_pos = 0;
@@ -412,11 +458,13 @@ __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
     } else {
       for (int i = tid; i < nbeat; i += kDecideThreads) atomicAdd(&hist[g->beat_step[i]], 1);
       __syncthreads();
-      if (tid == 0) {
-        int b = 0, sum = 0;
-        while (b <= count && sum + hist[b] <= kNewMost) sum += hist[b++];
-        s_cut = sum > 0 ? b : b + 1;  // (more than fit beat one step: some of them)
-        s_pos = 0;
+      if (tid == 0) s_cut = s_pos = 0;
+      __syncthreads();
+      // (more than fit beat the first step: some of them)
+      if (tid <= count) {
+        int sum = 0;
+        for (int b = 0; b <= tid; ++b) sum += hist[b];
+        if (sum <= kNewMost || sum == hist[tid]) atomicMax(&s_cut, tid + 1);
       }
       __syncthreads();
       for (int i = tid; i < nbeat; i += kDecideThreads)
@@ -471,7 +519,7 @@ __global__ __launch_bounds__(kCommitThreads) void k_sgram_commit(
   if (static_cast<int>(blockIdx.x) >= ablocks) {
     const int v = (static_cast<int>(blockIdx.x) - ablocks) * kCommitWaves + wave;
     if (v < grid && take > 0)
-      replay_rows<false>(bits, ws, n, ld, rows_per_wg, v, lane, take, inv_sqrt_n, g, r64, r32,
+      replay_rows_of<false>(bits, ws, n, ld, rows_per_wg, v, lane, take, inv_sqrt_n, g, r64, r32,
                          nullptr, grid, g->t0, tr);
     return;
   }
