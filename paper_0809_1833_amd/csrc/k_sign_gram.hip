@@ -14,9 +14,9 @@
 //           the first step at which they beat its atom; all rows of r replay
 //           it and leave each step's partial ||r||^2;
 //   decide  one workgroup: the steps up to the first stop or the first such
-//           beat stand; x~, the state, the trace; the atoms that beat a step
+//           beat stand; the state, the trace; the atoms that beat a step
 //           become active;
-//   commit  all atoms and all rows of r take the steps that stand; Gram
+//   commit  all atoms (with x~) and all rows of r take the steps that stand; Gram
 //           entries (16-bit integers, exact) of the atoms that became active
 //           against every atom.
 //
@@ -26,6 +26,8 @@
 // round brings.  Bound by the steps' chain of latencies and the launches of
 // a round.  N = 8192, M = 32768, K = 512: 1.3 us a step from 9.6 in one
 // persistent launch that exchanged every step between all CUs.
+#include <type_traits>
+
 #include "k_common.h"
 #include "k_sign_gram.h"
 #include "mp_internal.h"
@@ -41,12 +43,15 @@ constexpr int kDecideWaves = kDecideThreads / kWave;
 constexpr int kCommitAtoms = kWave;     // atoms per workgroup of the commit, one per lane
 constexpr int kCommitThreads = 256;
 constexpr int kCommitWaves = kCommitThreads / kWave;
-constexpr int kNewGroup = 8;            // new atoms a wave counts at once
+constexpr int kNewGroup = 16;           // new atoms a wave counts at once
+constexpr int kNewChunks = 32;          // 16-byte chunks of a column staged at a time
 constexpr int kFirstActive = 256;       // active atoms to begin with, about
 constexpr int kNewMost = 64;            // atoms that become active in a round, at most
 constexpr int kBins = 1024;
-constexpr int kReplay = 16;             // Gram entries in flight per lane of a replay
+constexpr int kReplay = 32;             // Gram entries in flight per lane of a replay
+constexpr int kTurn = kReplay + 1;      // stride of a lane's sums in LDS
 constexpr unsigned short kNoPos = 0xFFFFu;
+static_assert(kSignSteps % kReplay == 0, "a log is whole groups");
 static_assert(kPerThread == 4, "a thread's Gram entries are one 8-byte load");
 
 typedef short v4s __attribute__((ext_vector_type(4)));
@@ -58,6 +63,21 @@ __device__ inline double wave_max_f64(double v) {
   v = __builtin_fmax(v, dpp_f64<kDppRowRor8>(v));
   return __builtin_fmax(__builtin_fmax(lane_f64(v, 0), lane_f64(v, 16)),
                         __builtin_fmax(lane_f64(v, 32), lane_f64(v, 48)));
+}
+
+// wave_sum's value, bit for bit, in lane 63 alone: no scalar registers, so that
+// several sums overlap.  (wave_sum takes lane 0 of each row of 16, where the
+// quads Q meet as (Q0 + Q3) + (Q2 + Q1); a rotation by 12 gives the last lane
+// of the row the same pairs.)
+__device__ inline double wave_sum_lane63(double v) {
+  constexpr int kRowRor12 = 0x12C, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+  v += dpp_f64<kDppQuadSwap1>(v);
+  v += dpp_f64<kDppQuadSwap2>(v);
+  v += dpp_f64<kRowRor12>(v);
+  v += dpp_f64<kDppRowRor8>(v);
+  v += dpp_f64<kRowBcast15>(v);
+  v += dpp_f64<kRowBcast31>(v);
+  return v;
 }
 
 __global__ __launch_bounds__(256) void k_sgram_init(SignCarry* g, unsigned short* pos, int64_t m) {
@@ -120,21 +140,41 @@ __global__ __launch_bounds__(kStepThreads) void k_sgram_steps(
 #pragma unroll
       for (int e = 0; e < kPerThread; ++e)
         for (unsigned long long l = __ballot(mag[e] == top); l != 0; l &= l - 1) {
-          const int o = __builtin_ctzll(l);
-          const int p = kPerThread * (kWave * wave + o) + e;
-          if (pos < 0 || s_atom[p] < s_atom[pos]) {
-            pos = p;
-            val = lane_f64(c[e], o);
-          }
+          const int p = kPerThread * (kWave * wave + __builtin_ctzll(l)) + e;
+          const bool less = pos < 0 || s_atom[p] < s_atom[pos];
+          pos = __builtin_amdgcn_readfirstlane(less ? p : pos);
         }
+      double mine = c[0];
+#pragma unroll
+      for (int e = 1; e < kPerThread; ++e) mine = pos % kPerThread == e ? c[e] : mine;
+      val = lane_f64(mine, pos / kPerThread % kWave);
     }
     if (lane == 0) rec[s & 1][wave] = Rec{top, val, pos};
     __syncthreads();
+    // (selects and a second look at ties: with a tie's branch inside the loop
+    // the compiler kept the other record's c beside the new position)
     Rec w = rec[s & 1][0];
+    int ties = 0;
 #pragma unroll
     for (int k = 1; k < kStepWaves; ++k) {
       const Rec o = rec[s & 1][k];
-      if (o.mag > w.mag || (o.mag == w.mag && o.pos >= 0 && s_atom[o.pos] < s_atom[w.pos])) w = o;
+      const bool more = o.mag > w.mag;
+      ties = more ? 0 : ties + (o.mag == w.mag ? 1 : 0);
+      w.mag = more ? o.mag : w.mag;
+      w.c = more ? o.c : w.c;
+      w.pos = more ? o.pos : w.pos;
+    }
+    if (ties != 0) {  // of equal ones the smallest atom, by its place in LDS
+      int at = -1;
+      for (int k = 0; k < kStepWaves; ++k)
+        if (rec[s & 1][k].mag == w.mag && rec[s & 1][k].pos >= 0) {
+          const int here = s_atom[rec[s & 1][k].pos];
+          const int best = at < 0 ? 0x7FFFFFFF : s_atom[rec[s & 1][at].pos];
+          at = here < best ? k : at;
+        }
+      at = __builtin_amdgcn_readfirstlane(at);
+      w.c = rec[s & 1][at].c;
+      w.pos = rec[s & 1][at].pos;
     }
     const int row = __builtin_amdgcn_readfirstlane(w.pos);
     const v4s e4 =
@@ -164,31 +204,53 @@ __global__ __launch_bounds__(kStepThreads) void k_sgram_steps(
 }
 
 // ---------------------------------------------------------------------------
-// One atom through the first `count` logged steps; returns the first step at
-// which it beats the step's atom (count: none).
+// The log in LDS, filled up to whole replay groups with steps that change and
+// beat nothing, so that a replay has no branches and its reads run ahead
+// (with a test at each step 128 steps took 28 us, most of it LDS latency).
+struct SignLog {
+  double c[kSignSteps], a[kSignSteps];  // c*, c* / N
+  int pos[kSignSteps], atom[kSignSteps];
+};
+__device__ inline void stage_log(SignLog& l, const SignCarry* __restrict__ g, int count,
+                                 double inv_n) {
+  const int all = (count + kReplay - 1) / kReplay * kReplay;
+  for (int i = static_cast<int>(threadIdx.x); i < all; i += static_cast<int>(blockDim.x)) {
+    const bool on = i < count;
+    const double c = on ? g->log_c[i] : 0.0;
+    l.c[i] = on ? c : __builtin_inf();
+    l.a[i] = c * inv_n;
+    l.pos[i] = on ? g->log_pos[i] : 0;
+    l.atom[i] = on ? g->log_atom[i] : -1;
+  }
+  __syncthreads();
+}
+
+// One atom through the first `count` logged steps.  CHECK: returns the first
+// step at which it beats the step's atom (count: none).  Otherwise adds to x~
+// the coefficients of the steps that selected it.
 template <bool CHECK>
-__device__ inline int replay_atom(const short* __restrict__ gcol, int64_t mstride, int64_t a,
-                                  const SignCarry* __restrict__ g, int count, double inv_n,
-                                  double& c) {
+__device__ inline int replay_atom(const short* __restrict__ gcol, int64_t mstride, int a,
+                                  const SignLog& l, int count, double& c, float& x) {
   int beat = count;
   for (int s0 = 0; s0 < count; s0 += kReplay) {
     short e[kReplay];
 #pragma unroll
     for (int u = 0; u < kReplay; ++u) {
-      const int s = s0 + u < count ? s0 + u : count - 1;
-      e[u] = gcol[static_cast<int64_t>(g->log_pos[s]) * mstride + a];
+      const int p = __builtin_amdgcn_readfirstlane(l.pos[s0 + u]);
+      e[u] = gcol[static_cast<int64_t>(p) * mstride + a];
     }
 #pragma unroll
     for (int u = 0; u < kReplay; ++u) {
       const int s = s0 + u;
-      if (s < count) {
-        const double w = g->log_c[s];
-        if (CHECK) {
-          const double x = __builtin_fabs(c), y = __builtin_fabs(w);
-          if (beat == count && (x > y || (x == y && a < g->log_atom[s]))) beat = s;
-        }
-        c = __builtin_fma(-(w * inv_n), static_cast<double>(static_cast<int>(e[u])), c);
+      if constexpr (CHECK) {
+        const double mine = __builtin_fabs(c), best = __builtin_fabs(l.c[s]);
+        const bool won = (mine > best) | ((mine == best) & (a < l.atom[s]));
+        beat = won && s < beat ? s : beat;
+      } else {
+        const float more = x + static_cast<float>(l.c[s]);
+        x = a == l.atom[s] ? more : x;
       }
+      c = __builtin_fma(-l.a[s], static_cast<double>(static_cast<int>(e[u])), c);
     }
   }
   return beat;
@@ -197,15 +259,15 @@ __device__ inline int replay_atom(const short* __restrict__ gcol, int64_t mstrid
 // One wave: the rows of workgroup v of the stepping form through the first
 // `count` logged steps (r_n -/+ c* / sqrt(N), rows with a set bit get +), R
 // per lane.  CHECK: the steps' partial ||r||^2, summed as k_mp_step_sign does;
-// otherwise r is stored, and its trace entries from step t0 on.
-template <bool CHECK, int R>
+// otherwise r is stored, and (TRACE) its trace entries from step t0 on.
+template <bool CHECK, bool TRACE, int R>
 __device__ inline void replay_rows(const uint32_t* __restrict__ bits, int64_t ws, int n,
                                    int64_t row0, int64_t row1, int v, int lane, int count,
-                                   double inv_sqrt_n, const SignCarry* __restrict__ g,
+                                   double inv_sqrt_n, const SignLog& l,
                                    double* __restrict__ r64, float* __restrict__ r32,
                                    double* __restrict__ parts, int grid, long long t0,
-                                   const mp_trace& tr) {
-  constexpr int U = 16 / R;  // steps whose words are in flight
+                                   const mp_trace& tr, double* turn) {
+  constexpr int U = kReplay / R;  // steps whose words are in flight
   double r[R];
   bool in[R];   // rows of this workgroup
   bool up[R];   // and of Psi
@@ -224,8 +286,8 @@ __device__ inline void replay_rows(const uint32_t* __restrict__ bits, int64_t ws
     double sum[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int s = s0 + u < count ? s0 + u : count - 1;
-      const uint32_t* col = bits + static_cast<int64_t>(g->log_atom[s]) * ws;
+      const int atom = __builtin_amdgcn_readfirstlane(l.atom[s0 + u]);
+      const uint32_t* col = bits + static_cast<int64_t>(atom < 0 ? 0 : atom) * ws;
 #pragma unroll
       for (int q = 0; q < R; ++q) w[u][q] = col[word[q]];
     }
@@ -233,26 +295,44 @@ __device__ inline void replay_rows(const uint32_t* __restrict__ bits, int64_t ws
     for (int u = 0; u < U; ++u) {
       const int st = s0 + u;
       const bool on = st < count;
-      const double step = on ? g->log_c[st] * inv_sqrt_n : 0.0;
-      float* rt = !CHECK && on && tr.r && t0 + st < tr.cap ? tr.r + (t0 + st) * tr.ldr : nullptr;
+      const double step = l.c[st] * inv_sqrt_n;
       double s = 0.0;
 #pragma unroll
       for (int q = 0; q < R; ++q) {
-        double x = r[q];
-        if (up[q] && on) x = ((w[u][q] >> bit[q]) & 1u) ? x + step : x - step;
-        r[q] = x;
-        if (!CHECK && rt && up[q]) rt[row0 + lane + kWave * q] = static_cast<float>(x);
-        if (in[q]) s += x * x;
+        const double x = r[q] + (((w[u][q] >> bit[q]) & 1u) ? step : -step);
+        r[q] = up[q] && on ? x : r[q];
+        if constexpr (TRACE)
+          if (up[q] && on && t0 + st < tr.cap)
+            tr.r[(t0 + st) * tr.ldr + row0 + lane + kWave * q] = static_cast<float>(r[q]);
+        const double more = __builtin_fma(r[q], r[q], s);  // (k_mp_step_sign's contraction)
+        s = in[q] ? more : s;
       }
       sum[u] = s;
     }
     if constexpr (CHECK) {
+      // wave_sum's value of each step, the steps side by side: lane u adds
+      // rows 0 and 1 of 16 lanes of step u, lane u + 32 rows 2 and 3, each
+      // row's quads Q as (Q0 + Q3) + (Q2 + Q1)
 #pragma unroll
-      for (int u = 0; u < U; ++u) sum[u] = wave_sum(sum[u]);
+      for (int u = 0; u < U; ++u) turn[lane * kTurn + u] = sum[u];
+      __builtin_amdgcn_wave_barrier();
+      const int u = lane % 32, half = lane / 32;
+      double rows[2];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (lane == 0 && s0 + u < count)
-          parts[static_cast<int64_t>(s0 + u) * grid + v] = sum[u];
+      for (int k = 0; k < 2; ++k) {
+        const double* p = turn + (32 * half + 16 * k) * kTurn + (u < U ? u : 0);
+        double quad[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          quad[e] = (p[4 * e * kTurn] + p[(4 * e + 1) * kTurn]) +
+                    (p[(4 * e + 2) * kTurn] + p[(4 * e + 3) * kTurn]);
+        rows[k] = (quad[0] + quad[3]) + (quad[2] + quad[1]);
+      }
+      const double pair = rows[0] + rows[1];
+      const double all = pair + __shfl_xor(pair, 32, kWave);
+      __builtin_amdgcn_wave_barrier();
+      if (lane < U && s0 + lane < count)
+        parts[static_cast<int64_t>(s0 + lane) * grid + v] = all;
     }
   }
   if constexpr (!CHECK) {
@@ -269,18 +349,23 @@ __device__ inline void replay_rows(const uint32_t* __restrict__ bits, int64_t ws
 template <bool CHECK>
 __device__ inline void replay_rows_of(const uint32_t* __restrict__ bits, int64_t ws, int n,
                                       int64_t ld, int rows_per_wg, int v, int lane, int count,
-                                      double inv_sqrt_n, const SignCarry* __restrict__ g,
+                                      double inv_sqrt_n, const SignLog& l,
                                       double* __restrict__ r64, float* __restrict__ r32,
                                       double* __restrict__ parts, int grid, long long t0,
-                                      const mp_trace& tr) {
+                                      const mp_trace& tr, double* turn) {
   const int64_t row0 = static_cast<int64_t>(v) * rows_per_wg;
   const int64_t row1 = row0 + rows_per_wg < ld ? row0 + rows_per_wg : ld;
-  if (rows_per_wg <= kWave)
-    replay_rows<CHECK, 1>(bits, ws, n, row0, row1, v, lane, count, inv_sqrt_n, g, r64, r32, parts,
-                          grid, t0, tr);
-  else
-    replay_rows<CHECK, kSignRows>(bits, ws, n, row0, row1, v, lane, count, inv_sqrt_n, g, r64,
-                                  r32, parts, grid, t0, tr);
+  auto run = [&](auto trace) {
+    constexpr bool TRACE = decltype(trace)::value;
+    if (rows_per_wg <= kWave)
+      replay_rows<CHECK, TRACE, 1>(bits, ws, n, row0, row1, v, lane, count, inv_sqrt_n, l, r64,
+                                   r32, parts, grid, t0, tr, turn);
+    else
+      replay_rows<CHECK, TRACE, kSignRows>(bits, ws, n, row0, row1, v, lane, count, inv_sqrt_n, l,
+                                           r64, r32, parts, grid, t0, tr, turn);
+  };
+  if (!CHECK && tr.r) run(std::true_type{});
+  else run(std::false_type{});
 }
 
 __global__ __launch_bounds__(kCheckThreads) void k_sgram_check(
@@ -290,20 +375,24 @@ __global__ __launch_bounds__(kCheckThreads) void k_sgram_check(
     double* __restrict__ parts, const DevState* __restrict__ st, SignCarry* g) {
   const int count = g->count, total = count + g->stalled;
   if (st->done || total == 0) return;
+  __shared__ SignLog l;
+  __shared__ double turn[kCheckThreads / kWave][kWave * kTurn];
+  stage_log(l, g, total, inv_n);
   const int lane = static_cast<int>(threadIdx.x) % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   if (static_cast<int>(blockIdx.x) >= ablocks) {
     const int v = (static_cast<int>(blockIdx.x) - ablocks) * (kCheckThreads / kWave) + wave;
     if (v < grid)
-      replay_rows_of<true>(bits, ws, n, ld, rows_per_wg, v, lane, count, inv_sqrt_n, g, r64, nullptr,
-                        parts, grid, 0, mp_trace{});
+      replay_rows_of<true>(bits, ws, n, ld, rows_per_wg, v, lane, count, inv_sqrt_n, l, r64, nullptr,
+                        parts, grid, 0, mp_trace{}, turn[wave]);
     return;
   }
   const int64_t a = static_cast<int64_t>(blockIdx.x) * kCheckThreads + threadIdx.x;
   int beat = total;
   if (a < m) {
     double c = c64[a];
-    beat = replay_atom<true>(gcol, mstride, a, g, total, inv_n, c);
+    float x = 0.0f;
+    beat = replay_atom<true>(gcol, mstride, static_cast<int>(a), l, total, c, x);
   }
   const unsigned long long who = __ballot(beat < total);
   if (who == 0) return;
@@ -325,8 +414,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_sgram_check(
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
     const double* __restrict__ c64, int64_t m, const double* __restrict__ parts, int grid,
-    double thr, long long max_iters, float* __restrict__ x, unsigned short* __restrict__ pos,
-    DevState* __restrict__ st, SignCarry* __restrict__ g, mp_trace tr) {
+    double thr, long long max_iters, unsigned short* __restrict__ pos, DevState* __restrict__ st, SignCarry* __restrict__ g, mp_trace tr) {
   const int tid = static_cast<int>(threadIdx.x);
   const int lane = tid % kWave, wave = tid / kWave;
   if (st->done) {
@@ -353,24 +441,22 @@ __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
   }
   for (int i = tid; i < kBins; i += kDecideThreads) hist[i] = 0;
   // ||r||^2 after each step: the block sum of k_mp_step_sign over the partials
-  // (piece e: 64 partials of a step, as that sum's wave; then 16 lanes a step)
-  const int per = (grid + kWave - 1) / kWave, pieces = count * per;
-  constexpr int U = 8;
-  for (int e0 = wave; e0 < pieces; e0 += U * kDecideWaves) {
+  // (64 partials of a step at a time, as that sum's waves; then 16 lanes a step)
+  const int per = (grid + kWave - 1) / kWave;
+  constexpr int U = kSignSteps / kDecideWaves;
+  for (int k = 0; k < per; ++k) {
+    const int i = k * kWave + lane;
     double v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * kDecideWaves < pieces ? e0 + u * kDecideWaves : pieces - 1;
-      const int i = e % per * kWave + lane;
-      v[u] = i < grid ? parts[static_cast<int64_t>(e / per) * grid + i] : 0.0;
+      const int s = wave + u * kDecideWaves;
+      v[u] = i < grid && s < count ? parts[static_cast<int64_t>(s) * grid + i] : 0.0;
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = wave_sum(v[u]);
+    for (int u = 0; u < U; ++u) v[u] = wave_sum_lane63(v[u]);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * kDecideWaves;
-      if (lane == 0 && e < pieces) red[e / per][e % per] = v[u];
-    }
+    for (int u = 0; u < U; ++u)
+      if (lane == kWave - 1) red[wave + u * kDecideWaves][k] = v[u];
   }
   __syncthreads();
   for (int e = tid; e < count * 16; e += kDecideThreads) {  // (whole rows of 16 lanes)
@@ -393,22 +479,10 @@ __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
   if (take == stop + 1) reason = MP_STOP_CONVERGED;
   else if (t >= max_iters) reason = MP_STOP_MAX_ITERS;
   else if (g->stalled && take == count && first > count) reason = MP_STOP_STALLED;
-  // x~: the first of an atom's steps adds all of them in order
-  if (tid < take) {
-    const int a = s_atom[tid];
-    bool lead = true;
-    for (int k = 0; k < tid; ++k) lead = lead && s_atom[k] != a;
-    if (lead) {
-      float v = x[a];
-      for (int k = tid; k < take; ++k)
-        if (s_atom[k] == a) v += static_cast<float>(s_c[k]);
-      x[a] = v;
-    }
-    if (t0 + tid < tr.cap) {
-      if (tr.idx) tr.idx[t0 + tid] = a;
-      if (tr.coef) tr.coef[t0 + tid] = static_cast<float>(s_c[tid]);
-      if (tr.rr) tr.rr[t0 + tid] = s_rr[tid];
-    }
+  if (tid < take && t0 + tid < tr.cap) {
+    if (tr.idx) tr.idx[t0 + tid] = s_atom[tid];
+    if (tr.coef) tr.coef[t0 + tid] = static_cast<float>(s_c[tid]);
+    if (tr.rr) tr.rr[t0 + tid] = s_rr[tid];
   }
   const bool over = reason != -1;
   bool refill = false;
@@ -511,37 +585,36 @@ __global__ __launch_bounds__(kCommitThreads) void k_sgram_commit(
     double* __restrict__ c64, double* __restrict__ r64, float* __restrict__ r32,
     short* __restrict__ gcol, int64_t mstride, short* __restrict__ h,
     const unsigned short* __restrict__ pos, double inv_n, double inv_sqrt_n, int grid,
-    int rows_per_wg, int ablocks, const SignCarry* __restrict__ g, mp_trace tr) {
-  extern __shared__ v4u own[];  // nch x kCommitAtoms
+    int rows_per_wg, int rblocks, float* __restrict__ x, const SignCarry* __restrict__ g,
+    mp_trace tr) {
+  __shared__ v4u own[kNewChunks * kCommitAtoms];
+  __shared__ SignLog l;
   const int take = g->take, nnew = g->nnew;
+  if (take > 0) stage_log(l, g, take, inv_n);
   const int lane = static_cast<int>(threadIdx.x) % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
-  if (static_cast<int>(blockIdx.x) >= ablocks) {
-    const int v = (static_cast<int>(blockIdx.x) - ablocks) * kCommitWaves + wave;
+  if (static_cast<int>(blockIdx.x) < rblocks) {
+    const int v = static_cast<int>(blockIdx.x) * kCommitWaves + wave;
     if (v < grid && take > 0)
-      replay_rows_of<false>(bits, ws, n, ld, rows_per_wg, v, lane, take, inv_sqrt_n, g, r64, r32,
-                         nullptr, grid, g->t0, tr);
+      replay_rows_of<false>(bits, ws, n, ld, rows_per_wg, v, lane, take, inv_sqrt_n, l, r64, r32,
+                         nullptr, grid, g->t0, tr, nullptr);
     return;
   }
-  const int64_t a0 = static_cast<int64_t>(blockIdx.x) * kCommitAtoms;
+  const int64_t a0 = static_cast<int64_t>(static_cast<int>(blockIdx.x) - rblocks) * kCommitAtoms;
   const int64_t a = a0 + lane;
   if (take > 0 && wave == 0 && a < m) {
     double c = c64[a];
-    (void)replay_atom<false>(gcol, mstride, a, g, take, inv_n, c);
+    float v = x[a];
+    (void)replay_atom<false>(gcol, mstride, static_cast<int>(a), l, take, c, v);
     c64[a] = c;
+    x[a] = v;
   }
   if (nnew == 0) return;
   const int nch = static_cast<int>(ws / 4);
-  for (int i = static_cast<int>(threadIdx.x); i < nch * kCommitAtoms; i += kCommitThreads) {
-    const int at = i / nch, ch = i % nch;
-    const int64_t from = a0 + at < m ? a0 + at : m - 1;
-    own[ch * kCommitAtoms + (at ^ (ch % kCommitAtoms))] =
-        reinterpret_cast<const v4u*>(bits + from * ws)[ch];
-  }
-  __syncthreads();
   const int base = g->nact - nnew;
   const int mine = a < m ? pos[a] : kNoPos;
-  for (int i0 = kNewGroup * wave; i0 < nnew; i0 += kNewGroup * kCommitWaves) {
+  for (int g0 = 0; g0 < nnew; g0 += kNewGroup * kCommitWaves) {
+    const int i0 = g0 + kNewGroup * wave;
     const v4u* col[kNewGroup];
     int acc[kNewGroup];
 #pragma unroll
@@ -551,15 +624,29 @@ __global__ __launch_bounds__(kCommitThreads) void k_sgram_commit(
       col[k] = reinterpret_cast<const v4u*>(bits + static_cast<int64_t>(atom) * ws);
       acc[k] = 0;
     }
-    for (int ch = 0; ch < nch; ++ch) {
-      const v4u o = own[ch * kCommitAtoms + (lane ^ (ch % kCommitAtoms))];
+    for (int c0 = 0; c0 < nch; c0 += kNewChunks) {
+      const int len = nch - c0 < kNewChunks ? nch - c0 : kNewChunks;
+      __syncthreads();
+      for (int i = static_cast<int>(threadIdx.x); i < kNewChunks * kCommitAtoms;
+           i += kCommitThreads) {
+        const int at = i / kNewChunks, ch = i % kNewChunks;
+        const int64_t from = a0 + at < m ? a0 + at : m - 1;
+        if (ch < len)
+          own[ch * kCommitAtoms + (at ^ ch)] =
+              reinterpret_cast<const v4u*>(bits + from * ws)[c0 + ch];
+      }
+      __syncthreads();
+      if (i0 >= nnew) continue;
+      for (int ch = 0; ch < len; ++ch) {
+        const v4u o = own[ch * kCommitAtoms + (lane ^ ch)];
 #pragma unroll
-      for (int k = 0; k < kNewGroup; ++k) {
-        const v4u b = col[k][ch];
-        acc[k] += __builtin_popcount(o.x ^ b.x);
-        acc[k] += __builtin_popcount(o.y ^ b.y);
-        acc[k] += __builtin_popcount(o.z ^ b.z);
-        acc[k] += __builtin_popcount(o.w ^ b.w);
+        for (int k = 0; k < kNewGroup; ++k) {
+          const v4u b = col[k][c0 + ch];
+          acc[k] += __builtin_popcount(o.x ^ b.x);
+          acc[k] += __builtin_popcount(o.y ^ b.y);
+          acc[k] += __builtin_popcount(o.z ^ b.z);
+          acc[k] += __builtin_popcount(o.w ^ b.w);
+        }
       }
     }
 #pragma unroll
@@ -594,13 +681,7 @@ hipError_t launch_sgram_round(const uint32_t* bits, int64_t ws, int64_t n, int64
   const double inv_sqrt_n = 1.0 / sqrt(static_cast<double>(n));
   const int nn = static_cast<int>(n), grid = geom.grid;
   const int rows_per_wg = static_cast<int>((ld + grid - 1) / grid);
-  const size_t lds = static_cast<size_t>(ws) * 4 * kCommitAtoms;
-  if (rows_per_wg > kWave * kSignRows || grid > kDecideThreads || lds > 128 * 1024)
-    return hipErrorInvalidValue;
-  static const hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(k_sgram_commit),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-  if (attr != hipSuccess) return attr;
+  if (rows_per_wg > kWave * kSignRows || grid > kDecideThreads) return hipErrorInvalidValue;
   const int64_t mstride = sign_gram_stride(m);
   hipError_t e;
   k_sgram_steps<<<dim3(1), dim3(kStepThreads), 0, s>>>(c64, b.h, inv_n, max_iters, st, b.carry);
@@ -611,14 +692,14 @@ hipError_t launch_sgram_round(const uint32_t* bits, int64_t ws, int64_t n, int64
       bits, ws, nn, m, ld, c64, r64, b.g, mstride, inv_n, inv_sqrt_n, grid, rows_per_wg, ca,
       b.parts, st, b.carry);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_sgram_decide<<<dim3(1), dim3(kDecideThreads), 0, s>>>(c64, m, b.parts, grid, thr, max_iters, x,
+  k_sgram_decide<<<dim3(1), dim3(kDecideThreads), 0, s>>>(c64, m, b.parts, grid, thr, max_iters,
                                                           b.pos, st, b.carry, tr);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int oa = static_cast<int>((m + kCommitAtoms - 1) / kCommitAtoms);
   const int orows = (grid + kCommitWaves - 1) / kCommitWaves;
-  k_sgram_commit<<<dim3(oa + orows), dim3(kCommitThreads), lds, s>>>(
+  k_sgram_commit<<<dim3(oa + orows), dim3(kCommitThreads), 0, s>>>(
       bits, ws, nn, m, ld, c64, r64, r32, b.g, mstride, b.h, b.pos, inv_n, inv_sqrt_n, grid,
-      rows_per_wg, oa, b.carry, tr);
+      rows_per_wg, orows, x, b.carry, tr);
   return hipGetLastError();
 }
 

@@ -1175,7 +1175,7 @@ static bool ensure_sign_gram(mp_ctx* c) {
 // rounds in flight.  `over`: it reached its stop.
 static mp_status solve_sign_gram(mp_ctx* c, float* x, long long T, double thr, const mp_trace& tr,
                                  hipStream_t s, bool& over) {
-  constexpr int kRounds = 2;
+  constexpr int kRounds = 4;
   const bool timed = c->profiling;
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
   HIP_TRY(c, mp::launch_sgram_init(c->sign_gram, c->m, s));

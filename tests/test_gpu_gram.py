@@ -404,3 +404,75 @@ def test_omp_ties_caps_and_handing_back():
     _omp_same(near, (near[:40] + 0.5 * near[1200:1240]).sum(0), 1e-6, 120)
     rows[300:400] = rows[300]
     _omp_same(rows, rows[300].contiguous(), 1e-6, 20)
+
+
+# ---- one-bit dictionaries (batches of steps on the active atoms) -----------------
+
+def _signs(n, m, k, noise, seed=0):
+    """+-1 columns (M, N) int8, their packed bits and y."""
+    g = torch.Generator(device="cuda").manual_seed(seed * 77 + n * 5 + m)
+    neg = torch.randint(0, 2, (m, n), generator=g, device="cuda", dtype=torch.int8)
+    sup = torch.randperm(m, generator=g, device="cuda")[:k]
+    v = torch.randn(k, generator=g, device="cuda", dtype=torch.float64)
+    y = v @ (1 - 2 * neg[sup].double()) / math.sqrt(n)
+    y = y + noise * y.norm() / math.sqrt(n) * torch.randn(n, generator=g, device="cuda",
+                                                          dtype=torch.float64)
+    return neg, y.float()
+
+
+def _pack_signs(neg):
+    m, n = neg.shape
+    pad = torch.zeros((m, (n + 31) // 32 * 32), dtype=torch.uint8, device="cuda")
+    pad[:, :n] = neg.to(torch.uint8)
+    w = (pad.view(m, -1, 8) << torch.arange(8, device="cuda", dtype=torch.uint8)).sum(
+        2, dtype=torch.uint8)
+    return w.view(torch.int32)
+
+
+def _sign_same(neg, y, eps, cap):
+    from paper_0809_1833_amd.mp import Decoder
+    kw = dict(trace_cap=max(cap, 1), trace_r=True)
+    with Decoder(_pack_signs(neg), storage="sign", n=neg.shape[1]) as dec:
+        a = dec.solve(y, eps, cap, **kw)
+        plain = dec.solve(y, eps, cap)
+        b = dec.solve(y, eps, cap, step_launches=True, **kw)
+        torch.cuda.synchronize()
+    for key in ("iters", "stop", "yy", "rr"):
+        assert a[key] == b[key] == plain[key], (key, a[key], b[key], plain[key])
+    for key in ("x", "r", "idx", "coef", "rr_trace", "r_trace"):
+        assert torch.equal(a[key], b[key]), key
+    assert torch.equal(plain["x"], b["x"]) and torch.equal(plain["r"], b["r"])
+    return a
+
+
+@pytest.mark.parametrize("n,m,k,noise,cap", [
+    (200, 1024, 9, 0.0, 300), (200, 1025, 9, 0.0, 300),   # every atom active | some
+    (512, 4097, 20, 0.01, 127), (512, 4097, 20, 0.01, 129),  # a round's most steps, and around
+    (2048, 8192, 4, 20.0, 1500),                          # more atoms than can be active
+    (9000, 700, 20, 0.0, 200),                            # several rows of r per lane
+    (33, 65, 2, 0.0, 40),
+])
+def test_signs_equal_step_launches(n, m, k, noise, cap):
+    print(f"[gram signs {n}x{m}]", flush=True)
+    neg, y = _signs(n, m, k, noise)
+    a = _sign_same(neg, y, 0.0 if noise > 1 else 1e-6, cap)
+    assert a["iters"] >= min(cap, k)
+    if noise > 1:
+        assert torch.unique(a["idx"]).numel() > 1024
+
+
+def test_signs_ties_and_stall():
+    """Equal and opposite columns tie exactly and the smallest index wins; no
+    column correlates with y, at once and after one step."""
+    neg, y = _signs(96, 3000, 5, 0.0, seed=3)
+    neg[1500:2250] = neg[:750]
+    neg[2250:] = 1 - neg[750:1500]
+    a = _sign_same(neg, y, 1e-6, 100)
+    assert int(a["idx"].max()) < 1500
+    h = torch.zeros((1, 1), dtype=torch.int8, device="cuda")
+    for _ in range(6):
+        h = torch.cat([torch.cat([h, h], 1), torch.cat([h, 1 - h], 1)], 0)
+    for extra in (0.0, 2.0):
+        y = (1 - 2 * h[50].float()) + extra * (1 - 2 * h[7].float())
+        a = _sign_same(h[:40].contiguous(), y, 1e-6, 10)
+        assert a["stop"] == "stalled" and a["iters"] == (1 if extra else 0)
