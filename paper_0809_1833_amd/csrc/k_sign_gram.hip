@@ -88,14 +88,14 @@ __global__ __launch_bounds__(256) void k_sgram_init(SignCarry* g, unsigned short
     g->nact = g->nnew = g->count = g->stalled = g->take = g->nbeat = 0;
     g->first = kSignSteps;
     g->fill = 1;
-    g->steps = m <= kSignActive ? kSignSteps : 32;
+    g->steps = 32;
   }
 }
 
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kStepThreads) void k_sgram_steps(
     const double* __restrict__ c64, const short* __restrict__ h, double inv_n,
-    long long max_iters, const DevState* __restrict__ st, SignCarry* __restrict__ g) {
+    long long max_iters, double thr, const DevState* __restrict__ st, SignCarry* __restrict__ g) {
   if (st->done) return;
   struct Rec {
     double mag, c;
@@ -125,7 +125,10 @@ __global__ __launch_bounds__(kStepThreads) void k_sgram_steps(
   __syncthreads();
   int s = 0;
   bool stalled = false;
-  for (; s < steps; ++s) {
+  // ||r||^2 falls by c*^2 a step: where that reaches the threshold further
+  // steps would be for nothing (whether the run stops there is decided from r)
+  double rr = st->rr;
+  for (; s < steps && rr > thr; ++s) {
     // the wave's largest |c|; of equal ones the smallest atom
     double mag[kPerThread], best = -1.0;
 #pragma unroll
@@ -188,6 +191,7 @@ __global__ __launch_bounds__(kStepThreads) void k_sgram_steps(
       break;
     }
     const double a = w.c * inv_n;
+    rr -= w.c * w.c;
 #pragma unroll
     for (int e = 0; e < kPerThread; ++e)
       c[e] = __builtin_fma(-a, static_cast<double>(static_cast<int>(e4[e])), c[e]);
@@ -595,14 +599,14 @@ __global__ __launch_bounds__(kCommitThreads) void k_sgram_commit(
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   if (static_cast<int>(blockIdx.x) < rblocks) {
     const int v = static_cast<int>(blockIdx.x) * kCommitWaves + wave;
-    if (v < grid && take > 0)
+    if (v < grid && take > 0 && blockIdx.y == 0)
       replay_rows_of<false>(bits, ws, n, ld, rows_per_wg, v, lane, take, inv_sqrt_n, l, r64, r32,
                          nullptr, grid, g->t0, tr, nullptr);
     return;
   }
   const int64_t a0 = static_cast<int64_t>(static_cast<int>(blockIdx.x) - rblocks) * kCommitAtoms;
   const int64_t a = a0 + lane;
-  if (take > 0 && wave == 0 && a < m) {
+  if (take > 0 && wave == 0 && a < m && blockIdx.y == 0) {
     double c = c64[a];
     float v = x[a];
     (void)replay_atom<false>(gcol, mstride, static_cast<int>(a), l, take, c, v);
@@ -613,7 +617,9 @@ __global__ __launch_bounds__(kCommitThreads) void k_sgram_commit(
   const int nch = static_cast<int>(ws / 4);
   const int base = g->nact - nnew;
   const int mine = a < m ? pos[a] : kNoPos;
-  for (int g0 = 0; g0 < nnew; g0 += kNewGroup * kCommitWaves) {
+  constexpr int kAtOnce = kNewGroup * kCommitWaves;
+  for (int g0 = kAtOnce * static_cast<int>(blockIdx.y); g0 < nnew;
+       g0 += kAtOnce * static_cast<int>(gridDim.y)) {
     const int i0 = g0 + kNewGroup * wave;
     const v4u* col[kNewGroup];
     int acc[kNewGroup];
@@ -675,8 +681,8 @@ hipError_t launch_sgram_init(const SignGram& b, int64_t m, hipStream_t s) {
 
 hipError_t launch_sgram_round(const uint32_t* bits, int64_t ws, int64_t n, int64_t m, int64_t ld,
                               double* c64, double* r64, float* r32, const CorrGeom& geom,
-                              const SignGram& b, long long max_iters, double thr, float* x,
-                              DevState* st, mp_trace tr, hipStream_t s) {
+                              const SignGram& b, bool first, long long max_iters, double thr,
+                              float* x, DevState* st, mp_trace tr, hipStream_t s) {
   const double inv_n = 1.0 / static_cast<double>(n);
   const double inv_sqrt_n = 1.0 / sqrt(static_cast<double>(n));
   const int nn = static_cast<int>(n), grid = geom.grid;
@@ -684,20 +690,27 @@ hipError_t launch_sgram_round(const uint32_t* bits, int64_t ws, int64_t n, int64
   if (rows_per_wg > kWave * kSignRows || grid > kDecideThreads) return hipErrorInvalidValue;
   const int64_t mstride = sign_gram_stride(m);
   hipError_t e;
-  k_sgram_steps<<<dim3(1), dim3(kStepThreads), 0, s>>>(c64, b.h, inv_n, max_iters, st, b.carry);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (!first) {
+    k_sgram_steps<<<dim3(1), dim3(kStepThreads), 0, s>>>(c64, b.h, inv_n, max_iters, thr, st,
+                                                          b.carry);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   const int ca = static_cast<int>((m + kCheckThreads - 1) / kCheckThreads);
   const int cr = (grid + kCheckThreads / kWave - 1) / (kCheckThreads / kWave);
-  k_sgram_check<<<dim3(ca + cr), dim3(kCheckThreads), 0, s>>>(
-      bits, ws, nn, m, ld, c64, r64, b.g, mstride, inv_n, inv_sqrt_n, grid, rows_per_wg, ca,
-      b.parts, st, b.carry);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (!first) {
+    k_sgram_check<<<dim3(ca + cr), dim3(kCheckThreads), 0, s>>>(
+        bits, ws, nn, m, ld, c64, r64, b.g, mstride, inv_n, inv_sqrt_n, grid, rows_per_wg, ca,
+        b.parts, st, b.carry);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   k_sgram_decide<<<dim3(1), dim3(kDecideThreads), 0, s>>>(c64, m, b.parts, grid, thr, max_iters,
                                                           b.pos, st, b.carry, tr);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int oa = static_cast<int>((m + kCommitAtoms - 1) / kCommitAtoms);
   const int orows = (grid + kCommitWaves - 1) / kCommitWaves;
-  k_sgram_commit<<<dim3(oa + orows), dim3(kCommitThreads), 0, s>>>(
+  // (only the first active atoms are more than one group of workgroups takes)
+  const unsigned slices = first ? kSignActive / (kNewGroup * kCommitWaves) / 2 : 1;
+  k_sgram_commit<<<dim3(oa + orows, slices), dim3(kCommitThreads), 0, s>>>(
       bits, ws, nn, m, ld, c64, r64, r32, b.g, mstride, b.h, b.pos, inv_n, inv_sqrt_n, grid,
       rows_per_wg, orows, x, b.carry, tr);
   return hipGetLastError();

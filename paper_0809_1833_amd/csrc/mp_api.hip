@@ -1171,8 +1171,10 @@ static bool ensure_sign_gram(mp_ctx* c) {
   return true;
 }
 
-// The one-bit decode in batches of steps (k_sign_gram.hip), two chunks of
-// rounds in flight.  `over`: it reached its stop.
+// The one-bit decode in batches of steps (k_sign_gram.hip), in chunks of
+// rounds: one round at first, which is all that a short decode needs, then up
+// to kRounds with two chunks in flight (a readback leaves the device idle for
+// 10 us, a round after the stop costs 18).  `over`: it reached its stop.
 static mp_status solve_sign_gram(mp_ctx* c, float* x, long long T, double thr, const mp_trace& tr,
                                  hipStream_t s, bool& over) {
   constexpr int kRounds = 4;
@@ -1183,12 +1185,16 @@ static mp_status solve_sign_gram(mp_ctx* c, float* x, long long T, double thr, c
   const long long most = 4 * T + 64;
   long long issued = 0, seen = 0;
   over = false;
+  auto round = [&](bool first) {
+    return mp::launch_sgram_round(c->psis, c->sign_ws, c->n, c->m, c->ld, c->sign_c64, c->sign_r64,
+                                  c->r_work, c->geom, c->sign_gram, first, T, thr, x, c->st, tr,
+                                  s);
+  };
+  HIP_TRY(c, round(true));
   while (!over && seen < most) {
-    while (issued < most && issued - seen < 2) {
-      for (int k = 0; k < kRounds; ++k)
-        HIP_TRY(c, mp::launch_sgram_round(c->psis, c->sign_ws, c->n, c->m, c->ld, c->sign_c64,
-                                          c->sign_r64, c->r_work, c->geom, c->sign_gram, T, thr, x,
-                                          c->st, tr, s));
+    while (issued < most && issued - seen < (seen < 2 ? 1 : 2)) {
+      const int rounds = static_cast<int>(std::min<long long>(issued + 1, kRounds));
+      for (int k = 0; k < rounds; ++k) HIP_TRY(c, round(false));
       const int k = static_cast<int>(issued & 1);
       HIP_TRY(c, hipMemcpyAsync(&c->h_st[1 + k], c->st, sizeof(mp::DevState),
                                 hipMemcpyDeviceToHost, s));
@@ -1252,9 +1258,11 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
     const long long T = opts->max_iters;
     const double thr = c->h_st->thr;
     // batches of steps, unless the caller asks for one launch per step or
-    // limits the waits of the persistent launch, which only that has
+    // limits the waits of the persistent launch, which only that has.  A cap
+    // of a few steps takes the persistent launch where it fits: it costs 75 us
+    // and 7 a step at N = 48 .. 64, the batches 135 and 1.
     if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done &&
-        !getenv("MP_SIGN_SPIN_LIMIT") && ensure_sign_gram(c)) {
+        (T > 64 || !c->sign_persist) && !getenv("MP_SIGN_SPIN_LIMIT") && ensure_sign_gram(c)) {
       const mp_status gs = solve_sign_gram(c, x, T, thr, tr, s, persistent);
       if (gs != MP_OK) return gs;
       if (!persistent) {  // (not reached: every round makes progress)
