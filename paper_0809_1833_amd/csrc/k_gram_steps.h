@@ -300,7 +300,6 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
     } else {
       // wave W + h: half h of the column into LDS for the update, and its
       // lane chain of the product
-      if (tid == NT) x_old = p.x[win];
       const int off = wave == W ? 0 : (ONE ? ldu : h0);
       const int len = ONE ? ldu - off : h0;
       T acc = 0;
@@ -321,6 +320,9 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
           }
         }
       }
+      // x~_idx for the update's end; requested before the column's loop it is
+      // waited for ahead of that loop, a round trip a step
+      x_old = p.x[win];
       s_chain[wave - W][lane] = acc;
     }
     __syncthreads();

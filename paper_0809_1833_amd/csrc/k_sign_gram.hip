@@ -46,7 +46,7 @@ constexpr int kCommitWaves = kCommitThreads / kWave;
 constexpr int kNewGroup = 16;           // new atoms a wave counts at once
 constexpr int kNewChunks = 32;          // 16-byte chunks of a column staged at a time
 constexpr int kFirstActive = 256;       // active atoms to begin with, about
-constexpr int kNewMost = 64;            // atoms that become active in a round, at most
+constexpr int kNewMost = 128;           // atoms that become active in a round, at most
 constexpr int kBins = 1024;
 constexpr int kReplay = 32;             // Gram entries in flight per lane of a replay
 constexpr int kTurn = kReplay + 1;      // stride of a lane's sums in LDS
