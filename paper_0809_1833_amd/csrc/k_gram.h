@@ -163,9 +163,10 @@ hipError_t launch_gram_binit(const float* Y, int64_t ldy, int64_t n, int64_t ld,
 // Round `round`: the correlations of the signals still running, then their
 // steps.  again: two words; word round mod 2 is set if some signal goes on
 // (both launches return at once where the previous round's word is clear).
+// single: one signal's decode, whose ||r||^2 is summed in mp_solve's order.
 hipError_t launch_gram_bround(const GramBatch& b, const GramShape& sh, const GramBounds& bd,
-                              int nb, int num_cus, long long round, int* again, mp_trace tr,
-                              hipStream_t s);
+                              int nb, int num_cus, long long round, int* again, bool single,
+                              mp_trace tr, hipStream_t s);
 
 // ---- many independent problems (k_gram.hip) ---------------------------------
 struct GramGroup {     // one workgroup of the pass: tiles of problem id

@@ -239,7 +239,9 @@ hipError_t launch_gram_full(const float* psi, int64_t ld, int64_t m, float* g, i
 }
 
 // ---------------------------------------------------------------------------
-template <int NT, int CPT>
+// VN: threads of the workgroup whose order ||r||^2 is summed in: the batched
+// form's 512, or one signal's 1024.
+template <int NT, int CPT, int VN>
 __global__ __launch_bounds__(NT + 2 * kWave) void k_gram_bsteps(GramBatch b, GramBounds bd,
                                                                 mp_trace tr, int* again) {
   extern __shared__ v4f lds[];
@@ -256,27 +258,27 @@ __global__ __launch_bounds__(NT + 2 * kWave) void k_gram_bsteps(GramBatch b, Gra
   if (t.rr) t.rr += j * tr.cap;
   if (t.r) t.r += j * tr.cap * tr.ldr;
   const long long cap = st->max_iters;
-  if (threadIdx.x < NT) gram_steps<float, NT, CPT, true, true, 512, false>(p, bd, cap, 0, t, lds, sh);
-  else gram_steps<float, NT, CPT, false, true, 512, false>(p, bd, cap, 0, t, lds, sh);
+  if (threadIdx.x < NT) gram_steps<float, NT, CPT, true, true, VN, false>(p, bd, cap, 0, t, lds, sh);
+  else gram_steps<float, NT, CPT, false, true, VN, false>(p, bd, cap, 0, t, lds, sh);
   if (threadIdx.x == 0 && !st->done)
     (void)__hip_atomic_fetch_or(again, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int NT, int CPT>
+template <int NT, int CPT, int VN>
 static hipError_t launch_bsteps_t(const GramBatch& b, const GramBounds& bd, int nb, mp_trace tr,
                                   int* again, hipStream_t s) {
   static const hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(k_gram_bsteps<NT, CPT>),
+      hipFuncSetAttribute(reinterpret_cast<const void*>(k_gram_bsteps<NT, CPT, VN>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 16384 * 4);
   if (attr != hipSuccess) return attr;
-  k_gram_bsteps<NT, CPT><<<dim3(nb), dim3(NT + 2 * kWave), static_cast<size_t>(b.ld) * 8, s>>>(
+  k_gram_bsteps<NT, CPT, VN><<<dim3(nb), dim3(NT + 2 * kWave), static_cast<size_t>(b.ld) * 8, s>>>(
       b, bd, tr, again);
   return hipGetLastError();
 }
 
 hipError_t launch_gram_bround(const GramBatch& b, const GramShape& sh, const GramBounds& bd,
-                              int nb, int num_cus, long long round, int* again, mp_trace tr,
-                              hipStream_t s) {
+                              int nb, int num_cus, long long round, int* again, bool single,
+                              mp_trace tr, hipStream_t s) {
   if (b.ld > 16384) return hipErrorInvalidValue;
   // again[par]: some signal of this round's steps goes on
   const int par = static_cast<int>(round & 1);
@@ -293,13 +295,16 @@ hipError_t launch_gram_bround(const GramBatch& b, const GramShape& sh, const Gra
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (sh.threads == 256 && sh.per_thread == 4)
-    return launch_bsteps_t<256, 4>(b, bd, nb, tr, again + par, s);
+    return single ? launch_bsteps_t<256, 4, 1024>(b, bd, nb, tr, again + par, s)
+                  : launch_bsteps_t<256, 4, 512>(b, bd, nb, tr, again + par, s);
   if (sh.threads == 256 && sh.per_thread == 16)
-    return launch_bsteps_t<256, 16>(b, bd, nb, tr, again + par, s);
+    return single ? launch_bsteps_t<256, 16, 1024>(b, bd, nb, tr, again + par, s)
+                  : launch_bsteps_t<256, 16, 512>(b, bd, nb, tr, again + par, s);
   if (sh.threads == 512 && sh.per_thread == 16)
-    return launch_bsteps_t<512, 16>(b, bd, nb, tr, again + par, s);
-  if (sh.threads == 512 && sh.per_thread == 32)
-    return launch_bsteps_t<512, 32>(b, bd, nb, tr, again + par, s);
+    return single ? launch_bsteps_t<512, 16, 1024>(b, bd, nb, tr, again + par, s)
+                  : launch_bsteps_t<512, 16, 512>(b, bd, nb, tr, again + par, s);
+  if (sh.threads == 512 && sh.per_thread == 32 && !single)
+    return launch_bsteps_t<512, 32, 512>(b, bd, nb, tr, again + par, s);
   return hipErrorInvalidValue;
 }
 

@@ -547,6 +547,109 @@ mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* op
   return MP_OK;
 }
 
+// Whether a batched decode of at most tmax steps takes the carried
+// correlations, and the Gram columns and buffers for B signals if so.
+//
+// The Gram columns of all atoms cost m^2 n multiply-adds, once per context,
+// and m^2 floats; a step costs about 4 us on carried correlations and a round
+// of products and selections about 15.  They are made where a decode to the
+// cap would pay for them at once (at the 45 TFLOP/s the symmetric product
+// reaches, its 2 m^2 n / 2 operations against 11 us a step: N = 2048, M = 8192
+// from a cap of 280 steps on) and they fit 1 GiB (M <= 16384).
+bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
+  const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
+  if (sh.threads == 0 || c->m > 16384 || !(c->max_norm > 0.99) || !(c->max_norm < 1.01))
+    return false;
+  if (!c->gram_full) {
+    const double cost_us = static_cast<double>(c->m) * static_cast<double>(c->m) *
+                           static_cast<double>(c->ld) / 45e6;
+    if (cost_us > 11.0 * static_cast<double>(tmax) || c->gram_full_tried) return false;
+    c->gram_full_tried = true;
+    const int64_t stride = mp::gram_stride(sh);
+    const size_t bytes = sizeof(float) * static_cast<size_t>(stride) * static_cast<size_t>(c->m);
+    if (hipMalloc(&c->gram_full, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      c->gram_full = nullptr;
+      return false;
+    }
+    c->gram_full_mp = stride;
+    if ((stride != c->m && hipMemsetAsync(c->gram_full, 0, bytes, s) != hipSuccess) ||
+        mp::launch_gram_full(c->psi32, c->ld, c->m, c->gram_full, stride, c->num_cus, s) !=
+            hipSuccess) {
+      (void)hipFree(c->gram_full);
+      c->gram_full = nullptr;
+      return false;
+    }
+  }
+  if (B <= c->gram_bcap) return true;
+  free_gram_batch(c);
+  const size_t b = static_cast<size_t>(B);
+  const size_t cbytes = sizeof(float) * static_cast<size_t>(c->gram_full_mp) * b;
+  if (hipMalloc(&c->gram_bc, cbytes) != hipSuccess ||
+      hipMalloc(&c->gram_br, sizeof(float) * static_cast<size_t>(c->ld) * b) != hipSuccess ||
+      hipMalloc(&c->gram_bst, sizeof(mp::DevState) * b) != hipSuccess ||
+      hipMalloc(&c->gram_again, 2 * sizeof(int)) != hipSuccess ||
+      hipMalloc(&c->gram_btcap, sizeof(long long) * b) != hipSuccess ||
+      hipHostMalloc(&c->gram_hbst, sizeof(mp::DevState) * b, hipHostMallocDefault) !=
+          hipSuccess ||
+      hipHostMalloc(&c->gram_hagain, 4 * sizeof(int), hipHostMallocDefault) != hipSuccess ||
+      hipMemsetAsync(c->gram_bc, 0, cbytes, s) != hipSuccess) {
+    (void)hipGetLastError();
+    free_gram_batch(c);
+    return false;
+  }
+  c->gram_bcap = B;
+  return true;
+}
+
+// One signal of a small dictionary on every atom's Gram column (as the batched
+// decode holds them, made by the first decode): no passes, so a decode is the
+// products Psi^T y, then the steps in one workgroup, and again each time the
+// carried correlations have lost too many digits.  `used` false: not taken, or
+// handed back (the state then needs its init again).
+//
+// The one launch that holds the dictionary in LDS (k_f32_small) costs 25 us
+// and 5 a step (its exchange between workgroups), this 60 and 2.4, so caps
+// below kFullCap steps stay there; the Gram columns are made where they cost
+// at most 0.1 us a step of the cap (6 us at N = 256, M = 1024).
+constexpr long long kFullCap = 64;
+mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, const mp_opts* opts,
+                           const mp_trace& tr, hipStream_t s, bool& used) {
+  used = false;
+  const double cost_us = static_cast<double>(c->m) * static_cast<double>(c->m) *
+                         static_cast<double>(c->ld) / 45e6;
+  const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
+  if (opts->max_iters < kFullCap || sh.threads * sh.per_thread > 8192 ||
+      (!c->gram_full && cost_us > 0.1 * static_cast<double>(opts->max_iters)) ||
+      !ensure_gram_batch(c, 1, opts->max_iters, s))
+    return MP_OK;
+  const mp::GramBounds bounds = mp::gram_bounds_full(c->n, c->max_norm);
+  const mp::GramBatch b{c->psi32, c->ld, c->n, c->m, c->gram_full_mp, c->gram_full, c->gram_bc,
+                        r_work, x, c->m, c->st};
+  const bool timed = c->profiling;
+  if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
+  // every round takes a step (or gives up); two are all that most decodes need
+  const long long most = static_cast<long long>(opts->max_iters) + 1;
+  long long issued = 0;
+  do {
+    for (int k = 0; k < 2 && issued < most; ++k, ++issued)
+      HIP_TRY(c, mp::launch_gram_bround(b, sh, bounds, 1, c->num_cus, issued, c->gram_again, true,
+                                        tr, s));
+    if (timed) HIP_TRY(c, hipEventRecord(c->ev[1], s));
+    HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
+    HIP_TRY(c, hipStreamSynchronize(s));
+  } while (!c->h_st->done && issued < most);
+  if (timed) {
+    float ms = 0.f;
+    if (hipEventElapsedTime(&ms, c->ev[0], c->ev[1]) == hipSuccess) {
+      c->prof_ms = ms;
+      c->prof_launches = c->h_st->t > 0 ? c->h_st->t : 1;
+    }
+  }
+  used = c->h_st->done && !c->h_st->pad[0];
+  return MP_OK;
+}
+
 mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_opts* opts,
                         mp_result* res, const mp_trace& tr, hipStream_t s, const CarriedBufs& b,
                         bool allow_one_launch, bool allow_gram) {
@@ -555,6 +658,25 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
                              static_cast<long long>(opts->max_iters), s));
   if (allow_one_launch && c->storage == MP_F32 && c->small.grid > 0 &&
       !(opts->flags & MP_SOLVE_STEP_LAUNCHES)) {
+    // (MP_SMALL_SPIN_LIMIT limits the waits of the one launch, which only it has)
+    if (allow_gram && !async && opts->max_iters > 0 && !getenv("MP_SMALL_SPIN_LIMIT")) {
+      bool used = false;
+      const mp_status fs = solve_small_full(c, b.r_work, x, opts, tr, s, used);
+      if (fs != MP_OK) return fs;
+      if (used) {
+        if (r) {
+          HIP_TRY(c, mp::launch_copy_selected(b.r_work, c->ld, c->n, b.st, r, s));
+          HIP_TRY(c, hipStreamSynchronize(s));
+        }
+        const mp_status rs = finish_result(c, res);
+        if (rs == MP_OK && res) res->persistent = 1;
+        return rs;
+      }
+      c->prof_ms = 0.0;
+      c->prof_launches = 0;
+      HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
+                                 static_cast<long long>(opts->max_iters), s));
+    }
     // the whole decode in one launch, every share of the dictionary in LDS:
     // a new tag epoch for every decode (never 0 mod the epoch range: the
     // zeroed words match no step); when it wraps, clear the words so that
@@ -661,61 +783,6 @@ mp_status finish_result(mp_ctx* c, mp_result* res) {
   return MP_OK;
 }
 
-// Whether a batched decode of at most tmax steps takes the carried
-// correlations, and the Gram columns and buffers for B signals if so.
-//
-// The Gram columns of all atoms cost m^2 n multiply-adds, once per context,
-// and m^2 floats; a step costs about 4 us on carried correlations and a round
-// of products and selections about 15.  They are made where a decode to the
-// cap would pay for them at once (at the 45 TFLOP/s the symmetric product
-// reaches, its 2 m^2 n / 2 operations against 11 us a step: N = 2048, M = 8192
-// from a cap of 280 steps on) and they fit 1 GiB (M <= 16384).
-bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
-  const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
-  if (sh.threads == 0 || c->m > 16384 || !(c->max_norm > 0.99) || !(c->max_norm < 1.01))
-    return false;
-  if (!c->gram_full) {
-    const double cost_us = static_cast<double>(c->m) * static_cast<double>(c->m) *
-                           static_cast<double>(c->ld) / 45e6;
-    if (cost_us > 11.0 * static_cast<double>(tmax) || c->gram_full_tried) return false;
-    c->gram_full_tried = true;
-    const int64_t stride = mp::gram_stride(sh);
-    const size_t bytes = sizeof(float) * static_cast<size_t>(stride) * static_cast<size_t>(c->m);
-    if (hipMalloc(&c->gram_full, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      c->gram_full = nullptr;
-      return false;
-    }
-    c->gram_full_mp = stride;
-    if ((stride != c->m && hipMemsetAsync(c->gram_full, 0, bytes, s) != hipSuccess) ||
-        mp::launch_gram_full(c->psi32, c->ld, c->m, c->gram_full, stride, c->num_cus, s) !=
-            hipSuccess) {
-      (void)hipFree(c->gram_full);
-      c->gram_full = nullptr;
-      return false;
-    }
-  }
-  if (B <= c->gram_bcap) return true;
-  free_gram_batch(c);
-  const size_t b = static_cast<size_t>(B);
-  const size_t cbytes = sizeof(float) * static_cast<size_t>(c->gram_full_mp) * b;
-  if (hipMalloc(&c->gram_bc, cbytes) != hipSuccess ||
-      hipMalloc(&c->gram_br, sizeof(float) * static_cast<size_t>(c->ld) * b) != hipSuccess ||
-      hipMalloc(&c->gram_bst, sizeof(mp::DevState) * b) != hipSuccess ||
-      hipMalloc(&c->gram_again, 2 * sizeof(int)) != hipSuccess ||
-      hipMalloc(&c->gram_btcap, sizeof(long long) * b) != hipSuccess ||
-      hipHostMalloc(&c->gram_hbst, sizeof(mp::DevState) * b, hipHostMallocDefault) !=
-          hipSuccess ||
-      hipHostMalloc(&c->gram_hagain, 4 * sizeof(int), hipHostMallocDefault) != hipSuccess ||
-      hipMemsetAsync(c->gram_bc, 0, cbytes, s) != hipSuccess) {
-    (void)hipGetLastError();
-    free_gram_batch(c);
-    return false;
-  }
-  c->gram_bcap = B;
-  return true;
-}
-
 // The batched decode on carried correlations.  `gave_up`: some signal needs
 // the rounds of products instead (the whole batch is then decoded again).
 mp_status solve_gram_batch(mp_ctx* c, const float* Y, int64_t ldy, int64_t B, float* X,
@@ -741,7 +808,7 @@ mp_status solve_gram_batch(mp_ctx* c, const float* Y, int64_t ldy, int64_t B, fl
   while (!over) {
     while (issued - seen < 2) {
       HIP_TRY(c, mp::launch_gram_bround(b, sh, bounds, static_cast<int>(B), c->num_cus, issued,
-                                        c->gram_again, tr, s));
+                                        c->gram_again, false, tr, s));
       const int k = static_cast<int>(issued & 1);
       HIP_TRY(c, hipMemcpyAsync(c->gram_hagain + 2 * k, c->gram_again, 2 * sizeof(int),
                                 hipMemcpyDeviceToHost, s));

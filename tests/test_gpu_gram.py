@@ -476,3 +476,28 @@ def test_signs_ties_and_stall():
         y = (1 - 2 * h[50].float()) + extra * (1 - 2 * h[7].float())
         a = _sign_same(h[:40].contiguous(), y, 1e-6, 10)
         assert a["stop"] == "stalled" and a["iters"] == (1 if extra else 0)
+
+
+# ---- small dictionaries (every atom's Gram column) --------------------------------
+
+@pytest.mark.parametrize("n,m,cap", [
+    (256, 1024, 63), (256, 1024, 64),     # the cap below which the one launch stays
+    (256, 1025, 900), (64, 65, 400), (2048, 513, 900), (33, 17, 64), (700, 900, 2000),
+])
+def test_small_equals_step_launches(n, m, cap):
+    print(f"[gram small {n}x{m}]", flush=True)
+    rows, y = _draw(n, m, max(2, min(n, m) // 20))
+    a = _same(rows, y, 1e-6, cap)
+    assert a["persistent"] and a["iters"] > 3
+
+
+def test_small_ties_and_handing_back():
+    """Exact ties take the smallest index; more ties than a step can score go
+    back to the launch that holds the dictionary."""
+    rows, y = _draw(200, 900, 8, seed=9)
+    rows[450:] = -rows[:450]
+    a = _same(rows, y, 1e-5, 200)
+    assert int(a["idx"].max()) < 450 and a["persistent"]
+    rows[300:400] = rows[300]
+    a = _same(rows, rows[300].contiguous(), 1e-6, 100)
+    assert a["persistent"]
