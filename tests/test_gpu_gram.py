@@ -482,7 +482,7 @@ def test_signs_ties_and_stall():
 
 @pytest.mark.parametrize("n,m,cap", [
     (256, 1024, 63), (256, 1024, 64),     # the cap below which the one launch stays
-    (256, 1025, 900), (64, 65, 400), (2048, 513, 900), (33, 17, 64), (700, 900, 2000),
+    (256, 1025, 900), (64, 65, 400), (2048, 512, 900), (33, 17, 64), (700, 900, 2000),
 ])
 def test_small_equals_step_launches(n, m, cap):
     print(f"[gram small {n}x{m}]", flush=True)
