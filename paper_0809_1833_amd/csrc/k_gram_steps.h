@@ -119,6 +119,12 @@ __device__ inline T dot_column_narrow(const V* __restrict__ p, const V* __restri
   return wave_sum(acc_a + acc_b);
 }
 
+// sqrt(rr) from above, for the bounds: two instructions (v_rsq_f64 is good to
+// 2^-26) where the FP64 square root is a chain of 25.
+__device__ inline float norm_above(double rr) {
+  return 1.000001f * static_cast<float>(rr * __builtin_amdgcn_rsq(rr));
+}
+
 // max(m, |v|) over the four elements.
 __device__ inline float max_abs4(float m, const v4f& v) {
   return __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(m, __builtin_fabsf(v.x)),
@@ -217,7 +223,7 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
   if (data && lane == 0) s_wmax[wave] = wm;
   __syncthreads();
 
-  float rn = static_cast<float>(__builtin_sqrt(rr));
+  float rn = norm_above(rr);
   float err = bd.pass * rn;
   bool fresh = true;       // c~ straight from a pass
   int stop = -1;           // MP_STOP_* once the run is over
@@ -380,7 +386,7 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
       }
     }
     ++t;
-    rn = static_cast<float>(__builtin_sqrt(rr));
+    rn = norm_above(rr);
     err += __builtin_fabsf(static_cast<float>(c)) * bd.col + bd.step * rn;
     fresh = false;
     if (!(rr > thr)) {
