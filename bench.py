@@ -154,6 +154,14 @@ def time_decodes(dec, y, p, steps, warmup, profile_every, x, r, stream=None, omp
     return iters, dt, kt_ms / max(kt_n, 1), kt_n, stops
 
 
+def step_of_decode(avg_ms, kt_n, kernel):
+    """A decode that reads the dictionary for some of its steps only: its time
+    on the device over the steps it took, bound by the latency of a step (and
+    the passes' bytes), so it has no share of the HBM rate to report."""
+    return {"bound": "latency", "kernel": kernel, "avg_step_us": round(avg_ms * 1e3, 3),
+            "steps": kt_n}
+
+
 def bench_f64(seed: int, steps: int = 2, warmup: int = 1, profile_every: int = 16):
     """FP64 decode of the same N=8192, M=32768 workload (2 GiB FP64
     dictionary): iters/s and the step kernel's algorithmic HBM bandwidth."""
@@ -174,12 +182,17 @@ def bench_f64(seed: int, steps: int = 2, warmup: int = 1, profile_every: int = 1
         r = torch.empty(n, dtype=torch.float64, device="cuda")
         iters, dt, avg_ms, kt_n, stops = time_decodes(dec, y, p, steps, warmup, profile_every,
                                                       x, r)
+        step = step_of_decode(avg_ms, kt_n, "k_gram_steps, k_gram_pass")
+        # the same decode with one launch per step: the kernel's HBM rate
+        _, _, avg_ms, kt_n, _ = time_decodes(dec, y, p, 1, 0, profile_every, x, r,
+                                             step_launches=True)
     b = step_bytes(n, m, "f64")
     achieved = b / (avg_ms * 1e-3) / 1e9 if kt_n else None
     return {"workload": f"N={n}, M={m} (FP64 dictionary 2 GiB), K=512, eps=1e-5, T=10240, "
                         "single signal, FP64 throughout",
             "iters_per_s": round(iters / dt, 3), "ms_per_decode": round(dt / steps * 1e3, 3),
             "iters_per_decode": iters // max(steps, 1), "stop": sorted(stops),
+            "step": step,
             "roofline": {"bound": "hbm", "kernel": KERNEL["f64"],
                          "achieved": round(achieved, 2) if achieved else None,
                          "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -196,20 +209,14 @@ def sign_step_bytes(n, m):
     return n * m / 8.0 + 16.0 * m + 20.0 * n
 
 
-# LDS bandwidth of the chip: 256 CUs x 128 bytes per clock x 2.4 GHz
-LDS_PEAK_GBS = 256 * 128 * 2.4
-
-
 def bench_sign(seed: int, steps: int = 3, warmup: int = 1, profile_every: int = 16,
                max_iters=None):
     """Decode on the Bernoulli dictionary of eq. 13 held as sign bits
     (mp_create_signs): N=8192, M=32768 (32 MiB of bits), K=512, eps=1e-5,
     T=10240.  The correlations are carried by exact Gram updates (XOR and
-    bit count).  Where the decode runs as one persistent launch with the bits
-    held in LDS, its roofline is the time per step (bound by the exchange of
-    the workgroups' records) with the LDS rate of the bits beside it; the
-    same decode with one launch per step is timed too, each launch streaming
-    the bits once from HBM (algorithmic bytes per launch over its mean launch
+    bit count), in checked batches of steps: the time per step.  The same
+    decode with one launch per step is timed too, each launch streaming the
+    bits once from HBM (algorithmic bytes per launch over its mean launch
     time)."""
     import torch
 
@@ -233,10 +240,8 @@ def bench_sign(seed: int, steps: int = 3, warmup: int = 1, profile_every: int = 
                                                       x, r, step_launches=True)
     persistent = "persistent" in stops
     stops.discard("persistent")
-    bits = n * m / 8.0
     b = sign_step_bytes(n, m)
     s_ach = b / (s_ms * 1e-3) / 1e9 if s_n else None
-    lds = bits / (avg_ms * 1e-3) / 1e9 if kt_n else None
     step = {"bound": "hbm", "kernel": "k_mp_step_sign",
             "iters_per_s": round(s_it / s_dt, 3),
             "achieved": round(s_ach, 2) if s_ach else None, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -249,14 +254,7 @@ def bench_sign(seed: int, steps: int = 3, warmup: int = 1, profile_every: int = 
            "iters_per_decode": iters // max(steps, 1), "stop": sorted(stops),
            "persistent": persistent}
     if persistent:
-        # the bits stay in LDS for the whole decode: a step reads them from
-        # LDS, and waits for every workgroup's record of the step before
-        out["roofline"] = {"bound": "exchange", "kernel": "k_sign_persist",
-                           "avg_step_us": round(avg_ms * 1e3, 3), "steps": kt_n,
-                           "lds": {"achieved": round(lds, 2) if lds else None,
-                                   "peak": LDS_PEAK_GBS, "unit": "GB/s",
-                                   "frac": round(lds / LDS_PEAK_GBS, 4) if lds else None,
-                                   "bytes_per_step": bits}}
+        out["roofline"] = step_of_decode(avg_ms, kt_n, "k_sgram_steps")
         out["step_launches"] = step
     else:
         out["roofline"] = step
@@ -410,11 +408,11 @@ def bench_single(p, storage, steps, warmup, profile_every, ceiling, workload, re
         one_launch = "persistent" in stops
         stops.discard("persistent")
         conc = None
+        # the same decode with one launch per step, for comparison
+        s_it, s_dt, s_ms, s_n, _ = time_decodes(dec, y, p, steps if one_launch else 1,
+                                                warmup if one_launch else 0, profile_every,
+                                                x, r, rescore_k=rescore_k, step_launches=True)
         if one_launch:
-            # the same decode with one launch per step, for comparison
-            s_it, s_dt, s_ms, s_n, _ = time_decodes(dec, y, p, steps, warmup, profile_every,
-                                                    x, r, rescore_k=rescore_k,
-                                                    step_launches=True)
             conc = concurrent_decodes(psi, y, p, storage, steps)
         del psi
     leg = {"workload": workload, "storage": storage,
@@ -424,11 +422,8 @@ def bench_single(p, storage, steps, warmup, profile_every, ceiling, workload, re
            "one_launch": one_launch}
     b = step_bytes(n, m, storage)
     if one_launch:
-        # the whole decode in one launch with the dictionary's shares in LDS:
-        # the time per step, the dictionary bytes per step read from LDS
-        leg["roofline"] = {"bound": "exchange", "kernel": "k_f32_small",
-                           "avg_step_us": round(avg_ms * 1e3, 3), "steps": kt_n,
-                           "lds_bytes_per_step": 4.0 * n * m}
+        # no launch per step: the time per step
+        leg["roofline"] = step_of_decode(avg_ms, kt_n, "k_gram_bsteps")
         leg["step_launches"] = {
             "iters_per_s": round(s_it / s_dt, 3), "us_per_iter": round(s_dt / max(s_it, 1) * 1e6, 3),
             "roofline": hbm_roofline(KERNEL[storage], b, s_ms, s_n,
@@ -437,7 +432,8 @@ def bench_single(p, storage, steps, warmup, profile_every, ceiling, workload, re
         conc["over_one_stream"] = round(conc["iters_per_s"] / (iters / dt), 3)
         leg["concurrent"] = conc
     else:
-        leg["roofline"] = hbm_roofline(KERNEL[storage], b, avg_ms, kt_n,
+        leg["step"] = step_of_decode(avg_ms, kt_n, "k_gram_steps, k_gram_pass")
+        leg["roofline"] = hbm_roofline(KERNEL[storage], b, s_ms, s_n,
                                        traffic_from_counters(n, m, storage), ceiling)
     return leg, g
 
@@ -541,10 +537,9 @@ def _round_errors(d):
 def bench_batched(seed: int, reps: int = 3, warmup: int = 1, sequential: bool = True,
                   check: bool = True):
     """Batched workload: 256 signals, K_b ~ U{16..256}, sharing one N=2048,
-    M=8192 dictionary.  signals/s of mp_solve_batched (BF16 matrix-core
-    correlations, FP32 re-scoring) and, for comparison, of FP32 mp_solve run
-    signal after signal on the same inputs; MFMA utilisation of the product
-    kernel = 2 N M (sum of per-signal iterations) / (its summed launch time).
+    M=8192 dictionary.  signals/s of mp_solve_batched and, for comparison, of
+    FP32 mp_solve run signal after signal on the same inputs, and the time per
+    step of the longest signal.
     Returns (the record, the traced decode for the oracle's checks)."""
     import torch
 
@@ -584,21 +579,8 @@ def bench_batched(seed: int, reps: int = 3, warmup: int = 1, sequential: bool = 
         dec.solve_batched(Y, bt.eps, caps, want_r=False)
         ms, cnt = dec.kernel_time()
         dec.set_profiling(0)
-        flops = 2.0 * n * m * total_iters
-        gemm_s = ms * cnt * 1e-3
-        out["mfma"] = {"bound": "mfma", "kernel": "k_bcorr", "achieved": round(flops / gemm_s / 1e12, 2),
-                       "peak": 2500.0, "unit": "TFLOP/s",
-                       "frac": round(flops / gemm_s / 1e12 / 2500.0, 4),
-                       "rounds": cnt, "gemm_ms_per_batch": round(ms * cnt, 3)}
-        # the same products against memory: every round reads the BF16
-        # dictionary once and each active signal's BF16 residual once (below
-        # the BF16 ridge of about 312 flop/B even at 256 signals)
-        opnd = cnt * 2.0 * n * m + 2.0 * n * total_iters
-        out["operand_bytes"] = {"bound": "hbm", "kernel": "k_bcorr",
-                                "achieved": round(opnd / gemm_s / 1e9, 2), "peak": HBM_PEAK_GBS,
-                                "unit": "GB/s", "frac": round(opnd / gemm_s / 1e9 / HBM_PEAK_GBS, 4),
-                                "bytes_per_batch": opnd,
-                                "flop_per_byte": round(flops / opnd, 1)}
+        # the decode's time over the steps of its longest signal
+        out["step"] = step_of_decode(ms, cnt, "k_gram_bsteps")
         # one more decode with every signal's atoms recorded, for the checks
         g = None
         if check:
@@ -629,10 +611,9 @@ def bench_ragged(seed: int, storages=("f32", "bf16"), reps: int = 3, tune_reps: 
                  check: bool = True):
     """Ragged workload: 512 independent problems, N_i ~ U{128,256,512,1024},
     M_i = 4 N_i, K_i = N_i / 16, eps = 1e-5, T_i = 20 K_i, each with its own
-    dictionary, decoded in one persistent graph-replayed launch whose shape
-    the autotuner picks, once per dictionary storage.  Reports problems/s and
-    the aggregate algorithmic dictionary bandwidth sum_i iters_i * bytes(Psi_i)
-    / time.  Returns ({storage: record}, {storage: decode to check})."""
+    dictionary, once per dictionary storage (the persistent launch that the
+    autotuner shapes decodes the sets that do not take the carried
+    correlations).  Reports problems/s.  Returns ({storage: record}, {storage: decode to check})."""
     import torch
 
     import mpgen
@@ -645,7 +626,6 @@ def bench_ragged(seed: int, storages=("f32", "bf16"), reps: int = 3, tune_reps: 
     yp = torch.from_numpy(np.concatenate([p.y for p in probs]).astype(np.float32)).cuda()
     recs, checks = {}, {}
     for storage in storages:
-        esize = 4.0 if storage == "f32" else 2.0
         out = {"workload": "512 instances, N_i ~ U{128,256,512,1024}, M_i = 4 N_i, K_i = N_i/16, "
                            f"eps=1e-5, T_i = 20 K_i, own dictionary each, {storage} storage"}
         with RaggedDecoder(psis, storage=storage) as dec:
@@ -672,21 +652,11 @@ def bench_ragged(seed: int, storages=("f32", "bf16"), reps: int = 3, tune_reps: 
                 g = {"iters": tr["iters"], "stop": tr["stop"], "rr": tr["rr"], "yy": tr["yy"],
                      "idx": ti, "x": [xs[xo[i]:xo[i + 1]] for i in range(len(probs))],
                      "r": [rs[yo[i]:yo[i + 1]] for i in range(len(probs))]}
-        nbytes = sum(it * esize * p.n * p.m for it, p in zip(res["iters"], probs))
-        achieved = nbytes / (kms * 1e-3) / 1e9
         out.update(problems_per_s=round(len(probs) / dt, 2), solve_ms=round(dt * 1e3, 3),
                    total_iters=sum(res["iters"]), stops=sorted(set(res["stop"])),
                    config=tuned["config"], tuned_from_cache=tuned["cached"],
-                   roofline={"bound": "hbm", "kernel": "k_ragged", "achieved": round(achieved, 2),
-                             "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                             "frac": round(achieved / HBM_PEAK_GBS, 4),
-                             "traffic": traffic_from_counters(0, 0, "ragged_" + storage),
-                             "bytes_per_solve": nbytes,
-                             "launch_ms": round(kms, 3),
-                             "note": "algorithmic bytes count every instance's dictionary "
-                                     "once per iteration; the counters (traffic, bytes per "
-                                     "solve) show the dictionaries read from memory each "
-                                     "time, none re-read from L2"})
+                   step={"bound": "bytes of the passes, then the steps of the longest problem",
+                         "kernel": "k_gram_rpass, k_gram_rsteps", "device_ms": round(kms, 3)})
         recs[storage] = out
         checks[storage] = {"psis": [p.psi for p in probs], "ys": [p.y for p in probs],
                            "eps": 1e-5, "dict_of": list(range(len(probs))), "g": g}
@@ -804,14 +774,17 @@ def main():
     log(f"[bench] {iters} iterations in {dt:.3f} s")
     one_launch = "persistent" in stops
     stops.discard("persistent")
+    # one decode with one launch per step: the step kernel's HBM rate
+    s_ms, s_n = avg_ms, kt_n
+    if not one_launch:
+        _, _, s_ms, s_n, _ = time_decodes(dec, y, p, 1, 0, args.profile_every, x, r, stream,
+                                          step_launches=True)
     # the same decode once more, untimed, with its whole per-step record (for
     # the oracle's checks at the end)
     check = not args.no_cpu_baseline
     main_g = traced_decode(dec, y, p) if check else None
 
     bytes_per_launch = step_bytes(n, m, args.storage)
-    rsize = 8.0 if prec == "f64" else 4.0
-    bytes_per_iter = bytes_per_launch + 2 * rsize * n  # + residual read and written by the update
     line = {
         "metric": METRIC,
         "value": round(iters / dt, 3),
@@ -831,26 +804,28 @@ def main():
                    "iters_per_decode": iters // max(args.steps, 1),
                    "stop": sorted(stops), "seed": args.seed,
                    "max_iters": p.max_iters},
-        "effective_gbps_whole_step": round(iters * bytes_per_iter / dt / 1e9, 2),
-        "roofline": hbm_roofline(KERNEL[args.storage], bytes_per_launch, avg_ms, kt_n,
+        "step": step_of_decode(avg_ms, kt_n, "k_gram_steps, k_gram_pass"),
+        "roofline": hbm_roofline(KERNEL[args.storage], bytes_per_launch, s_ms, s_n,
                                  traffic_from_counters(n, m, args.storage), ceiling),
     }
     if one_launch:
-        # a small dictionary decoded in one launch from its shares in LDS: the
-        # time per step, bound by the exchange of the workgroups' best keys
+        # a small dictionary: no launch per step
         line["config"]["one_launch"] = True
-        line["roofline"] = {"bound": "exchange", "kernel": "k_f32_small",
-                            "avg_step_us": round(avg_ms * 1e3, 3), "steps": kt_n,
-                            "lds_bytes_per_step": 4.0 * n * m}
+        line["roofline"] = step_of_decode(avg_ms, kt_n, "k_gram_bsteps")
     if not args.no_omp and args.storage == "f32":
         log("[bench] OMP decode of the same signal")
         o_it, o_dt, o_ms, o_n, o_stops = time_decodes(dec, y, p, args.steps, args.warmup,
                                                       args.profile_every, x, r, stream, omp=True)
+        o_step = step_of_decode(o_ms, o_n, "k_omp_carry .. k_omp_update, k_gram_block_pass")
+        # the selection by a pass per step, for its HBM rate
+        _, _, o_ms, o_n, _ = time_decodes(dec, y, p, 1, 0, args.profile_every, x, r, stream,
+                                          omp=True, step_launches=True)
         o_ach = bytes_per_launch / (o_ms * 1e-3) / 1e9 if o_n else None
         line["omp"] = {
             "workload": f"{args.workload}, Orthogonal Matching Pursuit (QR re-fit, CGS2)",
             "iters_per_s": round(o_it / o_dt, 3), "ms_per_decode": round(o_dt / args.steps * 1e3, 3),
             "iters_per_decode": o_it // max(args.steps, 1), "stop": sorted(o_stops),
+            "step": o_step,
             "select_kernel": {"kernel": "k_omp_select", "avg_launch_us": round(o_ms * 1e3, 3),
                               "achieved": round(o_ach, 2) if o_ach else None, "unit": "GB/s",
                               "frac": round(o_ach / HBM_PEAK_GBS, 4) if o_ach else None,

@@ -97,7 +97,8 @@ typedef struct mp_opts {
    whole dictionary, even where the whole decode fits one persistent launch
    (the one-bit form MP_SIGN1, and MP_F32 contexts whose dictionary fits the
    LDS of at most 32 workgroups) or runs on carried correlations (see
-   mp_solve); the same results bit for bit; no effect on the other forms. */
+   mp_solve and mp_solve_omp); the same results bit for bit; no effect on the
+   other forms. */
 #define MP_SOLVE_STEP_LAUNCHES 0x1u
 
 /* mp_opts.flags: a stream-ordered decode (mp_solve and mp_solve_noalloc on
@@ -123,8 +124,8 @@ typedef struct mp_result {
     double yy;            /* ||y||^2, FP64 */
     double rr;            /* ||r||^2 at exit, FP64 (from the FP32 residual) */
     int32_t stop_reason;  /* MP_STOP_* */
-    int32_t persistent;   /* 1: the decode ran as one persistent launch that holds the
-                             whole dictionary on chip (one-bit and small FP32 forms) */
+    int32_t persistent;   /* 1: a one-bit or small FP32 decode (one whose dictionary fits
+                             the LDS of at most 32 workgroups) that took no launch per step */
 } mp_result;
 
 /* Optional per-step record, all arrays device memory of `cap` entries.
@@ -210,13 +211,19 @@ mp_status mp_create(mp_ctx** out, const float* psi, int64_t n, int64_t m, int64_
  * wait between its workgroups that exceeds the poll limit (2^22, or the
  * non-negative integer in the environment variable MP_SMALL_SPIN_LIMIT, read
  * at each decode; 0 gives up at the first wait) ends the decode with
- * MP_EDEVICE.
+ * MP_EDEVICE.  A blocking decode of such a context with a cap of at least 64
+ * steps and column norms within 1% of 1 decodes in one workgroup instead, on
+ * correlations carried by the Gram columns of all atoms (the same results bit
+ * for bit); the context makes these on the first such decode that may take
+ * enough steps (M * M floats, rounded up, kept until it is destroyed), and
+ * with MP_SMALL_SPIN_LIMIT set keeps the one launch.
  *
  * A larger MP_F32 context (M <= 32768, 8 N + 2 M <= 153600 with N rounded up
- * to a multiple of 64, column norms within 1% of 1) decodes on correlations carried from step to step by the Gram columns
- * of the selected atoms, with a pass over the dictionary only when an atom
- * without one is selected: the same results bit for bit as one launch per
- * step, which MP_SOLVE_STEP_LAUNCHES selects.  MP_BF16 and MP_FP8_E4M3
+ * to a multiple of 64, column norms within 1% of 1) decodes on correlations
+ * carried from step to step by the Gram columns of the selected atoms, with a
+ * pass over the dictionary only when an atom without one is selected: the
+ * same results bit for bit as one launch per step, which
+ * MP_SOLVE_STEP_LAUNCHES selects.  MP_BF16 and MP_FP8_E4M3
  * contexts with opts.rescore_k = 8 (or 0) do too, on their FP32 columns: the
  * atom selected is the FP32 form's (one launch per step finds the same one
  * wherever it is among the pass's 8 candidates).  The first such decode
@@ -389,13 +396,18 @@ mp_status mp_solve_f64(mp_ctx* ctx, const double* y, double* x, double* r, const
  * to eq. 11's r).  The correlations and r are kept in FP64 (c at the start is
  * Psi^T y in FP64), so the selections follow the exact iteration closely;
  * x~ accumulates fp32(c*) and r is returned rounded to FP32.  A pass reads
- * N/8 bytes per column instead of 4N.  Where the device can keep one
- * workgroup per compute unit resident with its share of the bits in LDS
- * (the share at most 150 KB, e.g. N = 8192 with M up to 32768 on 256 CUs),
- * mp_solve runs the whole decode as one persistent launch that keeps the
- * bits on chip and exchanges each step's candidates between workgroups
- * through device memory; otherwise, or with MP_SOLVE_STEP_LAUNCHES, one
- * launch per step.  Both give the same results bit for bit.  The persistent
+ * N/8 bytes per column instead of 4N.  mp_solve takes the steps in batches
+ * over the atoms of largest correlation, each batch checked against all atoms
+ * before its steps stand (work buffers of at most 2 M KiB and 3 MiB on the
+ * first such decode), where one launch per step would give a workgroup at
+ * most 256 rows of r (M above about N / 16).  With a cap of at most 64 steps,
+ * or MP_SIGN_SPIN_LIMIT set, it runs the whole decode as one persistent
+ * launch where the device can keep one workgroup per compute unit resident
+ * with its share of the bits in LDS (the share at most 150 KB, e.g. N = 8192
+ * with M up to 32768 on 256 CUs), exchanging each step's candidates between
+ * workgroups through device memory; otherwise, or with
+ * MP_SOLVE_STEP_LAUNCHES, one launch per step.  All give the same results bit
+ * for bit.  The persistent
  * launch needs every workgroup resident at once: run it on a device no other
  * kernel is holding.  A wait between its workgroups that exceeds the poll
  * limit (2^22, or the positive integer in the environment variable
@@ -438,11 +450,16 @@ mp_status mp_create_signs(mp_ctx** out, const uint32_t* signs, int64_t n, int64_
  *   ctx      from mp_create with MP_F32 storage
  *   y, x, r  as mp_solve (x~ is nonzero only on the selected atoms)
  *   opts     eps, max_iters (at most min(max_iters, N) atoms are selected),
- *            rescore_k ignored, flags 0 (or MP_SOLVE_STEP_LAUNCHES, no effect)
+ *            rescore_k ignored, flags 0 or MP_SOLVE_STEP_LAUNCHES (a pass over
+ *            the dictionary selects every atom)
  *   res      host or NULL
  *   trace    host struct of device arrays, or NULL: idx[t] the atom selected
  *            at step t, coef[t] its correlation <r, psi_idx>, rr[t] ||r||^2
  *            after the re-fit
+ *
+ * Dictionaries of at least 96 MiB with column norms within 1% of 1 select on
+ * carried correlations (see mp_solve), with a pass for each block of up to 31
+ * atoms: the same results bit for bit.
  *
  * A selection that repeats an atom, or a new atom that is a combination of
  * the selected ones to FP32 accuracy (||w||^2 <= 1e-10), ends the run with

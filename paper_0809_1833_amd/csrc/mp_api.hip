@@ -1448,8 +1448,11 @@ mp_status mp_solve_result(mp_ctx* ctx, mp_result* res) {
   return fs;
 }
 
-// Dictionaries below this many bytes select by a pass every step.
-constexpr int64_t kOmpCarryBytes = int64_t{1} << 22;
+// Dictionaries below this many bytes select by a pass every step, which then
+// costs no more than the launches that carrying adds (a decode by carried
+// correlations and by passes: 5.32 and 5.21 ms at N = 2048, M = 8192, 64 MiB;
+// 8.8 and 14.0 ms at N = 4096, M = 16384, 256 MiB).
+constexpr int64_t kOmpCarryBytes = int64_t{96} << 20;
 
 static mp_status ensure_omp(mp_ctx* c, int64_t tq) {
   mp::OmpBufs& b = c->omp;
@@ -1476,7 +1479,7 @@ static mp_status ensure_omp(mp_ctx* c, int64_t tq) {
 }
 
 // Whether OMP's selection takes the carried correlations, and their buffers if
-// so.  They save the pass of all steps but about one in twelve and cost two
+// so.  They save the pass of all steps but about one in fourteen and cost two
 // launches more a step and five more a pass.
 // Without them (column norms not near 1, no memory) every step selects by a
 // pass.

@@ -374,8 +374,9 @@ def _omp_same(rows, y, eps, cap):
 
 
 @pytest.mark.parametrize("n,m,k,noise", [
-    (1024, 1025, 60, 0.01), (1025, 1151, 40, 0.0), (700, 2049, 30, 0.01), (130, 16384, 12, 0.0),
-    (129, 8321, 6, 0.01), (4097, 300, 17, 0.0), (2048, 2000, 100, 0.0), (512, 4097, 2, 3.0),
+    (2048, 12289, 60, 0.01), (1025, 24575, 40, 0.0), (700, 36033, 30, 0.01),
+    (130, 131200, 12, 0.0), (4097, 6145, 17, 0.0), (16384, 1537, 100, 0.0), (1024, 24577, 2, 3.0),
+    (512, 4097, 8, 0.01),  # a pass per step
 ])
 def test_omp_equals_a_pass_per_step(n, m, k, noise):
     """OMP's selection on carried correlations: the atoms, coefficients, x~ and
@@ -390,11 +391,12 @@ def test_omp_equals_a_pass_per_step(n, m, k, noise):
 def test_omp_ties_caps_and_handing_back():
     """Exact ties take the smallest index; near copies of selected atoms; caps
     of 0 and 1; zero input; more ties than a step can score."""
-    rows, y = _draw(640, 2400, 24, seed=3)
+    rows, y = _draw(640, 40000, 24, seed=3)
     rows[1200:1800] = rows[:600]
-    rows[1800:] = -rows[600:1200]
+    rows[1800:2400] = -rows[600:1200]
+    y = (rows[:24] * torch.arange(1, 25, device="cuda")[:, None]).sum(0)
     a = _omp_same(rows, y, 1e-5, 60)
-    assert int(a["idx"].max()) < 1200
+    assert not bool(((a["idx"] >= 1200) & (a["idx"] < 2400)).any())
     for cap in (0, 1):
         assert _omp_same(rows, y, 1e-5, cap)["iters"] == cap
     _omp_same(rows, torch.zeros_like(y), 1e-5, 20)
