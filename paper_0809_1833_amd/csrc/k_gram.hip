@@ -28,8 +28,8 @@ namespace mp {
 // their own, summed in FP64, which keeps the rounding bound of the products at
 // that of one chain.
 //
-// 16 right-hand sides (16 atoms a wave) took 196 us at N = 8192, M = 32768
-// (5.5 TB/s) and 40 passes a decode.
+// N = 8192, M = 32768: 192 us (5.6 TB/s; a large copy reaches 6.64) and 22
+// passes a decode; with 16 right-hand sides (16 atoms a wave) 196 us and 40.
 constexpr int kPassThreads = 512;
 constexpr int kPassWaves = kPassThreads / kWave;
 constexpr int kPassRows = 64;           // rows of a piece: 8 steps of 8
@@ -358,10 +358,10 @@ template hipError_t launch_gram_steps<double>(const GramProb<double>&, const Gra
 // over arrays of problems.  A round packs every running problem's right-hand
 // sides, passes over their dictionaries (one launch, a list of tile groups)
 // and takes their steps (one workgroup each, most work first); the problems
-// share nothing.  Bound by the passes' bytes while many problems run (4.7
-// TB/s), then by the steps of the longest.  512 problems of N in {128 ...
-// 1024}, M = 4 N: 9.2 ms from 125 ms with a pass per step in one persistent
-// launch.
+// share nothing.  Bound by the passes' bytes while many problems run (4.9 ms
+// at 3.3 TB/s), then by the steps of the longest (3.0 ms).  512 problems of N
+// in {128 ... 1024}, M = 4 N: 8.0 ms from 125 ms with a pass per step in one
+// persistent launch (9.1 ms with 16 right-hand sides).
 __global__ __launch_bounds__(256) void k_gram_rinit(const GramProb<float>* __restrict__ probs,
                                                     const RInst* __restrict__ inst,
                                                     const float* __restrict__ Y,

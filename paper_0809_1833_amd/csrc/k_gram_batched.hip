@@ -10,9 +10,10 @@
 //
 // Bound by the steps of the longest signal (3.6 us each at N = 2048,
 // M = 8192).  Against rounds of BF16 products with a selection launch each:
-// N = 2048, M = 8192, 256 signals: 6.4 ms from 41 ms (1.8 ms more the first
-// time, for the Gram columns); N = 500, M = 1000, 500 signals: 2.8 ms from
-// 7.8 ms.
+// N = 2048, M = 8192, 256 signals: 6.6 ms from 42 ms (2 ms more the first
+// time, for the Gram columns); N = 500, M = 1000, 500 signals: 2.7 ms from
+// 7.8 ms.  One signal of a small dictionary, N = 256, M = 1024, 50 steps: 162
+// us from 264 in the launch that exchanges every step between workgroups.
 #include <algorithm>
 
 #include "k_common.h"

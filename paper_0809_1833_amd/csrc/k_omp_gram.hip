@@ -1,5 +1,5 @@
 // OMP's selection on carried correlations (k_gram.h): the pass over the
-// dictionary runs once for about a dozen atoms instead of once per atom.
+// dictionary runs once for about fourteen atoms instead of once per atom.
 //
 // A block starts with a pass that gives c~ = Psi^T r and, for up to kGramReq
 // candidate atoms, Psi^T w_i with w_i = psi_i - Q Q^T psi_i (the candidates
@@ -17,8 +17,9 @@
 // sum above misses (the rounding of both ways to orthogonalise) is measured,
 // not estimated: k_omp_orth leaves its norm.
 //
-// N = 8192, M = 32768, K = 512: the selection 160 -> 27 us a step with its
-// share of the passes.
+// Bound by a step's seven dependent launches (40 us with the factorisation's)
+// and the blocks' passes.  N = 8192, M = 32768, K = 512: 29.4 ms a decode from
+// 95.1 ms with a selection pass of 160 us each step (37 passes of 200 us).
 #include "k_common.h"
 #include "k_gram.h"
 #include "k_gram_steps.h"
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(kOrthWavesB* kWave) void k_omp_borth(
 // c~ after the last step, and each workgroup's two largest keys.  after_pass:
 // the launch follows a block's pass, whose c~ is taken as it is if it ran.
 // One atom per thread: bound by the latency of its (at most kGramReq + 1)
-// loads, 8 MB in all.
+// loads, 4 MB in all.
 __global__ __launch_bounds__(kCarryThreads) void k_omp_carry(
     float* __restrict__ c, float* __restrict__ p, int64_t mp, int64_t m,
     const float* __restrict__ rmat, int64_t tq, const double* __restrict__ z,

@@ -710,7 +710,7 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
   // the reduced-precision forms keep the FP32 columns too: with all 8
   // candidates re-scored (the default) the atom they select is the FP32
   // form's, which the carried correlations give without a pass per step
-  // (N = 8192, M = 32768, K = 256: BF16 12.9 ms from 89.4, FP8 11.5 from 41.4)
+  // (N = 8192, M = 32768, K = 256: BF16 8.1 ms from 89.0, FP8 7.4 from 42.1)
   if (allow_gram && (c->storage == MP_F32 || c->rescore_k == mp::kLpTopK) && !async &&
       !(opts->flags & MP_SOLVE_STEP_LAUNCHES) && ensure_gram(c, s)) {
     bool gave_up = false;
@@ -1513,8 +1513,8 @@ static bool ensure_omp_carry(mp_ctx* c) {
 // kernel: rounds of a block (which returns at once while the current one
 // lasts) and kOmpSlots steps (which return at once while they wait for a
 // block), enqueued in chunks of kOmpRounds with two chunks in flight.  A
-// block lasts 4 to 15 steps: with 4 steps a round the launches that return at
-// once come to about 3 us a step.  `gave_up`: as in solve_gram.
+// block lasts about fourteen steps: with 4 steps a round the launches that
+// return at once come to about 3 us a step.  `gave_up`: as in solve_gram.
 static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipStream_t s,
                                 bool& gave_up) {
   constexpr int kOmpSlots = 4, kOmpRounds = 4;
