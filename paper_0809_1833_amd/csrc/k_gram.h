@@ -97,7 +97,7 @@ inline int64_t gram_stride(const GramShape& sh) {
   const int64_t all = static_cast<int64_t>(sh.threads) * sh.per_thread;
   return all < kGramMaxAtoms ? all : kGramMaxAtoms;
 }
-GramBounds gram_bounds(int64_t n, double max_norm, bool f64, bool ragged);
+GramBounds gram_bounds(int64_t n, double max_norm, bool f64);
 
 template <typename T>
 struct GramTrace {

@@ -24,7 +24,7 @@ namespace mp {
 //
 // Each 32-atom tile's rows are split over `split` waves of the workgroup, so
 // that a short dictionary still gives every CU waves; their sums meet in LDS
-// in a fixed order.  Every 16 or 32 rows (gram_chain) are an FP32 chain of
+// in a fixed order.  Every 32 rows (FP64: 16; gram_chain) are an FP32 chain of
 // their own, summed in FP64, which keeps the rounding bound of the products at
 // that of one chain.
 //
@@ -34,8 +34,8 @@ constexpr int kPassThreads = 512;
 constexpr int kPassWaves = kPassThreads / kWave;
 constexpr int kPassRows = 64;           // rows of a piece: 8 steps of 8
 constexpr int kPassSteps = kPassRows / 8;
-// Rows summed in one FP32 chain with `d` pieces in flight.
-constexpr int gram_chain(int d) { return d == 1 ? 16 : 32; }
+// Rows summed in one FP32 chain.
+constexpr int gram_chain(bool f64) { return f64 ? 16 : 32; }
 constexpr int kRhs = kGramReq + 1;
 static_assert(kRhs == 32 && kGramTile == 32, "one 32 x 32 tile per wave");
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -75,15 +75,19 @@ __global__ __launch_bounds__(256) void k_gram_pack(GramProb<T> p, int first) {
 }
 
 // One workgroup's share of the pass: tiles group * (WAVES / split) ..., with D
-// pieces in flight per wave.
-// (every thread of the workgroup calls; there are barriers).
-template <typename T, int D, int WAVES>
+// pieces in flight per wave (every thread of the workgroup calls; there are
+// barriers).  SHARE (for split == 1, one piece in flight): the waves go through
+// the same rows of the right-hand sides, so each loads its part of a piece of
+// them and reads the piece from LDS.  A wave starts at its tile's own piece
+// and goes round, so that tiles do not all ask for the same rows at once.
+template <typename T, int D, int WAVES, bool SHARE = false>
 __device__ inline void gram_pass(const GramProb<T>& p, int64_t group, int split, int first) {
   constexpr int NL = kPassRows * kGramTile * sizeof(T) / 16 / kWave;  // 16-byte loads of a piece
   constexpr int LPA = kPassRows * sizeof(T) / 16;                     // of them per atom
-  // steps of an FP32 chain: two more flushes of 16 sums cost registers that two
-  // pieces in flight do not leave (232 us a pass from 192, 10 registers spilled)
-  constexpr int C = gram_chain(D) / 8;
+  // steps of an FP32 chain: with 16 rows two more flushes of 16 sums cost registers
+  // that two pieces in flight do not leave (232 us a pass from 192, 10 registers
+  // spilled)
+  constexpr int C = gram_chain(sizeof(T) == 8) / 8;
   typedef typename Vec16<T>::type vec;
   __shared__ v4f turn[WAVES][kGramTile * 16];  // then the split sums
   const int lane = threadIdx.x % kWave;
@@ -93,18 +97,19 @@ __device__ inline void gram_pass(const GramProb<T>& p, int64_t group, int split,
   const int64_t m0 = (group * tiles + wave / split) * kGramTile;
   const int i = lane % kGramTile, q = lane / kGramTile;
   const int nreq = first ? 0 : p.ctl->nreq;
+  const bool live = m0 < p.m;
   double tot[16];
 #pragma unroll
   for (int e = 0; e < 16; ++e) tot[e] = 0.0;
-  if (m0 < p.m) {
+  if (SHARE || live) {
     // load j of a piece: 16 bytes (j 64 + lane) % LPA of atom (j 64 + lane) / LPA
-    const vec* a0 = reinterpret_cast<const vec*>(p.psi + m0 * p.ld);
+    const vec* a0 = reinterpret_cast<const vec*>(p.psi + (live ? m0 : 0) * p.ld);
     unsigned at[NL];  // in 16 bytes
     int put[NL];      // in floats
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
       const int atom = (j * kWave + lane) / LPA, li = (j * kWave + lane) % LPA;
-      const int64_t in = m0 + atom < p.m ? atom : p.m - 1 - m0;
+      const int64_t in = m0 + atom < p.m ? atom : live ? p.m - 1 - m0 : 0;
       at[j] = static_cast<unsigned>(in * (p.ld * static_cast<int>(sizeof(T)) / 16) + li);
       const int f = li * (16 / static_cast<int>(sizeof(T)));  // first row of the 16 bytes
       put[j] = 4 * (atom * 16 + ((f / 4) ^ (atom % 16))) + f % 4;
@@ -113,21 +118,30 @@ __device__ inline void gram_pass(const GramProb<T>& p, int64_t group, int split,
     v4f* my = turn[wave];
     const int pieces = static_cast<int>(p.ld / kPassRows);
     const int k0 = pieces * part / split, k1 = pieces * (part + 1) / split;
+    const int len = k1 > k0 ? k1 - k0 : 1;
+    const int rot = static_cast<int>((m0 / kGramTile / (SHARE ? tiles : 1)) % len);
+    auto turned = [&](int k) {
+      const int t = (k < k1 ? k : k1 - 1) + rot;
+      return static_cast<int64_t>(t < k1 ? t : t - len);
+    };
     v16f acc[2];
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = 0.0f;
     vec va[D][NL];
-    v4f vb[D][kPassSteps];
+    constexpr int NB = SHARE ? kPassSteps / WAVES : kPassSteps;  // this wave's of a piece
+    static_assert(!SHARE || (D == 1 && NB * WAVES == kPassSteps), "an even part for each wave");
+    v4f vb[D][NB];
+    const int b0 = SHARE ? wave * NB : 0;
     // (past the end: read again, not used)
     auto load_a = [&](vec(&x)[NL], int k) {
-      const vec* ak = a0 + LPA * static_cast<int64_t>(k < k1 ? k : k1 - 1);
+      const vec* ak = a0 + LPA * turned(k);
 #pragma unroll
       for (int j = 0; j < NL; ++j) x[j] = __builtin_nontemporal_load(ak + at[j]);
     };
-    auto load_b = [&](v4f(&y)[kPassSteps], int k) {
-      const v4f* bk = b + kPassSteps * kWave * static_cast<int64_t>(k < k1 ? k : k1 - 1);
+    auto load_b = [&](v4f(&y)[NB], int k) {
+      const v4f* bk = b + kPassSteps * kWave * turned(k);
 #pragma unroll
-      for (int j = 0; j < kPassSteps; ++j) y[j] = bk[j * kWave + lane];
+      for (int j = 0; j < NB; ++j) y[j] = bk[(b0 + j) * kWave + lane];
     };
     auto flush = [&](v16f& x) {
 #pragma unroll
@@ -136,25 +150,31 @@ __device__ inline void gram_pass(const GramProb<T>& p, int64_t group, int split,
         x[e] = 0.0f;
       }
     };
-    auto use = [&](vec(&x)[NL], v4f(&y)[kPassSteps], int next) {
+    auto use = [&](vec(&x)[NL], v4f(&y)[NB], int next, v4f* bl) {
 #pragma unroll
       for (int j = 0; j < NL; ++j) put_floats(reinterpret_cast<float*>(my) + put[j], x[j]);
+      if (SHARE) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) bl[(b0 + j) * kWave + lane] = y[j];
+        load_b(y, next);
+      }
       __builtin_amdgcn_wave_barrier();
       load_a(x, next);
       __builtin_amdgcn_sched_barrier(0);
+      if (SHARE) __syncthreads();
 #pragma unroll
       for (int s = 0; s < kPassSteps; ++s) {
         const v4f xa = my[i * 16 + ((2 * s + q) ^ (i % 16))];
+        const v4f xb = SHARE ? bl[s * kWave + lane] : y[SHARE ? 0 : s];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           acc[s / C & 1] =
-              __builtin_amdgcn_mfma_f32_32x32x2f32(xa[e], y[s][e], acc[s / C & 1], 0, 0, 0);
+              __builtin_amdgcn_mfma_f32_32x32x2f32(xa[e], xb[e], acc[s / C & 1], 0, 0, 0);
         if (s % C == C - 1 && s > C) flush(acc[(s / C & 1) ^ 1]);  // the chain before
       }
-      if (C == kPassSteps / 2) flush(acc[0]);
       flush(acc[1]);
       __builtin_amdgcn_sched_barrier(0);
-      load_b(y, next);
+      if (!SHARE) load_b(y, next);
       __builtin_amdgcn_wave_barrier();
     };
     if (k0 < k1) {
@@ -163,10 +183,17 @@ __device__ inline void gram_pass(const GramProb<T>& p, int64_t group, int split,
         load_a(va[d], k0 + d);
         load_b(vb[d], k0 + d);
       }
+    }
+    if constexpr (!SHARE) {
       for (int k = k0; k < k1; k += D)
 #pragma unroll
         for (int d = 0; d < D; ++d)
-          if (k + d < k1) use(va[d], vb[d], k + d + D);
+          if (k + d < k1) use(va[d], vb[d], k + d + D, nullptr);
+    } else {
+      // One barrier a piece, with two buffers in turn: a wave that fills one has
+      // passed the barrier after which no wave reads it.
+      __shared__ v4f bsh[2][kPassSteps * kWave];
+      for (int k = 0; k < k1; ++k) use(va[0], vb[0], k + 1, bsh[k & 1]);
     }
   }
   __syncthreads();
@@ -267,11 +294,11 @@ hipError_t launch_gram_block_pass(const GramProb<float>& p, const int* hold, int
 // rest).  Each is at most (terms + additions) u sum |a b| <= (...) u ||a||
 // ||b||; a step adds r's rounding (u ||r'|| against a unit column; far less in
 // FP64), c~'s own (u |c~|) and that of the coefficient (u |c|, in col).
-GramBounds gram_bounds(int64_t n, double max_norm, bool f64, bool ragged) {
+GramBounds gram_bounds(int64_t n, double max_norm, bool f64) {
   const double u = 1.0 / 16777216.0, nn = static_cast<double>(n + 64);
   const double slack = 1.01;
   const double prod =
-      (std::min<double>(nn, gram_chain(f64 || ragged ? 1 : 2)) + 7) * u * slack;
+      (std::min<double>(nn, gram_chain(f64)) + 7) * u * slack;
   GramBounds b;
   b.pass = static_cast<float>(prod * max_norm);
   b.col = static_cast<float>(prod * max_norm * max_norm);
@@ -358,10 +385,10 @@ template hipError_t launch_gram_steps<double>(const GramProb<double>&, const Gra
 // over arrays of problems.  A round packs every running problem's right-hand
 // sides, passes over their dictionaries (one launch, a list of tile groups)
 // and takes their steps (one workgroup each, most work first); the problems
-// share nothing.  Bound by the passes' bytes while many problems run (4.9 ms
-// at 3.3 TB/s), then by the steps of the longest (3.0 ms).  512 problems of N
-// in {128 ... 1024}, M = 4 N: 8.0 ms from 125 ms with a pass per step in one
-// persistent launch (9.1 ms with 16 right-hand sides).
+// share nothing.  Bound by the passes' bytes while many problems run (4.4 ms
+// at 3.7 TB/s), then by the steps of the longest (2.9 ms).  512 problems of N
+// in {128 ... 1024}, M = 4 N: 7.4 ms from 125 ms with a pass per step in one
+// persistent launch.
 __global__ __launch_bounds__(256) void k_gram_rinit(const GramProb<float>* __restrict__ probs,
                                                     const RInst* __restrict__ inst,
                                                     const float* __restrict__ Y,
@@ -414,12 +441,20 @@ __global__ __launch_bounds__(256) void k_gram_rpack(const GramProb<float>* __res
   if (!p.st->done) gram_pack(p, first);
 }
 
+// Three waves per SIMD with a piece each in flight.  Where no tile is split
+// (many problems), its waves share the right-hand sides through LDS: their
+// misses to the L2 halve what a CU can have under way for the dictionaries
+// (512 problems of N in {128 ... 1024}: a solve 8.0 ms, shared 7.75, with
+// chains of 32 rows instead of 16 7.65, with the tiles' own starting pieces
+// 7.4).  In the pass over one long dictionary, where two pieces in flight hide
+// those misses, the barriers cost more (220 us from 193).
+template <bool SHARE>
 __global__ __launch_bounds__(kGramRaggedWaves* kWave) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 k_gram_rpass(const GramProb<float>* __restrict__ probs, const GramGroup* __restrict__ groups,
              int split, int first) {
   const GramGroup g = groups[blockIdx.x];
   const GramProb<float> p = probs[g.id];
-  if (!p.st->done) gram_pass<float, 1, kGramRaggedWaves>(p, g.group, split, first);
+  if (!p.st->done) gram_pass<float, 1, kGramRaggedWaves, SHARE>(p, g.group, split, first);
 }
 
 template <int NT, int CPT, bool ONE>
@@ -460,7 +495,7 @@ __global__ __launch_bounds__(NT + 2 * kWave) void k_gram_rsteps(
 }
 
 GramBounds gram_bounds_one(int64_t n, double max_norm) {
-  GramBounds b = gram_bounds(n, max_norm, false, true);
+  GramBounds b = gram_bounds(n, max_norm, false);
   const double nn = static_cast<double>(n + 64);
   b.dot = static_cast<float>((nn / 64 + 10) / 16777216.0 * max_norm * 1.01);
   return b;
@@ -519,7 +554,11 @@ hipError_t launch_gram_rround(const GramRagged& g, float* X, long long round, mp
   k_gram_rpack<<<dim3(packs, g.count), dim3(256), 0, s>>>(g.probs, g.again, par, first);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_gram_rpass<<<dim3(g.ngroups), dim3(kGramRaggedWaves * kWave), 0, s>>>(g.probs, g.groups, g.split, first);
+  const dim3 block(kGramRaggedWaves * kWave);
+  if (g.split == 1)
+    k_gram_rpass<true><<<dim3(g.ngroups), block, 0, s>>>(g.probs, g.groups, g.split, first);
+  else
+    k_gram_rpass<false><<<dim3(g.ngroups), block, 0, s>>>(g.probs, g.groups, g.split, first);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (g.small)
     return g.one ? launch_rsteps_t<256, 4, 16, true>(g, X, tr, par, first, s)

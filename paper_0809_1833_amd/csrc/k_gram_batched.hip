@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // added in FP32; the rest as in gram_bounds.
 GramBounds gram_bounds_full(int64_t n, double max_norm) {
   const double u = 1.0 / 16777216.0, nn = static_cast<double>(n + 64);
-  GramBounds b = gram_bounds(n, max_norm, false, false);
+  GramBounds b = gram_bounds(n, max_norm, false);
   const double prod = (std::min<double>(nn, kGemmChain) + nn / kGemmChain + 7) * u * 1.01;
   b.pass = static_cast<float>(prod * max_norm);
   b.col = static_cast<float>(prod * max_norm * max_norm);

@@ -505,7 +505,7 @@ template <typename T>
 mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* opts,
                      const typename mp::GramTrace<T>::type& tr, hipStream_t s, bool& gave_up) {
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, sizeof(T));
-  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, sizeof(T) == 8, false);
+  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, sizeof(T) == 8);
   const mp::GramProb<T> p{psi, c->ld, c->n, c->m, c->gram_mp, c->gram_c, c->gram_g, c->gram_map,
                           c->gram_slots, c->gram_rhs, r_work, x, c->st,
                           static_cast<mp::GramCtl*>(c->gram_ctl)};
@@ -934,7 +934,7 @@ void make_gram_ragged(mp_ctx* c, hipStream_t s) {
       p.x = nullptr;
       p.st = c->gram_rst + i;
       p.ctl = reinterpret_cast<mp::GramCtl*>(mem + o_ctl) + i;
-      bounds[i] = c->storage == MP_BF16 ? mp::gram_bounds(p.n, c->max_norm, false, true)
+      bounds[i] = c->storage == MP_BF16 ? mp::gram_bounds(p.n, c->max_norm, false)
                                         : mp::gram_bounds_one(p.n, c->max_norm);
     }
     return hipMemsetAsync(mem, 0, zeroed, s) == hipSuccess &&
@@ -1519,7 +1519,7 @@ static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipS
                                 bool& gave_up) {
   constexpr int kOmpSlots = 4, kOmpRounds = 4;
   mp::OmpBufs& b = c->omp;
-  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, false, false);
+  const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, false);
   const bool timed = c->profiling;
   gave_up = false;
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));

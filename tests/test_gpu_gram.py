@@ -331,6 +331,29 @@ def test_ragged_equals_persistent_launch(storage, sizes, monkeypatch):
         assert all(abs(u - v) <= 1e-13 * v for u, v in zip(a[key], b[key])), key
 
 
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_ragged_many_problems_share_right_hand_sides(storage, monkeypatch):
+    """So many tiles that none is split: the pass reads its right-hand sides
+    from LDS.  Columns of one piece and of several, tiles that do not fill
+    their workgroup or have no atoms; as the persistent launch decodes them."""
+    from paper_0809_1833_amd.mp import RaggedDecoder
+    sizes = [([1, 64, 65, 192, 300][i % 5], [897, 929, 961, 1000, 1024, 1025][i % 6])
+             for i in range(110)]
+    assert sum(-(-m // 32) for _, m in sizes) > 12 * torch.cuda.get_device_properties(
+        0).multi_processor_count
+    print(f"[gram ragged many {storage}]", flush=True)
+    probs = _ragged_probs(sizes, seed=40)
+    caps = [8 + i % 5 for i in range(len(sizes))]
+    with RaggedDecoder([rows.t() for rows, _ in probs], storage=storage) as dec:
+        y = dec.pack([p[1] for p in probs])
+        a = _ragged_out(dec, y, 0.003, caps, max(caps))
+        monkeypatch.setenv("MP_RAGGED_SPIN_LIMIT", "4194304")
+        b = _ragged_out(dec, y, 0.003, caps, max(caps))
+    assert a["iters"] == b["iters"] and a["stop"] == b["stop"] and max(a["iters"]) > 5
+    for key in ("x", "r", "idx", "coef", "r_trace"):
+        assert torch.equal(a[key], b[key]), key
+
+
 def test_ragged_odd_inputs_and_handing_back():
     """A zero y, a cap of zero, exact ties; a problem on which more atoms tie
     than a step can score sends the set to the persistent launch; NaN fails
