@@ -7,9 +7,10 @@ dictionary and y already resident in HBM.  Default workload: N=8192,
 M=32768 (1 GiB FP32 dictionary), K=512, eps=1e-5, T=20K.
 
 Prints ONE JSON line.  `value` is MP iterations per second over the timed
-steps; `roofline` is the correlation kernel's algorithmic HBM bandwidth
-(dictionary + residual bytes per launch / mean launch time from HIP events on
-the decode stream) against the 8 TB/s peak and against the read rate a plain
+steps; `step` is the device time of a decode per step it took; `roofline` is
+the stepping kernel's algorithmic HBM bandwidth (dictionary + residual bytes
+per launch / mean launch time from HIP events on the decode stream, in a
+decode with one launch per step) against the 8 TB/s peak and against the read rate a plain
 streaming kernel reaches on the same device; `cpu_baseline` is the FP64
 oracle timed on a bounded sample of the same decode on this host, on every
 core and on one.  The line also carries the reduced-precision forms (BF16 and
