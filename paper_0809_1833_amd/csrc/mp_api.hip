@@ -606,20 +606,23 @@ bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
 // decode holds them, made by the first decode): no passes, so a decode is the
 // products Psi^T y, then the steps in one workgroup, and again each time the
 // carried correlations have lost too many digits.  `used` false: not taken, or
-// handed back (the state then needs its init again).
+// handed back (`ran`: the state then needs its init again).
 //
 // The one launch that holds the dictionary in LDS (k_f32_small) costs 25 us
-// and 5 a step (its exchange between workgroups), this 60 and 2.4, so caps
-// below kFullCap steps stay there; the Gram columns are made where they cost
-// at most 0.1 us a step of the cap (6 us at N = 256, M = 1024).
-constexpr long long kFullCap = 64;
+// and 5 a step (its exchange between workgroups), this 60 and 2.4, so low caps
+// stay there (20 K steps allowed, decodes to ||r|| of 1e-6 .. 0.04, this
+// against that: M = 192, cap 80: 92 .. 51 us, 150 .. 55; M = 1024, cap 80: 86 ..
+// 61, 93 .. 55; cap 100: 95 .. 59, 114 .. 60; cap 160: 138 .. 70, 206 .. 84);
+// the Gram columns are made where they cost at most 0.1 us a step of the cap
+// (6 us at N = 256, M = 1024).
 mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, const mp_opts* opts,
-                           const mp_trace& tr, hipStream_t s, bool& used) {
-  used = false;
+                           const mp_trace& tr, hipStream_t s, bool& used, bool& ran) {
+  used = ran = false;
+  const long long least = c->m <= 512 ? 64 : 96;
   const double cost_us = static_cast<double>(c->m) * static_cast<double>(c->m) *
                          static_cast<double>(c->ld) / 45e6;
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
-  if (opts->max_iters < kFullCap || sh.threads * sh.per_thread > 8192 ||
+  if (opts->max_iters < least || sh.threads * sh.per_thread > 8192 ||
       (!c->gram_full && cost_us > 0.1 * static_cast<double>(opts->max_iters)) ||
       !ensure_gram_batch(c, 1, opts->max_iters, s))
     return MP_OK;
@@ -628,16 +631,20 @@ mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, const mp_opts* op
                         r_work, x, c->m, c->st};
   const bool timed = c->profiling;
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
-  // every round takes a step (or gives up); two are all that most decodes need
+  // every round takes a step (or gives up); two are all that most decodes need,
+  // and one brings ||r|| down by three decades
+  int rounds = opts->eps >= 1e-3 ? 1 : 2;
+  ran = true;
   const long long most = static_cast<long long>(opts->max_iters) + 1;
   long long issued = 0;
   do {
-    for (int k = 0; k < 2 && issued < most; ++k, ++issued)
+    for (int k = 0; k < rounds && issued < most; ++k, ++issued)
       HIP_TRY(c, mp::launch_gram_bround(b, sh, bounds, 1, c->num_cus, issued, c->gram_again, true,
                                         tr, s));
     if (timed) HIP_TRY(c, hipEventRecord(c->ev[1], s));
     HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
+    rounds = 2;
   } while (!c->h_st->done && issued < most);
   if (timed) {
     float ms = 0.f;
@@ -660,8 +667,8 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
       !(opts->flags & MP_SOLVE_STEP_LAUNCHES)) {
     // (MP_SMALL_SPIN_LIMIT limits the waits of the one launch, which only it has)
     if (allow_gram && !async && opts->max_iters > 0 && !getenv("MP_SMALL_SPIN_LIMIT")) {
-      bool used = false;
-      const mp_status fs = solve_small_full(c, b.r_work, x, opts, tr, s, used);
+      bool used = false, ran = false;
+      const mp_status fs = solve_small_full(c, b.r_work, x, opts, tr, s, used, ran);
       if (fs != MP_OK) return fs;
       if (used) {
         if (r) {
@@ -672,10 +679,12 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
         if (rs == MP_OK && res) res->persistent = 1;
         return rs;
       }
-      c->prof_ms = 0.0;
-      c->prof_launches = 0;
-      HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
-                                 static_cast<long long>(opts->max_iters), s));
+      if (ran) {
+        c->prof_ms = 0.0;
+        c->prof_launches = 0;
+        HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
+                                   static_cast<long long>(opts->max_iters), s));
+      }
     }
     // the whole decode in one launch, every share of the dictionary in LDS:
     // a new tag epoch for every decode (never 0 mod the epoch range: the

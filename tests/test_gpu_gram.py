@@ -506,7 +506,8 @@ def test_signs_ties_and_stall():
 # ---- small dictionaries (every atom's Gram column) --------------------------------
 
 @pytest.mark.parametrize("n,m,cap", [
-    (256, 1024, 63), (256, 1024, 64),     # the cap below which the one launch stays
+    (256, 1024, 95), (256, 1024, 96),     # the caps below which the one launch stays
+    (100, 512, 63), (100, 512, 64),
     (256, 1025, 900), (64, 65, 400), (2048, 512, 900), (33, 17, 64), (700, 900, 2000),
 ])
 def test_small_equals_step_launches(n, m, cap):
@@ -514,6 +515,14 @@ def test_small_equals_step_launches(n, m, cap):
     rows, y = _draw(n, m, max(2, min(n, m) // 20))
     a = _same(rows, y, 1e-6, cap)
     assert a["persistent"] and a["iters"] > 3
+
+
+@pytest.mark.parametrize("eps", [1e-3, 9e-4, 0.04])
+def test_small_loose_stop(eps):
+    """One round first from eps = 1e-3 on, two below."""
+    rows, y = _draw(256, 1024, 12, seed=4)
+    a = _same(rows, y, eps, 240)
+    assert a["persistent"] and a["stop"] == "converged"
 
 
 def test_small_ties_and_handing_back():
