@@ -26,6 +26,12 @@ constexpr int kRaggedDefaultSplit = 3;    // parts of an instance, at most, unle
 constexpr int64_t kLdAlign = 64;          // padded column length (floats): 256 B aligned
 constexpr int kMaxChunk = 64;             // iterations enqueued per host check
 constexpr double kNormTol = 1e-4;
+// Caps are cut to this (no decode gets there), so that the host's counts of
+// launches and rounds, small multiples of the cap, do not overflow.
+constexpr long long kMaxCap = LLONG_MAX / 8;
+long long step_cap(const mp_opts* opts) {
+  return std::min<long long>(opts->max_iters, kMaxCap);
+}
 
 mp_status fail(mp_ctx* ctx, mp_status s, const std::string& msg) {
   if (ctx) ctx->err = msg;
@@ -514,13 +520,13 @@ mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* op
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
   // a pair takes at least one step, unless it only renews the correlations,
   // which the next one then follows with a step
-  const long long most = 2 * static_cast<long long>(opts->max_iters) + 2;
+  const long long cap = step_cap(opts), most = 2 * cap + 2;
   long long issued = 0, seen = 0;
-  bool over = opts->max_iters <= 0;
+  bool over = cap <= 0;
   while (!over && seen < most) {
     while (issued < most && issued - seen < 2) {
       HIP_TRY(c, mp::launch_gram_pass(p, c->num_cus, issued == 0, s));
-      HIP_TRY(c, mp::launch_gram_steps(p, sh, bounds, opts->max_iters, issued == 0, tr, s));
+      HIP_TRY(c, mp::launch_gram_steps(p, sh, bounds, cap, issued == 0, tr, s));
       const int k = static_cast<int>(issued & 1);
       HIP_TRY(c, hipMemcpyAsync(&c->h_st[1 + k], c->st, sizeof(mp::DevState),
                                 hipMemcpyDeviceToHost, s));
@@ -533,6 +539,7 @@ mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* op
     over = c->h_st[1 + k].done != 0;
     gave_up = c->h_st[1 + k].pad[0] != 0;
   }
+  if (!over && cap > 0) gave_up = true;  // (not reached: unfinished is never a result)
   if (timed) {
     // the decode's time on the device over the steps it took
     HIP_TRY(c, hipEventRecord(c->ev[1], s));
@@ -635,7 +642,7 @@ mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, const mp_opts* op
   // and one brings ||r|| down by three decades
   int rounds = opts->eps >= 1e-3 ? 1 : 2;
   ran = true;
-  const long long most = static_cast<long long>(opts->max_iters) + 1;
+  const long long most = step_cap(opts) + 1;
   long long issued = 0;
   do {
     for (int k = 0; k < rounds && issued < most; ++k, ++issued)
@@ -662,7 +669,7 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
                         bool allow_one_launch, bool allow_gram) {
   const bool async = (opts->flags & MP_SOLVE_ASYNC) != 0;
   HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
-                             static_cast<long long>(opts->max_iters), s));
+                             step_cap(opts), s));
   if (allow_one_launch && c->storage == MP_F32 && c->small.grid > 0 &&
       !(opts->flags & MP_SOLVE_STEP_LAUNCHES)) {
     // (MP_SMALL_SPIN_LIMIT limits the waits of the one launch, which only it has)
@@ -683,7 +690,7 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
         c->prof_ms = 0.0;
         c->prof_launches = 0;
         HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
-                                   static_cast<long long>(opts->max_iters), s));
+                                   step_cap(opts), s));
       }
     }
     // the whole decode in one launch, every share of the dictionary in LDS:
@@ -697,7 +704,7 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
     const bool timed = c->profiling && !async;
     if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
     HIP_TRY(c, mp::launch_f32_small(c->psi32, c->ld, c->n, c->m, b.r_work, c->small,
-                                    c->small_slots, c->small_epoch, opts->max_iters, x, b.st, tr,
+                                    c->small_slots, c->small_epoch, step_cap(opts), x, b.st, tr,
                                     s));
     if (timed) HIP_TRY(c, hipEventRecord(c->ev[1], s));
     if (r) HIP_TRY(c, mp::launch_copy_selected(b.r_work, c->ld, c->n, b.st, r, s));
@@ -734,10 +741,10 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
     c->prof_ms = 0.0;
     c->prof_launches = 0;
     HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
-                               static_cast<long long>(opts->max_iters), s));
+                               step_cap(opts), s));
   }
   long long k = 0;
-  const long long T = opts->max_iters;
+  const long long T = step_cap(opts);
   auto step = [&](hipEvent_t e0, hipEvent_t e1) {
     hipError_t e;
     if (e0 && (e = hipEventRecord(e0, s)) != hipSuccess) return e;
@@ -1320,7 +1327,7 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
                          CarriedBufs{c->st, c->r_work, c->partials, c->bal}, true, true);
 
   HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st, opts->eps,
-                             static_cast<long long>(opts->max_iters), s));
+                             step_cap(opts), s));
   {
     // the host needs the threshold and whether the run is over before it
     // chooses between the persistent and the stepping decode
@@ -1331,7 +1338,7 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
     if (!c->h_st->done)
       HIP_TRY(c, mp::launch_sign_c0(c->psis, c->sign_ws, c->n, c->m, y, c->ld, c->sign_c64,
                                     c->sign_r64, s));
-    const long long T = opts->max_iters;
+    const long long T = step_cap(opts);
     const double thr = c->h_st->thr;
     // batches of steps, unless the caller asks for one launch per step or
     // limits the waits of the persistent launch, which only that has.  A cap
@@ -1343,7 +1350,7 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
       if (gs != MP_OK) return gs;
       if (!persistent) {  // (not reached: every round makes progress)
         HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st, opts->eps,
-                                   static_cast<long long>(opts->max_iters), s));
+                                   step_cap(opts), s));
         HIP_TRY(c, mp::launch_sign_c0(c->psis, c->sign_ws, c->n, c->m, y, c->ld, c->sign_c64,
                                       c->sign_r64, s));
       }
@@ -1791,7 +1798,7 @@ mp_status mp_solve_f64(mp_ctx* ctx, const double* y, double* x, double* r, const
   mp_ctx* c = ctx;
 
   HIP_TRY(c, mp::launch_init_f64(y, c->n, c->ld, x, c->m, c->r64_work, c->st, opts->eps,
-                                 static_cast<long long>(opts->max_iters), s));
+                                 step_cap(opts), s));
   HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
   bool carried = false;  // decoded on carried correlations (r is in half 0)
@@ -1804,13 +1811,13 @@ mp_status mp_solve_f64(mp_ctx* ctx, const double* y, double* x, double* r, const
       c->prof_ms = 0.0;
       c->prof_launches = 0;
       HIP_TRY(c, mp::launch_init_f64(y, c->n, c->ld, x, c->m, c->r64_work, c->st, opts->eps,
-                                     static_cast<long long>(opts->max_iters), s));
+                                     step_cap(opts), s));
     }
   }
   // launch k takes step k (k >= 1) and runs pass k+1: T steps take T+1
   // launches; r ends in the half the state names
   long long k = 0;
-  const long long T = opts->max_iters;
+  const long long T = step_cap(opts);
   const double thr = c->h_st->thr;
   const mp_status st = carried ? MP_OK : run_iterations(c, T > 0 ? T + 1 : 0, s, true, [&](hipEvent_t e0, hipEvent_t e1) {
     hipError_t e;
