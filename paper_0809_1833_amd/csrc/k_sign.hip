@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kSignThreads) void k_mp_step_sign(
     const uint32_t* __restrict__ bits, int64_t ws, int n, int64_t m, int64_t ld,
     double* __restrict__ c64, double* __restrict__ r64, float* __restrict__ r32,
     double* __restrict__ rrp, double inv_n, double inv_sqrt_n, int cols_per_wg, int rows_per_wg,
-    uint64_t* __restrict__ keys, long long k, long long max_iters, double thr,
+    uint64_t* __restrict__ keys, long long k, long long t0, long long max_iters, double thr,
     float* __restrict__ x, DevState* __restrict__ st, mp_trace tr) {
   __shared__ Key2 kred[kSignWaves];
   __shared__ double dred[kSignWaves];
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kSignThreads) void k_mp_step_sign(
     // Step k-1's residual: the stop test of the loop (the same sum, and so
     // the same decision, in every workgroup), then step k's atom.
     const double rr = block_sum<kSignThreads>(rrq, dred);
-    const long long t = k - 1;  // steps taken so far
+    const long long t = t0 + k - 1;  // steps taken so far
     const Key2 win = block_max_key2<kSignThreads>(kp, kred);
     idx = key2_index(win);
     cs = key2_value(win);
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(kSignThreads) void k_mp_step_sign(
     const double step = cs * inv_sqrt_n;
     const uint32_t* pw = bits + static_cast<int64_t>(idx < 0 ? 0 : idx) * ws;
     // the residual trace entry of step k - 1, if the trace asks for one
-    float* rt = !first && tr.r && k - 1 < tr.cap ? tr.r + (k - 1) * tr.ldr : nullptr;
+    float* rt = !first && tr.r && t0 + k - 1 < tr.cap ? tr.r + (t0 + k - 1) * tr.ldr : nullptr;
     double s = 0.0;
     for (int64_t i = row0 + lane; i < row1; i += kWave) {
       const bool lead = i == row0 + lane;
@@ -379,8 +379,8 @@ __global__ __launch_bounds__(kSignThreads) void k_sign_persist(
     const uint32_t* __restrict__ bits, int64_t ws, int n, int64_t m, int64_t ld,
     const double* __restrict__ c64, double* __restrict__ r64, float* __restrict__ r32,
     double inv_n, double inv_sqrt_n, int cols_per_wg, int rows_per_wg,
-    unsigned long long* slots, unsigned epoch, long long spin_limit, long long max_iters, double thr,
-    float* __restrict__ x, DevState* __restrict__ st, mp_trace tr) {
+    unsigned long long* slots, unsigned epoch, long long spin_limit, long long t0,
+    long long max_iters, double thr, float* __restrict__ x, DevState* __restrict__ st, mp_trace tr) {
   extern __shared__ v4u s_bits[];  // this workgroup's columns, nch chunks each
   __shared__ Key2 kred[kSignWaves];
   __shared__ double dred[kSignWaves];
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(kSignThreads) void k_sign_persist(
       }
       // the stop test for the j - 1 steps taken, then step j's atom
       const double rr = block_sum<kSignThreads>(rrq, dred);
-      const long long t = j - 1;
+      const long long t = t0 + j - 1;
       const Key2 win = block_max_key2<kSignThreads>(kp, kred);
       idx = key2_index(win);
       cs = key2_value(win);
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(kSignThreads) void k_sign_persist(
       const double step = cs * inv_sqrt_n;
       const uint32_t* win_words = reinterpret_cast<const uint32_t*>(s_win);
       // the residual trace entry of step j - 1, if the trace asks for one
-      float* rt = j > 0 && tr.r && j - 1 < tr.cap ? tr.r + (j - 1) * tr.ldr : nullptr;
+      float* rt = j > 0 && tr.r && t0 + j - 1 < tr.cap ? tr.r + (t0 + j - 1) * tr.ldr : nullptr;
       double s = 0.0;
 #pragma unroll
       for (int q = 0; q < RPL; ++q) {
@@ -678,8 +678,9 @@ bool sign_persist_resident(int64_t n, int64_t ws, const CorrGeom& g, int num_cus
 
 hipError_t launch_sign_persist(const uint32_t* bits, int64_t ws, int64_t n, int64_t m, int64_t ld,
                                const double* c64, double* r64, float* r32, const CorrGeom& g,
-                               unsigned long long* slots, unsigned epoch, long long max_iters,
-                               double thr, float* x, DevState* st, mp_trace tr, hipStream_t s) {
+                               unsigned long long* slots, unsigned epoch, long long t0,
+                               long long max_iters, double thr, float* x, DevState* st, mp_trace tr,
+                               hipStream_t s) {
   const double inv_n = 1.0 / static_cast<double>(n);
   const double inv_sqrt_n = 1.0 / sqrt(static_cast<double>(n));
   int rows_per_wg = static_cast<int>((ld + g.grid - 1) / g.grid);
@@ -700,7 +701,7 @@ hipError_t launch_sign_persist(const uint32_t* bits, int64_t ws, int64_t n, int6
     return hipErrorInvalidValue;
   void* args[] = {&bits, &ws, &nn, &m, &ld, &c64, &r64, &r32, const_cast<double*>(&inv_n),
                   const_cast<double*>(&inv_sqrt_n), &cols_per_wg, &rows_per_wg, &slots, &epoch,
-                  &spin_limit, &max_iters, &thr, &x, &st, &tr};
+                  &spin_limit, &t0, &max_iters, &thr, &x, &st, &tr};
   const void* fn = sign_persist_fn(n);
   if (hipError_t e = sign_persist_attr(sign_chunks_per_lane(n) == 1 ? 0 : 1, fn); e != hipSuccess)
     return e;
@@ -709,8 +710,9 @@ hipError_t launch_sign_persist(const uint32_t* bits, int64_t ws, int64_t n, int6
 
 hipError_t launch_mp_step_sign(const uint32_t* bits, int64_t ws, int64_t n, int64_t m, int64_t ld,
                                double* c64, double* r64, float* r32, double* rrp,
-                               const CorrGeom& g, uint64_t* keys, long long k, long long max_iters,
-                               double thr, float* x, DevState* st, mp_trace tr, hipStream_t s) {
+                               const CorrGeom& g, uint64_t* keys, long long k, long long t0,
+                               long long max_iters, double thr, float* x, DevState* st, mp_trace tr,
+                               hipStream_t s) {
   const double inv_n = 1.0 / static_cast<double>(n);
   const double inv_sqrt_n = 1.0 / sqrt(static_cast<double>(n));
   const int rows_per_wg = static_cast<int>((ld + g.grid - 1) / g.grid);
@@ -722,11 +724,11 @@ hipError_t launch_mp_step_sign(const uint32_t* bits, int64_t ws, int64_t n, int6
   if (sign_chunks_per_lane(n) == 1)
     k_mp_step_sign<1><<<dim3(g.grid), dim3(kSignThreads), 0, s>>>(
         bits, ws, static_cast<int>(n), m, ld, c64, r64, r32, rrp, inv_n, inv_sqrt_n,
-        g.cols_per_wg, rows_per_wg, keys, k, max_iters, thr, x, st, tr);
+        g.cols_per_wg, rows_per_wg, keys, k, t0, max_iters, thr, x, st, tr);
   else
     k_mp_step_sign<2><<<dim3(g.grid), dim3(kSignThreads), 0, s>>>(
         bits, ws, static_cast<int>(n), m, ld, c64, r64, r32, rrp, inv_n, inv_sqrt_n,
-        g.cols_per_wg, rows_per_wg, keys, k, max_iters, thr, x, st, tr);
+        g.cols_per_wg, rows_per_wg, keys, k, t0, max_iters, thr, x, st, tr);
   return hipGetLastError();
 }
 

@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "k_common.h"
+#include "k_key2.h"
 #include "k_sign_gram.h"
 #include "mp_internal.h"
 
@@ -432,15 +433,12 @@ __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
   __shared__ int s_atom[kSignSteps];
   __shared__ int s_stop, s_pos, s_cut;
   __shared__ int hist[kBins];
-  __shared__ unsigned s_max;
+  __shared__ Key2 s_keys[kDecideWaves];
   const int count = g->count, first = g->first, fill = g->fill;
   const int nbeat = g->nbeat < kSignBeats ? g->nbeat : kSignBeats;
   const long long t0 = st->t;
   int nact = g->nact;
-  if (tid == 0) {
-    s_stop = kSignSteps;
-    s_max = 0;
-  }
+  if (tid == 0) s_stop = kSignSteps;
   if (tid < count) {
     s_c[tid] = g->log_c[tid];
     s_atom[tid] = g->log_atom[tid];
@@ -495,17 +493,20 @@ __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
   int nnew = 0;
   if (!over && fill) {
     // the atoms of largest |c|: whole bins of its leading bits, down to about
-    // kFirstActive atoms (every atom where all can be active)
+    // kFirstActive atoms (every atom where all can be active), and as many as
+    // there is room for of a first bin that is larger.  The largest itself is
+    // always one, so that the next round's first step stands.
     const int want = m <= kSignActive ? static_cast<int>(m) : kFirstActive;
     const int room = m <= kSignActive ? kSignActive : 2 * kFirstActive;
     auto mag = [&](int64_t a) {
       return __builtin_bit_cast(unsigned, static_cast<float>(__builtin_fabs(c64[a]))) >> 19;
     };
-    unsigned top = 0;
-    for (int64_t a = tid; a < m; a += kDecideThreads) top = max(top, mag(a));
-    atomicMax(&s_max, top);
-    __syncthreads();
-    top = s_max;
+    Key2 best{0, 0};
+    for (int64_t a = tid; a < m; a += kDecideThreads)
+      best = key2_max(best, make_key2(c64[a], static_cast<int>(a)));
+    best = block_max_key2<kDecideThreads>(best, s_keys);
+    const int largest = key2_index(best);
+    const unsigned top = mag(largest);
     auto bin = [&](int64_t a) {
       const unsigned b = top - mag(a);
       return static_cast<int>(b < kBins ? b : kBins - 1);
@@ -517,11 +518,13 @@ __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
       if (want == m) b = kBins;
       while (b < kBins && sum < want) sum += hist[b++];
       s_cut = b;
-      s_pos = 0;
+      s_pos = 1;
+      g->atom[0] = largest;
+      pos[largest] = 0;
     }
     __syncthreads();
     for (int64_t a = tid; a < m; a += kDecideThreads)
-      if (bin(a) < s_cut) {
+      if (bin(a) < s_cut && a != largest) {
         const int p = atomicAdd(&s_pos, 1);
         if (p < room) {
           g->atom[p] = static_cast<int>(a);

@@ -336,9 +336,11 @@ int next_chunk(int doubling, long long issued, const mp::DevState* a, const mp::
 // (OMP: several kernels per iteration, `enqueue` brackets the selection
 // launch) every prof_every-th iteration is timed on its own.  Only launches
 // that performed an iteration are counted: a window, all its launches.
+// t0: steps the decode has behind it (the state's t counts from there).
 template <typename Enqueue>
 mp_status run_iterations(mp_ctx* c, long long T, hipStream_t s, bool windowed, Enqueue enqueue,
-                         bool known_running = false, const mp::DevState* dst = nullptr) {
+                         bool known_running = false, const mp::DevState* dst = nullptr,
+                         long long t0 = 0) {
   if (!dst) dst = c->st;
   c->prof_ms = 0.0;
   c->prof_launches = 0;
@@ -362,7 +364,7 @@ mp_status run_iterations(mp_ctx* c, long long T, hipStream_t s, bool windowed, E
     const mp::DevState& sl = h_slot[k];
     const bool late = c->storage == MP_SIGN1 ||
                       (sl.reason != MP_STOP_CONVERGED && sl.reason != MP_STOP_MAX_ITERS);
-    const long long stop_launch = sl.done ? sl.t + (late ? 1 : 0) : LLONG_MAX;
+    const long long stop_launch = sl.done ? sl.t - t0 + (late ? 1 : 0) : LLONG_MAX;
     const int w = windowed ? std::min(c->prof_every, kMaxChunk) : 1;
     for (int j = 0; j + w <= slot_len[k]; j += w) {
       if (slot_base[k] + j + w > stop_launch) break;
@@ -381,7 +383,7 @@ mp_status run_iterations(mp_ctx* c, long long T, hipStream_t s, bool windowed, E
   while (!finished && status == MP_OK) {
     while (inflight < 2 && issued < T && status == MP_OK) {
       const int k = next;
-      int want = next_chunk(chunk, issued, nhist == 2 ? &hist[0] : nullptr,
+      int want = next_chunk(chunk, t0 + issued, nhist == 2 ? &hist[0] : nullptr,
                             nhist >= 1 ? &hist[nhist - 1] : nullptr);
       if (want == 0) {
         if (inflight > 0) break;  // wait for what is in flight
@@ -1258,15 +1260,20 @@ static bool ensure_sign_gram(mp_ctx* c) {
 // rounds: one round at first, which is all that a short decode needs, then up
 // to kRounds with two chunks in flight (a readback leaves the device idle for
 // 10 us, a round after the stop costs 18).  `over`: it reached its stop.
+// Otherwise the rounds brought too few steps (more atoms near the largest
+// |c| than a round can add and name, in an order that names the wrong ones; a
+// round costs about 60 us, a step of the persistent launch 7 to 10): t0 steps
+// stand, and c64, r64, x~ and the state are as of them.
 static mp_status solve_sign_gram(mp_ctx* c, float* x, long long T, double thr, const mp_trace& tr,
-                                 hipStream_t s, bool& over) {
-  constexpr int kRounds = 4;
+                                 hipStream_t s, bool& over, long long& t0) {
+  constexpr int kRounds = 4, kSlowRounds = 8, kSlowSteps = 4;
   const bool timed = c->profiling;
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
   HIP_TRY(c, mp::launch_sgram_init(c->sign_gram, c->m, s));
-  // a round takes a step, makes an atom active or fills the active atoms anew
-  const long long most = 4 * T + 64;
   long long issued = 0, seen = 0;
+  long long total = 0, upto[2] = {0, 0};     // rounds enqueued; up to a chunk's end
+  long long mark_rounds = 0, mark_t = 0;     // where the rate of steps was last looked at
+  bool slow = false;
   over = false;
   auto round = [&](bool first) {
     return mp::launch_sgram_round(c->psis, c->sign_ws, c->n, c->m, c->ld, c->sign_c64, c->sign_r64,
@@ -1274,20 +1281,29 @@ static mp_status solve_sign_gram(mp_ctx* c, float* x, long long T, double thr, c
                                   s);
   };
   HIP_TRY(c, round(true));
-  while (!over && seen < most) {
-    while (issued < most && issued - seen < (seen < 2 ? 1 : 2)) {
+  while (!over && (!slow || issued > seen)) {
+    while (!slow && issued - seen < (seen < 2 ? 1 : 2)) {
       const int rounds = static_cast<int>(std::min<long long>(issued + 1, kRounds));
       for (int k = 0; k < rounds; ++k) HIP_TRY(c, round(false));
       const int k = static_cast<int>(issued & 1);
       HIP_TRY(c, hipMemcpyAsync(&c->h_st[1 + k], c->st, sizeof(mp::DevState),
                                 hipMemcpyDeviceToHost, s));
       HIP_TRY(c, hipEventRecord(c->done_ev[k], s));
+      total += rounds;
+      upto[k] = total;
       ++issued;
     }
     const int k = static_cast<int>(seen & 1);
     HIP_TRY(c, hipEventSynchronize(c->done_ev[k]));
     ++seen;
     over = c->h_st[1 + k].done != 0;
+    t0 = c->h_st[1 + k].t;
+    const long long rounds = upto[k] - mark_rounds;
+    if (rounds >= kSlowRounds) {
+      slow = slow || t0 - mark_t < kSlowSteps * rounds;
+      mark_rounds = upto[k];
+      mark_t = t0;
+    }
   }
   if (timed) {
     HIP_TRY(c, hipEventRecord(c->ev[1], s));
@@ -1320,7 +1336,8 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
   c->rescore_k = opts->rescore_k == 0 ? mp::kLpTopK : opts->rescore_k;
   c->prof_ms = 0.0;
   c->prof_launches = 0;
-  bool persistent = false;  // the one-bit decode ran as one persistent launch
+  bool persistent = false;  // the one-bit decode took no launch per step
+  long long timed_from = 0;  // steps before the launch the profiling events bracket
 
   if (c->storage != MP_SIGN1)
     return solve_carried(c, y, x, r, opts, res, tr, s,
@@ -1340,23 +1357,19 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
                                     c->sign_r64, s));
     const long long T = step_cap(opts);
     const double thr = c->h_st->thr;
+    long long t0 = 0;    // steps behind the launches below
     // batches of steps, unless the caller asks for one launch per step or
     // limits the waits of the persistent launch, which only that has.  A cap
     // of a few steps takes the persistent launch where it fits: it costs 75 us
     // and 7 a step at N = 48 .. 64, the batches 135 and 1.
     if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done &&
         (T > 64 || !c->sign_persist) && !getenv("MP_SIGN_SPIN_LIMIT") && ensure_sign_gram(c)) {
-      const mp_status gs = solve_sign_gram(c, x, T, thr, tr, s, persistent);
+      const mp_status gs = solve_sign_gram(c, x, T, thr, tr, s, persistent, t0);
       if (gs != MP_OK) return gs;
-      if (!persistent) {  // (not reached: every round makes progress)
-        HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st, opts->eps,
-                                   step_cap(opts), s));
-        HIP_TRY(c, mp::launch_sign_c0(c->psis, c->sign_ws, c->n, c->m, y, c->ld, c->sign_c64,
-                                      c->sign_r64, s));
-      }
     }
-    // otherwise the whole decode as one persistent launch when it fits; a
-    // launch the device refuses falls back to stepping
+    // otherwise the whole decode, or what the batches left of it, as one
+    // persistent launch when it fits; a launch the device refuses falls back to
+    // stepping
     if (!persistent && c->sign_persist && !(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done) {
       if (c->profiling) HIP_TRY(c, hipEventRecord(c->ev[0], s));
       // a new tag epoch for every decode (never 0 mod kSignEpochMod: the
@@ -1368,9 +1381,10 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
                                   sizeof(unsigned long long) * mp::kSignSlotWords * 2 *
                                       static_cast<size_t>(c->geom.grid),
                                   s));
+      timed_from = t0;
       const hipError_t e = mp::launch_sign_persist(
           c->psis, c->sign_ws, c->n, c->m, c->ld, c->sign_c64, c->sign_r64, c->r_work, c->geom,
-          c->sign_slots, c->sign_epoch, T, thr, x, c->st, tr, s);
+          c->sign_slots, c->sign_epoch, t0, T, thr, x, c->st, tr, s);
       if (e == hipSuccess) {
         persistent = true;
         if (c->profiling) HIP_TRY(c, hipEventRecord(c->ev[1], s));
@@ -1380,17 +1394,17 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
     }
     long long k = 0;
     const mp_status st = persistent ? MP_OK :
-        run_iterations(c, T > 0 ? T + 2 : 0, s, true, [&](hipEvent_t e0, hipEvent_t e1) {
+        run_iterations(c, T > 0 ? T - t0 + 2 : 0, s, true, [&](hipEvent_t e0, hipEvent_t e1) {
       hipError_t e;
       if (e0 && (e = hipEventRecord(e0, s)) != hipSuccess) return e;
       e = mp::launch_mp_step_sign(c->psis, c->sign_ws, c->n, c->m, c->ld, c->sign_c64,
-                                  c->sign_r64, c->r_work, c->sign_rrp, c->geom, c->partials, k, T,
-                                  thr, x, c->st, tr, s);
+                                  c->sign_r64, c->r_work, c->sign_rrp, c->geom, c->partials, k, t0,
+                                  T, thr, x, c->st, tr, s);
       ++k;
       if (e != hipSuccess) return e;
       if (e1 && (e = hipEventRecord(e1, s)) != hipSuccess) return e;
       return hipSuccess;
-    });
+    }, false, nullptr, t0);
     if (st != MP_OK) return st;
   }
 
@@ -1402,7 +1416,7 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, c->ev[0], c->ev[1]) == hipSuccess) {
       c->prof_ms = ms;
-      c->prof_launches = c->h_st->t + 2;
+      c->prof_launches = c->h_st->t - timed_from + 2;
     }
   }
   if (r) {

@@ -169,20 +169,23 @@ bool sign_persist_fits(int64_t n, int64_t m, int64_t ld, int64_t ws, const CorrG
 bool sign_persist_resident(int64_t n, int64_t ws, const CorrGeom& g, int num_cus);
 hipError_t launch_sign_persist(const uint32_t* bits, int64_t ws, int64_t n, int64_t m, int64_t ld,
                                const double* c64, double* r64, float* r32, const CorrGeom& g,
-                               unsigned long long* slots, unsigned epoch, long long max_iters,
-                               double thr, float* x, DevState* st, mp_trace tr, hipStream_t s);
+                               unsigned long long* slots, unsigned epoch, long long t0,
+                               long long max_iters, double thr, float* x, DevState* st, mp_trace tr,
+                               hipStream_t s);
 // Packed input (ldw words per column) -> ws words per column, rows >= n cleared.
 hipError_t launch_copy_signs(const uint32_t* in, int64_t ldw, int64_t n, int64_t m, int64_t ws,
                              uint32_t* out, hipStream_t s);
 // c(0) = Psi^T y and r = y, both FP64 (c64: m, r64: ld doubles).
 hipError_t launch_sign_c0(const uint32_t* bits, int64_t ws, int64_t n, int64_t m, const float* y,
                           int64_t ld, double* c64, double* r64, hipStream_t s);
-// Launch k of a decode: stop test for the k-1 steps taken, step k, the keys
-// of the next.  keys: 2 halves x 2 words x grid; rrp: 2 halves x grid.
+// Launch k of a decode that has t0 steps behind it (c64, r64, x~ and the state
+// as of them): stop test for the t0 + k - 1 steps taken, the next step, the
+// keys of the one after.  keys: 2 halves x 2 words x grid; rrp: 2 halves x grid.
 hipError_t launch_mp_step_sign(const uint32_t* bits, int64_t ws, int64_t n, int64_t m, int64_t ld,
                                double* c64, double* r64, float* r32, double* rrp,
-                               const CorrGeom& g, uint64_t* keys, long long k, long long max_iters,
-                               double thr, float* x, DevState* st, mp_trace tr, hipStream_t s);
+                               const CorrGeom& g, uint64_t* keys, long long k, long long t0,
+                               long long max_iters, double thr, float* x, DevState* st, mp_trace tr,
+                               hipStream_t s);
 
 // ---- Orthogonal Matching Pursuit, FP32 (k_omp.hip) --------------------------
 struct OmpState {           // the atom selected in the current iteration

@@ -76,3 +76,34 @@ def test_caps_near_the_largest_integer(form):
             _equal(dec.solve(y, 1e-5, cap), want)
             if form != "small":
                 _equal(dec.solve(y, 1e-5, cap, step_launches=True), want)
+
+
+# ---- one-bit dictionaries -------------------------------------------------------
+
+def _sign_same(neg, y, eps, cap):
+    from paper_0809_1833_amd.mp import Decoder
+    kw = dict(trace_cap=max(cap, 1), trace_r=True)
+    with Decoder(_pack(neg), storage="sign", n=neg.shape[1]) as dec:
+        a = dec.solve(y, eps, cap, **kw)
+        b = dec.solve(y, eps, cap, step_launches=True, **kw)
+    _equal(a, b, ("x", "r", "idx", "coef", "rr_trace", "r_trace"))
+    return a
+
+
+@pytest.mark.parametrize("n,m,noise", [(2048, 8192, 0.2), (9000, 16384, 0.05)])
+def test_signs_with_most_atoms_near_the_largest(n, m, noise):
+    """Nested columns, the last ones next to y: thousands of atoms within a few
+    percent of the largest |c|, in an order that fills the active atoms with
+    the smallest of them.  The batches hand the decode on, in the middle or
+    before its first step, and the results are one launch per step's."""
+    most = n // 32 - torch.arange(m, device="cuda") * (n // 32 + 1) // m
+    neg = (torch.arange(n, device="cuda")[None, :] < most[:, None]).to(torch.int8)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    y = 1 + noise * torch.randn(n, generator=g, device="cuda")
+    print(f"[signs nested {n}x{m}]", flush=True)
+    a = _sign_same(neg, y, 1e-6, 200)
+    assert a["iters"] > 20
+    # nested columns beside independent ones: quick steps first
+    neg[: m // 2] = torch.randint(0, 2, (m // 2, n), generator=g, device="cuda", dtype=torch.int8)
+    a = _sign_same(neg, y + 3 * (1 - 2 * neg[:40].float()).sum(0), 1e-6, 400)
+    assert a["iters"] > 40
