@@ -233,8 +233,9 @@ __device__ inline void stage_log(SignLog& l, const SignCarry* __restrict__ g, in
 }
 
 // One atom through the first `count` logged steps.  CHECK: returns the first
-// step at which it beats the step's atom (count: none).  Otherwise adds to x~
-// the coefficients of the steps that selected it.
+// step at which it beats the step's atom (count: none; a step on c* = 0, which
+// ends the run whatever its atom, is beaten by c != 0 alone).  Otherwise adds
+// to x~ the coefficients of the steps that selected it.
 template <bool CHECK>
 __device__ inline int replay_atom(const short* __restrict__ gcol, int64_t mstride, int a,
                                   const SignLog& l, int count, double& c, float& x) {
@@ -251,7 +252,7 @@ __device__ inline int replay_atom(const short* __restrict__ gcol, int64_t mstrid
       const int s = s0 + u;
       if constexpr (CHECK) {
         const double mine = __builtin_fabs(c), best = __builtin_fabs(l.c[s]);
-        const bool won = (mine > best) | ((mine == best) & (a < l.atom[s]));
+        const bool won = (mine > best) | ((mine == best) & (best > 0.0) & (a < l.atom[s]));
         beat = won && s < beat ? s : beat;
       } else {
         const float more = x + static_cast<float>(l.c[s]);

@@ -107,3 +107,28 @@ def test_signs_with_most_atoms_near_the_largest(n, m, noise):
     neg[: m // 2] = torch.randint(0, 2, (m // 2, n), generator=g, device="cuda", dtype=torch.int8)
     a = _sign_same(neg, y + 3 * (1 - 2 * neg[:40].float()).sum(0), 1e-6, 400)
     assert a["iters"] > 40
+
+
+@pytest.mark.parametrize("m", [40, 3000])
+@pytest.mark.parametrize("cap", [10, 100])
+def test_signs_stall(m, cap):
+    """No column correlates with y, at once or after one step: with caps that
+    take the persistent launch and the batches, and with every atom active and
+    only some of them (those that are not have c = 0 as well)."""
+    h = torch.zeros((1, 1), dtype=torch.int8, device="cuda")
+    for _ in range(6):
+        h = torch.cat([torch.cat([h, h], 1), torch.cat([h, 1 - h], 1)], 0)
+    cols = [j % 40 for j in range(m)]
+    for extra in (0.0, 2.0):
+        y = (1 - 2 * h[50].float()) + extra * (1 - 2 * h[7].float())
+        print(f"[signs stall {m} cap {cap} {extra}]", flush=True)
+        a = _sign_same(h[cols].contiguous(), y, 1e-6, cap)
+        assert a["stop"] == "stalled" and a["iters"] == (1 if extra else 0)
+        assert a["iters"] == 0 or int(a["idx"][0]) == 7
+
+
+def test_signs_small_with_a_large_cap():
+    g = torch.Generator(device="cuda").manual_seed(2)
+    neg = torch.randint(0, 2, (65, 33), generator=g, device="cuda", dtype=torch.int8)
+    a = _sign_same(neg, _signal((1 - 2 * neg.float()) / math.sqrt(33), 2), 1e-6, 100)
+    assert a["iters"] >= 2
