@@ -86,6 +86,34 @@ __global__ __launch_bounds__(kBThreads) void k_binit(
   }
 }
 
+// The rounds' state of signals decoded on carried correlations (`from`, with
+// residuals r): those handed on (pad[0]) run on from the steps they have taken,
+// the others have stopped.  x~ stays as it is.  One workgroup per signal.
+__global__ __launch_bounds__(kBThreads) void k_bresume(const DevState* __restrict__ from,
+                                                       const float* __restrict__ r, int64_t ld,
+                                                       float* __restrict__ R32,
+                                                       uint16_t* __restrict__ Rq, int64_t ldq,
+                                                       BSlot* __restrict__ slots) {
+  const int64_t b = blockIdx.x;
+  for (int64_t i = threadIdx.x; i < ld; i += kBThreads) {
+    const float v = r[b * ld + i];
+    R32[b * ld + i] = v;
+    Rq[b * ldq + i] = bf16_rne(v);
+  }
+  if (threadIdx.x == 0) {
+    const DevState& f = from[b];
+    BSlot d{};
+    d.yy = f.yy;
+    d.rr = f.rr;
+    d.thr = f.thr;
+    d.t = f.t;
+    d.max_iters = f.max_iters;
+    d.done = f.pad[0] ? 0 : 1;
+    d.reason = f.pad[0] ? MP_STOP_CONVERGED : f.reason;
+    slots[b] = d;
+  }
+}
+
 // The BF16 dictionary in product tiles: element (atom a, row k) goes to
 // tile (a / 16, k / 32), position (a % 16) * 32 + k % 32; atoms past m (up to
 // the next multiple of 16) are zero.  One 256-thread workgroup per tile row
@@ -690,6 +718,16 @@ hipError_t launch_binit(const float* Y, int64_t ldy, int64_t n, int64_t ld, floa
                         int* act, int* keep, int64_t cap, BState* bs, hipStream_t s) {
   k_binit<<<dim3(nslots), dim3(kBThreads), 0, s>>>(Y, ldy, n, ld, X, ldx, m, R32, Rq, ldq, slots,
                                                    tcap, tcap_all, eps);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_bcompact_init<<<dim3(1), dim3(kBThreads), 0, s>>>(nslots, slots, act, keep, cap, bs);
+  return hipGetLastError();
+}
+
+hipError_t launch_bresume(const DevState* from, const float* r, int64_t ld, float* R32,
+                          uint16_t* Rq, int64_t ldq, BSlot* slots, int nslots, int* act, int* keep,
+                          int64_t cap, BState* bs, hipStream_t s) {
+  k_bresume<<<dim3(nslots), dim3(kBThreads), 0, s>>>(from, r, ld, R32, Rq, ldq, slots);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   k_bcompact_init<<<dim3(1), dim3(kBThreads), 0, s>>>(nslots, slots, act, keep, cap, bs);

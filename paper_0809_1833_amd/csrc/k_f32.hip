@@ -115,13 +115,14 @@ hipError_t launch_init(const float* y, int64_t n, int64_t ld, float* x, int64_t 
 // loads (two per-lane FP32 FMA chains over the column halves, then a
 // butterfly sum across the wave), keys are max-reduced per wave and across
 // the 16 waves, and the workgroup stores its key for launch k+1.  Launch 0
-// runs the first pass on r = y; T steps take T+1 launches.
+// runs the first pass on r = y; T steps take T+1 launches.  (k0: the first
+// launch, k0 steps into a decode that another form began.)
 constexpr int kCorrThreads = 1024;
 
 __global__ __launch_bounds__(kCorrThreads) void k_mp_step_f32(
     const float* __restrict__ psi, int64_t ld, int64_t n, int64_t m, float* __restrict__ rbuf,
     int cols_per_wg, uint64_t* __restrict__ keys, BalState* __restrict__ bal, long long k,
-    long long max_iters, float* __restrict__ x, DevState* __restrict__ st,
+    long long k0, long long max_iters, float* __restrict__ x, DevState* __restrict__ st,
     mp_trace tr) {
   extern __shared__ v4f r_lds[];
   __shared__ uint64_t kred[kCorrThreads / kWave];
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(kCorrThreads) void k_mp_step_f32(
   constexpr int RPT = 16384 / 4 / kCorrThreads;  // float4s of r per thread (ld <= 16384)
   const int ld4 = static_cast<int>(ld / 4);
   const int par = static_cast<int>(k & 1);
-  const bool first = k == 0;
+  const bool first = k == k0;
   const v4f* r_in = reinterpret_cast<const v4f*>(rbuf + (par ? ld : 0));
   v4f* r_out = reinterpret_cast<v4f*>(rbuf + (par ? 0 : ld));
   const int nk = static_cast<int>(gridDim.x);  // <= kCorrThreads (host-checked)
@@ -233,7 +234,7 @@ constexpr unsigned kSmallEpochMod = 4096;
 __global__ __launch_bounds__(kCorrThreads) void k_f32_small(
     const float* __restrict__ psi, int64_t ld, int64_t n, int64_t m, float* __restrict__ rbuf,
     int cols_per_wg, unsigned long long* __restrict__ slots, unsigned epoch,
-    long long spin_limit, long long max_iters, float* __restrict__ x,
+    long long spin_limit, long long k0, long long max_iters, float* __restrict__ x,
     DevState* __restrict__ st, mp_trace tr) {
   extern __shared__ v4f smem[];  // r (ld4 float4s), then the share's columns
   __shared__ uint64_t s_keys[kSmallRecs];  // the polled keys of a pass
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(kCorrThreads) void k_f32_small(
   if (threadIdx.x == 0)
     s_flag = __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const double thr = st->thr;
-  // r = y (half 0, written by the init kernel) and the share's columns into LDS
+  // r (half 0: y, or what the steps before k0 left) and the share's columns into LDS
   const v4f* r_in = reinterpret_cast<const v4f*>(rbuf);
   for (int i = threadIdx.x; i < ld4; i += kCorrThreads) r_lds[i] = r_in[i];
   {
@@ -266,8 +267,8 @@ __global__ __launch_bounds__(kCorrThreads) void k_f32_small(
   if (threadIdx.x == 0) s_flag = 0;
   v4f* r_out = reinterpret_cast<v4f*>(rbuf + ld);  // workgroup 0 keeps r_k here (half 1)
 
-  for (long long k = 0;; ++k) {
-    if (k > 0) {
+  for (long long k = k0;; ++k) {
+    if (k > k0) {
       // every wave's key of pass k (published with step field k): record
       // wg * kSmallWaves + wave of the pass's half
       uint64_t kp = 0;
@@ -403,8 +404,8 @@ CorrGeom small_geometry(int64_t ld, int64_t m, int num_cus) {
 
 hipError_t launch_f32_small(const float* psi, int64_t ld, int64_t n, int64_t m, float* rbuf,
                             const CorrGeom& g, unsigned long long* slots, unsigned epoch,
-                            long long max_iters, float* x, DevState* st, mp_trace tr,
-                            hipStream_t s) {
+                            long long k0, long long max_iters, float* x, DevState* st,
+                            mp_trace tr, hipStream_t s) {
   if (g.grid < 1 || g.grid > kSmallMaxWgs) return hipErrorInvalidValue;
   // polls per wait before the run is marked failed; MP_SMALL_SPIN_LIMIT (a
   // non-negative integer; 0 gives up at the first wait) overrides it, so
@@ -418,8 +419,8 @@ hipError_t launch_f32_small(const float* psi, int64_t ld, int64_t n, int64_t m, 
   const size_t lds = static_cast<size_t>(4 * ld * (g.cols_per_wg + 1));
   if (lds > static_cast<size_t>(kSmallLds)) return hipErrorInvalidValue;
   k_f32_small<<<dim3(g.grid), dim3(kCorrThreads), lds, s>>>(psi, ld, n, m, rbuf, g.cols_per_wg,
-                                                            slots, epoch, spin_limit, max_iters,
-                                                            x, st, tr);
+                                                            slots, epoch, spin_limit, k0,
+                                                            max_iters, x, st, tr);
   return hipGetLastError();
 }
 
@@ -444,6 +445,27 @@ hipError_t launch_copy_selected(const float* rbuf, int64_t ld, int64_t n, const 
   return hipGetLastError();
 }
 
+// A decode on carried correlations that is handed on: it runs again, with r
+// (half 0) in half `half` as well.
+template <typename T>
+__global__ __launch_bounds__(1024) void k_resume(DevState* st, T* rbuf, int64_t ld, int half) {
+  if (half)
+    for (int64_t i = threadIdx.x; i < ld; i += 1024) rbuf[ld + i] = rbuf[i];
+  if (threadIdx.x == 0) {
+    st->done = 0;
+    st->reason = MP_STOP_CONVERGED;
+    st->pad[0] = 0;
+  }
+}
+
+template <typename T>
+hipError_t launch_resume(DevState* st, T* rbuf, int64_t ld, int half, hipStream_t s) {
+  k_resume<T><<<dim3(1), dim3(1024), 0, s>>>(st, rbuf, ld, half);
+  return hipGetLastError();
+}
+template hipError_t launch_resume<float>(DevState*, float*, int64_t, int, hipStream_t);
+template hipError_t launch_resume<double>(DevState*, double*, int64_t, int, hipStream_t);
+
 CorrGeom corr_f32_geometry(int64_t m, int num_cus) {
   // One 16-wave workgroup per CU (one LDS copy of r per CU, few keys);
   // a workgroup takes at least one column per wave.
@@ -460,8 +482,8 @@ CorrGeom corr_f32_geometry(int64_t m, int num_cus) {
 
 hipError_t launch_mp_step_f32(const float* psi, int64_t ld, int64_t n, int64_t m, float* rbuf,
                               const CorrGeom& g, uint64_t* keys, BalState* bal, long long k,
-                              long long max_iters, float* x, DevState* st, mp_trace tr,
-                              hipStream_t s) {
+                              long long k0, long long max_iters, float* x, DevState* st,
+                              mp_trace tr, hipStream_t s) {
   const size_t lds = static_cast<size_t>(ld) * sizeof(float);
   static bool big_lds = false;  // residuals above 60 KB need the opt-in limit
   if (!big_lds && lds > 60 * 1024) {
@@ -471,7 +493,7 @@ hipError_t launch_mp_step_f32(const float* psi, int64_t ld, int64_t n, int64_t m
     big_lds = true;
   }
   k_mp_step_f32<<<dim3(g.grid), dim3(kCorrThreads), lds, s>>>(
-      psi, ld, n, m, rbuf, g.cols_per_wg, keys, bal, k, max_iters, x, st, tr);
+      psi, ld, n, m, rbuf, g.cols_per_wg, keys, bal, k, k0, max_iters, x, st, tr);
   return hipGetLastError();
 }
 

@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256) void k_init_f64(const double* __restrict__ y, 
 __global__ __launch_bounds__(kF64Threads) void k_mp_step_f64(
     const double* __restrict__ psi, int64_t ld, int64_t n, int64_t m, double* __restrict__ rbuf,
     int cols_per_wg, uint64_t* __restrict__ keys, BalState* __restrict__ bal, long long k,
-    long long max_iters, double thr, double* __restrict__ x, DevState* __restrict__ st,
+    long long k0, long long max_iters, double thr, double* __restrict__ x, DevState* __restrict__ st,
     mp_trace_f64 tr) {
   extern __shared__ v2d r2_lds[];
   __shared__ Key2 kred[kF64Waves];
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kF64Threads) void k_mp_step_f64(
   constexpr int RPT = 16384 / 2 / kF64Threads;  // 16-byte chunks of r per thread (ld <= 16384)
   const int ld2 = static_cast<int>(ld / 2);
   const int par = static_cast<int>(k & 1);
-  const bool first = k == 0;
+  const bool first = k == k0;
   const v2d* r_in = reinterpret_cast<const v2d*>(rbuf + (par ? ld : 0));
   v2d* r_out = reinterpret_cast<v2d*>(rbuf + (par ? 0 : ld));
   const int nk = static_cast<int>(gridDim.x);  // <= kF64Threads (host-checked)
@@ -285,8 +285,8 @@ hipError_t launch_init_f64(const double* y, int64_t n, int64_t ld, double* x, in
 
 hipError_t launch_mp_step_f64(const double* psi, int64_t ld, int64_t n, int64_t m, double* rbuf,
                               const CorrGeom& g, uint64_t* keys, BalState* bal, long long k,
-                              long long max_iters, double thr, double* x, DevState* st,
-                              mp_trace_f64 tr, hipStream_t s) {
+                              long long k0, long long max_iters, double thr, double* x,
+                              DevState* st, mp_trace_f64 tr, hipStream_t s) {
   const size_t lds = static_cast<size_t>(ld) * sizeof(double);
   static size_t lds_set = 60 * 1024;  // above the default limit the opt-in is raised
   if (lds > lds_set) {
@@ -297,7 +297,7 @@ hipError_t launch_mp_step_f64(const double* psi, int64_t ld, int64_t n, int64_t 
     lds_set = lds;
   }
   k_mp_step_f64<<<dim3(g.grid), dim3(kF64Threads), lds, s>>>(
-      psi, ld, n, m, rbuf, g.cols_per_wg, keys, bal, k, max_iters, thr, x, st, tr);
+      psi, ld, n, m, rbuf, g.cols_per_wg, keys, bal, k, k0, max_iters, thr, x, st, tr);
   return hipGetLastError();
 }
 

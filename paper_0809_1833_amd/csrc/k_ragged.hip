@@ -30,6 +30,7 @@
 // of its columns; the workgroup merges them, re-scores up to 8 against the
 // FP32 columns and takes the best re-scored one.
 #include "k_common.h"
+#include "k_gram.h"
 #include "k_lowp.h"
 #include "mp_internal.h"
 
@@ -310,6 +311,9 @@ __device__ inline bool ragged_exchange(uint64_t mine, int lane, int part, int pa
   return ok;
 }
 
+// from: null, or the problems as a decode on carried correlations left them:
+// those it handed on (pad[0]) go on from the steps they have taken, the others
+// are passed over.
 template <int NT, int CC, bool LP>
 __global__ __launch_bounds__(NT) void k_ragged(const RInst* __restrict__ inst,
                                                const RItem* __restrict__ items, int nitems,
@@ -320,7 +324,9 @@ __global__ __launch_bounds__(NT) void k_ragged(const RInst* __restrict__ inst,
                                                RResult* __restrict__ res,
                                                RQueue* __restrict__ q,
                                                unsigned long long* __restrict__ slots,
-                                               long long spin_limit, mp_trace tr) {
+                                               long long spin_limit,
+                                               const GramProb<float>* __restrict__ from,
+                                               mp_trace tr) {
   constexpr int W = NT / kWave;
   extern __shared__ v4f r_lds[];
   float* rf = reinterpret_cast<float*>(r_lds);
@@ -354,21 +360,33 @@ __global__ __launch_bounds__(NT) void k_ragged(const RInst* __restrict__ inst,
         parts > 1 ? slots + static_cast<int64_t>(it.slot) * 2 * kRaggedMaxParts * kRaggedRecWords
                   : nullptr;
     const bool lead = part == 0;  // writes x~, the trace, r and the result
+    if (from && from[id].st->pad[0] == 0) continue;  // (the whole workgroup)
 
     // ---- init (eq. 8) ----
-    if (lead)
-      for (int64_t j = threadIdx.x; j < m; j += NT) x[j] = 0.0f;
-    double s = 0.0;
-    for (int64_t i = threadIdx.x; i < ld; i += NT) {
-      const float v = i < n ? y[i] : 0.0f;
-      rf[i] = v;
-      s += static_cast<double>(v) * v;
+    double s = 0.0, yy, thr, rr;
+    long long t;
+    if (from) {
+      const DevState* st = from[id].st;
+      for (int64_t i = threadIdx.x; i < ld; i += NT) rf[i] = from[id].r[i];
+      yy = st->yy;
+      thr = st->thr;
+      rr = st->rr;
+      t = st->t;
+      __syncthreads();
+    } else {
+      if (lead)
+        for (int64_t j = threadIdx.x; j < m; j += NT) x[j] = 0.0f;
+      for (int64_t i = threadIdx.x; i < ld; i += NT) {
+        const float v = i < n ? y[i] : 0.0f;
+        rf[i] = v;
+        s += static_cast<double>(v) * v;
+      }
+      yy = block_sum<NT>(s, dred);
+      thr = eps * eps * yy;
+      rr = yy;
+      t = 0;
     }
-    const double yy = block_sum<NT>(s, dred);
-    const double thr = eps * eps * yy;
     const long long T = caps ? caps[id] : cap_all;
-    double rr = yy;
-    long long t = 0;
     int reason;
     if (!__builtin_isfinite(yy)) {
       reason = kStopNonFinite;
@@ -530,12 +548,12 @@ static hipError_t launch_ragged_t(int grid, size_t lds, const RInst* inst, const
                                   int nitems, const float* Y, float* X, float* R,
                                   const long long* caps, long long cap_all, double eps,
                                   int rescore_k, RResult* res, RQueue* q,
-                                  unsigned long long* slots, long long spin_limit, mp_trace tr,
-                                  hipStream_t s) {
+                                  unsigned long long* slots, long long spin_limit,
+                                  const GramProb<float>* from, mp_trace tr, hipStream_t s) {
   // instances have n <= 8192, so the residual needs at most 32 KB of LDS
   k_ragged<NT, CC, LP><<<dim3(grid), dim3(NT), lds, s>>>(inst, items, nitems, Y, X, R, caps,
                                                          cap_all, eps, rescore_k, res, q, slots,
-                                                         spin_limit, tr);
+                                                         spin_limit, from, tr);
   return hipGetLastError();
 }
 
@@ -551,7 +569,8 @@ hipError_t launch_ragged(const RConfig& cf, bool lp, int grid, size_t lds, const
                          const RItem* items, int nitems, const float* Y, float* X, float* R,
                          const long long* caps, long long cap_all, double eps, int rescore_k,
                          RResult* res, RQueue* q, unsigned long long* slots, int nslots,
-                         long long spin_limit, mp_trace tr, hipStream_t s) {
+                         long long spin_limit, const GramProb<float>* from, mp_trace tr,
+                         hipStream_t s) {
   const int64_t nwords = static_cast<int64_t>(nslots) * 2 * kRaggedMaxParts * kRaggedRecWords;
   int64_t rb = (nwords + 255) / 256;
   rb = rb < 1 ? 1 : (rb > 256 ? 256 : rb);
@@ -561,8 +580,8 @@ hipError_t launch_ragged(const RConfig& cf, bool lp, int grid, size_t lds, const
 #define MP_RAGGED_CASE(NT, CC, LP)                                                          \
   if (cf.threads == NT && cf.cols_per_wave == CC && lp == LP)                               \
     return launch_ragged_t<NT, CC, LP>(grid, lds, inst, items, nitems, Y, X, R, caps,        \
-                                       cap_all, eps, rescore_k, res, q, slots, spin_limit, tr, \
-                                       s);
+                                       cap_all, eps, rescore_k, res, q, slots, spin_limit,     \
+                                       from, tr, s);
   MP_RAGGED_CASE(256, 1, false)
   MP_RAGGED_CASE(256, 2, false)
   MP_RAGGED_CASE(256, 4, false)

@@ -508,10 +508,13 @@ bool ensure_gram(mp_ctx* c, hipStream_t s) {
 // The decode on carried correlations (k_gram.h), after the init kernel: pairs
 // of a pass and the steps it allows, the host keeping two pairs in flight.
 // `gave_up` is set when the device asks for the stepping form instead (no
-// shortlist narrow enough, or norms outside the bounds' range).
+// shortlist narrow enough, or norms outside the bounds' range): the t0 steps
+// taken stand, and that form goes on from them (the state runs again, r is in
+// half t0 mod 2).
 template <typename T>
 mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* opts,
-                     const typename mp::GramTrace<T>::type& tr, hipStream_t s, bool& gave_up) {
+                     const typename mp::GramTrace<T>::type& tr, hipStream_t s, bool& gave_up,
+                     long long& t0) {
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, sizeof(T));
   const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, sizeof(T) == 8);
   const mp::GramProb<T> p{psi, c->ld, c->n, c->m, c->gram_mp, c->gram_c, c->gram_g, c->gram_map,
@@ -540,8 +543,13 @@ mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* op
     ++seen;
     over = c->h_st[1 + k].done != 0;
     gave_up = c->h_st[1 + k].pad[0] != 0;
+    t0 = c->h_st[1 + k].t;
   }
   if (!over && cap > 0) gave_up = true;  // (not reached: unfinished is never a result)
+  if (gave_up) {
+    HIP_TRY(c, mp::launch_resume<T>(c->st, r_work, c->ld, static_cast<int>(t0 & 1), s));
+    return MP_OK;
+  }
   if (timed) {
     // the decode's time on the device over the steps it took
     HIP_TRY(c, hipEventRecord(c->ev[1], s));
@@ -615,7 +623,7 @@ bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
 // decode holds them, made by the first decode): no passes, so a decode is the
 // products Psi^T y, then the steps in one workgroup, and again each time the
 // carried correlations have lost too many digits.  `used` false: not taken, or
-// handed back (`ran`: the state then needs its init again).
+// handed on after t0 steps, which stand.
 //
 // The one launch that holds the dictionary in LDS (k_f32_small) costs 25 us
 // and 5 a step (its exchange between workgroups), this 60 and 2.4, so low caps
@@ -625,8 +633,8 @@ bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
 // the Gram columns are made where they cost at most 0.1 us a step of the cap
 // (6 us at N = 256, M = 1024).
 mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, const mp_opts* opts,
-                           const mp_trace& tr, hipStream_t s, bool& used, bool& ran) {
-  used = ran = false;
+                           const mp_trace& tr, hipStream_t s, bool& used, long long& t0) {
+  used = false;
   const long long least = c->m <= 512 ? 64 : 96;
   const double cost_us = static_cast<double>(c->m) * static_cast<double>(c->m) *
                          static_cast<double>(c->ld) / 45e6;
@@ -643,7 +651,6 @@ mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, const mp_opts* op
   // every round takes a step (or gives up); two are all that most decodes need,
   // and one brings ||r|| down by three decades
   int rounds = opts->eps >= 1e-3 ? 1 : 2;
-  ran = true;
   const long long most = step_cap(opts) + 1;
   long long issued = 0;
   do {
@@ -655,6 +662,12 @@ mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, const mp_opts* op
     HIP_TRY(c, hipStreamSynchronize(s));
     rounds = 2;
   } while (!c->h_st->done && issued < most);
+  used = c->h_st->done && !c->h_st->pad[0];
+  if (!used) {
+    t0 = c->h_st->t;
+    HIP_TRY(c, mp::launch_resume<float>(c->st, r_work, c->ld, 0, s));
+    return MP_OK;
+  }
   if (timed) {
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, c->ev[0], c->ev[1]) == hipSuccess) {
@@ -662,7 +675,6 @@ mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, const mp_opts* op
       c->prof_launches = c->h_st->t > 0 ? c->h_st->t : 1;
     }
   }
-  used = c->h_st->done && !c->h_st->pad[0];
   return MP_OK;
 }
 
@@ -670,14 +682,15 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
                         mp_result* res, const mp_trace& tr, hipStream_t s, const CarriedBufs& b,
                         bool allow_one_launch, bool allow_gram) {
   const bool async = (opts->flags & MP_SOLVE_ASYNC) != 0;
+  long long t0 = 0;  // steps taken on carried correlations before another form goes on
   HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
                              step_cap(opts), s));
   if (allow_one_launch && c->storage == MP_F32 && c->small.grid > 0 &&
       !(opts->flags & MP_SOLVE_STEP_LAUNCHES)) {
     // (MP_SMALL_SPIN_LIMIT limits the waits of the one launch, which only it has)
     if (allow_gram && !async && opts->max_iters > 0 && !getenv("MP_SMALL_SPIN_LIMIT")) {
-      bool used = false, ran = false;
-      const mp_status fs = solve_small_full(c, b.r_work, x, opts, tr, s, used, ran);
+      bool used = false;
+      const mp_status fs = solve_small_full(c, b.r_work, x, opts, tr, s, used, t0);
       if (fs != MP_OK) return fs;
       if (used) {
         if (r) {
@@ -687,12 +700,6 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
         const mp_status rs = finish_result(c, res);
         if (rs == MP_OK && res) res->persistent = 1;
         return rs;
-      }
-      if (ran) {
-        c->prof_ms = 0.0;
-        c->prof_launches = 0;
-        HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
-                                   step_cap(opts), s));
       }
     }
     // the whole decode in one launch, every share of the dictionary in LDS:
@@ -706,7 +713,7 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
     const bool timed = c->profiling && !async;
     if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
     HIP_TRY(c, mp::launch_f32_small(c->psi32, c->ld, c->n, c->m, b.r_work, c->small,
-                                    c->small_slots, c->small_epoch, step_cap(opts), x, b.st, tr,
+                                    c->small_slots, c->small_epoch, t0, step_cap(opts), x, b.st, tr,
                                     s));
     if (timed) HIP_TRY(c, hipEventRecord(c->ev[1], s));
     if (r) HIP_TRY(c, mp::launch_copy_selected(b.r_work, c->ld, c->n, b.st, r, s));
@@ -714,11 +721,11 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
     HIP_TRY(c, hipMemcpyAsync(c->h_st, b.st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     if (c->profiling) {
-      // the launch time per step taken (t steps, t passes)
+      // the launch time per step it took (each with a pass)
       float ms = 0.f;
       if (hipEventElapsedTime(&ms, c->ev[0], c->ev[1]) == hipSuccess) {
         c->prof_ms = ms;
-        c->prof_launches = c->h_st->t > 0 ? c->h_st->t : 1;
+        c->prof_launches = c->h_st->t > t0 ? c->h_st->t - t0 : 1;
       }
     }
     const mp_status fs = finish_result(c, res);
@@ -732,7 +739,7 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
   if (allow_gram && (c->storage == MP_F32 || c->rescore_k == mp::kLpTopK) && !async &&
       !(opts->flags & MP_SOLVE_STEP_LAUNCHES) && ensure_gram(c, s)) {
     bool gave_up = false;
-    const mp_status gs = solve_gram<float>(c, c->psi32, b.r_work, x, opts, tr, s, gave_up);
+    const mp_status gs = solve_gram<float>(c, c->psi32, b.r_work, x, opts, tr, s, gave_up, t0);
     if (gs != MP_OK) return gs;
     if (!gave_up) {
       if (r) HIP_TRY(c, mp::launch_copy_selected(b.r_work, c->ld, c->n, b.st, r, s));
@@ -740,22 +747,19 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
       HIP_TRY(c, hipStreamSynchronize(s));
       return finish_result(c, res);
     }
-    c->prof_ms = 0.0;
-    c->prof_launches = 0;
-    HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, b.r_work, b.st, opts->eps,
-                               step_cap(opts), s));
   }
-  long long k = 0;
+  long long k = t0;
   const long long T = step_cap(opts);
   auto step = [&](hipEvent_t e0, hipEvent_t e1) {
     hipError_t e;
     if (e0 && (e = hipEventRecord(e0, s)) != hipSuccess) return e;
     if (c->storage == MP_F32)
       e = mp::launch_mp_step_f32(c->psi32, c->ld, c->n, c->m, b.r_work, c->geom, b.keys, b.bal,
-                                 k, T, x, b.st, tr, s);
+                                 k, t0, T, x, b.st, tr, s);
     else
       e = mp::launch_mp_step_lp(c->storage, c->psiq, c->scales, c->psi32, c->ld, c->n, c->m,
-                                b.r_work, c->geom, c->rescore_k, b.keys, k, T, x, b.st, tr, s);
+                                b.r_work, c->geom, c->rescore_k, b.keys, k, t0, T, x, b.st, tr,
+                                s);
     ++k;
     if (e != hipSuccess) return e;
     if (e1 && (e = hipEventRecord(e1, s)) != hipSuccess) return e;
@@ -770,8 +774,8 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
     if (r) HIP_TRY(c, mp::launch_copy_selected(b.r_work, c->ld, c->n, b.st, r, s));
     return enqueue_result(c, b.st, s, 0);
   }
-  const mp_status st = run_iterations(c, T > 0 ? T + 1 : 0, s, true, step,
-                                      /*known_running=*/true, b.st);
+  const mp_status st = run_iterations(c, T > 0 ? T - t0 + 1 : 0, s, true, step,
+                                      /*known_running=*/true, b.st, t0);
   if (st != MP_OK) return st;
   if (r) HIP_TRY(c, mp::launch_copy_selected(b.r_work, c->ld, c->n, b.st, r, s));
   HIP_TRY(c, hipMemcpyAsync(c->h_st, b.st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
@@ -801,12 +805,12 @@ mp_status finish_result(mp_ctx* c, mp_result* res) {
   return MP_OK;
 }
 
-// The batched decode on carried correlations.  `gave_up`: some signal needs
-// the rounds of products instead (the whole batch is then decoded again).
+// The batched decode on carried correlations.  `handed_on`: the signals that
+// need the rounds of products to go on from the steps they have taken.
 mp_status solve_gram_batch(mp_ctx* c, const float* Y, int64_t ldy, int64_t B, float* X,
                            int64_t ldx, const mp_opts* opts, const int64_t* max_iters_b,
-                           const mp_trace& tr, hipStream_t s, bool& gave_up) {
-  gave_up = false;
+                           const mp_trace& tr, hipStream_t s, int64_t& handed_on) {
+  handed_on = 0;
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
   const mp::GramBounds bounds = mp::gram_bounds_full(c->n, c->max_norm);
   if (max_iters_b)
@@ -844,7 +848,7 @@ mp_status solve_gram_batch(mp_ctx* c, const float* Y, int64_t ldy, int64_t B, fl
   HIP_TRY(c, hipStreamSynchronize(s));
   long long most = 0;
   for (int64_t j = 0; j < B; ++j) {
-    gave_up |= c->gram_hbst[j].pad[0] != 0;
+    handed_on += c->gram_hbst[j].pad[0] != 0;
     most = std::max(most, c->gram_hbst[j].t);
   }
   if (timed) {
@@ -978,7 +982,7 @@ void make_gram_ragged(mp_ctx* c, hipStream_t s) {
 }
 
 // The ragged decode on carried correlations.  `gave_up`: some problem needs
-// the persistent launch instead (all are then solved again).
+// the persistent launch to go on from the steps it has taken.
 mp_status solve_gram_ragged(mp_ctx* c, const float* Y, float* X, const mp_opts* opts,
                             const long long* caps, const mp_trace& tr, hipStream_t s,
                             bool& gave_up) {
@@ -1544,9 +1548,10 @@ static bool ensure_omp_carry(mp_ctx* c) {
 // lasts) and kOmpSlots steps (which return at once while they wait for a
 // block), enqueued in chunks of kOmpRounds with two chunks in flight.  A
 // block lasts about fourteen steps: with 4 steps a round the launches that
-// return at once come to about 3 us a step.  `gave_up`: as in solve_gram.
+// return at once come to about 3 us a step.  `gave_up`: as in solve_gram, after
+// `known` steps.
 static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipStream_t s,
-                                bool& gave_up) {
+                                bool& gave_up, long long& known) {
   constexpr int kOmpSlots = 4, kOmpRounds = 4;
   mp::OmpBufs& b = c->omp;
   const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, false);
@@ -1557,7 +1562,7 @@ static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipS
   // every two rounds take a step: a block is followed by a step of its own
   // atom unless it renewed the correlations, and then the next one is
   const long long most = (2 * T + 2) / kOmpRounds + 1;
-  long long issued = 0, seen = 0, known = 0, bound = 0;
+  long long issued = 0, seen = 0, bound = 0;
   bool over = T <= 0;
   while (!over && seen < most) {
     while (issued < most && issued - seen < 2) {
@@ -1588,6 +1593,10 @@ static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipS
     bound = std::min(known + (issued - seen) * kOmpRounds * kOmpSlots, T);
   }
   if (!over) gave_up = true;
+  if (gave_up) {
+    HIP_TRY(c, mp::launch_resume<float>(c->st, c->r_work, c->ld, 0, s));
+    return MP_OK;
+  }
   if (timed) {
     // the decode's time on the device over the steps it took
     HIP_TRY(c, hipEventRecord(c->ev[1], s));
@@ -1625,30 +1634,26 @@ mp_status mp_solve_omp(mp_ctx* ctx, const float* y, float* x, float* r, const mp
   const long long T = std::min<long long>(opts->max_iters, c->n);
   if (mp_status bs = ensure_omp(c, std::max<long long>(T, 1)); bs != MP_OK) return bs;
   mp::OmpBufs& b = c->omp;
-  auto init = [&]() {
-    const hipError_t e = hipMemsetAsync(b.in_s, 0, static_cast<size_t>(c->m), s);
-    return e != hipSuccess ? e : mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st,
-                                                 opts->eps, T, s);
-  };
-  HIP_TRY(c, init());
+  HIP_TRY(c, hipMemsetAsync(b.in_s, 0, static_cast<size_t>(c->m), s));
+  HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st, opts->eps, T, s));
   bool stepping = true;
+  long long it = 0;  // iterations behind or enqueued: a bound on the atoms selected
   if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && ensure_omp_carry(c)) {
-    const mp_status gs = solve_omp_gram(c, tr, T, s, stepping);
+    const mp_status gs = solve_omp_gram(c, tr, T, s, stepping, it);
     if (gs != MP_OK) return gs;
-    if (stepping) HIP_TRY(c, init());
   }
   if (stepping) {
     HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
-    long long it = 0;  // iterations enqueued so far: a bound on the atoms selected
-    const mp_status st = run_iterations(c, T, s, false, [&](hipEvent_t e0, hipEvent_t e1) {
+    const long long t0 = it;
+    const mp_status st = run_iterations(c, T - t0, s, false, [&](hipEvent_t e0, hipEvent_t e1) {
       hipError_t e = mp::launch_omp_select(c->psi32, c->ld, c->m, c->r_work, c->geom, c->partials,
                                            c->st, b, s, e0, e1);
       if (e == hipSuccess)
         e = mp::launch_omp_fit(c->psi32, c->ld, c->n, c->r_work, c->st, b, it, false, tr, s);
       ++it;
       return e;
-    });
+    }, false, nullptr, t0);
     if (st != MP_OK) return st;
   }
   HIP_TRY(c, mp::launch_omp_solve(b, c->st, x, s));
@@ -1816,33 +1821,29 @@ mp_status mp_solve_f64(mp_ctx* ctx, const double* y, double* x, double* r, const
   HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
   bool carried = false;  // decoded on carried correlations (r is in half 0)
+  long long t0 = 0;      // steps taken on them before the stepping form goes on
   if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done && ensure_gram(c, s)) {
     bool gave_up = false;
-    const mp_status gs = solve_gram<double>(c, c->psi64, c->r64_work, x, opts, tr, s, gave_up);
+    const mp_status gs =
+        solve_gram<double>(c, c->psi64, c->r64_work, x, opts, tr, s, gave_up, t0);
     if (gs != MP_OK) return gs;
     carried = !gave_up;
-    if (gave_up) {
-      c->prof_ms = 0.0;
-      c->prof_launches = 0;
-      HIP_TRY(c, mp::launch_init_f64(y, c->n, c->ld, x, c->m, c->r64_work, c->st, opts->eps,
-                                     step_cap(opts), s));
-    }
   }
   // launch k takes step k (k >= 1) and runs pass k+1: T steps take T+1
   // launches; r ends in the half the state names
-  long long k = 0;
+  long long k = t0;
   const long long T = step_cap(opts);
   const double thr = c->h_st->thr;
-  const mp_status st = carried ? MP_OK : run_iterations(c, T > 0 ? T + 1 : 0, s, true, [&](hipEvent_t e0, hipEvent_t e1) {
+  const mp_status st = carried ? MP_OK : run_iterations(c, T > 0 ? T - t0 + 1 : 0, s, true, [&](hipEvent_t e0, hipEvent_t e1) {
     hipError_t e;
     if (e0 && (e = hipEventRecord(e0, s)) != hipSuccess) return e;
     e = mp::launch_mp_step_f64(c->psi64, c->ld, c->n, c->m, c->r64_work, c->geom, c->partials,
-                               c->bal, k, T, thr, x, c->st, tr, s);
+                               c->bal, k, t0, T, thr, x, c->st, tr, s);
     ++k;
     if (e != hipSuccess) return e;
     if (e1 && (e = hipEventRecord(e1, s)) != hipSuccess) return e;
     return hipSuccess;
-  });
+  }, false, nullptr, t0);
   if (st != MP_OK) return st;
 
   HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
@@ -1934,11 +1935,11 @@ mp_status mp_solve_batched(mp_ctx* ctx, const float* Y, int64_t ldy, int64_t B, 
   c->prof_launches = 0;
   // with all 8 candidates re-scored the atom selected is the FP32 argmax,
   // which the carried correlations give without a product per round
+  int64_t left = B;  // signals the rounds decode, or go on with
   if (rk == mp::kLpTopK && tmax > 0 && ensure_gram_batch(c, B, tmax, s)) {
-    bool gave_up = false;
-    const mp_status gs = solve_gram_batch(c, Y, ldy, B, X, ldx, opts, max_iters_b, tr, s, gave_up);
+    const mp_status gs = solve_gram_batch(c, Y, ldy, B, X, ldx, opts, max_iters_b, tr, s, left);
     if (gs != MP_OK) return gs;
-    if (!gave_up) {
+    if (left == 0) {
       if (R) {
         HIP_TRY(c, hipMemcpy2DAsync(R, ldr * sizeof(float), c->gram_br, c->ld * sizeof(float),
                                     c->n * sizeof(float), B, hipMemcpyDeviceToDevice, s));
@@ -1948,16 +1949,20 @@ mp_status mp_solve_batched(mp_ctx* ctx, const float* Y, int64_t ldy, int64_t B, 
     }
     c->prof_ms = 0.0;
     c->prof_launches = 0;
+    if (mp_status st = ensure_batched(c, B, s); st != MP_OK) return st;
+    HIP_TRY(c, mp::launch_bresume(c->gram_bst, c->gram_br, c->ld, c->b_r32, c->b_rq, c->ldq,
+                                  c->b_slots, static_cast<int>(B), c->b_act, c->b_keep, c->bcap,
+                                  c->b_state, s));
+  } else {
+    if (mp_status st = ensure_batched(c, B, s); st != MP_OK) return st;
+    if (max_iters_b)
+      HIP_TRY(c, hipMemcpyAsync(c->b_tcap, max_iters_b, sizeof(long long) * B,
+                                hipMemcpyHostToDevice, s));
+    HIP_TRY(c, mp::launch_binit(Y, ldy, c->n, c->ld, X, ldx, c->m, c->b_r32, c->b_rq, c->ldq,
+                                c->b_slots, max_iters_b ? c->b_tcap : nullptr, opts->max_iters,
+                                opts->eps, static_cast<int>(B), c->b_act, c->b_keep, c->bcap,
+                                c->b_state, s));
   }
-  mp_status st = ensure_batched(c, B, s);
-  if (st != MP_OK) return st;
-  if (max_iters_b)
-    HIP_TRY(c, hipMemcpyAsync(c->b_tcap, max_iters_b, sizeof(long long) * B,
-                              hipMemcpyHostToDevice, s));
-  HIP_TRY(c, mp::launch_binit(Y, ldy, c->n, c->ld, X, ldx, c->m, c->b_r32, c->b_rq, c->ldq,
-                              c->b_slots,
-                              max_iters_b ? c->b_tcap : nullptr, opts->max_iters, opts->eps,
-                              static_cast<int>(B), c->b_act, c->b_keep, c->bcap, c->b_state, s));
 
   // Rounds in chunks, two chunks in flight; the kernels stop doing work once
   // the active list is empty.  No signal runs more than tmax rounds.
@@ -1971,8 +1976,8 @@ mp_status mp_solve_batched(mp_ctx* ctx, const float* Y, int64_t ldy, int64_t B, 
   bool finished = false;
   mp_status status = MP_OK;
   // upper bound on the active count used to size each round's grids: all
-  // B at first, then the count read back after each completed chunk
-  int nact_hint = static_cast<int>(B);
+  // left at first, then the count read back after each completed chunk
+  int nact_hint = static_cast<int>(left);
   auto account = [&](int k, int n_after) {
     if (!c->profiling) return;
     (void)n_after;
@@ -2318,20 +2323,21 @@ mp_status mp_solve_ragged(mp_ctx* ctx, const float* Y, float* X, float* R, const
                               hipMemcpyHostToDevice, s));
   // MP_RAGGED_SPIN_LIMIT limits the waits of the persistent launch, so it
   // selects that launch
+  const mp::GramProb<float>* from = nullptr;  // problems handed on to it
   if ((!lp || rk == mp::kLpTopK) && !getenv("MP_RAGGED_SPIN_LIMIT") && c->gram_rmem) {
     c->prof_ms = 0.0;
     c->prof_launches = 0;
     bool gave_up = false;
     const mp_status gs = solve_gram_ragged(c, Y, X, opts, caps, tr, s, gave_up);
     if (gs != MP_OK) return gs;
+    const auto* probs = static_cast<const mp::GramProb<float>*>(c->gram_rprobs);
+    if (R)
+      HIP_TRY(c, mp::launch_gram_rcopy(probs, c->r_inst, static_cast<int>(c->r_count), R, s));
     if (!gave_up) {
-      if (R) {
-        HIP_TRY(c, mp::launch_gram_rcopy(static_cast<const mp::GramProb<float>*>(c->gram_rprobs),
-                                         c->r_inst, static_cast<int>(c->r_count), R, s));
-        HIP_TRY(c, hipStreamSynchronize(s));
-      }
+      if (R) HIP_TRY(c, hipStreamSynchronize(s));
       return batched_results(c, c->gram_hrst, c->r_count, res, "an instance's y holds NaN or Inf");
     }
+    from = probs;
   }
   int grid = c->num_cus * c->r_cfg.wgs_per_cu;
   if (mp_status is = ragged_items(c, grid, s); is != MP_OK) return is;
@@ -2349,11 +2355,11 @@ mp_status mp_solve_ragged(mp_ctx* ctx, const float* Y, float* X, float* R, const
 
   // (re)capture the solve as a graph when its arguments change
   struct Key {
-    const void *y, *x, *r, *caps, *ti, *tc, *trr, *tres;
+    const void *y, *x, *r, *caps, *ti, *tc, *trr, *tres, *from;
     double eps;
     long long cap_all, tcap, tldr, spin;
     int rk, threads, cc, grid, split, nitems, nslots, pad;
-  } key{Y, X, R, caps, tr.idx, tr.coef, tr.rr, tr.r, opts->eps, opts->max_iters, tr.cap, tr.ldr,
+  } key{Y, X, R, caps, tr.idx, tr.coef, tr.rr, tr.r, from, opts->eps, opts->max_iters, tr.cap, tr.ldr,
         spin_limit, rk, c->r_cfg.threads, c->r_cfg.cols_per_wave, grid, c->r_cfg.split,
         c->r_nitems, c->r_nslots, 0};
   const unsigned char* kb = reinterpret_cast<const unsigned char*>(&key);
@@ -2367,7 +2373,7 @@ mp_status mp_solve_ragged(mp_ctx* ctx, const float* Y, float* X, float* R, const
     hipError_t le = mp::launch_ragged(c->r_cfg, lp, grid, lds, c->r_inst, c->r_items,
                                       c->r_nitems, Y, X, R, caps, opts->max_iters, opts->eps,
                                       rk, c->r_res, c->r_queue, c->r_slots, c->r_nslots,
-                                      spin_limit, tr, c->r_cap_stream);
+                                      spin_limit, from, tr, c->r_cap_stream);
     hipGraph_t g = nullptr;
     hipError_t ee = hipStreamEndCapture(c->r_cap_stream, &g);
     if (le != hipSuccess || ee != hipSuccess) {
@@ -2406,7 +2412,11 @@ mp_status mp_solve_ragged(mp_ctx* ctx, const float* Y, float* X, float* R, const
   }
   bool nonfinite = false, internal = false;
   for (int64_t i = 0; i < c->r_count; ++i) {
-    const mp::RResult& d = c->h_rres[i];
+    mp::RResult d = c->h_rres[i];
+    if (from && c->gram_hrst[i].pad[0] == 0) {  // decoded before the launch
+      const mp::DevState& g = c->gram_hrst[i];
+      d = mp::RResult{g.t, g.yy, g.rr, g.reason, 0};
+    }
     nonfinite |= d.reason == mp::kStopNonFinite;
     internal |= d.reason == mp::kStopInternal;
     if (res) {

@@ -107,8 +107,8 @@ hipError_t noalloc_scratch(int device, void** out);
 CorrGeom small_geometry(int64_t ld, int64_t m, int num_cus);
 hipError_t launch_f32_small(const float* psi, int64_t ld, int64_t n, int64_t m, float* rbuf,
                             const CorrGeom& g, unsigned long long* slots, unsigned epoch,
-                            long long max_iters, float* x, DevState* st, mp_trace tr,
-                            hipStream_t s);
+                            long long k0, long long max_iters, float* x, DevState* st,
+                            mp_trace tr, hipStream_t s);
 unsigned small_epoch_mod();
 int small_slot_words();
 
@@ -117,11 +117,17 @@ hipError_t launch_copy_selected(const float* rbuf, int64_t ld, int64_t n, const 
                                 float* r, hipStream_t s);
 // Launch k of an FP32 decode: step k (k >= 1) and pass k+1.  rbuf: 2 x ld
 // floats (r in half k mod 2); keys: 2 halves x one per workgroup.  The stop
-// threshold is read from st (set by the init kernel).
+// threshold is read from st (set by the init kernel).  k0: the decode's first
+// launch here, the number of steps it has behind it (r in half k0 mod 2, x~ and
+// the state as of them); also in the other forms.
 hipError_t launch_mp_step_f32(const float* psi, int64_t ld, int64_t n, int64_t m, float* rbuf,
                               const CorrGeom& g, uint64_t* keys, BalState* bal, long long k,
-                              long long max_iters, float* x, DevState* st, mp_trace tr,
-                              hipStream_t s);
+                              long long k0, long long max_iters, float* x, DevState* st,
+                              mp_trace tr, hipStream_t s);
+// A decode on carried correlations that is handed on to another form: the state
+// runs again, and r (in half 0) is in half `half` (0 or 1) of rbuf as well.
+template <typename T>
+hipError_t launch_resume(DevState* st, T* rbuf, int64_t ld, int half, hipStream_t s);
 
 // ---- kernels of the FP64 single-signal path (k_f64.hip) ---------------------
 hipError_t launch_norms_f64(const double* psi, int64_t ld, int64_t n, int64_t m, double* norm2,
@@ -133,8 +139,8 @@ hipError_t launch_init_f64(const double* y, int64_t n, int64_t ld, double* x, in
 // doubles (r in half k mod 2); keys: 2 halves x two words per workgroup.
 hipError_t launch_mp_step_f64(const double* psi, int64_t ld, int64_t n, int64_t m, double* rbuf,
                               const CorrGeom& g, uint64_t* keys, BalState* bal, long long k,
-                              long long max_iters, double thr, double* x, DevState* st,
-                              mp_trace_f64 tr, hipStream_t s);
+                              long long k0, long long max_iters, double thr, double* x,
+                              DevState* st, mp_trace_f64 tr, hipStream_t s);
 
 // ---- the one-bit decode in checked batches of steps (k_sign_gram.hip) ---------
 struct SignCarry;
@@ -255,6 +261,12 @@ hipError_t launch_binit(const float* Y, int64_t ldy, int64_t n, int64_t ld, floa
                         int64_t ldx, int64_t m, float* R32, uint16_t* Rq, int64_t ldq, BSlot* slots,
                         const long long* tcap, long long tcap_all, double eps, int nslots,
                         int* act, int* keep, int64_t cap, BState* bs, hipStream_t s);
+// The same start for signals that a decode on carried correlations leaves: the
+// ones it handed on (from[b].pad[0]) go on from their steps, with residuals r
+// (ld floats each) and x~ as they are; the others have stopped.
+hipError_t launch_bresume(const DevState* from, const float* r, int64_t ld, float* R32,
+                          uint16_t* Rq, int64_t ldq, BSlot* slots, int nslots, int* act, int* keep,
+                          int64_t cap, BState* bs, hipStream_t s);
 // Product tile by the number of active signals: 128 atoms (eight waves)
 // while more than atoms128_above are active, 64 atoms while more than
 // atoms64_above, 32 while more than atoms32_above, else 16; the two staged
@@ -318,12 +330,16 @@ struct RConfig {           // launch shape, chosen by the autotuner
 };
 bool ragged_config_valid(const RConfig& cf, bool lp);
 // slots: nslots x 2 x kRaggedMaxParts x kRaggedRecWords words (cleared by the
-// launch before the decode)
+// launch before the decode); from: null, or the problems of a decode on carried
+// correlations, of which those it handed on (st->pad[0]) go on
+template <typename T>
+struct GramProb;
 hipError_t launch_ragged(const RConfig& cf, bool lp, int grid, size_t lds, const RInst* inst,
                          const RItem* items, int nitems, const float* Y, float* X, float* R,
                          const long long* caps, long long cap_all, double eps, int rescore_k,
                          RResult* res, RQueue* q, unsigned long long* slots, int nslots,
-                         long long spin_limit, mp_trace tr, hipStream_t s);
+                         long long spin_limit, const GramProb<float>* from, mp_trace tr,
+                         hipStream_t s);
 
 // ---- reduced-precision storage (k_lowp.hip) ---------------------------------
 constexpr int kLpTopK = 8;  // candidates kept per pass and re-scored in FP32
@@ -336,7 +352,7 @@ hipError_t launch_quant_fp8(const float* psi, int64_t ld, int64_t m, uint8_t* ou
 hipError_t launch_mp_step_lp(mp_dtype storage, const void* psiq, const float* scales,
                              const float* psi32, int64_t ld, int64_t n, int64_t m, float* rbuf,
                              const CorrGeom& g, int rescore_k, uint64_t* keys, long long k,
-                             long long max_iters, float* x, DevState* st,
+                             long long k0, long long max_iters, float* x, DevState* st,
                              mp_trace tr, hipStream_t s);
 
 }  // namespace mp

@@ -132,3 +132,143 @@ def test_signs_small_with_a_large_cap():
     neg = torch.randint(0, 2, (65, 33), generator=g, device="cuda", dtype=torch.int8)
     a = _sign_same(neg, _signal((1 - 2 * neg.float()) / math.sqrt(33), 2), 1e-6, 100)
     assert a["iters"] >= 2
+
+
+@pytest.mark.parametrize("n,clusters", [(2048, 16), (9000, 17)])
+def test_signs_handed_on(n, clusters):
+    """Clusters of 1000 nested columns of about equal |c|: the atom after the
+    first is in a cluster of which no atom is active, and its best come last.
+    Too few steps a round: the persistent launch (17 x 1000 columns of 9000 do not
+    fit it: one launch per step) goes on from where the batches stopped."""
+    from paper_0809_1833_amd.mp import Decoder
+    g = torch.Generator(device="cuda").manual_seed(3)
+    u = torch.randint(0, 2, (clusters, n), generator=g, device="cuda", dtype=torch.int8)
+    flips = n // 32 - torch.arange(1000, device="cuda") * (n // 32 + 1) // 1000
+    flip = (torch.arange(n, device="cuda")[None, :] < flips[:, None]).to(torch.int8)
+    neg = (u[:, None, :] ^ flip[None]).reshape(1000 * clusters, n)
+    a = 1 - 0.003 * torch.arange(clusters, device="cuda")
+    y = (a[:, None] * (1 - 2 * u.float())).sum(0)
+    print(f"[signs clusters {n}]", flush=True)
+    out = _sign_same(neg, y, 1e-6, 300)
+    with Decoder(_pack(neg), storage="sign", n=n) as dec:
+        dec.set_profiling(1)
+        dec.solve(y, 1e-6, 300)
+        # the last form's launches alone (a whole decode counts as its steps and 2)
+        assert dec.kernel_time()[1] < out["iters"] + 2
+
+
+# ---- decodes that carried correlations hand on ------------------------------------
+
+@pytest.mark.parametrize("form,n,m", [("f32", 4096, 200), ("small", 300, 40),
+                                      ("f64", 2048, 100)])
+def test_handed_on_in_the_middle(form, n, m):
+    """Noise outside the span of fewer atoms than rows: the correlations fall
+    far below ||r||, no shortlist is narrow enough any more, and one launch per
+    step (the one launch, for a small dictionary) goes on from there.  Odd and
+    even numbers of steps before it."""
+    from paper_0809_1833_amd.mp import Decoder
+    rows = _rows(n, m, dtype=torch.float64 if form == "f64" else torch.float32)
+    kw = dict(trace_cap=900, trace_r=True)
+    with Decoder(rows.t(), storage="f64" if form == "f64" else "f32") as dec:
+        for seed in range(4):
+            y = _signal(rows, 5, noise=0.3, seed=seed)
+            print(f"[handed on {form} {seed}]", flush=True)
+            a = dec.solve(y, 1e-7, 900, **kw)
+            b = dec.solve(y, 1e-7, 900, step_launches=True, **kw)
+            _equal(a, b, ("x", "r", "idx", "coef", "rr_trace", "r_trace"))
+            assert a["iters"] == 900 and a["rr"] > 0.01 * a["yy"]
+            if form != "small":  # the last form's launches alone are counted
+                dec.set_profiling(1)
+                _equal(dec.solve(y, 1e-7, 900), b)
+                assert 0 < dec.kernel_time()[1] < 890
+                dec.set_profiling(0)
+
+
+@pytest.mark.parametrize("storage", ["bf16", "fp8"])
+def test_reduced_precision_handed_on(storage):
+    from paper_0809_1833_amd.mp import Decoder
+    rows = _rows(4096, 200)
+    with Decoder(rows.t(), storage=storage) as dec:
+        for seed in range(2):
+            y = _signal(rows, 5, noise=0.3, seed=seed)
+            a = dec.solve(y, 1e-7, 901, trace_cap=901, trace_r=True)
+            assert a["iters"] == 901 and float(a["rr_trace"][-1]) == a["rr"]
+            back = y.double() - a["x"].double() @ rows.double()
+            assert float((back - a["r"].double()).norm()) < 1e-4 * float(y.double().norm())
+            # every step takes its own coefficient off the step before's residual
+            r = torch.cat([y[None], a["r_trace"][:-1]])
+            want = torch.addcmul(r, -a["coef"][:, None], rows[a["idx"].long()])
+            assert float((want - a["r_trace"]).abs().max()) < 1e-6 * float(y.abs().max())
+
+
+def _tied(rows, extra=0.0):
+    """100 copies of one atom, and a y that reaches them at its third step."""
+    rows[300:400] = rows[300]
+    return 3 * rows[10] + 2 * rows[20] + rows[300] + extra
+
+
+def test_omp_handed_on():
+    from paper_0809_1833_amd.mp import Decoder
+    rows = _rows(640, 40000)
+    y = _tied(rows, 0.4 * rows[41] + 0.3 * rows[17])
+    kw = dict(trace_cap=40, trace_r=True, omp=True)
+    print("[omp handed on]", flush=True)
+    with Decoder(rows.t()) as dec:
+        a = dec.solve(y, 1e-5, 40, **kw)
+        b = dec.solve(y, 1e-5, 40, step_launches=True, **kw)
+    _equal(a, b, ("x", "r", "idx", "coef", "rr_trace", "r_trace"))
+    assert a["idx"][:3].tolist() == [10, 20, 300] and a["stop"] == "converged"
+
+
+def test_batched_hands_on_the_signals_that_need_it():
+    """One signal with more ties than a step scores, one with noise outside the
+    span, among ordinary ones, which keep the single decode's results."""
+    from paper_0809_1833_amd.mp import Decoder
+    rows = _rows(3000, 410)
+    tied = _tied(rows)
+    ys = [_signal(rows[:300], 6, seed=j) for j in range(5)]
+    ys += [tied, torch.zeros(3000, device="cuda"), _signal(rows[:300], 6, noise=0.3, seed=9)]
+    Y, caps = torch.stack(ys), [400] * 4 + [3] + [400] * 2 + [733]
+    print("[batched handed on]", flush=True)
+    with Decoder(rows.t()) as dec:
+        a = dec.solve_batched(Y.t(), 1e-6, caps, trace_cap=733, trace_r=True)
+        for j in range(7):
+            b = dec.solve(ys[j].contiguous(), 1e-6, caps[j], step_launches=True, trace_cap=400)
+            assert a["iters"][j] == b["iters"] and a["stop"][j] == b["stop"], j
+            assert abs(a["rr"][j] - b["rr"]) <= 1e-12 * b["rr"]
+            assert torch.equal(a["x"][:, j], b["x"]) and torch.equal(a["r"][:, j], b["r"])
+            assert torch.equal(a["idx"][j][: b["iters"]], b["idx"])
+            assert torch.equal(a["coef"][j][: b["iters"]], b["coef"])
+    assert a["idx"][5][:3].tolist() == [10, 20, 300]
+    assert a["iters"][7] == 733 and a["stop"][7] == "max_iters"
+    assert float(a["rr_trace"][7][732]) == a["rr"][7]
+    r = torch.cat([ys[7][None], a["r_trace"][7][:732]])
+    want = torch.addcmul(r, -a["coef"][7][:733, None], rows[a["idx"][7][:733].long()])
+    assert float((want - a["r_trace"][7][:733]).abs().max()) < 1e-6 * float(ys[7].abs().max())
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_ragged_hands_on_the_problems_that_need_it(storage, monkeypatch):
+    """As the persistent launch alone decodes them (BF16: where that finds the
+    FP32 argmax, so without noise outside the span)."""
+    from paper_0809_1833_amd.mp import RaggedDecoder
+    sizes = [(200, 800), (700, 500), (64, 256), (300, 40), (512, 1500)]
+    probs = [_rows(n, m, seed=j) for j, (n, m) in enumerate(sizes)]
+    ys = [_signal(p, 4, seed=j) for j, p in enumerate(probs)]
+    ys[1] = _tied(probs[1])
+    if storage == "f32":
+        ys[3] = _signal(probs[3], 4, noise=0.3)
+    caps = [300, 200, 100, 501, 0]
+    print(f"[ragged handed on {storage}]", flush=True)
+    with RaggedDecoder([p.t() for p in probs], storage=storage) as dec:
+        y = dec.pack(ys)
+        for _ in range(2):  # a second decode replays the launch
+            a = dec.solve(y, 1e-6, caps, trace_cap=501, trace_r=True)
+        monkeypatch.setenv("MP_RAGGED_SPIN_LIMIT", "4194304")
+        b = dec.solve(y, 1e-6, caps, trace_cap=501, trace_r=True)
+    assert a["iters"] == b["iters"] and a["stop"] == b["stop"]
+    assert all(abs(p - q) <= 1e-12 * q for p, q in zip(a["rr"], b["rr"]))
+    assert all(abs(p - q) <= 1e-12 * q for p, q in zip(a["yy"], b["yy"]))
+    for key in ("x", "r", "idx", "coef", "r_trace"):
+        assert torch.equal(a[key], b[key]), key
+    assert a["idx"][1][:3].tolist() == [10, 20, 300]
