@@ -120,7 +120,9 @@ hipError_t launch_gram_steps(const GramProb<T>& p, const GramShape& sh, const Gr
 // ---- Orthogonal Matching Pursuit (k_omp_gram.hip) ---------------------------
 struct OmpCarry {
   int hold;              // the next step waits for a block's pass
-  int cur;               // block position of the last selected atom; -1: P holds it already
+  int fit;               // the last selection is to be fitted by the launches after it
+  int cur;               // block position of the last selected atom; -1: P holds it already,
+                         // or it was not in the block
   long long t0;          // directions before the block
   float err;             // bound on |c~ - <r, psi_m>|
   int slot[kGramReq];    // block positions of the atoms selected from it, in order

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kOmpThreads) void k_omp_proj(
     const float* __restrict__ wv, bool from_atom, float* __restrict__ hp,
     const DevState* __restrict__ st, const OmpState* __restrict__ os,
     const OmpCarry* __restrict__ oc) {
-  if (st->done || (oc && oc->hold)) return;
+  if (st->done || (oc && !oc->fit)) return;
   const long long t = st->t;
   const int64_t j0 = static_cast<int64_t>(blockIdx.x) * kOmpWaves;
   if (j0 >= t) return;  // workgroup-uniform
@@ -125,9 +125,10 @@ __global__ __launch_bounds__(kOmpThreads) void k_omp_proj(
 // workgroup 0 also stores h for R's column): wave w sums j = w mod 16 in
 // increasing order, one row per lane; the 16 partial sums are added in a
 // fixed tree; the workgroup's FP64 sum of w^2 goes to part[b].
-// Pass 2 of a step on carried correlations (dpart): also the sum of squares of
-// d = w - (W_i - sum_s h_s q_s), s over the directions of the block the atom
-// was taken from at position i (split over the waves), with h the sum of both passes.
+// Pass 2 of a step on carried correlations (dpart) whose atom is in the block:
+// also the sum of squares of d = w - (W_i - sum_s h_s q_s), s over the
+// directions of the block the atom was taken from at position i (split over the
+// waves), with h the sum of both passes.
 __global__ __launch_bounds__(kOrthThreads) void k_omp_orth(
     const float* __restrict__ q, int64_t ld, const float* __restrict__ psi,
     const float* __restrict__ wv_in, bool from_atom, const float* __restrict__ hp,
@@ -135,7 +136,8 @@ __global__ __launch_bounds__(kOrthThreads) void k_omp_orth(
     const DevState* __restrict__ st, const OmpState* __restrict__ os,
     const OmpCarry* __restrict__ oc, const float* __restrict__ h1,
     const float* __restrict__ w15, double* __restrict__ dpart) {
-  if (st->done || (oc && oc->hold)) return;
+  if (st->done || (oc && !oc->fit)) return;
+  if (dpart && oc->cur < 0) dpart = nullptr;
   extern __shared__ float h_lds[];  // t floats
   __shared__ float ps[kOrthWaves][kOrthRows];
   __shared__ float pd[kOrthWaves][kOrthRows];
@@ -201,7 +203,7 @@ __global__ __launch_bounds__(kOmpThreads) void k_omp_update(
     int nparts, float* __restrict__ rmat, double* __restrict__ z, float* __restrict__ r,
     DevState* __restrict__ st, const OmpState* __restrict__ os,
     const OmpCarry* __restrict__ oc, mp_trace tr) {
-  if (st->done || (oc && oc->hold)) return;
+  if (st->done || (oc && !oc->fit)) return;
   __shared__ double dred[kOmpWaves];
   const long long t = st->t;
   // w and r in registers for the whole kernel (thread i holds elements

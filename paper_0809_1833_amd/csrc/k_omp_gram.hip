@@ -1,5 +1,5 @@
 // OMP's selection on carried correlations (k_gram.h): the pass over the
-// dictionary runs once for about fourteen atoms instead of once per atom.
+// dictionary runs once for about fifteen atoms instead of once per atom.
 //
 // A block starts with a pass that gives c~ = Psi^T r and, for up to kGramReq
 // candidate atoms, Psi^T w_i with w_i = psi_i - Q Q^T psi_i (the candidates
@@ -9,17 +9,22 @@
 //   Psi^T q_t = (Psi^T w_i - sum_s h_s Psi^T q_s) / rho,  s in the block,
 //
 // a sum over at most kGramReq - 1 stored columns of M (k_omp_carry); the
-// block ends when an atom outside it is selected.  The factorisation itself
-// (k_omp.hip) is computed as without the block, so the carried correlations
-// only shortlist: k_omp_pick bounds their difference from the exact products
-// and scores every atom within it by dot_column_f32, and the selected atoms,
-// Q, R, z and r are the stepping form's bit for bit.  The part of q_t that the
+// block ends with the first atom outside it, which is fitted as well: the next
+// block's pass starts from the r it leaves, so that every pass, the first
+// included, brings a step (decodes of 1 and 4 atoms at N = 4096, M = 8192: 0.15
+// and 0.34 ms; 1.05 and 1.14 while such an atom waited for a pass of its own and
+// 8 rounds were enqueued before the first look at the state; 0.30 and 0.33 with a
+// pass per step).  The factorisation itself (k_omp.hip) is computed as without
+// the block, so the carried correlations only shortlist: k_omp_pick bounds their
+// difference from the exact products and scores every atom within it by
+// dot_column_f32, and the selected atoms, Q, R, z and r are the stepping form's
+// bit for bit.  The part of q_t that the
 // sum above misses (the rounding of both ways to orthogonalise) is measured,
 // not estimated: k_omp_orth leaves its norm.
 //
 // Bound by a step's seven dependent launches (40 us with the factorisation's)
-// and the blocks' passes.  N = 8192, M = 32768, K = 512: 29.4 ms a decode from
-// 95.1 ms with a selection pass of 160 us each step (37 passes of 200 us).
+// and the blocks' passes.  N = 8192, M = 32768, K = 512: 27.9 ms a decode from
+// 95.1 ms with a selection pass of 160 us each step.
 #include "k_common.h"
 #include "k_gram.h"
 #include "k_gram_steps.h"
@@ -37,6 +42,7 @@ constexpr int kOrthChunk = 256;      // rows of H staged at a time
 
 __global__ void k_omp_carry_init(OmpCarry* oc) {
   oc->hold = 1;
+  oc->fit = 0;
   oc->cur = -1;
   oc->t0 = 0;
   oc->err = 0.0f;
@@ -152,9 +158,9 @@ __global__ __launch_bounds__(kCarryThreads) void k_omp_carry(
 
 // ---------------------------------------------------------------------------
 // One workgroup: the error bound after the last step, the atoms within it,
-// the winner; where it is in the block, the step's selection, and otherwise
-// the next block's candidates (the winner, then each wave's best atoms not
-// yet fitted).
+// the winner, which is the step's selection; where it is not in the block (or
+// the correlations have to be renewed first), also the next block's candidates:
+// each wave's best atoms not yet fitted, by the correlations before this step.
 __global__ __launch_bounds__(kPickThreads) void k_omp_pick(
     const float* __restrict__ psi, int64_t ld, int64_t m, const float* __restrict__ r,
     const float* __restrict__ c, const uint64_t* __restrict__ tops, int ntops, GramBounds bd,
@@ -163,7 +169,11 @@ __global__ __launch_bounds__(kPickThreads) void k_omp_pick(
     unsigned char* __restrict__ in_s, int* __restrict__ sel, DevState* __restrict__ st,
     OmpState* __restrict__ os, OmpCarry* __restrict__ oc) {
   const int hold = oc->hold;
-  if (st->done || (hold && !after_pass)) return;
+  if (st->done) return;
+  if (hold && !after_pass) {  // no selection
+    if (threadIdx.x == 0) oc->fit = 0;
+    return;
+  }
   __shared__ uint64_t red[kPickWaves];
   __shared__ Key2 keys[kGramMaxCand];
   __shared__ int cand[kGramMaxCand];
@@ -264,27 +274,28 @@ __global__ __launch_bounds__(kPickThreads) void k_omp_pick(
   }
   const bool fitted = !renew && in_s[win] != 0;
   __syncthreads();  // (before the state below changes)
-  if (bail || fitted || cur >= 0) {
-    if (tid == 0) {
-      if (bail) {
-        st->done = 1;
-        st->pad[0] = 1;
-      } else if (fitted) {  // an atom already fitted
-        st->done = 1;
-        st->reason = MP_STOP_STALLED;
-      } else {
+  if (tid == 0) {
+    if (bail) {
+      st->done = 1;
+      st->pad[0] = 1;
+    } else if (fitted) {  // an atom already fitted
+      st->done = 1;
+      st->reason = MP_STOP_STALLED;
+    } else {
+      if (!renew) {
         os->sel = win;
         os->c = coef;
         sel[t] = win;
         in_s[win] = 1;
-        oc->cur = cur;
-        oc->err = err;
-        if (hold) oc->t0 = t;
-        oc->hold = 0;
       }
+      oc->fit = renew ? 0 : 1;
+      oc->cur = cur;
+      oc->err = err;
+      if (hold) oc->t0 = t;
+      oc->hold = cur >= 0 ? 0 : 1;
     }
-    return;
   }
+  if (bail || fitted || cur >= 0) return;
   // the next block
   float mine[kPickTop];
   int at[kPickTop];
@@ -324,18 +335,12 @@ __global__ __launch_bounds__(kPickThreads) void k_omp_pick(
   __syncthreads();
   if (wave == 0) {
     // the best of the proposals, by rank
-    const int base = win >= 0 ? 1 : 0;
     const uint64_t k0 = lane < kPickWaves * kPickTop ? want[lane] : 0;
     int rank = 0;
     for (int j = 0; j < kPickWaves * kPickTop; ++j) rank += want[j] > k0;
-    if (k0 != 0 && base + rank < kGramReq) oc->ctl.req[base + rank] = key_index(k0);
+    if (k0 != 0 && rank < kGramReq) oc->ctl.req[rank] = key_index(k0);
     const int found = static_cast<int>(__popcll(__ballot(k0 != 0)));
-    if (lane == 0) {
-      if (win >= 0) oc->ctl.req[0] = win;
-      oc->ctl.nreq = base + found < kGramReq ? base + found : kGramReq;
-      oc->hold = 1;
-      oc->cur = -1;
-    }
+    if (lane == 0) oc->ctl.nreq = found < kGramReq ? found : kGramReq;
   }
 }
 

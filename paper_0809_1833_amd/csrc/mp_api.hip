@@ -1483,9 +1483,13 @@ mp_status mp_solve_result(mp_ctx* ctx, mp_result* res) {
 }
 
 // Dictionaries below this many bytes select by a pass every step, which then
-// costs no more than the launches that carrying adds (a decode by carried
-// correlations and by passes: 5.32 and 5.21 ms at N = 2048, M = 8192, 64 MiB;
-// 8.8 and 14.0 ms at N = 4096, M = 16384, 256 MiB).
+// costs no more than the launches that carrying adds (decodes of 16, 64 and 128
+// atoms by carried correlations and by passes, ms: N = 2048, M = 8192, 64 MiB:
+// 5.32 and 5.21 at 128; M = 12288, 96 MiB: 0.84 and 1.37, 3.06 and 3.52, 5.8 and
+// 7.0; N = 4096, M = 8192, 128 MiB: 1.09 and 1.43, 3.1 and 4.0).  Short decodes
+// come to the same: 1, 2, 4 and 8 atoms at 96 MiB 0.16 and 0.29, 0.29 and 0.29,
+// 0.32 and 0.30, 0.48 and 0.61; only two atoms of a large dictionary, a pass
+// each either way, cost more (1 GiB: 0.65 and 0.55).
 constexpr int64_t kOmpCarryBytes = int64_t{96} << 20;
 
 static mp_status ensure_omp(mp_ctx* c, int64_t tq) {
@@ -1513,7 +1517,7 @@ static mp_status ensure_omp(mp_ctx* c, int64_t tq) {
 }
 
 // Whether OMP's selection takes the carried correlations, and their buffers if
-// so.  They save the pass of all steps but about one in fourteen and cost two
+// so.  They save the pass of all steps but about one in fifteen and cost two
 // launches more a step and five more a pass.
 // Without them (column norms not near 1, no memory) every step selects by a
 // pass.
@@ -1545,31 +1549,36 @@ static bool ensure_omp_carry(mp_ctx* c) {
 
 // The OMP decode on carried correlations (k_omp_gram.hip), after the init
 // kernel: rounds of a block (which returns at once while the current one
-// lasts) and kOmpSlots steps (which return at once while they wait for a
-// block), enqueued in chunks of kOmpRounds with two chunks in flight.  A
-// block lasts about fourteen steps: with 4 steps a round the launches that
-// return at once come to about 3 us a step.  `gave_up`: as in solve_gram, after
-// `known` steps.
+// lasts) and some steps (which return at once while they wait for a block),
+// enqueued in chunks.  A block lasts about fifteen steps: with kOmpSlots steps
+// a round the launches that return at once come to about 3 us a step.  The
+// first chunk is one round of one step (its block has no candidates yet), the
+// second one of three, the third one, each looked at before the next is
+// enqueued, so that a decode of a few atoms does not wait for launches past its
+// stop (3 us each); then two chunks in flight, soon of kOmpRounds.  `gave_up`:
+// as in solve_gram, after `known` steps.
 static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipStream_t s,
                                 bool& gave_up, long long& known) {
-  constexpr int kOmpSlots = 4, kOmpRounds = 4;
+  constexpr int kOmpSlots = 4, kOmpRounds = 2;
   mp::OmpBufs& b = c->omp;
   const mp::GramBounds bounds = mp::gram_bounds(c->n, c->max_norm, false);
   const bool timed = c->profiling;
   gave_up = false;
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
   HIP_TRY(c, mp::launch_omp_carry_init(b, s));
-  // every two rounds take a step: a block is followed by a step of its own
-  // atom unless it renewed the correlations, and then the next one is
-  const long long most = (2 * T + 2) / kOmpRounds + 1;
+  // every two rounds take a step: a block is followed by one unless it renewed
+  // the correlations, and then the next one is
+  const long long most = 2 * T + 2;
+  long long rounds = 0, steps = 0, upto[2] = {0, 0};  // enqueued; steps up to a chunk's end
   long long issued = 0, seen = 0, bound = 0;
   bool over = T <= 0;
-  while (!over && seen < most) {
-    while (issued < most && issued - seen < 2) {
-      for (int round = 0; round < kOmpRounds; ++round) {
+  while (!over && (rounds < most || issued > seen)) {
+    while (rounds < most && issued - seen < (seen < 3 ? 1 : 2)) {
+      const int slots = issued == 0 ? 1 : issued == 1 ? 3 : kOmpSlots;
+      for (int round = 0; round < (issued < 5 ? 1 : kOmpRounds); ++round, ++rounds) {
         HIP_TRY(c, mp::launch_omp_block(c->psi32, c->ld, c->n, c->m, c->r_work, b, c->st, bound,
                                         c->num_cus, s));
-        for (int k = 0; k < kOmpSlots; ++k) {
+        for (int k = 0; k < slots; ++k, ++steps) {
           HIP_TRY(c, mp::launch_omp_pick(c->psi32, c->ld, c->m, c->r_work, b, bounds, k == 0,
                                          tr.coef != nullptr, c->st, s));
           HIP_TRY(c, mp::launch_omp_fit(c->psi32, c->ld, c->n, c->r_work, c->st, b, bound, true,
@@ -1581,6 +1590,7 @@ static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipS
       HIP_TRY(c, hipMemcpyAsync(&c->h_st[1 + k], c->st, sizeof(mp::DevState),
                                 hipMemcpyDeviceToHost, s));
       HIP_TRY(c, hipEventRecord(c->done_ev[k], s));
+      upto[k] = steps;
       ++issued;
     }
     const int k = static_cast<int>(seen & 1);
@@ -1590,7 +1600,7 @@ static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipS
     gave_up = c->h_st[1 + k].pad[0] != 0;
     known = c->h_st[1 + k].t;
     // directions there can be once the chunks in flight are done
-    bound = std::min(known + (issued - seen) * kOmpRounds * kOmpSlots, T);
+    bound = std::min(known + steps - upto[k], T);
   }
   if (!over) gave_up = true;
   if (gave_up) {

@@ -272,3 +272,20 @@ def test_ragged_hands_on_the_problems_that_need_it(storage, monkeypatch):
     for key in ("x", "r", "idx", "coef", "r_trace"):
         assert torch.equal(a[key], b[key]), key
     assert a["idx"][1][:3].tolist() == [10, 20, 300]
+
+
+@pytest.mark.parametrize("cap", [1, 2, 3, 4, 7, 15, 16, 31, 33])
+def test_omp_short_decodes(cap):
+    """Stops inside the first chunks and blocks, by the cap and by convergence:
+    an atom outside the block is fitted before the next block's pass."""
+    from paper_0809_1833_amd.mp import Decoder
+    rows = _rows(700, 36033, seed=2)
+    kw = dict(trace_cap=40, trace_r=True, omp=True)
+    print(f"[omp short {cap}]", flush=True)
+    with Decoder(rows.t()) as dec:
+        for k, noise in ((cap, 0.0), (40, 0.05)):
+            y = _signal(rows, k, noise=noise, seed=cap)
+            a = dec.solve(y, 1e-5, cap if noise else 40, **kw)
+            b = dec.solve(y, 1e-5, cap if noise else 40, step_launches=True, **kw)
+            _equal(a, b, ("x", "r", "idx", "coef", "rr_trace", "r_trace"))
+            assert a["iters"] == (cap if noise else a["iters"]) >= min(cap, 5)
