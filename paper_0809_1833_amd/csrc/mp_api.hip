@@ -632,7 +632,7 @@ bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
 // 61, 93 .. 55; cap 100: 95 .. 59, 114 .. 60; cap 160: 138 .. 70, 206 .. 84);
 // the Gram columns are made where they cost at most 0.1 us a step of the cap
 // (6 us at N = 256, M = 1024).
-mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, const mp_opts* opts,
+mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, float* r, const mp_opts* opts,
                            const mp_trace& tr, hipStream_t s, bool& used, long long& t0) {
   used = false;
   const long long least = c->m <= 512 ? 64 : 96;
@@ -658,6 +658,7 @@ mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, const mp_opts* op
       HIP_TRY(c, mp::launch_gram_bround(b, sh, bounds, 1, c->num_cus, issued, c->gram_again, true,
                                         tr, s));
     if (timed) HIP_TRY(c, hipEventRecord(c->ev[1], s));
+    if (r) HIP_TRY(c, mp::launch_copy_selected(r_work, c->ld, c->n, c->st, r, s));
     HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     rounds = 2;
@@ -690,13 +691,9 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
     // (MP_SMALL_SPIN_LIMIT limits the waits of the one launch, which only it has)
     if (allow_gram && !async && opts->max_iters > 0 && !getenv("MP_SMALL_SPIN_LIMIT")) {
       bool used = false;
-      const mp_status fs = solve_small_full(c, b.r_work, x, opts, tr, s, used, t0);
+      const mp_status fs = solve_small_full(c, b.r_work, x, r, opts, tr, s, used, t0);
       if (fs != MP_OK) return fs;
       if (used) {
-        if (r) {
-          HIP_TRY(c, mp::launch_copy_selected(b.r_work, c->ld, c->n, b.st, r, s));
-          HIP_TRY(c, hipStreamSynchronize(s));
-        }
         const mp_status rs = finish_result(c, res);
         if (rs == MP_OK && res) res->persistent = 1;
         return rs;
