@@ -29,7 +29,7 @@ hipError_t launch_sgram_init(const SignGram& b, int64_t m, hipStream_t s);
 // first: no atom is active yet, so there are no steps to take or check.
 hipError_t launch_sgram_round(const uint32_t* bits, int64_t ws, int64_t n, int64_t m, int64_t ld,
                               double* c64, double* r64, float* r32, const CorrGeom& geom,
-                              const SignGram& b, bool first, long long max_iters, double thr,
-                              float* x, DevState* st, mp_trace tr, hipStream_t s);
+                              const SignGram& b, bool first, long long max_iters, float* x,
+                              DevState* st, mp_trace tr, hipStream_t s);
 
 }  // namespace mp

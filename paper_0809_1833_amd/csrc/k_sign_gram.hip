@@ -98,8 +98,9 @@ __global__ __launch_bounds__(256) void k_sgram_init(SignCarry* g, unsigned short
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kStepThreads) void k_sgram_steps(
     const double* __restrict__ c64, const short* __restrict__ h, double inv_n,
-    long long max_iters, double thr, const DevState* __restrict__ st, SignCarry* __restrict__ g) {
+    long long max_iters, const DevState* __restrict__ st, SignCarry* __restrict__ g) {
   if (st->done) return;
+  const double thr = st->thr;
   struct Rec {
     double mag, c;
     int pos;
@@ -422,7 +423,9 @@ __global__ __launch_bounds__(kCheckThreads) void k_sgram_check(
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kDecideThreads) void k_sgram_decide(
     const double* __restrict__ c64, int64_t m, const double* __restrict__ parts, int grid,
-    double thr, long long max_iters, unsigned short* __restrict__ pos, DevState* __restrict__ st, SignCarry* __restrict__ g, mp_trace tr) {
+    long long max_iters, unsigned short* __restrict__ pos, DevState* __restrict__ st,
+    SignCarry* __restrict__ g, mp_trace tr) {
+  const double thr = st->thr;
   const int tid = static_cast<int>(threadIdx.x);
   const int lane = tid % kWave, wave = tid / kWave;
   if (st->done) {
@@ -687,8 +690,8 @@ hipError_t launch_sgram_init(const SignGram& b, int64_t m, hipStream_t s) {
 
 hipError_t launch_sgram_round(const uint32_t* bits, int64_t ws, int64_t n, int64_t m, int64_t ld,
                               double* c64, double* r64, float* r32, const CorrGeom& geom,
-                              const SignGram& b, bool first, long long max_iters, double thr,
-                              float* x, DevState* st, mp_trace tr, hipStream_t s) {
+                              const SignGram& b, bool first, long long max_iters, float* x,
+                              DevState* st, mp_trace tr, hipStream_t s) {
   const double inv_n = 1.0 / static_cast<double>(n);
   const double inv_sqrt_n = 1.0 / sqrt(static_cast<double>(n));
   const int nn = static_cast<int>(n), grid = geom.grid;
@@ -697,8 +700,7 @@ hipError_t launch_sgram_round(const uint32_t* bits, int64_t ws, int64_t n, int64
   const int64_t mstride = sign_gram_stride(m);
   hipError_t e;
   if (!first) {
-    k_sgram_steps<<<dim3(1), dim3(kStepThreads), 0, s>>>(c64, b.h, inv_n, max_iters, thr, st,
-                                                          b.carry);
+    k_sgram_steps<<<dim3(1), dim3(kStepThreads), 0, s>>>(c64, b.h, inv_n, max_iters, st, b.carry);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const int ca = static_cast<int>((m + kCheckThreads - 1) / kCheckThreads);
@@ -709,8 +711,8 @@ hipError_t launch_sgram_round(const uint32_t* bits, int64_t ws, int64_t n, int64
         b.parts, st, b.carry);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  k_sgram_decide<<<dim3(1), dim3(kDecideThreads), 0, s>>>(c64, m, b.parts, grid, thr, max_iters,
-                                                          b.pos, st, b.carry, tr);
+  k_sgram_decide<<<dim3(1), dim3(kDecideThreads), 0, s>>>(c64, m, b.parts, grid, max_iters, b.pos,
+                                                          st, b.carry, tr);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int oa = static_cast<int>((m + kCommitAtoms - 1) / kCommitAtoms);
   const int orows = (grid + kCommitWaves - 1) / kCommitWaves;

@@ -1264,9 +1264,11 @@ static bool ensure_sign_gram(mp_ctx* c) {
 // Otherwise the rounds brought too few steps (more atoms near the largest
 // |c| than a round can add and name, in an order that names the wrong ones; a
 // round costs about 60 us, a step of the persistent launch 7 to 10): t0 steps
-// stand, and c64, r64, x~ and the state are as of them.
-static mp_status solve_sign_gram(mp_ctx* c, float* x, long long T, double thr, const mp_trace& tr,
-                                 hipStream_t s, bool& over, long long& t0) {
+// stand, and c64, r64, x~ and the state are as of them.  The state as last seen
+// is left in *c->h_st; r (not null) is copied with the first chunks, and
+// `r_done` says that it was the last one, so that nothing is left to wait for.
+static mp_status solve_sign_gram(mp_ctx* c, float* x, float* r, long long T, const mp_trace& tr,
+                                 hipStream_t s, bool& over, long long& t0, bool& r_done) {
   constexpr int kRounds = 4, kSlowRounds = 8, kSlowSteps = 4;
   const bool timed = c->profiling;
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
@@ -1278,8 +1280,7 @@ static mp_status solve_sign_gram(mp_ctx* c, float* x, long long T, double thr, c
   over = false;
   auto round = [&](bool first) {
     return mp::launch_sgram_round(c->psis, c->sign_ws, c->n, c->m, c->ld, c->sign_c64, c->sign_r64,
-                                  c->r_work, c->geom, c->sign_gram, first, T, thr, x, c->st, tr,
-                                  s);
+                                  c->r_work, c->geom, c->sign_gram, first, T, x, c->st, tr, s);
   };
   HIP_TRY(c, round(true));
   while (!over && (!slow || issued > seen)) {
@@ -1287,6 +1288,8 @@ static mp_status solve_sign_gram(mp_ctx* c, float* x, long long T, double thr, c
       const int rounds = static_cast<int>(std::min<long long>(issued + 1, kRounds));
       for (int k = 0; k < rounds; ++k) HIP_TRY(c, round(false));
       const int k = static_cast<int>(issued & 1);
+      if (r && issued < 2)
+        HIP_TRY(c, hipMemcpyAsync(r, c->r_work, c->n * sizeof(float), hipMemcpyDeviceToDevice, s));
       HIP_TRY(c, hipMemcpyAsync(&c->h_st[1 + k], c->st, sizeof(mp::DevState),
                                 hipMemcpyDeviceToHost, s));
       HIP_TRY(c, hipEventRecord(c->done_ev[k], s));
@@ -1306,6 +1309,8 @@ static mp_status solve_sign_gram(mp_ctx* c, float* x, long long T, double thr, c
       mark_t = t0;
     }
   }
+  *c->h_st = c->h_st[1 + static_cast<int>((seen - 1) & 1)];
+  r_done = over && seen <= 2;  // (one chunk in flight until then)
   if (timed) {
     HIP_TRY(c, hipEventRecord(c->ev[1], s));
     HIP_TRY(c, hipEventSynchronize(c->ev[1]));
@@ -1346,32 +1351,38 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
 
   HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st, opts->eps,
                              step_cap(opts), s));
+  bool r_done = false;  // r and the state are there already
   {
-    // the host needs the threshold and whether the run is over before it
-    // chooses between the persistent and the stepping decode
-    HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipStreamSynchronize(s));
-    // c(0) = Psi^T y and r = y in FP64; launch k runs the stop test for the
-    // k-1 steps taken and takes step k, so T steps take T+2 launches
-    if (!c->h_st->done)
-      HIP_TRY(c, mp::launch_sign_c0(c->psis, c->sign_ws, c->n, c->m, y, c->ld, c->sign_c64,
-                                    c->sign_r64, s));
     const long long T = step_cap(opts);
-    const double thr = c->h_st->thr;
+    const bool stepwise = (opts->flags & MP_SOLVE_STEP_LAUNCHES) != 0;
     long long t0 = 0;    // steps behind the launches below
     // batches of steps, unless the caller asks for one launch per step or
     // limits the waits of the persistent launch, which only that has.  A cap
     // of a few steps takes the persistent launch where it fits: it costs 75 us
-    // and 7 a step at N = 48 .. 64, the batches 135 and 1.
-    if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done &&
-        (T > 64 || !c->sign_persist) && !getenv("MP_SIGN_SPIN_LIMIT") && ensure_sign_gram(c)) {
-      const mp_status gs = solve_sign_gram(c, x, T, thr, tr, s, persistent, t0);
-      if (gs != MP_OK) return gs;
+    // and 7 a step at N = 48 .. 64, the batches 110 and 1.
+    const bool batches = !stepwise && (T > 64 || !c->sign_persist) &&
+                         !getenv("MP_SIGN_SPIN_LIMIT") && ensure_sign_gram(c);
+    if (!batches) {
+      // the host passes on the threshold, and launches nothing after a stop
+      HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
+      HIP_TRY(c, hipStreamSynchronize(s));
     }
+    // c(0) = Psi^T y and r = y in FP64; launch k runs the stop test for the
+    // k-1 steps taken and takes step k, so T steps take T+2 launches
+    if (batches || !c->h_st->done)
+      HIP_TRY(c, mp::launch_sign_c0(c->psis, c->sign_ws, c->n, c->m, y, c->ld, c->sign_c64,
+                                    c->sign_r64, s));
+    if (batches) {
+      const mp_status gs = solve_sign_gram(c, x, r, T, tr, s, persistent, t0, r_done);
+      if (gs != MP_OK) return gs;
+      // (a decode that the init kernel ended took none of the forms)
+      if (persistent && c->h_st->t == 0 && c->h_st->reason != MP_STOP_STALLED) persistent = false;
+    }
+    const double thr = c->h_st->thr;
     // otherwise the whole decode, or what the batches left of it, as one
     // persistent launch when it fits; a launch the device refuses falls back to
     // stepping
-    if (!persistent && c->sign_persist && !(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done) {
+    if (!persistent && c->sign_persist && !stepwise && !c->h_st->done) {
       if (c->profiling) HIP_TRY(c, hipEventRecord(c->ev[0], s));
       // a new tag epoch for every decode (never 0 mod kSignEpochMod: the
       // zeroed words match no step); when it wraps, clear the words so that
@@ -1409,8 +1420,13 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
     if (st != MP_OK) return st;
   }
 
-  HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
-  HIP_TRY(c, hipStreamSynchronize(s));
+  if (!r_done) {
+    // the one-bit form keeps its FP32 r in the first n floats of r_work
+    if (r)
+      HIP_TRY(c, hipMemcpyAsync(r, c->r_work, c->n * sizeof(float), hipMemcpyDeviceToDevice, s));
+    HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
+    HIP_TRY(c, hipStreamSynchronize(s));
+  }
   if (persistent && c->profiling) {
     // the persistent launch runs t + 2 steps (step j of it does what launch
     // j of the stepping form does): the launch time over the steps
@@ -1420,11 +1436,6 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
       c->prof_launches = c->h_st->t - timed_from + 2;
     }
   }
-  if (r) {
-    // the one-bit form keeps its FP32 r in the first n floats of r_work
-    HIP_TRY(c, hipMemcpyAsync(r, c->r_work, c->n * sizeof(float), hipMemcpyDeviceToDevice, s));
-  }
-  HIP_TRY(c, hipStreamSynchronize(s));
   const mp_status fs = finish_result(c, res);
   if (fs == MP_OK && res) res->persistent = persistent ? 1 : 0;
   return fs;
