@@ -981,7 +981,7 @@ void make_gram_ragged(mp_ctx* c, hipStream_t s) {
 // The ragged decode on carried correlations.  `gave_up`: some problem needs
 // the persistent launch to go on from the steps it has taken.
 mp_status solve_gram_ragged(mp_ctx* c, const float* Y, float* X, const mp_opts* opts,
-                            const long long* caps, const mp_trace& tr, hipStream_t s,
+                            float* R, const long long* caps, const mp_trace& tr, hipStream_t s,
                             bool& gave_up) {
   gave_up = false;
   const mp::GramRagged g{static_cast<const mp::GramProb<float>*>(c->gram_rprobs),
@@ -1017,6 +1017,7 @@ mp_status solve_gram_ragged(mp_ctx* c, const float* Y, float* X, const mp_opts* 
     ++seen;
   }
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[1], s));
+  if (R) HIP_TRY(c, mp::launch_gram_rcopy(g.probs, c->r_inst, g.count, R, s));
   HIP_TRY(c, hipMemcpyAsync(c->gram_hrst, c->gram_rst, sizeof(mp::DevState) * c->r_count,
                             hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
@@ -2346,16 +2347,11 @@ mp_status mp_solve_ragged(mp_ctx* ctx, const float* Y, float* X, float* R, const
     c->prof_ms = 0.0;
     c->prof_launches = 0;
     bool gave_up = false;
-    const mp_status gs = solve_gram_ragged(c, Y, X, opts, caps, tr, s, gave_up);
+    const mp_status gs = solve_gram_ragged(c, Y, X, opts, R, caps, tr, s, gave_up);
     if (gs != MP_OK) return gs;
-    const auto* probs = static_cast<const mp::GramProb<float>*>(c->gram_rprobs);
-    if (R)
-      HIP_TRY(c, mp::launch_gram_rcopy(probs, c->r_inst, static_cast<int>(c->r_count), R, s));
-    if (!gave_up) {
-      if (R) HIP_TRY(c, hipStreamSynchronize(s));
+    if (!gave_up)
       return batched_results(c, c->gram_hrst, c->r_count, res, "an instance's y holds NaN or Inf");
-    }
-    from = probs;
+    from = static_cast<const mp::GramProb<float>*>(c->gram_rprobs);
   }
   int grid = c->num_cus * c->r_cfg.wgs_per_cu;
   if (mp_status is = ragged_items(c, grid, s); is != MP_OK) return is;
