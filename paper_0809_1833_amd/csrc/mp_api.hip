@@ -472,6 +472,21 @@ mp_status enqueue_result(mp_ctx* c, const mp::DevState* st, hipStream_t s, int p
   return MP_OK;
 }
 
+// Whether a cap leaves carried correlations their start: a decode pays for two
+// passes with all right-hand sides before it gains, and takes its steps, if it
+// is allowed only a few, sooner in the form with a launch each.  Carried and
+// that form, us, N x M of 1024 x 4096, 4096 x 16384 and 8192 x 32768:
+//   FP32  cap 3: 124 66, 221 182, 490 532    cap 4: 135 104, 222 264, 493 729
+//   FP64  cap 2: 138 89, 296 238, 766 706    cap 3: 142 102, 298 323, 764 1027
+//   BF16  cap 4: 127 114, 226 191, 486 436   cap 6: 136 131, 233 248, 499 617
+//   FP8   cap 6: 125 130, 229 196, 493 377   cap 8: 138 151, 236 235, 507 476
+//   OMP   cap 3 (96 MiB, 256 MiB, 1 GiB): 288 187, 331 261, 632 617
+//         cap 4: 303 223, 352 323, 644 799
+bool cap_pays(mp_dtype storage, long long cap) {
+  const int few = storage == MP_F64 ? 2 : storage == MP_BF16 ? 4 : storage == MP_FP8_E4M3 ? 6 : 3;
+  return cap > few;
+}
+
 // The buffers of the decode on carried correlations, made by the first
 // decode that takes it: Gram columns for at most a quarter of the
 // dictionary's bytes (n / 4 columns; a decode of K atoms needs little more
@@ -734,7 +749,8 @@ mp_status solve_carried(mp_ctx* c, const float* y, float* x, float* r, const mp_
   // form's, which the carried correlations give without a pass per step
   // (N = 8192, M = 32768, K = 256: BF16 8.1 ms from 89.0, FP8 7.4 from 42.1)
   if (allow_gram && (c->storage == MP_F32 || c->rescore_k == mp::kLpTopK) && !async &&
-      !(opts->flags & MP_SOLVE_STEP_LAUNCHES) && ensure_gram(c, s)) {
+      !(opts->flags & MP_SOLVE_STEP_LAUNCHES) && cap_pays(c->storage, opts->max_iters) &&
+      ensure_gram(c, s)) {
     bool gave_up = false;
     const mp_status gs = solve_gram<float>(c, c->psi32, b.r_work, x, opts, tr, s, gave_up, t0);
     if (gs != MP_OK) return gs;
@@ -1657,7 +1673,7 @@ mp_status mp_solve_omp(mp_ctx* ctx, const float* y, float* x, float* r, const mp
   HIP_TRY(c, mp::launch_init(y, c->n, c->ld, x, c->m, c->r_work, c->st, opts->eps, T, s));
   bool stepping = true;
   long long it = 0;  // iterations behind or enqueued: a bound on the atoms selected
-  if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && ensure_omp_carry(c)) {
+  if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && cap_pays(MP_F32, T) && ensure_omp_carry(c)) {
     const mp_status gs = solve_omp_gram(c, tr, T, s, stepping, it);
     if (gs != MP_OK) return gs;
   }
@@ -1841,7 +1857,8 @@ mp_status mp_solve_f64(mp_ctx* ctx, const double* y, double* x, double* r, const
   HIP_TRY(c, hipStreamSynchronize(s));
   bool carried = false;  // decoded on carried correlations (r is in half 0)
   long long t0 = 0;      // steps taken on them before the stepping form goes on
-  if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done && ensure_gram(c, s)) {
+  if (!(opts->flags & MP_SOLVE_STEP_LAUNCHES) && !c->h_st->done &&
+      cap_pays(MP_F64, opts->max_iters) && ensure_gram(c, s)) {
     bool gave_up = false;
     const mp_status gs =
         solve_gram<double>(c, c->psi64, c->r64_work, x, opts, tr, s, gave_up, t0);
@@ -1955,7 +1972,7 @@ mp_status mp_solve_batched(mp_ctx* ctx, const float* Y, int64_t ldy, int64_t B, 
   // with all 8 candidates re-scored the atom selected is the FP32 argmax,
   // which the carried correlations give without a product per round
   int64_t left = B;  // signals the rounds decode, or go on with
-  if (rk == mp::kLpTopK && tmax > 0 && ensure_gram_batch(c, B, tmax, s)) {
+  if (rk == mp::kLpTopK && tmax > 1 && ensure_gram_batch(c, B, tmax, s)) {
     const mp_status gs = solve_gram_batch(c, Y, ldy, B, X, ldx, opts, max_iters_b, tr, s, left);
     if (gs != MP_OK) return gs;
     if (left == 0) {

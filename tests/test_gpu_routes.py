@@ -289,3 +289,19 @@ def test_omp_short_decodes(cap):
             b = dec.solve(y, 1e-5, cap if noise else 40, step_launches=True, **kw)
             _equal(a, b, ("x", "r", "idx", "coef", "rr_trace", "r_trace"))
             assert a["iters"] == (cap if noise else a["iters"]) >= min(cap, 5)
+
+
+@pytest.mark.parametrize("form", ["f32", "bf16", "fp8", "f64", "omp"])
+def test_low_caps(form):
+    """Around the caps below which a launch per step is taken: those steps."""
+    from paper_0809_1833_amd.mp import Decoder
+    n, m = (640, 40000) if form == "omp" else (900, 3000)
+    rows = _rows(n, m, dtype=torch.float64 if form == "f64" else torch.float32)
+    y = _signal(rows, 12)
+    kw = dict(omp=True) if form == "omp" else {}
+    with Decoder(rows.t(), storage="f32" if form == "omp" else form) as dec:
+        for cap in range(1, 9):
+            a = dec.solve(y, 0.0, cap, trace_cap=cap, **kw)
+            b = dec.solve(y, 0.0, cap, trace_cap=cap, step_launches=True, **kw)
+            _equal(a, b, ("x", "r", "idx", "coef", "rr_trace"))
+            assert a["iters"] == cap
