@@ -881,7 +881,12 @@ mp_status solve_gram_batch(mp_ctx* c, const float* Y, int64_t ldy, int64_t B, fl
 // 17 rounds against 11 for 512 problems); in all at most the dictionaries'
 // bytes and 128 MiB (many tiny problems, whose rounding up would dominate, keep the
 // persistent launch, as do problems past the steps kernel's limits, and a
-// context whose memory does not reach).
+// context whose memory does not reach).  So do FP32 sets of dictionaries that
+// the launch's passes take in a few microseconds a step, several short columns
+// side by side in a wave (whole decodes, carried and that launch with its
+// default and its best shape, us: 64 x 256, 16 problems 233, 133, 118; 64 x
+// 2048 267, 240, 179; 128 x 512 320, 281, 231; 128 x 1024 335, 475, 333, 128
+// problems 540, 912, 649; 192 x 768 415, 937, 712; BF16, 64 x 256 241, 280, 253).
 void make_gram_ragged(mp_ctx* c, hipStream_t s) {
   if (!(c->max_norm > 0.99) || !(c->max_norm < 1.01) || c->r_count > 65535) return;
   const size_t count = static_cast<size_t>(c->r_count);
@@ -889,8 +894,10 @@ void make_gram_ragged(mp_ctx* c, hipStream_t s) {
   if (max_m > 32768) return;
   int64_t lds = 0, work = 0, gcols = 0, maps = 0, tiles = 0, dict = 0;
   std::vector<int64_t> stride(count), slots(count);
+  bool quick = c->storage == MP_F32;  // passes of a few microseconds
   for (size_t i = 0; i < count; ++i) {
     const int64_t ld = round_up(c->r_n[i], kLdAlign), m = c->r_m[i];
+    quick = quick && ld <= 128 && m * (ld / 64) * (ld / 64) <= 2048;
     stride[i] = mp::gram_ragged_stride(c->r_max_ld, max_m, m);
     slots[i] = round_up(
         std::min<int64_t>(std::max<int64_t>(64, c->r_n[i] / 4) + 4 * mp::kGramReq, m) +
@@ -902,7 +909,7 @@ void make_gram_ragged(mp_ctx* c, hipStream_t s) {
     tiles += (m + mp::kGramTile - 1) / mp::kGramTile;
     dict += ld * m;
   }
-  if (lds > 150 * 1024 || gcols > dict + (int64_t{1} << 25)) return;
+  if (quick || lds > 150 * 1024 || gcols > dict + (int64_t{1} << 25)) return;
   const int per = mp::gram_ragged_groups(tiles, c->num_cus);
   std::vector<mp::GramGroup> groups;
   for (int id : c->r_order) {

@@ -305,3 +305,21 @@ def test_low_caps(form):
             b = dec.solve(y, 0.0, cap, trace_cap=cap, step_launches=True, **kw)
             _equal(a, b, ("x", "r", "idx", "coef", "rr_trace"))
             assert a["iters"] == cap
+
+
+def test_ragged_sets_of_quick_problems(monkeypatch):
+    """Around the line below which an FP32 set takes the persistent launch."""
+    from paper_0809_1833_amd.mp import RaggedDecoder
+    for sizes in ([(64, 2048), (40, 100), (128, 512)], [(64, 2049), (40, 100)], [(128, 513)],
+                  [(129, 300), (17, 33)]):
+        probs = [_rows(n, m, seed=j) for j, (n, m) in enumerate(sizes)]
+        ys = [_signal(p, 3, seed=j) for j, p in enumerate(probs)]
+        with RaggedDecoder([p.t() for p in probs]) as dec:
+            y = dec.pack(ys)
+            a = dec.solve(y, 1e-5, 60, trace_cap=60)
+            monkeypatch.setenv("MP_RAGGED_SPIN_LIMIT", "4194304")
+            b = dec.solve(y, 1e-5, 60, trace_cap=60)
+            monkeypatch.delenv("MP_RAGGED_SPIN_LIMIT")
+        assert a["iters"] == b["iters"] and a["stop"] == b["stop"]
+        for key in ("x", "r", "idx", "coef"):
+            assert torch.equal(a[key], b[key]), (sizes, key)
