@@ -313,11 +313,14 @@ __global__ __launch_bounds__(kBCorrThreads) __attribute__((amdgpu_waves_per_eu(2
     for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = v4f{0.f, 0.f, 0.f, 0.f};
 
   const int nsteps = static_cast<int>(ld / 32);
-  // this wave's K-steps: wave, wave + 4, ...; `q` counts them
+  // this wave's K-steps: wave, wave + 4, ...; `q` counts them.  (Columns of 64
+  // rows have two: waves 2 and 3 then load step 0 of the column, unused.  Their own
+  // first step lies past the tile row, and past the dictionary in its last.)
   const int nmine = nsteps > wave ? (nsteps - wave + kBCorrWaves - 1) / kBCorrWaves : 0;
+  const int first = nmine > 0 ? wave : 0;
   v8bf ra[kBPre][TI], rb[kBPre][4];
   auto load_step = [&](int slot, int q) {
-    const int64_t k = static_cast<int64_t>(wave + q * kBCorrWaves) * 32;
+    const int64_t k = static_cast<int64_t>(first + q * kBCorrWaves) * 32;
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti)
       ra[slot][ti] = *reinterpret_cast<const v8bf*>(arow[ti] + k * 16);  // K chunk k / 32

@@ -323,3 +323,27 @@ def test_ragged_sets_of_quick_problems(monkeypatch):
         assert a["iters"] == b["iters"] and a["stop"] == b["stop"]
         for key in ("x", "r", "idx", "coef"):
             assert torch.equal(a[key], b[key]), (sizes, key)
+
+
+@pytest.mark.parametrize("n,m", [(1, 64), (33, 16384), (64, 16384), (64, 16400), (65, 8192)])
+def test_rounds_on_short_columns(n, m):
+    """The rounds of products on columns of at most 64 rows, which two of the
+    product's four waves have no part of (a BF16 dictionary of exactly 2 MiB at
+    M = 16384), and on the next longer ones."""
+    from paper_0809_1833_amd.mp import Decoder
+    rows = _rows(n, m)
+    ys = [_signal(rows, 1 + j % 2, seed=j) for j in range(5)]
+    print(f"[rounds {n}x{m}]", flush=True)
+    with Decoder(rows.t()) as dec:
+        a = dec.solve_batched(torch.stack(ys).t(), 1e-3, 30, trace_cap=30, trace_r=True,
+                              rescore_k=7)
+    for j, y in enumerate(ys):
+        k = a["iters"][j]
+        assert 0 < k <= 30
+        r = torch.cat([y[None], a["r_trace"][j][:k]])
+        want = torch.addcmul(r[:-1], -a["coef"][j][:k, None], rows[a["idx"][j][:k].long()])
+        assert float((want - r[1:]).abs().max()) <= 1e-6 * float(y.abs().max())
+        c = (r[:-1].double() @ rows.double().t()).abs()
+        best = c.gather(1, a["idx"][j][:k, None].long())[:, 0]
+        # BF16 products are off by at most 2^-8 ||r||: 7 candidates are no further behind
+        assert bool((best >= c.max(1).values - r[:-1].double().norm(dim=1) / 128).all())
