@@ -212,11 +212,13 @@ mp_status mp_create(mp_ctx** out, const float* psi, int64_t n, int64_t m, int64_
  * non-negative integer in the environment variable MP_SMALL_SPIN_LIMIT, read
  * at each decode; 0 gives up at the first wait) ends the decode with
  * MP_EDEVICE.  A blocking decode of such a context with a cap of at least 64
- * steps and column norms within 1% of 1 decodes in one workgroup instead, on
- * correlations carried by the Gram columns of all atoms (the same results bit
- * for bit); the context makes these on the first such decode that may take
- * enough steps (M * M floats, rounded up, kept until it is destroyed), and
- * with MP_SMALL_SPIN_LIMIT set keeps the one launch.
+ * steps (96 for M > 512) and column norms within 1% of 1 decodes in one
+ * workgroup instead, on correlations carried by the Gram columns of all atoms
+ * (the same results bit for bit); the context makes these on the first such
+ * decode that may take enough steps (M * M floats, rounded up, at most 64 MiB
+ * or 8 times the dictionary's bytes and an eighth of the free memory, kept
+ * until the context is destroyed), and with MP_SMALL_SPIN_LIMIT set keeps the
+ * one launch.
  *
  * A larger MP_F32 context (M <= 32768, 8 N + 2 M <= 153600 with N rounded up
  * to a multiple of 64, column norms within 1% of 1) decodes on correlations
@@ -228,8 +230,11 @@ mp_status mp_create(mp_ctx** out, const float* psi, int64_t n, int64_t m, int64_
  * atom selected is the FP32 form's (one launch per step finds the same one
  * wherever it is among the pass's 8 candidates).  The first such decode
  * allocates its work buffers on the context (the Gram columns take at most
- * about a quarter of the dictionary's bytes, or M * 1 KiB if that is more);
- * where they cannot be allocated the decode takes one launch per step.
+ * about a quarter of the dictionary's bytes, or M * 1 KiB if that is more, and
+ * no more than an eighth of the free memory); where they cannot be allocated,
+ * with caps of a few steps (3; 4 for MP_BF16, 6 for MP_FP8_E4M3), and from the
+ * step on at which the carried correlations no longer give a short list of
+ * candidates, the decode takes one launch per step.
  *
  * y, x and r must not overlap.  Errors: MP_EINVAL (NULL ctx/y/x/opts, eps < 0
  * or not finite, max_iters < 0, unknown flags, rescore_k outside 0..8),
@@ -287,12 +292,17 @@ mp_status mp_solve_noalloc(mp_ctx* ctx, const float* y, float* x, float* r, cons
  * MP_FP8_E4M3 storage gets a BF16 copy of its dictionary on first use.
  *
  * Where M <= 16384, rescore_k is 8 (or 0), the column norms are within 1% of 1
- * and the caps allow enough steps to pay for them, the context computes the
- * Gram columns of all atoms on first use (M * M floats, rounded up, kept until
- * it is destroyed) and every signal decodes on carried correlations (see
- * mp_solve) in a workgroup of its own: the atom selected each step is the
- * FP32 form's, the one the rounds of products select wherever it is among
- * their 8 candidates.
+ * and a cap is above 1, the context computes the Gram columns of all atoms
+ * (M * M floats, rounded up, at most 64 MiB or 8 times the dictionary's bytes
+ * and an eighth of the free memory, kept until it is destroyed) once a decode
+ * of N / 16 steps would pay for them or its decodes so far would have, and from
+ * then on every signal decodes on carried correlations (see mp_solve) in a
+ * workgroup of its own: the atom selected each step is the FP32 form's, the one
+ * the rounds of products select wherever it is among their 8 candidates.  (So
+ * the same call can select another atom on a context that has made the
+ * columns, where those 8 miss the FP32 argmax.)  A signal whose carried
+ * correlations no longer give a short list of candidates goes on in the rounds
+ * of products.
  *
  *   Y         device: N x B, column b = y of signal b, leading dimension ldy >= N
  *   X         device: M x B, overwritten with the x~ columns, ldx >= M
@@ -515,8 +525,10 @@ mp_status mp_create_ragged(mp_ctx** out, const mp_instance* inst, int64_t count,
  * all instances' passes in one launch and each instance's steps in a
  * workgroup of its own, where every instance has M <= 32768 and 8 N + 2 M <=
  * 153600, the column norms are within 1% of 1, rescore_k is 8 or 0 (MP_BF16)
- * and the Gram columns, allocated with the context (at most the dictionaries'
- * FP32 bytes and 64 MiB), were available; MP_RAGGED_SPIN_LIMIT, if set in the
+ * and the Gram columns, allocated with the context (with their work buffers
+ * about the dictionaries' FP32 bytes and 128 MiB at most, and at most an eighth
+ * of the free memory), were available; an MP_F32 set in which no instance has
+ * more than 128 rows and 2048 columns (512 above 64 rows) does not; MP_RAGGED_SPIN_LIMIT, if set in the
  * environment, selects the persistent launch below, whose waits it limits.
  * The same atoms, coefficients, x~ and r either way.
  *

@@ -472,6 +472,17 @@ mp_status enqueue_result(mp_ctx* c, const mp::DevState* st, hipStream_t s, int p
   return MP_OK;
 }
 
+// Buffers that only make a decode faster take at most an eighth of the memory
+// that is free, so that what a program sets up beside them still fits.
+bool room_for(size_t bytes) {
+  size_t free = 0, total = 0;
+  if (hipMemGetInfo(&free, &total) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return bytes <= free / 8;
+}
+
 // Whether a cap leaves carried correlations their start: a decode pays for two
 // passes with all right-hand sides before it gains, and takes its steps, if it
 // is allowed only a few, sooner in the form with a launch each.  Carried and
@@ -503,7 +514,8 @@ bool ensure_gram(mp_ctx* c, hipStream_t s) {
   const int64_t want = std::max<int64_t>(256, c->n / 4);
   const int64_t slots = round_up(std::min<int64_t>(want, c->m) + mp::kGramReq, 16);
   const size_t row = static_cast<size_t>(c->gram_mp) * sizeof(float);
-  if (hipMalloc(&c->gram_c, row) != hipSuccess ||
+  if (!room_for(row * static_cast<size_t>(slots)) ||
+      hipMalloc(&c->gram_c, row) != hipSuccess ||
       hipMalloc(&c->gram_g, row * static_cast<size_t>(slots)) != hipSuccess ||
       hipMalloc(&c->gram_map, sizeof(uint16_t) * static_cast<size_t>(c->m)) != hipSuccess ||
       hipMalloc(&c->gram_rhs, sizeof(float) * (mp::kGramReq + 1) * static_cast<size_t>(c->ld)) !=
@@ -579,45 +591,78 @@ mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* op
   return MP_OK;
 }
 
-// Whether a batched decode of at most tmax steps takes the carried
-// correlations, and the Gram columns and buffers for B signals if so.
-//
-// The Gram columns of all atoms cost m^2 n multiply-adds, once per context,
-// and m^2 floats; a step costs about 4 us on carried correlations and a round
-// of products and selections about 15.  They are made where a decode to the
-// cap would pay for them at once (at the 45 TFLOP/s the symmetric product
-// reaches, its 2 m^2 n / 2 operations against 11 us a step: N = 2048, M = 8192
-// from a cap of 280 steps on) and they fit 1 GiB (M <= 16384).
-bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
+// Whether the Gram columns of all atoms (m^2 floats, rounded up) suit the
+// context: norms near 1, M <= 16384, and their memory in proportion, at most
+// 64 MiB (M = 4096) or 8 times the dictionary's (M = 8 N).
+bool gram_full_suits(const mp_ctx* c) {
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
-  if (sh.threads == 0 || c->m > 16384 || !(c->max_norm > 0.99) || !(c->max_norm < 1.01))
+  const int64_t bytes = 4 * mp::gram_stride(sh) * c->m;
+  return sh.threads != 0 && c->m <= 16384 && c->max_norm > 0.99 && c->max_norm < 1.01 &&
+         bytes <= std::max<int64_t>(int64_t{64} << 20, 8 * 4 * c->ld * c->m);
+}
+
+// What making them costs, us: the symmetric product's 2 m^2 n / 2 operations at
+// the 70 TFLOP/s that it reaches with the allocation (N = 2048, M = 8192: 1.9 ms;
+// N = 4096, M = 16384: 11.5 ms).
+double gram_full_us(const mp_ctx* c) {
+  return static_cast<double>(c->m) * static_cast<double>(c->m) * static_cast<double>(c->ld) / 70e6;
+}
+
+// What B signals gain on them by every step of the longest, us, against a round
+// of products (rounds of 64 steps less 16, and carried: 500 x 1000, 500 signals
+// 15.1 and 2.4; 2048 x 8192, 2 signals 17.3 and 2.6, 256 signals 32 and 3.0; 4096 x
+// 16384, 4 signals 35.4 and 3.9).
+double gram_gain_us(const mp_ctx* c, int64_t B) {
+  const double elems = static_cast<double>(c->m) * static_cast<double>(c->ld);
+  return 9.0 + 0.33e-6 * elems + 3.3e-9 * elems * static_cast<double>(B);
+}
+
+// The Gram columns of all atoms, made once per context, with one signal's c~
+// and flags behind them; false where they are not there.
+bool make_gram_full(mp_ctx* c, hipStream_t s) {
+  if (c->gram_full || c->gram_full_tried) return c->gram_full != nullptr;
+  c->gram_full_tried = true;
+  const int64_t stride = mp::gram_stride(mp::gram_shape(c->ld, c->m, 4));
+  const size_t bytes = sizeof(float) * static_cast<size_t>(stride) * static_cast<size_t>(c->m);
+  const size_t one = sizeof(float) * static_cast<size_t>(stride);
+  if (!room_for(bytes + one) || hipMalloc(&c->gram_full, bytes + one + 2 * sizeof(int)) != hipSuccess) {
+    (void)hipGetLastError();
+    c->gram_full = nullptr;
     return false;
-  if (!c->gram_full) {
-    const double cost_us = static_cast<double>(c->m) * static_cast<double>(c->m) *
-                           static_cast<double>(c->ld) / 45e6;
-    if (cost_us > 11.0 * static_cast<double>(tmax) || c->gram_full_tried) return false;
-    c->gram_full_tried = true;
-    const int64_t stride = mp::gram_stride(sh);
-    const size_t bytes = sizeof(float) * static_cast<size_t>(stride) * static_cast<size_t>(c->m);
-    if (hipMalloc(&c->gram_full, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      c->gram_full = nullptr;
-      return false;
-    }
-    c->gram_full_mp = stride;
-    if ((stride != c->m && hipMemsetAsync(c->gram_full, 0, bytes, s) != hipSuccess) ||
-        mp::launch_gram_full(c->psi32, c->ld, c->m, c->gram_full, stride, c->num_cus, s) !=
-            hipSuccess) {
-      (void)hipFree(c->gram_full);
-      c->gram_full = nullptr;
-      return false;
-    }
   }
+  c->gram_full_mp = stride;
+  c->gram_sc = c->gram_full + static_cast<size_t>(stride) * static_cast<size_t>(c->m);
+  c->gram_sagain = reinterpret_cast<int*>(c->gram_sc + stride);
+  if (hipMemsetAsync(stride != c->m ? c->gram_full : c->gram_sc, 0,
+                     stride != c->m ? bytes + one : one, s) != hipSuccess ||
+      mp::launch_gram_full(c->psi32, c->ld, c->m, c->gram_full, stride, c->num_cus, s) !=
+          hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(c->gram_full);
+    c->gram_full = nullptr;
+    return false;
+  }
+  return true;
+}
+
+// Whether a batched decode of at most tmax steps takes the carried
+// correlations, with the buffers for B signals if so.  The Gram columns are
+// made where a decode of N / 16 steps (of the cap, if that is lower) would pay for
+// them, or once the rounds of this context's decodes have cost as much more as
+// they would have saved (gram_owed): a context that decodes a few short batches
+// never makes columns that cost more than all of them.
+bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
+  if (!gram_full_suits(c)) return false;
+  const double likely = std::min<double>(static_cast<double>(tmax), std::max<double>(2.0, c->n / 16.0));
+  if (!c->gram_full && gram_full_us(c) > std::max(gram_gain_us(c, B) * likely, c->gram_owed))
+    return false;
+  if (!make_gram_full(c, s)) return false;
   if (B <= c->gram_bcap) return true;
   free_gram_batch(c);
   const size_t b = static_cast<size_t>(B);
   const size_t cbytes = sizeof(float) * static_cast<size_t>(c->gram_full_mp) * b;
-  if (hipMalloc(&c->gram_bc, cbytes) != hipSuccess ||
+  if (!room_for(cbytes + sizeof(float) * static_cast<size_t>(c->ld) * b) ||
+      hipMalloc(&c->gram_bc, cbytes) != hipSuccess ||
       hipMalloc(&c->gram_br, sizeof(float) * static_cast<size_t>(c->ld) * b) != hipSuccess ||
       hipMalloc(&c->gram_bst, sizeof(mp::DevState) * b) != hipSuccess ||
       hipMalloc(&c->gram_again, 2 * sizeof(int)) != hipSuccess ||
@@ -640,26 +685,26 @@ bool ensure_gram_batch(mp_ctx* c, int64_t B, long long tmax, hipStream_t s) {
 // carried correlations have lost too many digits.  `used` false: not taken, or
 // handed on after t0 steps, which stand.
 //
-// The one launch that holds the dictionary in LDS (k_f32_small) costs 25 us
-// and 5 a step (its exchange between workgroups), this 60 and 2.4, so low caps
-// stay there (20 K steps allowed, decodes to ||r|| of 1e-6 .. 0.04, this
-// against that: M = 192, cap 80: 92 .. 51 us, 150 .. 55; M = 1024, cap 80: 86 ..
-// 61, 93 .. 55; cap 100: 95 .. 59, 114 .. 60; cap 160: 138 .. 70, 206 .. 84);
-// the Gram columns are made where they cost at most 0.1 us a step of the cap
-// (6 us at N = 256, M = 1024).
+// The one launch that holds the dictionary in LDS (k_f32_small) costs 30 us
+// and 5 a step (its exchange between workgroups), this 43 and 2.4, so low caps
+// stay there.  Decodes of K atoms under a cap of 20 K, to ||r|| of 1e-6 ||y|| and of
+// 0.04 ||y||, here and in that launch, us: M = 192, K = 4: 92 and 150, 51 and 55; M =
+// 1024, K = 4: 86 and 93, 61 and 55; K = 5: 95 and 114, 59 and 60; K = 8: 138 and
+// 206, 70 and 84.  (A decode that takes a few steps of a large cap is slower here:
+// N = 256, M = 1024, 1 step 45 and 36, 5 steps 63 and 56, 12 steps 78 and 90.)  The
+// Gram columns are made where they cost at most 0.065 us a step of the cap (4 us
+// at N = 256, M = 1024).
 mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, float* r, const mp_opts* opts,
                            const mp_trace& tr, hipStream_t s, bool& used, long long& t0) {
   used = false;
   const long long least = c->m <= 512 ? 64 : 96;
-  const double cost_us = static_cast<double>(c->m) * static_cast<double>(c->m) *
-                         static_cast<double>(c->ld) / 45e6;
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
-  if (opts->max_iters < least || sh.threads * sh.per_thread > 8192 ||
-      (!c->gram_full && cost_us > 0.1 * static_cast<double>(opts->max_iters)) ||
-      !ensure_gram_batch(c, 1, opts->max_iters, s))
+  if (opts->max_iters < least || sh.threads * sh.per_thread > 8192 || !gram_full_suits(c) ||
+      (!c->gram_full && gram_full_us(c) > 0.065 * static_cast<double>(opts->max_iters)) ||
+      !make_gram_full(c, s))
     return MP_OK;
   const mp::GramBounds bounds = mp::gram_bounds_full(c->n, c->max_norm);
-  const mp::GramBatch b{c->psi32, c->ld, c->n, c->m, c->gram_full_mp, c->gram_full, c->gram_bc,
+  const mp::GramBatch b{c->psi32, c->ld, c->n, c->m, c->gram_full_mp, c->gram_full, c->gram_sc,
                         r_work, x, c->m, c->st};
   const bool timed = c->profiling;
   if (timed) HIP_TRY(c, hipEventRecord(c->ev[0], s));
@@ -670,8 +715,8 @@ mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, float* r, const m
   long long issued = 0;
   do {
     for (int k = 0; k < rounds && issued < most; ++k, ++issued)
-      HIP_TRY(c, mp::launch_gram_bround(b, sh, bounds, 1, c->num_cus, issued, c->gram_again, true,
-                                        tr, s));
+      HIP_TRY(c, mp::launch_gram_bround(b, sh, bounds, 1, c->num_cus, issued, c->gram_sagain,
+                                        true, tr, s));
     if (timed) HIP_TRY(c, hipEventRecord(c->ev[1], s));
     if (r) HIP_TRY(c, mp::launch_copy_selected(r_work, c->ld, c->n, c->st, r, s));
     HIP_TRY(c, hipMemcpyAsync(c->h_st, c->st, sizeof(mp::DevState), hipMemcpyDeviceToHost, s));
@@ -934,7 +979,7 @@ void make_gram_ragged(mp_ctx* c, hipStream_t s) {
                o_ctl = piece(sizeof(mp::GramCtl) * count),
                o_st = piece(sizeof(mp::DevState) * count), o_again = piece(2 * sizeof(int));
   auto make = [&]() {
-    if (hipMalloc(&c->gram_rmem, total) != hipSuccess) return false;
+    if (!room_for(total) || hipMalloc(&c->gram_rmem, total) != hipSuccess) return false;
     if (hipHostMalloc(&c->gram_hrmem, sizeof(mp::DevState) * count + 4 * sizeof(int),
                       hipHostMallocDefault) != hipSuccess)
       return false;
@@ -1267,7 +1312,8 @@ static bool ensure_sign_gram(mp_ctx* c) {
   b.tried = true;
   if ((c->ld + c->geom.grid - 1) / c->geom.grid > 64 * mp::kSignRows) return false;
   const size_t act = mp::kSignActive;
-  if (hipMalloc(&b.carry, sizeof(mp::SignCarry)) != hipSuccess ||
+  if (!room_for(sizeof(short) * act * static_cast<size_t>(mp::sign_gram_stride(c->m))) ||
+      hipMalloc(&b.carry, sizeof(mp::SignCarry)) != hipSuccess ||
       hipMalloc(&b.pos, sizeof(unsigned short) * static_cast<size_t>(c->m)) != hipSuccess ||
       hipMalloc(&b.g, sizeof(short) * act * static_cast<size_t>(mp::sign_gram_stride(c->m))) !=
           hipSuccess ||
@@ -1562,7 +1608,8 @@ static bool ensure_omp_carry(mp_ctx* c) {
   b.mp = round_up(c->m, mp::kGramTile);
   b.ldh = round_up(b.tq, mp::kGramTile);
   const size_t stride = static_cast<size_t>(b.mp), ldh = static_cast<size_t>(b.ldh);
-  if (hipMalloc(&b.oc, sizeof(mp::OmpCarry)) != hipSuccess ||
+  if (!room_for(sizeof(float) * (stride + ldh + 2 * ld) * (req + 1)) ||
+      hipMalloc(&b.oc, sizeof(mp::OmpCarry)) != hipSuccess ||
       hipMalloc(&b.c, sizeof(float) * stride) != hipSuccess ||
       hipMalloc(&b.p, sizeof(float) * stride * req) != hipSuccess ||
       hipMalloc(&b.w15, sizeof(float) * ld * req) != hipSuccess ||
@@ -2101,6 +2148,12 @@ mp_status mp_solve_batched(mp_ctx* ctx, const float* Y, int64_t ldy, int64_t B, 
   HIP_TRY(c, hipMemcpyAsync(c->h_slots, c->b_slots, sizeof(mp::BSlot) * B, hipMemcpyDeviceToHost,
                             s));
   HIP_TRY(c, hipStreamSynchronize(s));
+  if (rk == mp::kLpTopK && !c->gram_full) {
+    // what the Gram columns would have saved this call
+    long long longest = 0;
+    for (int64_t b = 0; b < B; ++b) longest = std::max(longest, c->h_slots[b].t);
+    c->gram_owed += gram_gain_us(c, B) * static_cast<double>(longest);
+  }
   return batched_results(c, c->h_slots, B, res);
 }
 

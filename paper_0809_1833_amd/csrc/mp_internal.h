@@ -473,8 +473,11 @@ struct mp_ctx {
   // the batched decode on carried correlations: every atom's Gram column (made
   // by the first decode that takes it) and buffers per signal (grown on demand)
   bool gram_full_tried = false;
-  float* gram_full = nullptr;    // m x gram_full_mp
+  float* gram_full = nullptr;    // m x gram_full_mp, in one allocation with:
+  float* gram_sc = nullptr;      // gram_full_mp: one signal's carried correlations
+  int* gram_sagain = nullptr;    // 2: its flags
   int64_t gram_full_mp = 0;
+  double gram_owed = 0.0;        // us that rounds have cost more than they would with it
   int64_t gram_bcap = 0;
   float* gram_bc = nullptr;      // gram_bcap x gram_full_mp
   float* gram_br = nullptr;      // gram_bcap x ld

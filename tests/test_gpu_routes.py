@@ -347,3 +347,36 @@ def test_rounds_on_short_columns(n, m):
         best = c.gather(1, a["idx"][j][:k, None].long())[:, 0]
         # BF16 products are off by at most 2^-8 ||r||: 7 candidates are no further behind
         assert bool((best >= c.max(1).values - r[:-1].double().norm(dim=1) / 128).all())
+
+
+def test_gram_columns_in_proportion_and_when_they_pay():
+    """The Gram columns of all atoms are not made for a dictionary far smaller
+    than they are, nor for a few short batches; then for the next long one."""
+    from paper_0809_1833_amd.mp import Decoder
+
+    def grown(fn):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        fn()
+        torch.cuda.synchronize()
+        return (before - torch.cuda.mem_get_info()[0]) >> 20
+
+    rows = _rows(64, 8192)  # 2 MiB; its columns would be 256
+    y = _signal(rows, 4)
+    Y = torch.stack([_signal(rows, 3, seed=j) for j in range(8)])
+    with Decoder(rows.t()) as dec:
+        a = dec.solve(y, 1e-5, 2000)
+        _equal(dec.solve(y, 1e-5, 2000, step_launches=True), a)
+        assert grown(lambda: dec.solve(y, 1e-5, 2000)) < 64
+        assert grown(lambda: dec.solve_batched(Y.t(), 1e-5, 2000)) < 64
+    rows = _rows(1024, 8192)  # 32 MiB and 256
+    Y = torch.stack([_signal(rows, 3, seed=j) for j in range(2)])
+    with Decoder(rows.t()) as dec:
+        first = {}
+        assert grown(lambda: first.update(dec.solve_batched(Y.t(), 1e-5, 10000))) < 128
+        for _ in range(100):
+            a = dec.solve_batched(Y.t(), 1e-5, 10000)
+            assert a["iters"] == first["iters"] and torch.equal(a["x"], first["x"])
+        b = dec.solve(Y[0].contiguous(), 1e-5, 10000)
+        assert torch.equal(a["x"][:, 0], b["x"])
+        assert grown(lambda: dec.close()) <= -256  # the columns were made on the way
