@@ -45,7 +45,6 @@ constexpr unsigned kGramNone = 0xFFFFu;  // map entry of an atom without a Gram 
 
 // What the steps kernel leaves for the pass, and the other way round.
 struct GramCtl {
-  float err;           // bound on |c~ - <r, psi_m>| (not used after a pass)
   int nreq;            // Gram columns wanted: atoms req[0 .. nreq)
   int slot0;           // the first of the nreq slots they go to
   int used;            // slots in use

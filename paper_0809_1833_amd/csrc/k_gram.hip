@@ -289,11 +289,16 @@ hipError_t launch_gram_block_pass(const GramProb<float>& p, const int* hold, int
 
 // The bounds (u = 2^-24): a product of the pass is a chain of at most
 // gram_chain terms, rounded once more to FP32 (and, from an FP64 dictionary, both
-// operands rounded to FP32 first); dot_column_f32 is two lane chains of
-// ld / 128 terms, then 7 additions (in FP64 its rounding is far below the
+// operands rounded to FP32 first); dot_column_f32 is two lane chains of at most
+// 4 ceil(ld / 512) terms, then 7 additions (in FP64 its rounding is far below the
 // rest).  Each is at most (terms + additions) u sum |a b| <= (...) u ||a||
 // ||b||; a step adds r's rounding (u ||r'|| against a unit column; far less in
 // FP64), c~'s own (u |c~|) and that of the coefficient (u |c|, in col).
+static double dot_roundings(int64_t n, int chains) {
+  const int64_t ld = (n + 63) / 64 * 64, per = 256 * chains;  // rows in 4 terms of every lane
+  return 4.0 * static_cast<double>((ld + per - 1) / per) + 8.0;
+}
+
 GramBounds gram_bounds(int64_t n, double max_norm, bool f64) {
   const double u = 1.0 / 16777216.0, nn = static_cast<double>(n + 64);
   const double slack = 1.01;
@@ -304,7 +309,7 @@ GramBounds gram_bounds(int64_t n, double max_norm, bool f64) {
   b.col = static_cast<float>(prod * max_norm * max_norm);
   b.step = static_cast<float>((f64 ? 1e-3 : 1.01) * u * max_norm * slack);
   b.carry = static_cast<float>(1.01 * u * slack);
-  b.dot = static_cast<float>((f64 ? 0.1 : nn / 128 + 10) * u * max_norm * slack);
+  b.dot = static_cast<float>((f64 ? 0.1 : dot_roundings(n, 2)) * u * max_norm * slack);
   return b;
 }
 
@@ -496,8 +501,7 @@ __global__ __launch_bounds__(NT + 2 * kWave) void k_gram_rsteps(
 
 GramBounds gram_bounds_one(int64_t n, double max_norm) {
   GramBounds b = gram_bounds(n, max_norm, false);
-  const double nn = static_cast<double>(n + 64);
-  b.dot = static_cast<float>((nn / 64 + 10) / 16777216.0 * max_norm * 1.01);
+  b.dot = static_cast<float>(dot_roundings(n, 1) / 16777216.0 * max_norm * 1.01);
   return b;
 }
 

@@ -481,7 +481,6 @@ __device__ void gram_steps(const GramProb<T>& p, const GramBounds& bd, long long
       ctl->nreq = nreq;
       ctl->slot0 = used;
       ctl->used = used + nreq;
-      ctl->err = err;
     }
   }
 }
