@@ -593,6 +593,29 @@ const char* mp_last_error(const mp_ctx* ctx);
 mp_status mp_get_storage(const mp_ctx* ctx, void* codes, float* scales, void* stream);
 
 /*
+ * mp_set_carried -- whether the blocking decodes of ctx may run on carried
+ * correlations (the one-bit form: in batches of steps) and hold the buffers
+ * these need.
+ *
+ *   on        host: 1 (as contexts are created) or 0: those buffers are freed
+ *             and decodes take their other form (one launch per step, the one
+ *             launch of a small dictionary or of the one-bit form, the rounds
+ *             of products, the ragged launch), with the results that each
+ *             entry point describes for it
+ * Errors: MP_EINVAL (NULL ctx, on neither 0 nor 1, a stream-ordered decode
+ * pending), MP_EDEVICE.
+ */
+mp_status mp_set_carried(mp_ctx* ctx, int on);
+
+/*
+ * mp_carried_steps -- how many steps the last decode of ctx took on carried
+ * correlations, before its stop or before another form went on (batched and
+ * ragged decodes: the most that a signal or instance took); 0 where it took
+ * another form from its start.  Errors: MP_EINVAL (NULL ctx or steps).
+ */
+mp_status mp_carried_steps(const mp_ctx* ctx, int64_t* steps);
+
+/*
  * mp_set_profiling / mp_kernel_time -- per-launch timing of the kernel that
  * makes one MP iteration (the pass over the whole dictionary, eq. 9, with the
  * step of eqs. 10-12 carried into it) during the last mp_solve, or of the

@@ -506,6 +506,7 @@ bool cap_pays(mp_dtype storage, long long cap) {
 // not near 1) or the memory is not there: the decode then takes one launch
 // per step.
 bool ensure_gram(mp_ctx* c, hipStream_t s) {
+  if (!c->carried_on) return false;
   if (c->gram_tried) return c->gram_slots > 0;
   c->gram_tried = true;
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, c->storage == MP_F64 ? 8 : 4);
@@ -573,6 +574,7 @@ mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* op
     t0 = c->h_st[1 + k].t;
   }
   if (!over && cap > 0) gave_up = true;  // (not reached: unfinished is never a result)
+  c->carried_steps = t0;
   if (gave_up) {
     HIP_TRY(c, mp::launch_resume<T>(c->st, r_work, c->ld, static_cast<int>(t0 & 1), s));
     return MP_OK;
@@ -597,7 +599,7 @@ mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* op
 bool gram_full_suits(const mp_ctx* c) {
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
   const int64_t bytes = 4 * mp::gram_stride(sh) * c->m;
-  return sh.threads != 0 && c->m <= 16384 && c->max_norm > 0.99 && c->max_norm < 1.01 &&
+  return c->carried_on && sh.threads != 0 && c->m <= 16384 && c->max_norm > 0.99 && c->max_norm < 1.01 &&
          bytes <= std::max<int64_t>(int64_t{64} << 20, 8 * 4 * c->ld * c->m);
 }
 
@@ -724,6 +726,7 @@ mp_status solve_small_full(mp_ctx* c, float* r_work, float* x, float* r, const m
     rounds = 2;
   } while (!c->h_st->done && issued < most);
   used = c->h_st->done && !c->h_st->pad[0];
+  c->carried_steps = c->h_st->t;
   if (!used) {
     t0 = c->h_st->t;
     HIP_TRY(c, mp::launch_resume<float>(c->st, r_work, c->ld, 0, s));
@@ -909,6 +912,7 @@ mp_status solve_gram_batch(mp_ctx* c, const float* Y, int64_t ldy, int64_t B, fl
     handed_on += c->gram_hbst[j].pad[0] != 0;
     most = std::max(most, c->gram_hbst[j].t);
   }
+  c->carried_steps = most;
   if (timed) {
     // the decode's time on the device over the steps of its longest signal
     float ms = 0.f;
@@ -1089,7 +1093,10 @@ mp_status solve_gram_ragged(mp_ctx* c, const float* Y, float* X, const mp_opts* 
   HIP_TRY(c, hipMemcpyAsync(c->gram_hrst, c->gram_rst, sizeof(mp::DevState) * c->r_count,
                             hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
-  for (int64_t i = 0; i < c->r_count; ++i) gave_up |= c->gram_hrst[i].pad[0] != 0;
+  for (int64_t i = 0; i < c->r_count; ++i) {
+    gave_up |= c->gram_hrst[i].pad[0] != 0;
+    c->carried_steps = std::max<int64_t>(c->carried_steps, c->gram_hrst[i].t);
+  }
   if (timed) {
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, c->ev[0], c->ev[1]) == hipSuccess) {
@@ -1275,6 +1282,36 @@ mp_status mp_kernel_time(const mp_ctx* ctx, double* avg_ms, int64_t* launches) {
   return MP_OK;
 }
 
+mp_status mp_set_carried(mp_ctx* ctx, int on) {
+  if (!ctx) return MP_EINVAL;
+  ctx->err.clear();
+  mp_ctx* c = ctx;
+  if (on != 0 && on != 1) return fail(c, MP_EINVAL, "on must be 0 or 1");
+  if (mp_status ps = check_not_pending(c); ps != MP_OK) return ps;
+  HIP_TRY(c, hipSetDevice(c->device));
+  if (c->carried_on == (on != 0)) return MP_OK;
+  c->carried_on = on != 0;
+  if (on) {
+    if (c->ragged) make_gram_ragged(c, nullptr);
+    return MP_OK;
+  }
+  free_gram(c);
+  free_sign_gram(c);
+  free_omp_carry(c);
+  free_gram_batch(c);
+  free_gram_ragged(c);
+  (void)hipFree(c->gram_full);
+  c->gram_full = nullptr;
+  c->gram_tried = c->gram_full_tried = false;
+  return MP_OK;
+}
+
+mp_status mp_carried_steps(const mp_ctx* ctx, int64_t* steps) {
+  if (!ctx || !steps) return MP_EINVAL;
+  *steps = ctx->carried_steps;
+  return MP_OK;
+}
+
 mp_status mp_get_storage(const mp_ctx* ctx, void* codes, float* scales, void* stream) {
   if (!ctx || !codes) return MP_EINVAL;
   mp_ctx* c = const_cast<mp_ctx*>(ctx);
@@ -1307,6 +1344,7 @@ mp_status mp_get_storage(const mp_ctx* ctx, void* codes, float* scales, void* st
 // holds: M below N / 16) or the memory is not there.
 static bool ensure_sign_gram(mp_ctx* c) {
   mp::SignGram& b = c->sign_gram;
+  if (!c->carried_on) return false;
   if (b.tried) return b.carry != nullptr;
   const size_t grid = static_cast<size_t>(c->geom.grid);
   b.tried = true;
@@ -1381,6 +1419,7 @@ static mp_status solve_sign_gram(mp_ctx* c, float* x, float* r, long long T, con
   }
   *c->h_st = c->h_st[1 + static_cast<int>((seen - 1) & 1)];
   r_done = over && seen <= 2;  // (one chunk in flight until then)
+  c->carried_steps = t0;
   if (timed) {
     HIP_TRY(c, hipEventRecord(c->ev[1], s));
     HIP_TRY(c, hipEventSynchronize(c->ev[1]));
@@ -1409,6 +1448,7 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   hipStream_t s = static_cast<hipStream_t>(stream);
   mp_ctx* c = ctx;
+  c->carried_steps = 0;
   c->rescore_k = opts->rescore_k == 0 ? mp::kLpTopK : opts->rescore_k;
   c->prof_ms = 0.0;
   c->prof_launches = 0;
@@ -1536,6 +1576,7 @@ mp_status mp_solve_noalloc(mp_ctx* ctx, const float* y, float* x, float* r, cons
   void* base = nullptr;
   HIP_TRY(c, mp::noalloc_scratch(c->device, &base));
   unsigned char* b = static_cast<unsigned char*>(base);
+  c->carried_steps = 0;
   c->rescore_k = opts->rescore_k == 0 ? mp::kLpTopK : opts->rescore_k;
   c->prof_ms = 0.0;
   c->prof_launches = 0;
@@ -1601,7 +1642,7 @@ static mp_status ensure_omp(mp_ctx* c, int64_t tq) {
 // pass.
 static bool ensure_omp_carry(mp_ctx* c) {
   mp::OmpBufs& b = c->omp;
-  if (c->ld * c->m * 4 < kOmpCarryBytes || !(c->max_norm > 0.99) || !(c->max_norm < 1.01))
+  if (!c->carried_on || c->ld * c->m * 4 < kOmpCarryBytes || !(c->max_norm > 0.99) || !(c->max_norm < 1.01))
     return false;
   if (b.oc) return true;
   const size_t ld = static_cast<size_t>(c->ld), req = mp::kGramReq;
@@ -1682,6 +1723,7 @@ static mp_status solve_omp_gram(mp_ctx* c, const mp_trace& tr, long long T, hipS
     bound = std::min(known + steps - upto[k], T);
   }
   if (!over) gave_up = true;
+  c->carried_steps = known;
   if (gave_up) {
     HIP_TRY(c, mp::launch_resume<float>(c->st, c->r_work, c->ld, 0, s));
     return MP_OK;
@@ -1719,6 +1761,7 @@ mp_status mp_solve_omp(mp_ctx* ctx, const float* y, float* x, float* r, const mp
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   hipStream_t s = static_cast<hipStream_t>(stream);
   mp_ctx* c = ctx;
+  c->carried_steps = 0;
   // at most min(T, N) atoms: beyond N the selected atoms span the whole space
   const long long T = std::min<long long>(opts->max_iters, c->n);
   if (mp_status bs = ensure_omp(c, std::max<long long>(T, 1)); bs != MP_OK) return bs;
@@ -1904,6 +1947,7 @@ mp_status mp_solve_f64(mp_ctx* ctx, const double* y, double* x, double* r, const
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   hipStream_t s = static_cast<hipStream_t>(stream);
   mp_ctx* c = ctx;
+  c->carried_steps = 0;
 
   HIP_TRY(c, mp::launch_init_f64(y, c->n, c->ld, x, c->m, c->r64_work, c->st, opts->eps,
                                  step_cap(opts), s));
@@ -2020,6 +2064,7 @@ mp_status mp_solve_batched(mp_ctx* ctx, const float* Y, int64_t ldy, int64_t B, 
   if (trace) tr = *trace;
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t s = static_cast<hipStream_t>(stream);
+  c->carried_steps = 0;
   const int rk = opts->rescore_k == 0 ? mp::kLpTopK : opts->rescore_k;
   c->prof_ms = 0.0;
   c->prof_launches = 0;
@@ -2411,6 +2456,7 @@ mp_status mp_solve_ragged(mp_ctx* ctx, const float* Y, float* X, float* R, const
   if (trace) tr = *trace;
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t s = static_cast<hipStream_t>(stream);
+  c->carried_steps = 0;
   const bool lp = c->storage == MP_BF16;
   const int rk = opts->rescore_k == 0 ? mp::kLpTopK : opts->rescore_k;
   const long long* caps = max_iters ? c->r_caps : nullptr;

@@ -459,6 +459,8 @@ struct mp_ctx {
   std::vector<int64_t> r_psi_off;     // host: offsets of the dictionaries in r_psi32
   // OMP decode buffers (grown on demand)
   mp::OmpBufs omp;
+  bool carried_on = true;        // mp_set_carried
+  int64_t carried_steps = 0;     // of the last decode, taken on carried correlations
   // the decode on carried correlations (k_gram.h): largest column norm (0: not
   // known) and buffers made by the first decode that takes it
   double max_norm = 0.0;

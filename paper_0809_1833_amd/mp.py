@@ -123,6 +123,10 @@ def _load():
     lib.mp_set_profiling.argtypes = [p, ctypes.c_int]
     lib.mp_kernel_time.restype = ctypes.c_int
     lib.mp_kernel_time.argtypes = [p, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)]
+    lib.mp_set_carried.restype = ctypes.c_int
+    lib.mp_set_carried.argtypes = [p, ctypes.c_int]
+    lib.mp_carried_steps.restype = ctypes.c_int
+    lib.mp_carried_steps.argtypes = [p, ctypes.POINTER(i64)]
     lib.mp_solve_omp.restype = ctypes.c_int
     lib.mp_solve_omp.argtypes = [p, p, p, p, ctypes.POINTER(Opts), ctypes.POINTER(Result),
                                  ctypes.POINTER(Trace), p]
@@ -336,6 +340,16 @@ def mp_kernel_time(ctx):
     return avg.value, n.value
 
 
+def mp_set_carried(ctx, on: bool) -> None:
+    _check(_load().mp_set_carried(ctx, int(on)), "mp_set_carried", ctx)
+
+
+def mp_carried_steps(ctx) -> int:
+    n = ctypes.c_int64()
+    _check(_load().mp_carried_steps(ctx, ctypes.byref(n)), "mp_carried_steps", ctx)
+    return n.value
+
+
 # ---- torch-facing convenience ------------------------------------------------
 
 def _check_psi(psi: torch.Tensor, dtype=torch.float32):
@@ -412,8 +426,8 @@ class Decoder:
               trace_r: bool = False, noalloc: bool = False, asynchronous: bool = False):
         """Decode one signal.  Returns dict(x, r, iters, yy, rr, stop, persistent,
         trace...).  ``omp=True`` decodes with Orthogonal Matching Pursuit
-        (mp_solve_omp; MP_F32 storage).  ``step_launches=True``: the one-bit
-        form steps with one launch per iteration (MP_SOLVE_STEP_LAUNCHES).
+        (mp_solve_omp; MP_F32 storage).  ``step_launches=True``: one launch
+        per iteration (MP_SOLVE_STEP_LAUNCHES).
         ``trace_r=True`` (with ``trace_cap``): also the residual after every
         traced step, ``r_trace`` of shape (steps, N).  ``noalloc=True``:
         mp_solve_noalloc (the library's static scratch; MP_F32, MP_BF16 or
@@ -481,6 +495,14 @@ class Decoder:
         return dict(iters=res.iters, yy=res.yy, rr=res.rr,
                     stop=STOP_NAMES.get(res.stop_reason, res.stop_reason),
                     persistent=bool(res.persistent))
+
+    def set_carried(self, on: bool) -> None:
+        """Whether decodes may run on carried correlations (mp_set_carried)."""
+        mp_set_carried(self._ctx, on)
+
+    def carried_steps(self) -> int:
+        """Steps the last decode took on carried correlations."""
+        return mp_carried_steps(self._ctx)
 
     def set_batched_config(self, atoms128_above: int, atoms64_above: int,
                            atoms32_above: int = 0) -> None:
@@ -614,6 +636,14 @@ class RaggedDecoder:
     @property
     def handle(self):
         return self._ctx
+
+    def set_carried(self, on: bool) -> None:
+        """Whether decodes may run on carried correlations (mp_set_carried)."""
+        mp_set_carried(self._ctx, on)
+
+    def carried_steps(self) -> int:
+        """Steps of the last decode's longest instance on carried correlations."""
+        return mp_carried_steps(self._ctx)
 
     def set_config(self, threads: int, cols_per_wave: int, wgs_per_cu: int, split: int = 0):
         """Launch shape; ``split``: most parts one instance is cut into (0:
