@@ -1,6 +1,11 @@
 """Autotuners for the ragged decode's launch shape and the batched product's tiles.
 
-The ragged decode (``mp_solve_ragged``) runs one persistent launch whose
+What is tuned are the forms without carried correlations: the decoder is
+switched to them (``set_carried``) while they are timed.  A decode that runs on
+carried correlations does not read the settings; one that they are not taken
+for, or that is handed on by them, does.
+
+The ragged decode (``mp_solve_ragged``) then runs one persistent launch whose
 shape -- workgroup size, columns streamed per wave, workgroups per CU, and
 the most parts one large instance is cut into -- changes speed but never
 results.  ``tune_ragged`` times every valid shape on the actual instances
@@ -9,7 +14,7 @@ shapes, and keeps the fastest; the choice is cached in a JSON file keyed by the 
 architecture, the storage type and the multiset of instance sizes, so later
 runs with the same shape of work reuse it.
 
-The batched decode (``mp_solve_batched``) picks the product's tile every
+The batched decode (``mp_solve_batched``) then picks the product's tile every
 round from the number of signals still active: 128, 64, 32 or 16 atoms per
 workgroup.  ``tune_batched`` times whole batched decodes under each rule of
 a small grid of the 128- and 64-atom switch points, then the 16-atom switch
@@ -25,6 +30,7 @@ import json
 import os
 import time
 from collections import Counter
+from contextlib import contextmanager
 from typing import Iterable, Optional
 
 import torch
@@ -34,6 +40,24 @@ BF16_SHAPES = FP32_SHAPES
 SPLITS = (1, 2, 3, 4)
 RANK_SPLIT = 2  # the split every shape is first timed at
 SPLIT_SHAPES = 6  # shapes whose other splits are timed too
+
+
+# Part of the cache's keys: entries of another version are not used (those
+# without one may have been timed on decodes that did not read the settings).
+VERSION = "v2"
+
+
+@contextmanager
+def _without_carried(dec):
+    """The decoder's other forms, which read the settings, for a while."""
+    switch = getattr(dec, "set_carried", None)
+    if switch:
+        switch(False)
+    try:
+        yield
+    finally:
+        if switch:
+            switch(True)
 
 
 def cache_path() -> str:
@@ -46,7 +70,7 @@ def workload_key(dec, arch: Optional[str] = None) -> str:
         arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
     sizes = sorted(Counter(zip(dec.ns, dec.ms)).items())
     digest = hashlib.sha256(json.dumps(sizes).encode()).hexdigest()[:16]
-    return f"{arch}|{dec.storage}|{dec.count}|{digest}"
+    return f"{VERSION}|{arch}|{dec.storage}|{dec.count}|{digest}"
 
 
 def _load_cache() -> dict:
@@ -71,7 +95,8 @@ def _store_cache(cache: dict) -> None:
 
 def tune_ragged(dec, y_packed: torch.Tensor, eps: float, max_iters, reps: int = 2,
                 shapes: Optional[Iterable] = None, use_cache: bool = True, log=None) -> dict:
-    """Time each launch shape on this workload, apply and return the fastest.
+    """Time each launch shape of the persistent launch on this workload, apply
+    and return the fastest.
 
     Returns dict(config=..., ms=..., timings=[...], cached=bool)."""
     key = workload_key(dec)
@@ -100,15 +125,16 @@ def tune_ragged(dec, y_packed: torch.Tensor, eps: float, max_iters, reps: int = 
         if log:
             log(f"[tune] threads={t} cols/wave={c} wgs/cu={w} split={sp}: {best * 1e3:.2f} ms")
 
-    for (t, c, w) in shapes:
-        time_shape(t, c, w, RANK_SPLIT)
-    # the other splits on the best few shapes: the best split depends on the
-    # shape (shapes that tie at split 2 can part at another)
-    ranked = sorted(timings, key=lambda d: d["ms"])[:SPLIT_SHAPES]
-    for d in ranked:
-        for sp in SPLITS:
-            if sp != RANK_SPLIT:
-                time_shape(d["threads"], d["cols_per_wave"], d["wgs_per_cu"], sp)
+    with _without_carried(dec):
+        for (t, c, w) in shapes:
+            time_shape(t, c, w, RANK_SPLIT)
+        # the other splits on the best few shapes: the best split depends on the
+        # shape (shapes that tie at split 2 can part at another)
+        ranked = sorted(timings, key=lambda d: d["ms"])[:SPLIT_SHAPES]
+        for d in ranked:
+            for sp in SPLITS:
+                if sp != RANK_SPLIT:
+                    time_shape(d["threads"], d["cols_per_wave"], d["wgs_per_cu"], sp)
     win = min(timings, key=lambda d: d["ms"])
     cfg = dict(threads=win["threads"], cols_per_wave=win["cols_per_wave"],
                wgs_per_cu=win["wgs_per_cu"], split=win["split"])
@@ -131,7 +157,7 @@ def batched_key(dec, n_signals: int, max_iters, arch: Optional[str] = None) -> s
         arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
     caps = [int(v) for v in max_iters] if hasattr(max_iters, "__len__") else [int(max_iters)]
     digest = hashlib.sha256(json.dumps(sorted(Counter(caps).items())).encode()).hexdigest()[:16]
-    return f"batched|{arch}|{dec.n}|{dec.m}|{n_signals}|{digest}"
+    return f"{VERSION}|batched|{arch}|{dec.n}|{dec.m}|{n_signals}|{digest}"
 
 
 def batched_rules():
@@ -172,12 +198,13 @@ def tune_batched(dec, Y: torch.Tensor, eps: float, max_iters, reps: int = 2,
             log(f"[tune] batched tiles: 128 above {a128}, 64 above {a64}, 32 above {a32}: "
                 f"{best * 1e3:.2f} ms")
 
-    for rule in (rules if rules is not None else batched_rules()):
-        time_rule(*rule)
-    if rules is None:
-        w = min(timings, key=lambda d: d["ms"])
-        for a32 in ATOMS32_ABOVE:
-            time_rule(w["atoms128_above"], w["atoms64_above"], a32)
+    with _without_carried(dec):
+        for rule in (rules if rules is not None else batched_rules()):
+            time_rule(*rule)
+        if rules is None:
+            w = min(timings, key=lambda d: d["ms"])
+            for a32 in ATOMS32_ABOVE:
+                time_rule(w["atoms128_above"], w["atoms64_above"], a32)
     win = min(timings, key=lambda d: d["ms"])
     cfg = dict(atoms128_above=win["atoms128_above"], atoms64_above=win["atoms64_above"],
                atoms32_above=win["atoms32_above"])
