@@ -56,7 +56,7 @@ typedef enum mp_status {
     MP_EUNSUPPORTED = 6   /* the request is valid but this build/device cannot do it */
 } mp_status;
 
-/* Storage of the dictionary copy the correlation pass streams. */
+/* Storage of the dictionary, and of the copy that a pass per step streams. */
 typedef enum mp_dtype {
     MP_F32 = 0,           /* FP32, as given */
     MP_BF16 = 1,          /* BF16, round to nearest even from FP32 */
@@ -97,8 +97,9 @@ typedef struct mp_opts {
    whole dictionary, even where the whole decode fits one persistent launch
    (the one-bit form MP_SIGN1, and MP_F32 contexts whose dictionary fits the
    LDS of at most 32 workgroups) or runs on carried correlations (see
-   mp_solve and mp_solve_omp); the same results bit for bit; no effect on the
-   other forms. */
+   mp_solve and mp_solve_omp); the same results bit for bit, for MP_BF16 and
+   MP_FP8_E4M3 wherever each step's FP32 argmax is among the pass's 8
+   candidates; no effect on the other forms. */
 #define MP_SOLVE_STEP_LAUNCHES 0x1u
 
 /* mp_opts.flags: a stream-ordered decode (mp_solve and mp_solve_noalloc on
@@ -108,10 +109,10 @@ typedef struct mp_opts {
    result (iterations, norms, stop reason, and the errors only the device can
    find: non-finite y, a wait that gave up) is collected with mp_solve_result.
    res must be NULL.  Since the host cannot see when the decode stops, it
-   enqueues every launch the cap allows (max_iters + 1; the one launch of a
-   decode held in LDS); a launch past the stop returns at once, costing its
-   dispatch only (about 4 us at N=8192, M=32768), so a cap far above the steps
-   needed costs that per spare step.  Decodes on different contexts overlap
+   enqueues every launch the cap allows (max_iters + 1, a pass each; the one
+   launch of a decode held in LDS); a launch past the stop returns at once,
+   costing its dispatch only (about 4 us at N=8192, M=32768), so a cap far above
+   the steps needed costs that per spare step.  Decodes on different contexts overlap
    on different streams; a context holds one stream-ordered decode at a time
    (every decode call on it returns MP_EINVAL until mp_solve_result).
    mp_solve_noalloc decodes all use the library's one static scratch per
@@ -167,11 +168,17 @@ typedef struct mp_trace_f64 {
  *   psi      device: FP32 N x M column-major dictionary, leading dimension ld
  *   n, m     rows N >= 1 and columns M >= 1 (M < 2^31, N <= 16384)
  *   ld       leading dimension, ld >= n
- *   storage  which copy the correlation pass streams (mp_dtype).  MP_BF16 and
+ *   storage  which copy a pass per step streams (mp_dtype).  MP_BF16 and
  *            MP_FP8_E4M3 keep an FP32 master as well, for re-scoring and the
- *            residual update: each pass keeps the 8 best reduced-precision
+ *            residual update: such a pass keeps the 8 best reduced-precision
  *            candidates, re-computes up to opts.rescore_k of them in FP32 and
  *            selects the best re-computed one (smallest index on ties).
+ *            Blocking decodes with all 8 re-scored mostly run on carried
+ *            correlations instead (see mp_solve), which read the FP32 master
+ *            alone; the reduced-precision copy is read by decodes with few
+ *            steps allowed, with a lower rescore_k, with
+ *            MP_SOLVE_STEP_LAUNCHES, MP_SOLVE_ASYNC or mp_solve_noalloc, and
+ *            where carried correlations do not apply or hand on.
  *   flags    MP_SKIP_NORM_CHECK or 0
  *   stream   hipStream_t as void*
  *
@@ -196,8 +203,8 @@ mp_status mp_create(mp_ctx** out, const float* psi, int64_t n, int64_t m, int64_
  *   r        device: N floats or NULL; receives the final residual (FP32)
  *   opts     host: tolerance, cap, re-score count, flags (0 or
  *            MP_SOLVE_STEP_LAUNCHES)
- *   res      host or NULL: iteration count, norms, stop reason, and whether
- *            the decode ran as one persistent launch
+ *   res      host or NULL: iteration count, norms, stop reason, and
+ *            mp_result.persistent
  *   trace    host struct of device arrays, or NULL (see mp_trace)
  *   stream   hipStream_t as void*
  *
@@ -246,7 +253,8 @@ mp_status mp_solve(mp_ctx* ctx, const float* y, float* x, float* r, const mp_opt
 /*
  * mp_solve_result -- wait for the stream-ordered decode (MP_SOLVE_ASYNC) last
  * issued on ctx and return its result: the same result and errors mp_solve
- * gives for that decode.  The context can then decode again.
+ * with MP_SOLVE_STEP_LAUNCHES gives for that decode.  The context can then
+ * decode again.
  *
  *   res      host or NULL: as for mp_solve
  * Errors: MP_EINVAL (NULL ctx, or no stream-ordered decode pending), and the
@@ -258,8 +266,8 @@ mp_status mp_solve_result(mp_ctx* ctx, mp_result* res);
  * mp_solve_noalloc -- mp_solve for callers that cannot allocate memory while
  * they decode: code under stream capture, tight serving loops, harnesses
  * that forbid hipMalloc.  Same arguments, results and errors as mp_solve for
- * an MP_F32, MP_BF16 or MP_FP8_E4M3 context from mp_create (the same kernels,
- * bit-identical results), but the decode's device work buffers (state,
+ * an MP_F32, MP_BF16 or MP_FP8_E4M3 context from mp_create (with
+ * MP_SOLVE_STEP_LAUNCHES: the same kernels, bit-identical results), but the decode's device work buffers (state,
  * residual double buffer, per-workgroup keys, column-share state) live in
  * a static array of 256 KiB that the library holds on each GPU it runs on
  * until the process ends (the decode always takes one launch per step), and
@@ -353,9 +361,10 @@ mp_status mp_batched_get_config(const mp_ctx* ctx, mp_batched_config* cfg);
 /*
  * mp_create_f64 -- mp_create for an FP64 dictionary: the double-precision
  * configuration of the decoder (the paper times single- and double-precision
- * builds of the same loop, Section 4).  The correlation pass streams the FP64
- * copy (8 bytes per element) and every inner product, coefficient, residual
- * and norm is FP64.  The context has storage MP_F64 and is decoded only with
+ * builds of the same loop, Section 4).  A pass per step streams the FP64
+ * copy (8 bytes per element), and every inner product that an atom is selected
+ * by, every coefficient, residual and norm is FP64 (mp_solve_f64 says what is
+ * not).  The context has storage MP_F64 and is decoded only with
  * mp_solve_f64 (mp_solve and mp_solve_batched return MP_EINVAL for it).
  *
  *   out      host: receives the new context (set to NULL on failure)
@@ -384,9 +393,11 @@ mp_status mp_create_f64(mp_ctx** out, const double* psi, int64_t n, int64_t m, i
  *   trace    host struct of device arrays, or NULL (see mp_trace_f64)
  *
  * Decodes on carried correlations as mp_solve does (M <= 32768, N <= 9600,
- * column norms within 1% of 1), with the same results bit for bit as one
- * launch per step; the carried correlations are FP32 and only shortlist the
- * atoms that are scored in FP64.
+ * column norms within 1% of 1, a cap above 2), with the same results bit for
+ * bit as one launch per step.  The correlations it carries, and the products
+ * that give them, are FP32, of the dictionary and r rounded to FP32, with a
+ * bound on how far they are off the exact ones: they tell which atoms could be
+ * the largest, and these are scored, and the largest selected, in FP64.
  *
  * y, x and r must not overlap.  Errors: MP_EINVAL (not an MP_F64 context,
  * NULL ctx/y/x/opts, bad opts), MP_ENONFINITE (y holds NaN/Inf),
@@ -410,7 +421,8 @@ mp_status mp_solve_f64(mp_ctx* ctx, const double* y, double* x, double* r, const
  * over the atoms of largest correlation, each batch checked against all atoms
  * before its steps stand (work buffers of at most 2 M KiB and 3 MiB on the
  * first such decode), where one launch per step would give a workgroup at
- * most 256 rows of r (M above about N / 16).  With a cap of at most 64 steps,
+ * most 256 rows of r (M above about N / 16); where the batches bring too few
+ * steps, another form goes on.  With a cap of at most 64 steps,
  * or MP_SIGN_SPIN_LIMIT set, it runs the whole decode as one persistent
  * launch where the device can keep one workgroup per compute unit resident
  * with its share of the bits in LDS (the share at most 150 KB, e.g. N = 8192
@@ -630,7 +642,8 @@ mp_status mp_carried_steps(const mp_ctx* ctx, int64_t* steps);
  *             average includes the gaps between consecutive launches (the
  *             persistent one-bit decode: its launch, over its t + 2 steps;
  *             decodes on carried correlations: all their launches together,
- *             over the steps taken); OMP
+ *             over the steps taken, or, where they hand on, the launches of
+ *             the form that goes on); OMP
  *             times every k-th selection launch on its own; mp_solve_batched
  *             every k-th round's product launch, or on carried correlations
  *             all its launches together, over the steps of its longest signal.

@@ -380,3 +380,24 @@ def test_gram_columns_in_proportion_and_when_they_pay():
         b = dec.solve(Y[0].contiguous(), 1e-5, 10000)
         assert torch.equal(a["x"][:, 0], b["x"])
         assert grown(lambda: dec.close()) <= -256  # the columns were made on the way
+
+
+@pytest.mark.parametrize("apart", [1e-7, 1e-9, 1e-12])
+def test_f64_selects_beyond_fp32(apart):
+    """Pairs of columns that FP32 cannot tell apart: the shortlist is made in
+    FP32, the selection in FP64, so the atoms are one launch per step's and, for
+    the first step, the FP64 argmax."""
+    from paper_0809_1833_amd.mp import Decoder
+    rows = _rows(900, 3000, dtype=torch.float64)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    rows[1500:] = rows[:1500] + apart * torch.randn((1500, 900), generator=g, device="cuda",
+                                                    dtype=torch.float64) / 30
+    rows /= rows.norm(dim=1, keepdim=True)
+    pick = torch.tensor([7, 1600, 30, 1802, 200, 1999, 2500], device="cuda")
+    y = (rows[pick] * torch.linspace(1, 0.4, 7, device="cuda", dtype=torch.float64)[:, None]).sum(0)
+    with Decoder(rows.t(), storage="f64") as dec:
+        a = dec.solve(y, 1e-12, 400, trace_cap=400, trace_r=True)
+        assert dec.carried_steps() > 7
+        b = dec.solve(y, 1e-12, 400, step_launches=True, trace_cap=400, trace_r=True)
+    _equal(a, b, ("x", "r", "idx", "coef", "rr_trace", "r_trace"))
+    assert int(a["idx"][0]) == int((rows @ y).abs().argmax())
