@@ -20,6 +20,13 @@ the ragged instances (FP32 and BF16), the FP64 decode and the OMP decode of
 the same workload, the decode on the sign-bit Bernoulli dictionary of the
 same sizes, and the Fig. 1 error grid (each skippable, see --help).
 
+Decodes run on carried correlations where the library takes them (the
+reduced-precision forms then select from the FP32 columns, as they re-score):
+their `step` is bound by the latency of a step.  A `roofline` beside one is of
+the kernel that streams the dictionary once a step, from a decode with one
+launch per step.  The batched and ragged legs tune, and record a config, only
+where a decode does not run on carried correlations.
+
 Errors per result: after the GPU legs, the oracle checks what each leg
 decoded (untimed): every step of a single-signal decode is judged against
 the FP64 correlations of the decode's own state (selections that differ from
@@ -67,13 +74,6 @@ TRAFFIC = {
                                                "mp_internal.h")]),
     "omp": (os.path.join(ROOT, "profiles", "omp_select_traffic.json"),
             [os.path.join(_CSRC, f) for f in ("k_omp.hip", "k_common.h", "mp_internal.h")]),
-    # ragged solves: bytes per solve of the 512-instance workload (n = m = 0)
-    "ragged_f32": (os.path.join(ROOT, "profiles", "ragged_f32_traffic.json"),
-                   [os.path.join(_CSRC, f) for f in ("k_ragged.hip", "k_common.h", "k_lowp.h",
-                                                     "mp_internal.h")]),
-    "ragged_bf16": (os.path.join(ROOT, "profiles", "ragged_bf16_traffic.json"),
-                    [os.path.join(_CSRC, f) for f in ("k_ragged.hip", "k_common.h", "k_lowp.h",
-                                                      "mp_internal.h")]),
 }
 ESIZE = {"f64": 8.0, "f32": 4.0, "bf16": 2.0, "fp8": 1.0}
 KERNEL = {"f64": "k_mp_step_f64", "f32": "k_mp_step_f32", "bf16": "k_mp_step_lp",
@@ -408,6 +408,7 @@ def bench_single(p, storage, steps, warmup, profile_every, ceiling, workload, re
         g = traced_decode(dec, y, p, rescore_k=rescore_k) if check else None
         one_launch = "persistent" in stops
         stops.discard("persistent")
+        kernel = "k_gram_bsteps" if dec.carried_steps() else "k_f32_small"
         conc = None
         # the same decode with one launch per step, for comparison
         s_it, s_dt, s_ms, s_n, _ = time_decodes(dec, y, p, steps if one_launch else 1,
@@ -424,7 +425,7 @@ def bench_single(p, storage, steps, warmup, profile_every, ceiling, workload, re
     b = step_bytes(n, m, storage)
     if one_launch:
         # no launch per step: the time per step
-        leg["roofline"] = step_of_decode(avg_ms, kt_n, "k_gram_bsteps")
+        leg["roofline"] = step_of_decode(avg_ms, kt_n, kernel)
         leg["step_launches"] = {
             "iters_per_s": round(s_it / s_dt, 3), "us_per_iter": round(s_dt / max(s_it, 1) * 1e6, 3),
             "roofline": hbm_roofline(KERNEL[storage], b, s_ms, s_n,
@@ -556,15 +557,13 @@ def bench_batched(seed: int, reps: int = 3, warmup: int = 1, sequential: bool = 
     out = {"workload": f"N={n}, M={m}, B={nb} signals, K_b ~ U{{16..256}}, eps={bt.eps}, "
                        "T_b=20 K_b, shared dictionary"}
     with Decoder(psi, storage="bf16") as dec:
-        # the product's tile rule, from the tuner's cache or timed here
-        tn = tune.tune_batched(dec, Y, bt.eps, caps, reps=2, log=log)
-        out["config"] = tn["config"]
-        out["tuned_from_cache"] = tn["cached"]
-        if not tn["cached"]:
-            out["tile_rule_ms"] = {
-                f"{d['atoms128_above']}/{d['atoms64_above']}/{d['atoms32_above']}": d["ms"]
-                for d in tn["timings"]}
-        for _ in range(warmup):
+        for _ in range(max(warmup, 1)):
+            dec.solve_batched(Y, bt.eps, caps, want_r=False)
+        if not dec.carried_steps():
+            # the rounds' tile rule, from the tuner's cache or timed here
+            tn = tune.tune_batched(dec, Y, bt.eps, caps, reps=2, log=log)
+            out["config"] = tn["config"]
+            out["tuned_from_cache"] = tn["cached"]
             dec.solve_batched(Y, bt.eps, caps, want_r=False)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
@@ -581,7 +580,8 @@ def bench_batched(seed: int, reps: int = 3, warmup: int = 1, sequential: bool = 
         ms, cnt = dec.kernel_time()
         dec.set_profiling(0)
         # the decode's time over the steps of its longest signal
-        out["step"] = step_of_decode(ms, cnt, "k_gram_bsteps")
+        out["step"] = step_of_decode(ms, cnt, "k_gram_bsteps" if dec.carried_steps() else
+                                     "k_bcorr_s, k_bcorr, k_bselect")
         # one more decode with every signal's atoms recorded, for the checks
         g = None
         if check:
@@ -612,9 +612,9 @@ def bench_ragged(seed: int, storages=("f32", "bf16"), reps: int = 3, tune_reps: 
                  check: bool = True):
     """Ragged workload: 512 independent problems, N_i ~ U{128,256,512,1024},
     M_i = 4 N_i, K_i = N_i / 16, eps = 1e-5, T_i = 20 K_i, each with its own
-    dictionary, once per dictionary storage (the persistent launch that the
-    autotuner shapes decodes the sets that do not take the carried
-    correlations).  Reports problems/s.  Returns ({storage: record}, {storage: decode to check})."""
+    dictionary, once per dictionary storage (a set that does not take carried
+    correlations runs in the persistent launch, which is tuned first).  Reports
+    problems/s.  Returns ({storage: record}, {storage: decode to check})."""
     import torch
 
     import mpgen
@@ -630,9 +630,12 @@ def bench_ragged(seed: int, storages=("f32", "bf16"), reps: int = 3, tune_reps: 
         out = {"workload": "512 instances, N_i ~ U{128,256,512,1024}, M_i = 4 N_i, K_i = N_i/16, "
                            f"eps=1e-5, T_i = 20 K_i, own dictionary each, {storage} storage"}
         with RaggedDecoder(psis, storage=storage) as dec:
-            tuned = tune.tune_ragged(dec, yp, 1e-5, caps, reps=tune_reps, log=log)
             x = torch.empty(dec.x_off[-1], dtype=torch.float32, device="cuda")
             dec.solve(yp, 1e-5, caps, want_r=False, x_out=x)
+            if not dec.carried_steps():
+                tuned = tune.tune_ragged(dec, yp, 1e-5, caps, reps=tune_reps, log=log)
+                out.update(config=tuned["config"], tuned_from_cache=tuned["cached"])
+                dec.solve(yp, 1e-5, caps, want_r=False, x_out=x)
             torch.cuda.synchronize()
             t0 = time.perf_counter()
             for _ in range(reps):
@@ -655,9 +658,9 @@ def bench_ragged(seed: int, storages=("f32", "bf16"), reps: int = 3, tune_reps: 
                      "r": [rs[yo[i]:yo[i + 1]] for i in range(len(probs))]}
         out.update(problems_per_s=round(len(probs) / dt, 2), solve_ms=round(dt * 1e3, 3),
                    total_iters=sum(res["iters"]), stops=sorted(set(res["stop"])),
-                   config=tuned["config"], tuned_from_cache=tuned["cached"],
                    step={"bound": "bytes of the passes, then the steps of the longest problem",
-                         "kernel": "k_gram_rpass, k_gram_rsteps", "device_ms": round(kms, 3)})
+                         "kernel": "k_gram_rpass, k_gram_rsteps" if dec.carried_steps() else
+                         "k_ragged", "device_ms": round(kms, 3)})
         recs[storage] = out
         checks[storage] = {"psis": [p.psi for p in probs], "ys": [p.y for p in probs],
                            "eps": 1e-5, "dict_of": list(range(len(probs))), "g": g}
@@ -775,6 +778,7 @@ def main():
     log(f"[bench] {iters} iterations in {dt:.3f} s")
     one_launch = "persistent" in stops
     stops.discard("persistent")
+    kernel = "k_gram_bsteps" if dec.carried_steps() else "k_f32_small"
     # one decode with one launch per step: the step kernel's HBM rate
     s_ms, s_n = avg_ms, kt_n
     if not one_launch:
@@ -812,7 +816,7 @@ def main():
     if one_launch:
         # a small dictionary: no launch per step
         line["config"]["one_launch"] = True
-        line["roofline"] = step_of_decode(avg_ms, kt_n, "k_gram_bsteps")
+        line["roofline"] = step_of_decode(avg_ms, kt_n, kernel)
     if not args.no_omp and args.storage == "f32":
         log("[bench] OMP decode of the same signal")
         o_it, o_dt, o_ms, o_n, o_stops = time_decodes(dec, y, p, args.steps, args.warmup,
