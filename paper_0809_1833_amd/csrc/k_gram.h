@@ -24,7 +24,7 @@
 //
 // Against one pass per step (whole decodes, to eps = 1e-5): N = 8192,
 // M = 32768, K = 512: 19.5 ms from 384 ms (2,367 steps of about 6 us, 22
-// passes of 192 us); N = 2048, M = 8192, K = 128: 2.3 ms from 9.0 ms (562 steps
+// passes of 192 us); N = 2048, M = 8192, K = 128: 2.2 ms from 9.0 ms (562 steps
 // of 3.3 us, 9 passes).  A signal without structure (noise,
 // every step a new atom) is no slower either: the wanted columns cover the
 // next several choices (N = 2048, M = 8192, with 16 right-hand sides: 8.4 us a
@@ -75,7 +75,7 @@ struct GramProb {
   float* rhs;          // 32 x ld: a pass's right-hand sides in operand order
   T* r;                // ld elements
   T* x;
-  DevState* st;        // pad[0]: the decode gave up (the host runs the stepping form)
+  DevState* st;        // pad[0]: the decode gave up (another form goes on from its steps)
   GramCtl* ctl;
 };
 

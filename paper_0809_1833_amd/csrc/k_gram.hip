@@ -28,8 +28,10 @@ namespace mp {
 // their own, summed in FP64, which keeps the rounding bound of the products at
 // that of one chain.
 //
-// N = 8192, M = 32768: 192 us (5.6 TB/s; a large copy reaches 6.64) and 22
-// passes a decode; with 16 right-hand sides (16 atoms a wave) 196 us and 40.
+// N = 8192, M = 32768: 192 us (5.6 TB/s of the dictionary's bytes, 5.8 of the
+// 1.03 times as many that the counters show; a large copy reaches 6.64) and 22
+// passes a decode; in FP64 314 us (6.8 and 7.0 TB/s); with 16 right-hand sides
+// (16 atoms a wave) 196 us and 40.
 constexpr int kPassThreads = 512;
 constexpr int kPassWaves = kPassThreads / kWave;
 constexpr int kPassRows = 64;           // rows of a piece: 8 steps of 8

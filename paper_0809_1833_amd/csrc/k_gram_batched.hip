@@ -12,7 +12,7 @@
 // M = 8192).  Against rounds of BF16 products with a selection launch each:
 // N = 2048, M = 8192, 256 signals: 6.6 ms from 42 ms (2 ms more the first
 // time, for the Gram columns); N = 500, M = 1000, 500 signals: 2.7 ms from
-// 7.8 ms.  One signal of a small dictionary, N = 256, M = 1024, 50 steps: 162
+// 7.8 ms.  One signal of a small dictionary, N = 256, M = 1024, 50 steps: 142
 // us from 264 in the launch that exchanges every step between workgroups.
 #include <algorithm>
 

@@ -23,7 +23,7 @@
 // not estimated: k_omp_orth leaves its norm.
 //
 // Bound by a step's seven dependent launches (40 us with the factorisation's)
-// and the blocks' passes.  N = 8192, M = 32768, K = 512: 27.9 ms a decode from
+// and the blocks' passes.  N = 8192, M = 32768, K = 512: 27.7 ms a decode from
 // 95.1 ms with a selection pass of 160 us each step.
 #include "k_common.h"
 #include "k_gram.h"

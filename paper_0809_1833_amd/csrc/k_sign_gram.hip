@@ -26,7 +26,7 @@
 // round brings.  Bound by the steps' chain of latencies and the launches of
 // a round: a step 0.96 us (about a third are taken again in a later round),
 // check 18, decide 10, commit 15 us for 128 of them.  N = 8192, M = 32768,
-// K = 512 (2,376 steps): 5.4 ms a decode from 23.4 in one persistent launch
+// K = 512 (2,376 steps): 5.5 ms a decode from 23.4 in one persistent launch
 // that exchanged every step between all CUs.
 #include <type_traits>
 

@@ -599,8 +599,8 @@ mp_status solve_gram(mp_ctx* c, const T* psi, T* r_work, T* x, const mp_opts* op
 bool gram_full_suits(const mp_ctx* c) {
   const mp::GramShape sh = mp::gram_shape(c->ld, c->m, 4);
   const int64_t bytes = 4 * mp::gram_stride(sh) * c->m;
-  return c->carried_on && sh.threads != 0 && c->m <= 16384 && c->max_norm > 0.99 && c->max_norm < 1.01 &&
-         bytes <= std::max<int64_t>(int64_t{64} << 20, 8 * 4 * c->ld * c->m);
+  return c->carried_on && sh.threads != 0 && c->m <= 16384 && c->max_norm > 0.99 &&
+         c->max_norm < 1.01 && bytes <= std::max<int64_t>(int64_t{64} << 20, 8 * 4 * c->ld * c->m);
 }
 
 // What making them costs, us: the symmetric product's 2 m^2 n / 2 operations at
@@ -1642,7 +1642,8 @@ static mp_status ensure_omp(mp_ctx* c, int64_t tq) {
 // pass.
 static bool ensure_omp_carry(mp_ctx* c) {
   mp::OmpBufs& b = c->omp;
-  if (!c->carried_on || c->ld * c->m * 4 < kOmpCarryBytes || !(c->max_norm > 0.99) || !(c->max_norm < 1.01))
+  if (!c->carried_on || c->ld * c->m * 4 < kOmpCarryBytes || !(c->max_norm > 0.99) ||
+      !(c->max_norm < 1.01))
     return false;
   if (b.oc) return true;
   const size_t ld = static_cast<size_t>(c->ld), req = mp::kGramReq;
