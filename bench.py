@@ -646,6 +646,7 @@ def bench_ragged(seed: int, storages=("f32", "bf16"), reps: int = 3, tune_reps: 
             dec.solve(yp, 1e-5, caps, want_r=False, x_out=x)
             kms, _ = dec.kernel_time()
             dec.set_profiling(0)
+            kernel = "k_gram_rpass, k_gram_rsteps" if dec.carried_steps() else "k_ragged"
             g = None
             if check:
                 tr = dec.solve(yp, 1e-5, caps, trace_cap=max(caps))
@@ -659,8 +660,7 @@ def bench_ragged(seed: int, storages=("f32", "bf16"), reps: int = 3, tune_reps: 
         out.update(problems_per_s=round(len(probs) / dt, 2), solve_ms=round(dt * 1e3, 3),
                    total_iters=sum(res["iters"]), stops=sorted(set(res["stop"])),
                    step={"bound": "bytes of the passes, then the steps of the longest problem",
-                         "kernel": "k_gram_rpass, k_gram_rsteps" if dec.carried_steps() else
-                         "k_ragged", "device_ms": round(kms, 3)})
+                         "kernel": kernel, "device_ms": round(kms, 3)})
         recs[storage] = out
         checks[storage] = {"psis": [p.psi for p in probs], "ys": [p.y for p in probs],
                            "eps": 1e-5, "dict_of": list(range(len(probs))), "g": g}
