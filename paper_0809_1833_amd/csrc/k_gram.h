@@ -24,8 +24,8 @@
 //
 // Against one pass per step (whole decodes, to eps = 1e-5): N = 8192,
 // M = 32768, K = 512: 19.5 ms from 384 ms (2,367 steps of about 6 us, 22
-// passes of 192 us); N = 2048, M = 8192, K = 128: 2.2 ms from 9.0 ms (562 steps
-// of 3.3 us, 9 passes).  A signal without structure (noise,
+// passes of 199 us); N = 2048, M = 8192, K = 128: 2.2 ms from 9.0 ms (562 steps
+// of 3.2 us, 8 passes).  A signal without structure (noise,
 // every step a new atom) is no slower either: the wanted columns cover the
 // next several choices (N = 2048, M = 8192, with 16 right-hand sides: 8.4 us a
 // step against 15.0; N = 1000, M = 3001: 437 us a decode against 807).  FP64,

@@ -28,10 +28,10 @@ namespace mp {
 // their own, summed in FP64, which keeps the rounding bound of the products at
 // that of one chain.
 //
-// N = 8192, M = 32768: 192 us (5.6 TB/s of the dictionary's bytes, 5.8 of the
-// 1.03 times as many that the counters show; a large copy reaches 6.64) and 22
-// passes a decode; in FP64 314 us (6.8 and 7.0 TB/s); with 16 right-hand sides
-// (16 atoms a wave) 196 us and 40.
+// N = 8192, M = 32768: 199 us in a decode (5.4 TB/s of the dictionary's bytes,
+// 5.6 of the 1.04 times as many that the counters show; a large copy reaches
+// 6.64) and 22 passes; in FP64 310 us (6.9 and 7.1 TB/s).  Passes alone take
+// 192; with 16 right-hand sides (16 atoms a wave) 196, and a decode 40 of them.
 constexpr int kPassThreads = 512;
 constexpr int kPassWaves = kPassThreads / kWave;
 constexpr int kPassRows = 64;           // rows of a piece: 8 steps of 8

@@ -1,5 +1,5 @@
 // OMP's selection on carried correlations (k_gram.h): the pass over the
-// dictionary runs once for about fifteen atoms instead of once per atom.
+// dictionary runs once for fifteen to twenty atoms instead of once per atom.
 //
 // A block starts with a pass that gives c~ = Psi^T r and, for up to kGramReq
 // candidate atoms, Psi^T w_i with w_i = psi_i - Q Q^T psi_i (the candidates

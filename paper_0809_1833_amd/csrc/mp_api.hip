@@ -1636,7 +1636,7 @@ static mp_status ensure_omp(mp_ctx* c, int64_t tq) {
 }
 
 // Whether OMP's selection takes the carried correlations, and their buffers if
-// so.  They save the pass of all steps but about one in fifteen and cost two
+// so.  They save the pass of all steps but one in fifteen or more and cost two
 // launches more a step and five more a pass.
 // Without them (column norms not near 1, no memory) every step selects by a
 // pass.
@@ -1671,7 +1671,7 @@ static bool ensure_omp_carry(mp_ctx* c) {
 // The OMP decode on carried correlations (k_omp_gram.hip), after the init
 // kernel: rounds of a block (which returns at once while the current one
 // lasts) and some steps (which return at once while they wait for a block),
-// enqueued in chunks.  A block lasts about fifteen steps: with kOmpSlots steps
+// enqueued in chunks.  A block lasts fifteen to twenty steps: with kOmpSlots steps
 // a round the launches that return at once come to about 3 us a step.  The
 // first chunk is one round of one step (its block has no candidates yet), the
 // second one of three, the third one, each looked at before the next is

@@ -13,7 +13,7 @@ Usage (after the four counter runs described in the profile summaries):
         --source paper_0809_1833_amd/csrc/k_f32.hip \\
         --source paper_0809_1833_amd/csrc/k_common.h \\
         --source paper_0809_1833_amd/csrc/mp_internal.h --n 8192 --m 32768 \\
-        --fetch gpurun_out/pmc_FETCH_SIZE --write gpurun_out/pmc_WRITE_SIZE \\
+        --fetch out/pmc_FETCH_SIZE --write out/pmc_WRITE_SIZE \\
         --copy-bytes 1073741824 --out profiles/mp_step_f32_traffic.json
 """
 from __future__ import annotations
