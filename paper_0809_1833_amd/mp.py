@@ -496,9 +496,12 @@ class Decoder:
                     stop=STOP_NAMES.get(res.stop_reason, res.stop_reason),
                     persistent=bool(res.persistent))
 
+    carried = True  # as set_carried left it
+
     def set_carried(self, on: bool) -> None:
         """Whether decodes may run on carried correlations (mp_set_carried)."""
         mp_set_carried(self._ctx, on)
+        self.carried = bool(on)
 
     def carried_steps(self) -> int:
         """Steps the last decode took on carried correlations."""
@@ -637,9 +640,12 @@ class RaggedDecoder:
     def handle(self):
         return self._ctx
 
+    carried = True  # as set_carried left it
+
     def set_carried(self, on: bool) -> None:
         """Whether decodes may run on carried correlations (mp_set_carried)."""
         mp_set_carried(self._ctx, on)
+        self.carried = bool(on)
 
     def carried_steps(self) -> int:
         """Steps of the last decode's longest instance on carried correlations."""

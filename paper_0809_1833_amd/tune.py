@@ -49,8 +49,9 @@ VERSION = "v2"
 
 @contextmanager
 def _without_carried(dec):
-    """The decoder's other forms, which read the settings, for a while."""
-    switch = getattr(dec, "set_carried", None)
+    """The decoder's other forms, which read the settings, for a while (and for
+    good where its program has chosen them)."""
+    switch = getattr(dec, "set_carried", None) if getattr(dec, "carried", True) else None
     if switch:
         switch(False)
     try:

@@ -61,3 +61,17 @@ def test_tuners_time_the_forms_that_read_the_settings(run, tmp_path, monkeypatch
     with pytest.raises(RuntimeError):
         run(tune, failing)
     assert failing.calls == 3 and failing.carried
+
+
+@pytest.mark.parametrize("run", [_ragged, _batched])
+def test_tuners_leave_a_declined_form_off(run, tmp_path, monkeypatch):
+    from paper_0809_1833_amd import tune
+    monkeypatch.setenv("MP_TUNE_CACHE", str(tmp_path / "tune.json"))
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda *a, **k: None)
+    monkeypatch.setattr(torch.cuda, "get_device_properties",
+                        lambda *a: type("P", (), {"gcnArchName": "gfx950:x"}))
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: None)
+    dec = Switched()
+    dec.set_carried(False)
+    assert not run(tune, dec)["cached"]
+    assert dec.calls > 3 and dec.on == 0 and not dec.carried
