@@ -2194,8 +2194,8 @@ mp_status mp_solve_batched(mp_ctx* ctx, const float* Y, int64_t ldy, int64_t B, 
   HIP_TRY(c, hipMemcpyAsync(c->h_slots, c->b_slots, sizeof(mp::BSlot) * B, hipMemcpyDeviceToHost,
                             s));
   HIP_TRY(c, hipStreamSynchronize(s));
-  if (rk == mp::kLpTopK && !c->gram_full) {
-    // what the Gram columns would have saved this call
+  if (rk == mp::kLpTopK && tmax > 1 && !c->gram_full && gram_full_suits(c)) {
+    // what the Gram columns would have saved this call, which may take them
     long long longest = 0;
     for (int64_t b = 0; b < B; ++b) longest = std::max(longest, c->h_slots[b].t);
     c->gram_owed += gram_gain_us(c, B) * static_cast<double>(longest);

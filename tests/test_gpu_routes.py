@@ -382,6 +382,21 @@ def test_gram_columns_in_proportion_and_when_they_pay():
         assert grown(lambda: dec.close()) <= -256  # the columns were made on the way
 
 
+def test_declined_batches_do_not_pay_for_gram_columns():
+    """Batches decoded while carried correlations are off are the caller's
+    choice, not rounds that Gram columns would have saved."""
+    from paper_0809_1833_amd.mp import Decoder
+    rows = _rows(1024, 8192)
+    Y = torch.stack([_signal(rows, 3, seed=j) for j in range(2)])
+    with Decoder(rows.t()) as dec:
+        dec.set_carried(False)
+        for _ in range(100):
+            dec.solve_batched(Y.t(), 1e-5, 10000)
+        dec.set_carried(True)
+        dec.solve_batched(Y.t(), 1e-5, 10000)
+        assert dec.carried_steps() == 0
+
+
 @pytest.mark.parametrize("apart", [1e-7, 1e-9, 1e-12])
 def test_f64_selects_beyond_fp32(apart):
     """Pairs of columns that FP32 cannot tell apart: the shortlist is made in
